@@ -177,13 +177,14 @@ int adapt_approx_conv_transpose2d(const adapt_lut *lut, const int8_t *x_dev, con
 /* ------------------------------------------------------------------------------------------------
  * Pre-packed weights (the weights of a trained layer are static; the paper expands the filters into
  * a 2-D matrix once, Sec. III-B, and generates the table offline, Sec. III-C).  Packing combines the
- * two: for every inner index k and every block of 8 output channels it stores the table entries
- * T[a][w[n][k]] for all activations a, in the orders the two long-matrix kernels stream them (128-byte
- * lines; 256-byte lines of two-digit entries for the kernel that sums on the matrix pipe; both are made
- * by the pack call, nothing is added to a handle later, so a handle may be used from several threads).
- * The handle owns 2 * K * N * 2^b * 2 bytes of device memory, K and N rounded up to the kernels' tiles
- * (the first order twice for tables with entries beyond int16, which only that order serves) and
- * is tied to the device, the table contents and the weight values at pack time; w_dev may be freed
+ * two: for every inner index k and every block of output channels it stores the table entries
+ * T[a][w[n][k]] for all activations a, in the order the long-matrix kernels stream them.  Tables that
+ * are an exact product (of the operands, or of the operands without up to three low bits) plus an error
+ * spanning at most 255 are stored as that error, one byte per entry, beside the weights: K * N * (2^b + 1)
+ * bytes, K and N rounded up to the kernel's tiles.  Other tables take two orders (128-byte lines; 256-byte lines
+ * of two-digit entries), 2 * K * N * 2^b * 2 bytes (the first order twice, and only that, for entries
+ * beyond int16).  Everything is made by the pack call, nothing is added to a handle later, so a handle
+ * may be used from several threads.  The handle is tied to the device, the table contents and the weight values at pack time; w_dev may be freed
  * once the stream has passed the call.  The handle keeps a pointer to `lut`: the table handle must stay alive as long
  * as the weights handle is used (short linear layers run on the whole-table kernel with pre-packed row offsets).  The packed entry points give the same integers as the plain
  * ones; they skip the per-call packing that the plain entry points do for long matrices.
@@ -208,12 +209,12 @@ int adapt_weights_destroy(adapt_weights *w);
 /* Diagnostic, host only (no device call when cu > 0): how a product on a packed handle of this shape is spread over the
  * chip (Sec. IV: the matrix product is where the time goes, so which kernel runs it and in which launch shape is what a
  * profile has to be read against).  kind 0 linear (kh = kw = 1), 1 conv2d, 2 transposed conv2d with `stride`; storage as
- * adapt_lut_info reports it; rows = rows of the product (linear: M; convolution: N Ho Wo; transposed convolution: N Ho Wo
- * / stride^2, the rows of one phase), Wo = output width of one image row (linear: M; transposed: Wo / stride), sw =
+ * adapt_lut_info reports it, or 2 for a single-pass table stored as one-byte errors (see above); rows = rows of the
+ * product (linear: M; convolution: N Ho Wo; transposed convolution: N Ho Wo / stride^2, the rows of one phase), Wo = output width of one image row (linear: M; transposed: Wo / stride), sw =
  * horizontal stride; cu = compute units to plan for (<= 0: those of the current device).
  * *kernel: -1 whole-table kernel (lut_rows_kernel), 0 lut_lines_kernel, 1 lut_lines_fast_kernel, 2 the same on the
- * x-major copy, 3 lut_quad_kernel; *rows_per_workgroup; *ksplit = workgroups that share an output tile, each with a slice
- * of the inner dimension; *steps = table steps of the whole inner dimension (16 inner indices each for kernel 3, 8
+ * x-major copy, 3 lut_quad_kernel, 4 lut_byte_kernel; *rows_per_workgroup; *ksplit = workgroups that share an output tile, each with a slice
+ * of the inner dimension; *steps = table steps of the whole inner dimension (16 inner indices each for kernels 3 and 4, 8
  * otherwise); *workgroups = size of the launch.  Any output pointer may be NULL. */
 int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh, int kw, int stride, int rows, int Wo, int sw, int cu,
                       int *kernel, int *rows_per_workgroup, int *ksplit, int *steps, int *workgroups);

@@ -325,7 +325,7 @@ def adapt_approx_linear(lut: Lut, a, w, out=None, stream=None):
 
 
 PLAN_KERNELS = {-1: "lut_rows_kernel", 0: "lut_lines_kernel", 1: "lut_lines_fast_kernel", 2: "lut_lines_fast_kernel (x-major)",
-                3: "lut_quad_kernel"}
+                3: "lut_quad_kernel", 4: "lut_byte_kernel"}
 
 
 def adapt_plan_packed(kind, bits, storage, Cout, Cin, kh, kw, stride, rows, Wo, sw, cu=0):

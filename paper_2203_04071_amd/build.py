@@ -9,12 +9,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libadapt_mi355.so")
-SOURCES = [os.path.join(CSRC, f) for f in ("api_core.hip", "api_layers.hip", "api_i16.hip", "api_backward.hip")]
+SOURCES = [os.path.join(CSRC, f) for f in ("api_core.hip", "api_layers.hip", "byte_kernels.hip", "api_i16.hip", "api_backward.hip")]
 # ceiling probes for bench.py: a library of their own, not part of the product
 PROBES_LIB = os.path.join(HERE, "libadapt_probes.so")
 PROBES_SOURCE = os.path.join(CSRC, "probes.hip")
-# translation units whose kernels issue loads from inline assembly (what isa_check.py scans)
-HAND_SCHEDULED = [os.path.join(CSRC, "api_layers.hip")]
+# translation units whose kernels issue loads from inline assembly (what isa_check.py scans): kernels checked in the order of
+# the text, kernels checked along their control-flow graph
+HAND_SCHEDULED = [(os.path.join(CSRC, "api_layers.hip"), "lut_lines_(fast_)?kernel|lut_grouped_tiled_kernel", "lut_quad_kernel"),
+                  (os.path.join(CSRC, "byte_kernels.hip"), None, "lut_byte_kernel")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -131,4 +131,7 @@ struct adapt_lut {
     int img_bytes;          // per image, multiple of 16
     uint16_t *img_dev[2];   // [0] = only / low half, [1] = high half
     uint16_t *lut16_dev[2]; // same halves, plain [a & mask][w & mask] order (source of the derived line tables)
+    // byte form (lut_byte.hpp): T[a][w] = (a & byte_am) * (w & byte_wm) + byte_c + an error of one byte, if there is one
+    bool byte_form;
+    int byte_c, byte_am, byte_wm;
 };

@@ -7,6 +7,8 @@
 #include "lut_lines.hpp"
 #include "lut_quad.hpp"
 #include "lines_plan.hpp"
+#include "byte_launch.hpp"
+#include "byte_plan.hpp"
 #include "lut_rows.hpp"
 #include "lut_grouped.hpp"
 
@@ -79,7 +81,15 @@ struct adapt_weights {
     // row offsets with the columns in cell order (see adapt::RowsParams), made at pack time
     uint32_t *wofs_cell_dev;
     int cell_G;
+    // tables with a byte form: one-byte derived tables and the weights of the exact product (lut_byte.hpp) in place of
+    // dt_dev and dtq_dev, which are nullptr then
+    bool byte_form;
+    uint4 *dtb_dev;
+    int8_t *wx_dev;
+    uint32_t *arrived_dev;
 };
+
+#include "byte_host.hpp"
 
 /* ------------------------------------------------------------------ table-lookup matrix products */
 
@@ -896,6 +906,14 @@ int lines_conv_transpose2d(int bits, int storage, const LinesShape &q, uint4 *co
     return ADAPT_OK;
 }
 
+int pack_zero_sums(const adapt_lut *lut, const int8_t *w, int Cout, int Cin, int taps, int32_t *zsum, hipStream_t s) {
+    const int nz = Cout * taps;
+    adapt::convt_zero_sums_kernel<<<(unsigned)((nz + 255) / 256), 256, 0, s>>>(lut->lut16_dev[0], lut->storage ? lut->lut16_dev[1] : nullptr,
+                                                                              w, zsum, lut->bits, Cout, Cin, taps);
+    HIP_TRY(hipGetLastError());
+    return ADAPT_OK;
+}
+
 // derived tables of all phases + zero sums into caller-provided buffers
 int pack_convt(const adapt_lut *lut, const int8_t *w, const LinesShape &q, int kh, int kw, int st, uint4 *const dt[2], int32_t *zsum,
                hipStream_t s) {
@@ -907,11 +925,7 @@ int pack_convt(const adapt_lut *lut, const int8_t *w, const LinesShape &q, int k
                                                                              kw, st, q.Cc, q.n_tiles);
         HIP_TRY(hipGetLastError());
     }
-    const int nz = q.N * kh * kw;
-    adapt::convt_zero_sums_kernel<<<(unsigned)((nz + 255) / 256), 256, 0, s>>>(lut->lut16_dev[0], lut->storage ? lut->lut16_dev[1] : nullptr,
-                                                                              w, zsum, lut->bits, q.N, q.Cin, kh * kw);
-    HIP_TRY(hipGetLastError());
-    return ADAPT_OK;
+    return pack_zero_sums(lut, w, q.N, q.Cin, kh * kw, zsum, s);
 }
 
 // limits of the lines path: 32-bit byte offsets into the activation copy, and a sane table stream
@@ -981,6 +995,18 @@ int convt_any(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *a
               int kw, int stride, int pad, hipStream_t s) {
     const int Ho = (H - 1) * stride - 2 * pad + kh, Wo = (W - 1) * stride - 2 * pad + kw;
     const long long M = (long long)N * Ho * Wo;
+    if (convt_phases_ok(H, W, kh, kw, stride, pad) && M >= LINES_MIN_ROWS && stride <= 8 && lut->byte_form) {
+        const ByteShape q = byte_shape(lut->bits, Cout, Cin, kh, kw, stride);
+        if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * (q.kh - 1), W + 2 * (q.kw - 1), 1))
+            return with_temp_byte_tables(lut, w, q, true, s, [&](const ByteTables &t) {
+                int32_t *zsum = nullptr;
+                HIP_TRY(dbg_malloc_async((void **)&zsum, (size_t)Cout * kh * kw * sizeof(int32_t), s));
+                int rc = pack_zero_sums(lut, w, Cout, Cin, kh * kw, zsum, s);
+                if (rc == ADAPT_OK) rc = byte_conv_transpose2d(lut, t, q, zsum, x, acc, N, H, W, pad, s, nullptr);
+                (void)hipFreeAsync(zsum, s);
+                return rc;
+            });
+    }
     if (convt_phases_ok(H, W, kh, kw, stride, pad) && M >= LINES_MIN_ROWS && Cin >= 4) {
         const LinesShape q = convt_phase_shape(lut->bits, Cout, Cin, kh, kw, stride);
         const long long xt_bytes = (long long)N * (H + 2LL * (q.kh - 1)) * (W + 2LL * (q.kw - 1)) * q.Cp;
@@ -1021,6 +1047,13 @@ int adapt_approx_linear(const adapt_lut *lut, const int8_t *a_dev, const int8_t 
     g.mode = adapt::MODE_GEMM; g.M = M; g.N = N; g.Cin = K; g.taps = 1; g.kw = 1;
     g.H = 1; g.W = 1; g.Wo = 1; g.HoWo = 1; g.sh = g.sw = g.dh = g.dw = 1; g.ph = g.pw = 0;
     g.kstride = 1; g.img_stride = K;
+    if (M >= LINES_MIN_ROWS && K >= 8 && lut->byte_form) {
+        const ByteShape q = byte_shape(lut->bits, N, K, 1, 1);
+        if (byte_packable(q, (size_t)4 << 30) && (long long)q.cg * 4 * (M + 4) < 0x7fffff00LL)
+            return with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
+                return byte_linear(lut, t, q, a_dev, acc_dev, M, (hipStream_t)stream, nullptr, nullptr);
+            });
+    }
     if (M >= LINES_MIN_ROWS && K >= 8) {
         const LinesShape q = lines_shape(0, lut->bits, N, K, 1, 1);
         if (lines_fits((long long)M * q.Cp, q.dt_bytes, lut->storage))
@@ -1080,6 +1113,14 @@ int adapt_approx_conv2d(const adapt_lut *lut, const int8_t *x_dev, const int8_t 
     g.H = H; g.W = W; g.Wo = (int)Wo; g.HoWo = (int)(Ho * Wo);
     g.sh = stride_h; g.sw = stride_w; g.ph = pad_h; g.pw = pad_w; g.dh = dil_h; g.dw = dil_w;
     g.kstride = H * W; g.img_stride = Cin * H * W; g.groups = groups;
+    if (groups == 1 && g.M >= LINES_MIN_ROWS && lut->byte_form) {
+        const ByteShape q = byte_shape(lut->bits, Cout, Cin, kh, kw);
+        if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * pad_h, W + 2 * pad_w, stride_w))
+            return with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
+                return byte_conv2d(lut, t, q, x_dev, acc_dev, N, H, W, (int)Ho, (int)Wo, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w,
+                                   (hipStream_t)stream, nullptr);
+            });
+    }
     if (groups == 1 && g.M >= LINES_MIN_ROWS && Cin >= 4) {
         const LinesShape q = lines_shape(1, lut->bits, Cout, Cin, kh, kw, lut->storage == 0);
         const long long xt_bytes = (long long)N * (H + 2LL * pad_h) * (W + 2LL * pad_w) * q.Cp;
@@ -1130,6 +1171,52 @@ static int pack_cell_offsets(adapt_weights *h, hipStream_t s, const char *who) {
     return ADAPT_OK;
 }
 
+// derived tables of a handle in the byte form
+static int pack_byte_handle(adapt_weights *h, const int8_t *w_dev, const ByteShape &q, bool convt, hipStream_t s, const char *who) {
+    hipError_t e = dbg_malloc((void **)&h->dtb_dev, q.dt_bytes);
+    if (e == hipSuccess) e = dbg_malloc((void **)&h->wx_dev, q.wx_bytes);
+    if (e == hipSuccess) e = dbg_malloc((void **)&h->arrived_dev, adapt::BYTE_MAX_TILES * sizeof(uint32_t));
+    if (e != hipSuccess)
+        return fail(e == hipErrorOutOfMemory ? ADAPT_ERR_OUT_OF_MEMORY : ADAPT_ERR_HIP, "%s: hipMalloc(%zu): %s", who, q.dt_bytes, hipGetErrorString(e));
+    h->byte_form = true;
+    return pack_byte(h->lut, w_dev, q, ByteTables{h->dtb_dev, h->wx_dev, h->arrived_dev}, convt, s);
+}
+
+static ByteTables byte_tables_of(const adapt_weights *h) { return ByteTables{h->dtb_dev, h->wx_dev, h->arrived_dev}; }
+static ByteShape byte_shape_of(const adapt_weights *h) {
+    return byte_shape(h->bits, h->N, h->Cin, h->kh, h->kw, h->kind == 2 ? h->stride : 1);
+}
+
+// Place and layout of the input copy that the layer before a prepared handle writes (its own output quantised with s_next)
+static adapt::ChainOut chain_out_of(const adapt_weights *next, float s_next) {
+    const auto &ci = next->chain_in;
+    adapt::ChainOut o{};
+    o.buf = static_cast<int8_t *>(next->ws.ptr);
+    o.xmajor = ci.xmajor; o.Hp = ci.H + 2 * ci.ph; o.Wp = ci.W + 2 * ci.pw; o.Cp = next->Cp;
+    o.ph = ci.ph; o.pw = ci.pw;
+    o.scale = s_next; o.Q = (float)((1 << (next->bits - 1)) - 1); o.mask = (1u << next->bits) - 1u;
+    if (next->byte_form) {
+        const int sw = next->kind == 1 ? ci.sw : 1, wsub = (o.Wp + sw - 1) / sw;
+        o.xmajor = 1; o.Cp = (next->Cin + 3) / 4 * 4; o.Wp = sw * wsub; o.wsub = (uint32_t)wsub; o.dsw = fast_div((uint32_t)sw); o.mask = 0xffu;
+    }
+    return o;
+}
+
+// room for and zeroes in the input copy of a handle in the byte form (all the layer before does not write stays zero)
+static int byte_chain_prepare(const adapt_weights *h, size_t copy_bytes, int N, int Ho, int Wo, hipStream_t s) {
+    if (!copy_bytes) return fail(ADAPT_ERR_UNSUPPORTED, "chain prepare: input copy of 2 GiB or more");
+    const ByteShape q = byte_shape_of(h);
+    // (the producer decides whether the codes are known to be >= 0, which may change the plan)
+    const size_t p0 = byte_partial_bytes(byte_plan_of(q, h->bits, N, Ho, Wo, false), q, N, Ho, Wo);
+    const size_t p1 = byte_partial_bytes(byte_plan_of(q, h->bits, N, Ho, Wo, true), q, N, Ho, Wo);
+    void *xt = nullptr;
+    int rc = ws_get(&h->ws, copy_bytes + (p0 > p1 ? p0 : p1), s, &xt);
+    if (rc) return rc;
+    adapt::fill_u32_kernel<<<ew_grid(copy_bytes / 4), 256, 0, s>>>(static_cast<uint32_t *>(xt), 0u, copy_bytes / 4);
+    HIP_TRY(hipGetLastError());
+    return ADAPT_OK;
+}
+
 static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t *w_dev, int kind, int N, int Cin, int kh,
                         int kw, void *stream, const char *who) {
     if (!out) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: out is NULL", who);
@@ -1140,7 +1227,9 @@ static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t 
     if (!w_dev) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: w_dev is NULL", who);
     if ((long long)N * Cin * kh * kw > 0x7fffffffLL) return fail(ADAPT_ERR_UNSUPPORTED, "%s: more than 2^31-1 weights", who);
     const LinesShape q = lines_shape(kind, lut->bits, N, Cin, kh, kw, lut->storage == 0);
-    if (q.dt_bytes * (size_t)(lut->storage + 1) > ((size_t)64 << 30))
+    const ByteShape bq = byte_shape(lut->bits, N, Cin, kh, kw);
+    const bool byte_form = lut->byte_form && byte_packable(bq, (size_t)64 << 30);
+    if (!byte_form && q.dt_bytes * (size_t)(lut->storage + 1) > ((size_t)64 << 30))
         return fail(ADAPT_ERR_OUT_OF_MEMORY, "%s: packed tables would need %zu bytes", who, q.dt_bytes * (size_t)(lut->storage + 1));
     adapt_weights *h = new (std::nothrow) adapt_weights();
     if (!h) return fail(ADAPT_ERR_OUT_OF_MEMORY, "%s: host allocation failed", who);
@@ -1150,6 +1239,7 @@ static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t 
     h->dt_dev[0] = h->dt_dev[1] = nullptr;
     h->stride = 1; h->phased = false; h->zsum_dev = nullptr; h->w8_dev = nullptr; h->lut = lut;
     h->wofs_dev = nullptr; h->wofs_npad = 0; h->wofs1_dev = nullptr; h->wofs1_npad = 0; h->dtq_dev = nullptr; h->dtq_c = 0; h->dtq_bytes = 0; h->wofs_cell_dev = nullptr; h->cell_G = 0;
+    h->byte_form = false; h->dtb_dev = nullptr; h->wx_dev = nullptr; h->arrived_dev = nullptr;
     {   // copy of the weights (for table orders made later)
         const size_t wbytes = (size_t)N * Cin * kh * kw;
         hipError_t e = dbg_malloc((void **)&h->w8_dev, wbytes);
@@ -1171,17 +1261,21 @@ static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t 
         adapt::pack_row_offsets_kernel<<<(unsigned)((pack_n + 255) / 256), 256, 0, (hipStream_t)stream>>>(
             w_dev, h->wofs_dev, Cin, N, h->wofs_npad, Cin, 1, (int)adapt::MODE_GEMM, 1 << (lut->bits - 1), (1 << lut->bits) - 1, lut->rs * 2);
     }
-    for (int half = 0; half <= lut->storage; ++half) {
-        hipError_t e = dbg_malloc((void **)&h->dt_dev[half], q.dt_bytes);
-        if (e != hipSuccess) {
-            const size_t want = q.dt_bytes;
-            adapt_weights_destroy(h);
-            return fail(e == hipErrorOutOfMemory ? ADAPT_ERR_OUT_OF_MEMORY : ADAPT_ERR_HIP, "%s: hipMalloc(%zu): %s", who, want,
-                        hipGetErrorString(e));
+    if (byte_form) {
+        rc = pack_byte_handle(h, w_dev, bq, false, (hipStream_t)stream, who);
+    } else {
+        for (int half = 0; half <= lut->storage; ++half) {
+            hipError_t e = dbg_malloc((void **)&h->dt_dev[half], q.dt_bytes);
+            if (e != hipSuccess) {
+                const size_t want = q.dt_bytes;
+                adapt_weights_destroy(h);
+                return fail(e == hipErrorOutOfMemory ? ADAPT_ERR_OUT_OF_MEMORY : ADAPT_ERR_HIP, "%s: hipMalloc(%zu): %s", who, want,
+                            hipGetErrorString(e));
+            }
         }
+        rc = pack_lines(lut, w_dev, q, h->dt_dev, (hipStream_t)stream);
+        if (rc == ADAPT_OK) rc = pack_quad(h, (hipStream_t)stream, who);
     }
-    rc = pack_lines(lut, w_dev, q, h->dt_dev, (hipStream_t)stream);
-    if (rc == ADAPT_OK) rc = pack_quad(h, (hipStream_t)stream, who);
     if (rc == ADAPT_OK && kind == 0) rc = pack_cell_offsets(h, (hipStream_t)stream, who);
     if (rc != ADAPT_OK) {
         adapt_weights_destroy(h);
@@ -1234,6 +1328,7 @@ int adapt_weights_pack_conv_transpose2d(adapt_weights **out, const adapt_lut *lu
     h->dt_dev[0] = h->dt_dev[1] = nullptr;
     h->zsum_dev = nullptr; h->w8_dev = nullptr; h->lut = lut;
     h->wofs_dev = nullptr; h->wofs_npad = 0; h->wofs1_dev = nullptr; h->wofs1_npad = 0; h->dtq_dev = nullptr; h->dtq_c = 0; h->dtq_bytes = 0; h->wofs_cell_dev = nullptr; h->cell_G = 0;
+    h->byte_form = false; h->dtb_dev = nullptr; h->wx_dev = nullptr; h->arrived_dev = nullptr;
     h->phased = kh % stride == 0 && kw % stride == 0 && stride <= 8;
     const size_t wbytes = (size_t)Cout * Cin * kh * kw;
     hipError_t e = dbg_malloc((void **)&h->w8_dev, wbytes);
@@ -1255,7 +1350,19 @@ int adapt_weights_pack_conv_transpose2d(adapt_weights **out, const adapt_lut *lu
     if (e == hipSuccess && h->phased) {
         const LinesShape q = convt_phase_shape(lut->bits, Cout, Cin, kh, kw, stride);
         const size_t all = q.dt_bytes * stride * stride;
-        if (all * (size_t)(lut->storage + 1) > ((size_t)64 << 30)) {
+        const ByteShape bq = byte_shape(lut->bits, Cout, Cin, kh, kw, stride);
+        if (lut->byte_form && byte_packable(bq, (size_t)64 << 30)) {
+            h->Cp = q.Cp; h->Cc = q.Cc; h->n_tiles = q.n_tiles;
+            e = dbg_malloc((void **)&h->zsum_dev, (size_t)Cout * kh * kw * sizeof(int32_t));
+            if (e == hipSuccess) {
+                rc = pack_byte_handle(h, w_dev, bq, true, (hipStream_t)stream, who);
+                if (rc == ADAPT_OK) rc = pack_zero_sums(lut, w_dev, Cout, Cin, kh * kw, h->zsum_dev, (hipStream_t)stream);
+                if (rc != ADAPT_OK) {
+                    adapt_weights_destroy(h);
+                    return rc;
+                }
+            }
+        } else if (all * (size_t)(lut->storage + 1) > ((size_t)64 << 30)) {
             h->phased = false;      // too large to hold: this handle keeps to the plain form
         } else {
             h->Cp = q.Cp; h->Cc = q.Cc; h->n_tiles = q.n_tiles; h->dt_bytes = all;
@@ -1288,6 +1395,9 @@ int adapt_weights_destroy(adapt_weights *h) {
     if (h->wofs1_dev) (void)hipFree(h->wofs1_dev);
     if (h->dtq_dev) (void)hipFree(h->dtq_dev);
     if (h->wofs_cell_dev) (void)hipFree(h->wofs_cell_dev);
+    if (h->dtb_dev) (void)hipFree(h->dtb_dev);
+    if (h->wx_dev) (void)hipFree(h->wx_dev);
+    if (h->arrived_dev) (void)hipFree(h->arrived_dev);
     if (h->zsum_dev) (void)hipFree(h->zsum_dev);
     if (h->w8_dev) (void)hipFree(h->w8_dev);
     delete h;
@@ -1306,7 +1416,9 @@ int adapt_approx_conv_transpose2d_packed(const adapt_weights *h, const int8_t *x
     if (!x_dev || !acc_dev) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: NULL pointer", who);
     if ((long long)N * h->N * Ho * Wo > 0x7fffffffLL || (long long)N * h->Cin * H * W > 0x7fffffffLL)
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: tensor with more than 2^31-1 elements", who);
-    if (h->phased && convt_phases_ok(H, W, h->kh, h->kw, h->stride, pad)) {
+    if (h->byte_form && convt_phases_ok(H, W, h->kh, h->kw, h->stride, pad) && byte_copy_bytes(N, h->Cin, H + 2 * (h->kh / h->stride - 1), W + 2 * (h->kw / h->stride - 1), 1))
+        return byte_conv_transpose2d(h->lut, byte_tables_of(h), byte_shape_of(h), h->zsum_dev, x_dev, acc_dev, N, H, W, pad, (hipStream_t)stream, &h->ws, nullptr, h);
+    if (h->phased && !h->byte_form && convt_phases_ok(H, W, h->kh, h->kw, h->stride, pad)) {
         LinesShape q = convt_phase_shape(h->bits, h->N, h->Cin, h->kh, h->kw, h->stride);
         const long long xt_bytes = (long long)N * (H + 2LL * (q.kh - 1)) * (W + 2LL * (q.kw - 1)) * q.Cp;
         if (xt_bytes < 0x7fffff00LL)
@@ -1320,7 +1432,7 @@ int adapt_approx_conv_transpose2d_packed(const adapt_weights *h, const int8_t *x
 int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh, int kw, int stride, int rows, int Wo, int sw, int cu,
                       int *kernel, int *rows_per_workgroup, int *ksplit, int *steps, int *workgroups) {
     const char *who = "adapt_plan_packed";
-    if (kind < 0 || kind > 2 || bits < 2 || bits > 8 || storage < 0 || storage > 1 || Cout < 1 || Cin < 1 || kh < 1 || kw < 1 || stride < 1 ||
+    if (kind < 0 || kind > 2 || bits < 2 || bits > 8 || storage < 0 || storage > 2 || Cout < 1 || Cin < 1 || kh < 1 || kw < 1 || stride < 1 ||
         rows < 1 || Wo < 1 || sw < 1)
         return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: bad argument", who);
     int k = 0, rpw = 0, ks = 1, st = 0, wg = 0;
@@ -1329,6 +1441,13 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
         k = -1;                                 // whole-table kernel (lut_rows_kernel)
     } else if (kind == 2 && !phased) {
         k = -1;
+    } else if (storage == 2) {                  // lut_byte_kernel
+        const ByteShape q = byte_shape(bits, Cout, Cin, kh, kw, kind == 2 ? stride : 1);
+        const int lines = rows / Wo;            // image rows of the output
+        const BytePlan pl = byte_plan_of(q, bits, 1, lines > 0 ? lines : 1, Wo, false, cu);
+        const int V = pl.R < 4 ? pl.R : 4;
+        k = 4; rpw = 256 * pl.R; ks = pl.ksplit; st = q.steps;
+        wg = (int)(((long long)(lines > 0 ? lines : 1) * ((Wo + V - 1) / V * V) + rpw - 1) / rpw) * q.n_tiles * q.phases * ks;
     } else {
         const LinesShape q = kind == 2 ? convt_phase_shape(bits, Cout, Cin, kh, kw, stride) : lines_shape(kind, bits, Cout, Cin, kh, kw, storage == 0);
         const int phases = kind == 2 ? stride * stride : 1;
@@ -1361,6 +1480,7 @@ int adapt_approx_linear_packed(const adapt_weights *h, const int8_t *a_dev, int3
         g.kstride = 1; g.img_stride = h->Cin;
         return run_rows(h->lut, a_dev, nullptr, acc_dev, g, (hipStream_t)stream, h->wofs_dev, h->wofs_npad);
     }
+    if (h->byte_form) return byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), a_dev, acc_dev, M, (hipStream_t)stream, &h->ws, nullptr);
     return lines_linear(h->bits, h->storage, shape_of(h), h->dt_dev, a_dev, acc_dev, M, (hipStream_t)stream, &h->ws, nullptr, h);
 }
 
@@ -1379,6 +1499,9 @@ int adapt_approx_conv2d_packed(const adapt_weights *h, const int8_t *x_dev, int3
     const long long xt_bytes = (long long)N * (H + 2LL * pad_h) * (W + 2LL * pad_w) * h->Cp;
     if (xt_bytes >= 0x7fffff00LL || (long long)N * h->N * Ho * Wo > 0x7fffffffLL || (long long)N * Ho * Wo > 0x7fffffffLL)
         return fail(ADAPT_ERR_UNSUPPORTED, "adapt_approx_conv2d_packed: tensor with more than 2^31-1 elements");
+    if (h->byte_form)
+        return byte_conv2d(h->lut, byte_tables_of(h), byte_shape_of(h), x_dev, acc_dev, N, H, W, (int)Ho, (int)Wo, stride_h, stride_w, pad_h, pad_w,
+                           dil_h, dil_w, (hipStream_t)stream, &h->ws, nullptr, h);
     return lines_conv2d(h->bits, h->storage, shape_of(h), h->dt_dev, x_dev, acc_dev, N, H, W, (int)Ho, (int)Wo, stride_h, stride_w,
                         pad_h, pad_w, dil_h, dil_w, (hipStream_t)stream, &h->ws, nullptr, h);
 }
@@ -1428,6 +1551,7 @@ int adapt_linear_layer_f32(const adapt_weights *h, const float *x_dev, float *y_
         g.kstride = 1; g.img_stride = h->Cin;
         return run_rows(h->lut, q, nullptr, out, g, s, h->wofs_dev, h->wofs_npad, &io);
     }
+    if (h->byte_form) return byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), nullptr, out, M, s, &h->ws, &io);
     return lines_linear(h->bits, h->storage, shape_of(h), h->dt_dev, nullptr, out, M, s, &h->ws, &io, h);
 }
 
@@ -1481,13 +1605,14 @@ static int conv2d_layer(const adapt_weights *h, const float *x_dev, float *y_dev
         if (!ci.valid || ci.N != N || ci.H != g.Ho || ci.W != g.Wo || next->Cin != h->N || !next->ws.ptr)
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: the next layer was not prepared for this layer's output", who);
         if (!(s_next > 0.0f)) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: s_next must be > 0", who);
-        io.chain.buf = static_cast<int8_t *>(next->ws.ptr);
-        io.chain.xmajor = ci.xmajor; io.chain.Hp = ci.H + 2 * ci.ph; io.chain.Wp = ci.W + 2 * ci.pw; io.chain.Cp = next->Cp;
-        io.chain.ph = ci.ph; io.chain.pw = ci.pw;
-        io.chain.scale = s_next; io.chain.Q = (float)((1 << (next->bits - 1)) - 1); io.chain.mask = (1u << next->bits) - 1u;
+        io.chain = chain_out_of(next, s_next);
         io.chain_wo = (int)g.Wo;
     }
-    rc = lines_conv2d(h->bits, h->storage, shape_of(h), h->dt_dev, nullptr, reinterpret_cast<int32_t *>(y_dev), N, H, W, (int)g.Ho,
+    if (h->byte_form)
+        rc = byte_conv2d(h->lut, byte_tables_of(h), byte_shape_of(h), nullptr, reinterpret_cast<int32_t *>(y_dev), N, H, W, (int)g.Ho, (int)g.Wo, stride_h,
+                         stride_w, pad_h, pad_w, dil_h, dil_w, (hipStream_t)stream, &h->ws, &io, h, input_ready);
+    else
+        rc = lines_conv2d(h->bits, h->storage, shape_of(h), h->dt_dev, nullptr, reinterpret_cast<int32_t *>(y_dev), N, H, W, (int)g.Ho,
                       (int)g.Wo, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, (hipStream_t)stream, &h->ws, &io, h, input_ready);
     // (only a call that has written next's copy may say what the copy holds)
     if (rc == ADAPT_OK && next) next->chain_in.nonneg = act == 1;
@@ -1512,6 +1637,15 @@ int adapt_conv2d_chain_prepare(const adapt_weights *h, int N, int H, int W, int 
     if ((rc = conv_geo(h, N, H, W, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, &g, who))) return rc;
     h->chain_in.valid = false;
     if (N == 0) return ADAPT_OK;
+    auto &ci = h->chain_in;
+    ci.N = N; ci.H = H; ci.W = W; ci.sh = stride_h; ci.sw = stride_w; ci.ph = pad_h; ci.pw = pad_w; ci.dh = dil_h; ci.dw = dil_w;
+    ci.xmajor = 1; ci.nonneg = false;
+    if (h->byte_form) {
+        if ((rc = byte_chain_prepare(h, byte_copy_bytes(N, h->Cin, H + 2 * pad_h, W + 2 * pad_w, stride_w), N, (int)g.Ho, (int)g.Wo, (hipStream_t)stream)))
+            return rc;
+        ci.valid = true;
+        return ADAPT_OK;
+    }
     // the layout decisions of lines_conv2d
     const LinesShape q = shape_of(h);
     const int M = (int)(N * g.Ho * g.Wo);
@@ -1524,9 +1658,7 @@ int adapt_conv2d_chain_prepare(const adapt_weights *h, int N, int H, int W, int 
     if ((rc = ws_get(&h->ws, copy_bytes + part_bytes, (hipStream_t)stream, (void **)&xt))) return rc;
     adapt::fill_u32_kernel<<<ew_grid(copy_bytes / 4), 256, 0, (hipStream_t)stream>>>(reinterpret_cast<uint32_t *>(xt), 0u, copy_bytes / 4);
     HIP_TRY(hipGetLastError());
-    auto &ci = h->chain_in;
-    ci.N = N; ci.H = H; ci.W = W; ci.sh = stride_h; ci.sw = stride_w; ci.ph = pad_h; ci.pw = pad_w; ci.dh = dil_h; ci.dw = dil_w;
-    ci.xmajor = xmajor; ci.nonneg = false; ci.valid = true;
+    ci.xmajor = xmajor; ci.valid = true;
     return ADAPT_OK;
 }
 
@@ -1571,10 +1703,7 @@ int adapt_conv2d_grouped_layer_f32(const adapt_lut *lut, const float *x_dev, con
         if (!ci.valid || ci.N != N || ci.H != Ho || ci.W != Wo || next->Cin != Cout || !next->ws.ptr)
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: the next layer was not prepared for this layer's output", who);
         if (!(s_next > 0.0f)) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: s_next must be > 0", who);
-        io.chain.buf = static_cast<int8_t *>(next->ws.ptr);
-        io.chain.xmajor = ci.xmajor; io.chain.Hp = ci.H + 2 * ci.ph; io.chain.Wp = ci.W + 2 * ci.pw; io.chain.Cp = next->Cp;
-        io.chain.ph = ci.ph; io.chain.pw = ci.pw;
-        io.chain.scale = s_next; io.chain.Q = (float)((1 << (next->bits - 1)) - 1); io.chain.mask = (1u << next->bits) - 1u;
+        io.chain = chain_out_of(next, s_next);
         io.chain_wo = (int)Wo;
     }
     if (wide_groups) {
@@ -1621,7 +1750,9 @@ int adapt_conv_transpose2d_layer_f32(const adapt_weights *h, const float *x_dev,
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: tensor with more than 2^31-1 elements", who);
     hipStream_t s = (hipStream_t)stream;
     int32_t *out = reinterpret_cast<int32_t *>(y_dev);
-    if (h->phased && convt_phases_ok(H, W, h->kh, h->kw, h->stride, pad)) {
+    if (h->byte_form && convt_phases_ok(H, W, h->kh, h->kw, h->stride, pad) && byte_copy_bytes(N, h->Cin, H + 2 * (h->kh / h->stride - 1), W + 2 * (h->kw / h->stride - 1), 1))
+        return byte_conv_transpose2d(h->lut, byte_tables_of(h), byte_shape_of(h), h->zsum_dev, nullptr, out, N, H, W, pad, (hipStream_t)stream, &h->ws, &io, h);
+    if (h->phased && !h->byte_form && convt_phases_ok(H, W, h->kh, h->kw, h->stride, pad)) {
         LinesShape q = convt_phase_shape(h->bits, h->N, h->Cin, h->kh, h->kw, h->stride);
         const long long xt_bytes = (long long)N * (H + 2LL * (q.kh - 1)) * (W + 2LL * (q.kw - 1)) * q.Cp;
         if (xt_bytes < 0x7fffff00LL)
@@ -1657,8 +1788,17 @@ int adapt_conv_transpose2d_chain_prepare(const adapt_weights *h, int N, int H, i
     long long Ho, Wo;
     if ((rc = convt_chain_geo(h, N, H, W, pad, &q, &Ho, &Wo, who))) return rc;
     if (N == 0) return ADAPT_OK;
-    // the layout decisions of lines_conv_transpose2d
     const int st = h->stride, Ty = q.kh, Tx = q.kw;
+    auto &ci = h->chain_in;
+    ci.N = N; ci.H = H; ci.W = W; ci.sh = ci.sw = st; ci.ph = Ty - 1; ci.pw = Tx - 1; ci.dh = ci.dw = pad;     // (dh, dw: the layer's padding)
+    ci.xmajor = 1; ci.nonneg = false;
+    if (h->byte_form) {
+        if ((rc = byte_chain_prepare(h, byte_copy_bytes(N, h->Cin, H + 2 * (Ty - 1), W + 2 * (Tx - 1), 1), N, (int)(Ho / st), (int)(Wo / st), (hipStream_t)stream)))
+            return rc;
+        ci.valid = true;
+        return ADAPT_OK;
+    }
+    // the layout decisions of lines_conv_transpose2d
     const int Qy = (int)(Ho / st), Qx = (int)(Wo / st), M = N * Qy * Qx;
     const LinesPlan plan = plan_product(q, h->bits, h->storage, M, st * st, Qx, 1, h->dtq_dev != nullptr);
     const int xmajor = plan.xmajor;
@@ -1669,9 +1809,7 @@ int adapt_conv_transpose2d_chain_prepare(const adapt_weights *h, int N, int H, i
     if ((rc = ws_get(&h->ws, copy_bytes + part_bytes, (hipStream_t)stream, (void **)&xt))) return rc;
     adapt::fill_u32_kernel<<<ew_grid(copy_bytes / 4), 256, 0, (hipStream_t)stream>>>(reinterpret_cast<uint32_t *>(xt), 0u, copy_bytes / 4);
     HIP_TRY(hipGetLastError());
-    auto &ci = h->chain_in;
-    ci.N = N; ci.H = H; ci.W = W; ci.sh = ci.sw = st; ci.ph = Ty - 1; ci.pw = Tx - 1; ci.dh = ci.dw = pad;     // (dh, dw: the layer's padding)
-    ci.xmajor = xmajor; ci.nonneg = false; ci.valid = true;
+    ci.xmajor = xmajor; ci.valid = true;
     return ADAPT_OK;
 }
 
@@ -1713,15 +1851,14 @@ int adapt_conv_transpose2d_layer_chain_f32(const adapt_weights *h, const float *
         if (!ci.valid || ci.N != N || ci.H != Ho || ci.W != Wo || next->Cin != h->N || !next->ws.ptr)
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: the next layer was not prepared for this layer's output", who);
         if (!(s_next > 0.0f)) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: s_next must be > 0", who);
-        io.chain.buf = static_cast<int8_t *>(next->ws.ptr);
-        io.chain.xmajor = ci.xmajor; io.chain.Hp = ci.H + 2 * ci.ph; io.chain.Wp = ci.W + 2 * ci.pw; io.chain.Cp = next->Cp;
-        io.chain.ph = ci.ph; io.chain.pw = ci.pw;
-        io.chain.scale = s_next; io.chain.Q = (float)((1 << (next->bits - 1)) - 1); io.chain.mask = (1u << next->bits) - 1u;
+        io.chain = chain_out_of(next, s_next);
         io.chain_wo = (int)Wo;
     }
     hipStream_t s = (hipStream_t)stream;
     int32_t *out = reinterpret_cast<int32_t *>(y_dev);
-    if (input_ready || phase_form) {
+    if ((input_ready || phase_form) && h->byte_form) {
+        rc = byte_conv_transpose2d(h->lut, byte_tables_of(h), byte_shape_of(h), h->zsum_dev, nullptr, out, N, H, W, pad, s, &h->ws, &io, h, input_ready);
+    } else if (input_ready || phase_form) {
         rc = lines_conv_transpose2d(h->bits, h->storage, q, h->dt_dev, h->zsum_dev, nullptr, out, N, H, W, h->kh, h->kw, h->stride, pad, s,
                                     &h->ws, &io, h, input_ready);
     } else {

@@ -27,7 +27,7 @@
 
 #include <type_traits>
 
-#include "elementwise.hpp"
+#include "epilogue.hpp"
 
 namespace adapt {
 
@@ -37,35 +37,6 @@ constexpr int LINE_BYTES = 128;      // 8 k-subs x 8 channels x int16
 typedef short short2_t __attribute__((ext_vector_type(2)));
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-// A layer's output written a second time as the NEXT convolution's input copy: quantised with that layer's activation
-// scale (the quantiser of Sec. III-A), as table line indices, at the element's place in the zero-padded x-major or
-// channel-last copy (see pad_channels_last_kernel) whose borders and padded channels were zeroed beforehand.  The next
-// layer then needs no copy kernel of its own.  buf == nullptr: nothing to do.
-struct ChainOut {
-    int8_t *buf;
-    int xmajor, Hp, Wp, Cp, ph, pw;
-    float scale, Q;
-    uint32_t mask;
-    // element (image, channel c, row oy, column ox) of the producing layer's fp32 output y
-    __device__ __forceinline__ void put(int img, int c, int oy, int ox, float y) const {
-        const uint32_t q = (uint32_t)quant1(y, scale, Q) & mask;
-        // (a copy is smaller than 2^31 bytes: 32-bit offsets)
-        const uint32_t row = (uint32_t)img * (uint32_t)Hp + (uint32_t)(oy + ph), col = (uint32_t)(ox + pw);
-        const uint32_t a = xmajor ? ((row * (uint32_t)(Cp >> 2) + (uint32_t)(c >> 2)) * (uint32_t)Wp + col) * 4u + (uint32_t)(c & 3)
-                                  : (row * (uint32_t)Wp + col) * (uint32_t)Cp + (uint32_t)c;
-        buf[a] = (int8_t)q;
-    }
-    // the same for channels c .. c + 3 (c a multiple of 4, Cp a multiple of 4) of one pixel: they are one aligned word
-    // of either copy
-    __device__ __forceinline__ uint32_t code(float y) const { return (uint32_t)quant1(y, scale, Q) & mask; }
-    __device__ __forceinline__ void put4(int img, int c, int oy, int ox, uint32_t codes) const {
-        const uint32_t row = (uint32_t)img * (uint32_t)Hp + (uint32_t)(oy + ph), col = (uint32_t)(ox + pw);
-        const uint32_t a = xmajor ? ((row * (uint32_t)(Cp >> 2) + (uint32_t)(c >> 2)) * (uint32_t)Wp + col) * 4u
-                                  : (row * (uint32_t)Wp + col) * (uint32_t)Cp + (uint32_t)c;
-        *reinterpret_cast<uint32_t *>(buf + a) = codes;
-    }
-};
 
 // Epilogues of the x-major kernels: lane (hq, cq) of a group of 8 lanes (j = 2 cq + hq) holds four consecutive pixels of
 // channel cq (and cq + 4) of its channel tile.  `mine` = its four codes of one of them (byte i = pixel i).  Returned:
@@ -139,89 +110,6 @@ struct LinesParams {
     const int32_t *zsum;
     FastDiv cv_s;                       // division by the stride
     int cv_Ho, cv_Wo, cv_H, cv_W, cv_kh, cv_kw, cv_pad, cv_Ly, cv_Lx;
-};
-
-// what is stored for the finished sum v of output channel n (see LinesParams::deq)
-// off: element offset of the output position (for the residual input)
-// What the window taps WITHOUT an input pixel added to output pixel (oy, ox) of channel co of a transposed convolution
-// (see LinesParams::zsum); zero away from the border.
-__device__ __forceinline__ uint32_t convt_border_terms(const LinesParams &p, int co, int oy, int ox) {
-    const int st = (int)p.cv_s.d;
-    const int qy = (int)p.cv_s.div((uint32_t)(oy + p.cv_pad)), ry = oy + p.cv_pad - qy * st;
-    const int qx = (int)p.cv_s.div((uint32_t)(ox + p.cv_pad)), rx = ox + p.cv_pad - qx * st;
-    uint32_t extra = 0;
-    for (int m = 0; m * st + ry < p.cv_kh; ++m) {
-        const bool yin = qy - m >= 0 && qy - m < p.cv_H;
-        for (int nn = 0; nn * st + rx < p.cv_kw; ++nn) {
-            const bool xin = qx - nn >= 0 && qx - nn < p.cv_W;
-            if (!(yin && xin)) extra += (uint32_t)p.zsum[(size_t)co * p.cv_kh * p.cv_kw + (ry + st * m) * p.cv_kw + (rx + st * nn)];
-        }
-    }
-    return extra;
-}
-
-// The same for the four pixels (oy, ox + i * stride), i = 0 .. 3, of one phase: they share the row's taps and the column
-// residue, so every zero sum is loaded once.
-__device__ __forceinline__ void convt_border_terms4(const LinesParams &p, int co, int oy, int ox, uint32_t (&extra)[4]) {
-    const int st = (int)p.cv_s.d;
-    const int qy = (int)p.cv_s.div((uint32_t)(oy + p.cv_pad)), ry = oy + p.cv_pad - qy * st;
-    const int qx = (int)p.cv_s.div((uint32_t)(ox + p.cv_pad)), rx = ox + p.cv_pad - qx * st;
-    const int32_t *z = p.zsum + (size_t)co * p.cv_kh * p.cv_kw;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) extra[i] = 0;
-    for (int m = 0; m * st + ry < p.cv_kh; ++m) {
-        const bool yin = qy - m >= 0 && qy - m < p.cv_H;
-        for (int nn = 0; nn * st + rx < p.cv_kw; ++nn) {
-            const int x0 = qx - nn;             // input column of pixel 0; pixel i has x0 + i
-            if (yin && x0 >= 0 && x0 + 3 < p.cv_W) continue;
-            const uint32_t zz = (uint32_t)z[(ry + st * m) * p.cv_kw + (rx + st * nn)];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (!(yin && (unsigned)(x0 + i) < (unsigned)p.cv_W)) extra[i] += zz;
-        }
-    }
-}
-
-// EXTRA: the instantiation also knows tanh; the plain one does not (eight inlined copies of that code in an epilogue
-// cost the ordinary layers about a microsecond per launch)
-template <bool EXTRA = false>
-__device__ __forceinline__ uint32_t finish_sum(const LinesParams &p, uint32_t v, int n, size_t off) {
-    if (!p.deq) return v;
-    float y = (float)(int32_t)v * (p.scales ? p.scales[n] : p.scale);
-    if (p.bias) y = y + p.bias[n];
-    if (p.resid) y = y + p.resid[off];
-    if (p.act == 1) y = y > 0.0f ? y : 0.0f;
-    else if (EXTRA && p.act == 2) y = tanh_spec(y);
-    return __float_as_uint(y);
-}
-
-// per-phase launch parameters without indexing the by-value argument block dynamically
-template <typename T>
-__device__ __forceinline__ T pick4(const T *v, int i) {
-    return i == 0 ? v[0] : (i == 1 ? v[1] : (i == 2 ? v[2] : v[3]));
-}
-
-// Activation sources of the copy kernels: already quantised int8, or fp32 quantised on the fly with the quantiser of
-// quantize_kernel (Sec. III-A), so that a layer needs no separate quantisation pass.  The copies hold table line
-// indices (the kernels that extract a bit field do not care, the quad kernel relies on it).
-// byte(): the operand as a table line index, i.e. its two's-complement bits below 2^b (mask = 2^b - 1)
-// load() / code(): the two halves of byte(), for kernels that request several operands before they convert the first
-struct SrcI8 {
-    typedef int8_t raw_t;
-    const int8_t *x;
-    uint32_t mask;
-    __device__ __forceinline__ uint32_t byte(size_t i) const { return (uint32_t)(uint8_t)x[i] & mask; }
-    __device__ __forceinline__ raw_t load(uint32_t i) const { return x[i]; }
-    __device__ __forceinline__ uint32_t code(raw_t v) const { return (uint32_t)(uint8_t)v & mask; }
-};
-struct SrcF32 {
-    typedef float raw_t;
-    const float *x;
-    float scale, Q;
-    uint32_t mask;
-    __device__ __forceinline__ uint32_t byte(size_t i) const { return (uint32_t)quant1(x[i], scale, Q) & mask; }
-    __device__ __forceinline__ raw_t load(uint32_t i) const { return x[i]; }
-    __device__ __forceinline__ uint32_t code(raw_t v) const { return (uint32_t)quant1(v, scale, Q) & mask; }
 };
 
 // NCHW int8 -> zero-padded copy, Cp (a multiple of 8) channels per pixel, in one of two orders:

@@ -456,7 +456,7 @@ __global__ __launch_bounds__(LINES_THREADS) void lut_quad_kernel(const LinesPara
             for (int i = 0; i < 4; ++i) v[i] = w[4 * run + i][cc];
             if (EXTRA && near_border) {     // (out_sx is the stride there)
                 uint32_t extra[4];
-                convt_border_terms4(p, n, oy, ox, extra);
+                convt_border_terms<4>(p, n, oy, ox, extra);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] -= extra[i];
             }

@@ -1,0 +1,127 @@
+"""GPU parity of the byte kernel (tables that are an exact product plus an error of one byte) against the CPU oracle: every
+sum bit-exact, at the edges of its tiles, runs and slices, and of what counts as such a table."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2203_04071_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2203_04071_amd import binding
+    binding.load()
+    assert torch.cuda.is_available()
+    return binding
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    return t.detach().cpu().numpy()
+
+
+def table(kind, bits, rng):
+    """A table with a byte form (the whole byte in use), or one that misses it by one."""
+    h = 1 << (bits - 1)
+    v = np.arange(-h, h, dtype=np.int64)
+    n = 2 * h
+    if kind == "product":           # exact product + an error that spans 255
+        t = v[:, None] * v[None, :] + rng.integers(-77, 179, size=(n, n))
+        t[0, 0], t[-1, -1] = h * h - 77, (h - 1) ** 2 + 178
+    elif kind == "dropped":         # both operands lose low bits
+        d = min(2, bits - 1)
+        t = ((v >> d) << d)[:, None] * ((v >> d) << d)[None, :] + rng.integers(-9, 10, size=(n, n))
+    elif kind == "one_side":        # only the activation loses bits
+        t = ((v >> 1) << 1)[:, None] * v[None, :] + rng.integers(-100, 101, size=(n, n))
+    else:                           # spans 256: no byte form
+        t = v[:, None] * v[None, :] + rng.integers(-128, 128, size=(n, n))
+        t[0, 0], t[-1, -1] = h * h - 128, (h - 1) ** 2 + 128
+    return np.ascontiguousarray(np.clip(t, -32768, 32767).astype(np.int32))
+
+
+CONVS = [
+    # N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, dh, dw
+    (1, 1, 1, 1, 1, 1, 1, 1, 1, 0, 0, 1, 1),            # one lookup
+    (2, 3, 9, 9, 15, 3, 3, 1, 1, 1, 1, 1, 1),           # one channel group per tap, packed over taps; one tile less one channel
+    (3, 5, 8, 13, 17, 3, 3, 2, 2, 1, 1, 1, 1),          # two groups per tap, odd width, stride 2, one tile and one channel
+    (2, 13, 10, 7, 33, 5, 3, 1, 3, 2, 1, 1, 1),         # horizontal stride 3
+    (2, 20, 12, 14, 16, 3, 3, 1, 2, 2, 2, 2, 2),        # dilation with stride 2
+    (1, 64, 8, 8, 64, 3, 3, 1, 1, 1, 1, 1, 1),          # few pixels: slices of the inner dimension
+    (1, 100, 7, 7, 40, 3, 3, 1, 1, 1, 1, 1, 1),         # the same with a ragged last step
+    (9, 16, 32, 33, 32, 1, 1, 1, 1, 0, 0, 1, 1),        # one step, several row tiles
+    (40, 24, 28, 30, 48, 3, 3, 1, 1, 1, 1, 1, 1),       # many pixels, runs that end inside a row
+]
+
+
+@pytest.mark.parametrize("bits,kind", [(8, "product"), (8, "dropped"), (8, "beyond"), (7, "product"), (6, "one_side"), (5, "product"),
+                                       (4, "product"), (3, "product"), (2, "product")])
+@pytest.mark.parametrize("case", CONVS)
+def test_convolution(B, bits, kind, case):
+    N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, dh, dw = case
+    rng = np.random.default_rng(1000 * bits + sum(case))
+    lut = table(kind, bits, rng)
+    L = B.Lut(lut, bits)
+    x = wl.random_i8(rng, (N, Cin, H, W), bits)         # uniform over all codes, the most negative included
+    w = wl.random_i8(rng, (Cout, Cin, kh, kw), bits)
+    pw_ = B.adapt_weights_pack_conv2d(L, dev(w))
+    want = orc.approx_conv2d(lut, bits, x, w, (sh, sw), (ph, pw), (dh, dw), threads=4)
+    for _ in range(2):              # (the second call finds the arrival counters as the first left them)
+        got = host(B.adapt_approx_conv2d_packed(pw_, dev(x), (sh, sw), (ph, pw), (dh, dw)))
+        assert got.shape == want.shape and (got == want).all()
+    plain = host(B.adapt_approx_conv2d(L, dev(x), dev(w), (sh, sw), (ph, pw), (dh, dw)))
+    assert (plain == want).all()
+
+
+@pytest.mark.parametrize("bits", [6, 8])
+@pytest.mark.parametrize("shape", [(4096, 1, 1), (4097, 15, 17), (4099, 130, 33), (9000, 64, 16), (5000, 517, 100)])
+def test_linear(B, bits, shape):
+    M, K, N = shape
+    rng = np.random.default_rng(bits + sum(shape))
+    lut = table("product", bits, rng)
+    L = B.Lut(lut, bits)
+    a, w = wl.random_i8(rng, (M, K), bits), wl.random_i8(rng, (N, K), bits)
+    want = orc.approx_linear(lut, bits, a, w, threads=4)
+    pw = B.adapt_weights_pack_linear(L, dev(w))
+    assert (host(B.adapt_approx_linear_packed(pw, dev(a))) == want).all()
+    assert (host(B.adapt_approx_linear(L, dev(a), dev(w))) == want).all()
+
+
+@pytest.mark.parametrize("bits", [6, 8])
+@pytest.mark.parametrize("case", [(3, 7, 5, 6, 9, 4, 2, 1), (2, 20, 4, 4, 33, 2, 2, 0), (1, 33, 3, 7, 16, 3, 3, 0), (2, 16, 9, 5, 17, 3, 1, 1)])
+def test_transposed_convolution(B, bits, case):
+    N, Cin, H, W, Cout, k, st, pad = case
+    rng = np.random.default_rng(bits + sum(case))
+    lut = table("product", bits, rng)
+    L = B.Lut(lut, bits)
+    x, w = wl.random_i8(rng, (N, Cin, H, W), bits), wl.random_i8(rng, (Cin, Cout, k, k), bits)
+    pw = B.adapt_weights_pack_conv_transpose2d(L, dev(w), st)
+    want = orc.approx_conv_transpose2d(lut, bits, x, w, st, pad, threads=4)
+    assert (host(B.adapt_approx_conv_transpose2d_packed(pw, dev(x), pad)) == want).all()
+
+
+@pytest.mark.parametrize("bits", [6, 8])
+@pytest.mark.parametrize("stride,kind", [(1, "product"), (2, "product"), (2, "beyond")])
+def test_chain_into_a_strided_layer(B, bits, stride, kind):
+    """The copy a producer writes for a layer that moves by `stride` pixels, behind a ReLU (half of every table) and without,
+    between handles with and without a byte form."""
+    rng = np.random.default_rng(bits + stride)
+    lut1, lut2 = table("product", bits, rng), table(kind, bits, rng)
+    L1, L2 = B.Lut(lut1, bits), B.Lut(lut2, bits)
+    x = dev(rng.standard_normal((3, 6, 11, 13)).astype(np.float32))
+    w1, w2 = wl.random_i8(rng, (18, 6, 3, 3), bits), wl.random_i8(rng, (21, 18, 3, 3), bits)
+    p1, p2 = B.adapt_weights_pack_conv2d(L1, dev(w1)), B.adapt_weights_pack_conv2d(L2, dev(w2))
+    s_x, s_1, s_2, s_o = 0.05, 1e-3, 0.3, 1e-3
+    B.adapt_conv2d_chain_prepare(p2, 3, 11, 13, (stride, stride), (1, 1))
+    for act in (B.ACT_RELU, B.ACT_NONE, B.ACT_RELU):
+        y1 = B.adapt_conv2d_layer_f32(p1, x, s_x, s_1, (1, 1), (1, 1), act=act)
+        want = B.adapt_dequant_i32(B.adapt_approx_conv2d(L2, B.adapt_quantize_f32(y1, s_2, bits), dev(w2), (stride, stride), (1, 1)), s_o, 1, 1, 3 * 21 * (-(-11 // stride)) * (-(-13 // stride)))
+        out1, out2 = torch.empty_like(y1), torch.empty_like(want)
+        B.adapt_conv2d_layer_chain_f32(p1, x, s_x, s_1, out1, (1, 1), (1, 1), act=act, next_pw=p2, s_next=s_2)
+        B.adapt_conv2d_layer_chain_f32(p2, None, s_2, s_o, out2, (stride, stride), (1, 1), in_shape=(3, 11, 13))
+        assert torch.equal(out1, y1) and torch.equal(out2, want)
