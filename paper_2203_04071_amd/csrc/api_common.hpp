@@ -42,6 +42,12 @@ inline unsigned ew_grid(size_t work_items) {
     return (unsigned)g;
 }
 
+// workgroups of the kernels that end in atomics (absmax_kernel, histogram_abs_kernel): at most RED_BLOCKS, at least 4 elements a thread
+inline unsigned red_grid(size_t n) {
+    const size_t g = (n + adapt::RED_THREADS * 4 - 1) / (adapt::RED_THREADS * 4);
+    return (unsigned)(g < 1 ? 1 : (g > adapt::RED_BLOCKS ? adapt::RED_BLOCKS : g));
+}
+
 // Debugging aid: with ADAPT_POISON_ALLOC set in the environment every device allocation of the library is filled with
 // 0xA5 bytes before use, so that code which relies on fresh memory being zero shows up in the tests.
 inline bool poison_on() {

@@ -132,7 +132,7 @@ int adapt_absmax_f32(const float *x_dev, size_t n, float *amax_dev, void *stream
     adapt::fill_u32_kernel<<<1, 64, 0, s>>>(reinterpret_cast<uint32_t *>(amax_dev), 0u, 1);
     if (n) {
         const int vec = aligned16(x_dev) ? 1 : 0;
-        adapt::absmax_kernel<<<ew_grid(n / 8 + 1), adapt::EW_THREADS, 0, s>>>(x_dev, n, reinterpret_cast<uint32_t *>(amax_dev), vec);
+        adapt::absmax_kernel<<<red_grid(n), adapt::RED_THREADS, 0, s>>>(x_dev, n, reinterpret_cast<uint32_t *>(amax_dev), vec);
     }
     HIP_TRY(hipGetLastError());
     return ADAPT_OK;
@@ -202,7 +202,7 @@ int adapt_histogram_abs_f32(const float *x_dev, size_t n, float amax, int bins, 
     if (n == 0) return ADAPT_OK;
     const float width = amax / (float)bins;
     const int vec = (reinterpret_cast<uintptr_t>(x_dev) & 15u) == 0 ? 1 : 0;
-    adapt::histogram_abs_kernel<<<ew_grid(n / 8 + 1), adapt::EW_THREADS, 0, (hipStream_t)stream>>>(x_dev, n, width, bins, counts_dev, vec);
+    adapt::histogram_abs_kernel<<<red_grid(n), adapt::RED_THREADS, 0, (hipStream_t)stream>>>(x_dev, n, width, bins, counts_dev, vec);
     HIP_TRY(hipGetLastError());
     return ADAPT_OK;
 }
@@ -213,7 +213,7 @@ int adapt_percentile_from_histogram(const uint32_t *counts_dev, int bins, float 
     if (!(amax > 0.0f) || den == 0 || num > den || den > (1u << 20))
         return fail(ADAPT_ERR_INVALID_ARGUMENT, "adapt_percentile_from_histogram: need amax > 0 and 0 <= num <= den <= 2^20");
     if (!counts_dev || !calib_max_dev) return fail(ADAPT_ERR_INVALID_ARGUMENT, "adapt_percentile_from_histogram: NULL pointer");
-    adapt::percentile_kernel<<<1, 64, 0, (hipStream_t)stream>>>(counts_dev, bins, amax / (float)bins, num, den, calib_max_dev);
+    adapt::percentile_kernel<<<1, 1024, 0, (hipStream_t)stream>>>(counts_dev, bins, amax / (float)bins, num, den, calib_max_dev);
     HIP_TRY(hipGetLastError());
     return ADAPT_OK;
 }
@@ -229,7 +229,7 @@ int adapt_mse_from_histogram(const uint32_t *counts_dev, int bins, float amax, i
     adapt::mse_candidates_kernel<<<(unsigned)((bins + 255) / 256), 256, 0, s>>>(counts_dev, bins, width, (float)((1 << (bits - 1)) - 1), err);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
-        adapt::mse_pick_kernel<<<1, 64, 0, s>>>(err, bins, width, calib_max_dev);
+        adapt::mse_pick_kernel<<<1, 1024, 0, s>>>(err, bins, width, calib_max_dev);
         e = hipGetLastError();
     }
     hipError_t fe = hipFreeAsync(err, s);
@@ -249,7 +249,7 @@ int adapt_entropy_from_histogram(const uint32_t *counts_dev, int bins, float ama
     adapt::entropy_candidates_kernel<<<(unsigned)((bins + 255) / 256), 256, 0, s>>>(counts_dev, bins, 1 << (bits - 1), loss);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
-        adapt::mse_pick_kernel<<<1, 64, 0, s>>>(loss, bins, width, calib_max_dev);      // first smallest: calib_max = k * width
+        adapt::mse_pick_kernel<<<1, 1024, 0, s>>>(loss, bins, width, calib_max_dev);      // first smallest: calib_max = k * width
         e = hipGetLastError();
     }
     hipError_t fe = hipFreeAsync(loss, s);

@@ -28,11 +28,16 @@ static __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, size_t n) {     
 
 // max |x|: the bit pattern of a non-negative float orders like an unsigned integer, so the final
 // combine is an integer atomic max; NaNs fail the comparison and are skipped.
-static __global__ __launch_bounds__(EW_THREADS) void absmax_kernel(const float *__restrict__ x, size_t n,
-                                                            uint32_t *__restrict__ out_bits, int vec) {
-    __shared__ float wave_max[EW_THREADS / 64];
+// Atomics on one word are served one after the other, about 10 ns each: with one workgroup of 256 per 8 K elements (4096 of
+// them at 64 MB) they took 40 of 52 us.  Hence few large workgroups, two per compute unit (RED_BLOCKS), each of which first
+// looks whether its maximum still matters: 64 MB in 18 us.
+constexpr int RED_THREADS = 1024;
+constexpr int RED_BLOCKS = 512;
+static __global__ __launch_bounds__(RED_THREADS) void absmax_kernel(const float *__restrict__ x, size_t n,
+                                                             uint32_t *__restrict__ out_bits, int vec) {
+    __shared__ float wave_max[RED_THREADS / 64];
     float m = 0.0f;
-    const size_t stride = (size_t)gridDim.x * EW_THREADS;
+    const size_t stride = (size_t)gridDim.x * RED_THREADS;
     const size_t n4 = vec ? n / 4 : 0;   // vec: x is 16-byte aligned
     const float4 *x4 = reinterpret_cast<const float4 *>(x);
     auto fold = [&](const float4 v) {
@@ -41,13 +46,13 @@ static __global__ __launch_bounds__(EW_THREADS) void absmax_kernel(const float *
         a = fabsf(v.z); if (a > m) m = a;
         a = fabsf(v.w); if (a > m) m = a;
     };
-    size_t i = (size_t)blockIdx.x * EW_THREADS + threadIdx.x;
+    size_t i = (size_t)blockIdx.x * RED_THREADS + threadIdx.x;
     for (; i + 3 * stride < n4; i += 4 * stride) {      // four loads in flight per lane
         const float4 v0 = x4[i], v1 = x4[i + stride], v2 = x4[i + 2 * stride], v3 = x4[i + 3 * stride];
         fold(v0); fold(v1); fold(v2); fold(v3);
     }
     for (; i < n4; i += stride) fold(x4[i]);
-    for (size_t j = n4 * 4 + (size_t)blockIdx.x * EW_THREADS + threadIdx.x; j < n; j += stride) {
+    for (size_t j = n4 * 4 + (size_t)blockIdx.x * RED_THREADS + threadIdx.x; j < n; j += stride) {
         const float a = fabsf(x[j]);
         if (a > m) m = a;
     }
@@ -55,14 +60,15 @@ static __global__ __launch_bounds__(EW_THREADS) void absmax_kernel(const float *
         const float o = __shfl_xor(m, off, 64);
         if (o > m) m = o;
     }
-    // one atomic per workgroup: thousands of them on one address are what a short launch would otherwise wait for
     if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int w = 1; w < EW_THREADS / 64; ++w)
+        for (int w = 1; w < RED_THREADS / 64; ++w)
             if (wave_max[w] > m) m = wave_max[w];
-        atomicMax(out_bits, __float_as_uint(m));
+        // (the word only grows: a stale value can only cause an atomic too many)
+        const uint32_t bits = __float_as_uint(m);
+        if (bits > __hip_atomic_load(out_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(out_bits, bits);
     }
 }
 
@@ -148,44 +154,79 @@ static __global__ __launch_bounds__(EW_THREADS) void dequant_pc_kernel(const int
 // counts[bin(|x_i|)] += 1 with bins equal bins over [0, amax]: bin(a) = min(bins - 1, trunc(a / width)), width = amax / bins
 // (both IEEE fp32 divisions); NaN is not counted.  Per-workgroup histogram in LDS (bins <= 4096), then one atomic per
 // non-empty bin.
-static __global__ __launch_bounds__(EW_THREADS) void histogram_abs_kernel(const float *__restrict__ x, size_t n, float width, int bins,
+// Every workgroup adds its whole histogram to `counts` at the end, so there are few of them (RED_BLOCKS; with 4096 workgroups
+// these 8 M atomics were most of the 83 us that 64 MB and 2048 bins took; 19 us now).
+// The bin is decided by the IEEE quotient.  The product with the reciprocal is within 2^-22 of it (relative), i.e. within 1e-3
+// for up to 4096 bins: only a value that close to an edge is divided.
+static __global__ __launch_bounds__(RED_THREADS) void histogram_abs_kernel(const float *__restrict__ x, size_t n, float width, int bins,
                                                                    uint32_t *__restrict__ counts, int vec) {
     __shared__ uint32_t h[4096];
-    for (int b = threadIdx.x; b < bins; b += EW_THREADS) h[b] = 0;
+    for (int b = threadIdx.x; b < bins; b += RED_THREADS) h[b] = 0;
     __syncthreads();
-    const size_t stride = (size_t)gridDim.x * EW_THREADS;
+    const size_t stride = (size_t)gridDim.x * RED_THREADS;
+    const float inv = 1.0f / width;
+    const bool inv_ok = inv > 1.0e-30f && inv < 1.0e30f;        // (else neither it nor the products are normal numbers)
     auto count = [&](float v) {
         const float a = fabsf(v);
         if (a != a) return;
-        const float t = a / width;
+        float t = a * inv;
+        if (!inv_ok || fabsf(t - rintf(t)) < 1.0e-3f) t = a / width;
         const int b = t >= (float)bins ? bins - 1 : (int)t;
         atomicAdd(&h[b < bins ? b : bins - 1], 1u);
     };
     const size_t n4 = vec ? n / 4 : 0;      // vec: x is 16-byte aligned
-    for (size_t i = (size_t)blockIdx.x * EW_THREADS + threadIdx.x; i < n4; i += stride) {
+    for (size_t i = (size_t)blockIdx.x * RED_THREADS + threadIdx.x; i < n4; i += stride) {
         const float4 v = reinterpret_cast<const float4 *>(x)[i];
         count(v.x); count(v.y); count(v.z); count(v.w);
     }
-    for (size_t i = n4 * 4 + (size_t)blockIdx.x * EW_THREADS + threadIdx.x; i < n; i += stride) count(x[i]);
+    for (size_t i = n4 * 4 + (size_t)blockIdx.x * RED_THREADS + threadIdx.x; i < n; i += stride) count(x[i]);
     __syncthreads();
-    for (int b = threadIdx.x; b < bins; b += EW_THREADS)
+    for (int b = threadIdx.x; b < bins; b += RED_THREADS)
         if (h[b]) atomicAdd(&counts[b], h[b]);
 }
 
 // calib_max = (k + 1) * width for the first bin k at which the cumulative count reaches ceil(total * num / den)
-static __global__ void percentile_kernel(const uint32_t *__restrict__ counts, int bins, float width, unsigned long long num,
-                                  unsigned long long den, float *__restrict__ out) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    unsigned long long total = 0;
-    for (int b = 0; b < bins; ++b) total += counts[b];
-    const unsigned long long target = (total * num + den - 1) / den;
-    unsigned long long cum = 0;
-    int k = bins - 1;
-    for (int b = 0; b < bins; ++b) {
-        cum += counts[b];
-        if (cum >= target) { k = b; break; }
+// One workgroup; a thread owns four consecutive bins, the cumulative counts come from a scan over its waves (a single thread
+// walking the bins took 180 us for 2048 of them; 5 us).
+static __global__ __launch_bounds__(1024) void percentile_kernel(const uint32_t *__restrict__ counts, int bins, float width, unsigned long long num,
+                                                          unsigned long long den, float *__restrict__ out) {
+    __shared__ unsigned long long wave_sum[16];
+    __shared__ int first;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t c[4];
+    unsigned long long own = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        c[j] = tid * 4 + j < bins ? counts[tid * 4 + j] : 0u;
+        own += c[j];
     }
-    out[0] = (float)(k + 1) * width;
+    unsigned long long incl = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long o = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += o;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    if (tid == 0) first = bins - 1;
+    __syncthreads();
+    unsigned long long before = incl - own, total = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) before += wave_sum[w];
+        total += wave_sum[w];
+    }
+    const unsigned long long target = (total * num + den - 1) / den;
+    unsigned long long cum = before;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        cum += c[j];
+        if (tid * 4 + j < bins && cum >= target) {
+            atomicMin(&first, tid * 4 + j);
+            break;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) out[0] = (float)(first + 1) * width;
 }
 
 // Least-squares range from the histogram: candidate k has range t_k = (k + 1) * width and scale s = t_k / Q (fp32); a
@@ -215,13 +256,34 @@ static __global__ __launch_bounds__(256) void mse_candidates_kernel(const uint32
 }
 
 // the first candidate with the smallest error: calib_max = (k + 1) * width
-static __global__ void mse_pick_kernel(const double *__restrict__ err, int bins, float width, float *__restrict__ out) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    int best_k = 0;
-    double best = err[0];
-    for (int k = 1; k < bins; ++k)
-        if (err[k] < best) { best = err[k]; best_k = k; }
-    out[0] = (float)(best_k + 1) * width;
+// (NaN loses every comparison: one in front keeps the first candidate, one elsewhere is never taken)
+static __global__ __launch_bounds__(1024) void mse_pick_kernel(const double *__restrict__ err, int bins, float width, float *__restrict__ out) {
+    __shared__ double wave_err[16];
+    __shared__ int wave_k[16];
+    const int tid = threadIdx.x;
+    const double inf = __builtin_inf();
+    double best = inf;
+    int best_k = 0x7fffffff;
+    auto take = [&](double e, int k) {
+        if (e < best || (e == best && k < best_k)) { best = e; best_k = k; }
+    };
+    for (int k = tid; k < bins; k += 1024) {
+        const double e = err[k];
+        take(e == e ? e : inf, k);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double e = __shfl_xor(best, off, 64);
+        const int k = __shfl_xor(best_k, off, 64);
+        take(e, k);
+    }
+    if ((tid & 63) == 0) { wave_err[tid >> 6] = best; wave_k[tid >> 6] = best_k; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < 16; ++w) take(wave_err[w], wave_k[w]);
+        if (!(err[0] == err[0])) best_k = 0;
+        out[0] = (float)(best_k + 1) * width;
+    }
 }
 
 // Information-loss range from the histogram (the third calibrator Sec. III-A names; the definition is this library's,
