@@ -81,8 +81,7 @@ BytePlan byte_plan_of(const ByteShape &q, int bits, int images, int Ho, int Wo, 
     if (const char *e = getenv("ADAPT_BYTE_PLAN")) {        // "R,ksplit": tuning experiments only (not compiled into the product)
         int R = 0, ks = 0;
         if (sscanf(e, "%d,%d", &R, &ks) == 2 && ks >= 1 && ks <= q.steps) {
-            const int gps = (q.steps + ks - 1) / ks;
-            pl.R = R; pl.gps = gps; pl.ksplit = (q.steps + gps - 1) / gps;
+            pl.R = R; pl.ksplit = ks; pl.even = byte_even_steps(q.steps, ks);
         }
     }
 #endif
@@ -108,13 +107,13 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
     if (Mv + 4096 > 0x7fffffffLL) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: more than 2^31 rows");
     p.Mv = (int)Mv;
     p.N = q.N; p.n_tiles = q.n_tiles; p.m_tiles = (int)((Mv + 256 * R - 1) / (256 * R));
-    p.cg = q.cg; p.taps = q.kh * q.kw; p.kw = q.kw; p.steps = q.steps; p.gps = pl.gps; p.ksplit = pl.ksplit;
+    p.cg = q.cg; p.taps = q.kh * q.kw; p.kw = q.kw; p.steps = q.steps; p.ksplit = pl.ksplit; p.even = pl.even;
     p.bits = bits; p.copy_lines = (1 << bits) >> (c.nonneg ? 1 : 0);
     p.img_stride = c.img_stride; p.oy_stride = c.oy_stride; p.ch_stride = c.ch_stride; p.ky_stride = c.ky_stride; p.dw = c.dw; p.wsub = c.wsub;
     p.amask = (uint32_t)(lut->byte_am & 0xff) * 0x01010101u;
     p.corr = (int)(uint32_t)((long long)q.kh * q.kw * q.Cin * lut->byte_c);
     p.d_HoWv = fast_div((uint32_t)(c.Ho * p.Wv)); p.d_Wv = fast_div((uint32_t)p.Wv);
-    p.d_ntiles = fast_div((uint32_t)q.n_tiles); p.d_mtiles = fast_div((uint32_t)p.m_tiles);
+    p.d_ntiles = fast_div((uint32_t)q.n_tiles); p.d_mtiles = fast_div((uint32_t)p.m_tiles); p.d_ksplit = fast_div((uint32_t)p.ksplit);
     p.d_taps = fast_div((uint32_t)p.taps); p.d_rest = fast_div((uint32_t)((q.cg & 3) ? q.cg & 3 : 1)); p.d_kw = fast_div((uint32_t)q.kw);
     p.d_sw = fast_div((uint32_t)c.sw);
     p.out_step = c.out_step; p.linear = c.linear ? 1 : 0; p.out_plane = c.out_plane; p.out_w = c.out_w;
@@ -127,7 +126,7 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
     p.zsum = c.zsum; p.cv_s = fast_div((uint32_t)c.cv_s);
     p.cv_Ho = c.cv_Ho; p.cv_Wo = c.cv_Wo; p.cv_H = c.cv_H; p.cv_W = c.cv_W; p.cv_kh = c.cv_kh; p.cv_kw = c.cv_kw; p.cv_pad = c.cv_pad;
     p.cv_Ly = c.cv_Ly; p.cv_Lx = c.cv_Lx;
-    const bool extra = p.zsum || p.chain.buf || p.act == 2;
+    const int level = lut->byte_am != -1 ? 3 : p.act == 2 ? 2 : (p.zsum || p.chain.buf ? 1 : 0);
     if (p.ksplit > 1 && !partial) return fail(ADAPT_ERR_HIP, "byte path: no room for partial sums");
     const int n_phases = (int)c.xt_off.size();
     const size_t tables = (size_t)q.n_tiles * q.steps;          // of one phase
@@ -143,7 +142,7 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
         const long long grid = (long long)p.m_tiles * q.n_tiles * p.phases * p.ksplit;
         if (grid > 0x7fffffffLL) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: grid too large");
         if (p.ksplit > 1 && grid / p.ksplit > adapt::BYTE_MAX_TILES) return fail(ADAPT_ERR_HIP, "byte path: more tiles than arrival counters");
-        HIP_TRY(launch_byte(p, (unsigned)grid, R, extra, s));
+        HIP_TRY(launch_byte(p, (unsigned)grid, R, level, s));
     }
     return ADAPT_OK;
 }

@@ -6,24 +6,26 @@ namespace adapt_api {
 namespace {
 
 template <int DOPS, int R>
-void launch(const adapt::ByteParams &p, unsigned grid, bool extra, hipStream_t s) {
-    if (extra) adapt::lut_byte_kernel<DOPS, R, true><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
-    else adapt::lut_byte_kernel<DOPS, R, false><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
+void launch(const adapt::ByteParams &p, unsigned grid, int level, hipStream_t s) {
+    if (level == 3) adapt::lut_byte_kernel<DOPS, R, 3><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
+    else if (level == 2) adapt::lut_byte_kernel<DOPS, R, 2><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
+    else if (level == 1) adapt::lut_byte_kernel<DOPS, R, 1><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
+    else adapt::lut_byte_kernel<DOPS, R, 0><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
 }
 
 template <int R>
-void launch_r(const adapt::ByteParams &p, unsigned grid, bool extra, hipStream_t s) {
-    if (p.copy_lines == 256) launch<4, R>(p, grid, extra, s);
-    else if (p.copy_lines == 128) launch<2, R>(p, grid, extra, s);
-    else launch<1, R>(p, grid, extra, s);
+void launch_r(const adapt::ByteParams &p, unsigned grid, int level, hipStream_t s) {
+    if (p.copy_lines == 256) launch<4, R>(p, grid, level, s);
+    else if (p.copy_lines == 128) launch<2, R>(p, grid, level, s);
+    else launch<1, R>(p, grid, level, s);
 }
 
 }  // namespace
 
-hipError_t launch_byte(const adapt::ByteParams &p, unsigned grid, int R, bool extra, hipStream_t s) {
-    if (R == 8) launch_r<8>(p, grid, extra, s);
-    else if (R == 4) launch_r<4>(p, grid, extra, s);
-    else launch_r<2>(p, grid, extra, s);
+hipError_t launch_byte(const adapt::ByteParams &p, unsigned grid, int R, int level, hipStream_t s) {
+    if (R == 8) launch_r<8>(p, grid, level, s);
+    else if (R == 4) launch_r<4>(p, grid, level, s);
+    else launch_r<2>(p, grid, level, s);
     return hipGetLastError();
 }
 

@@ -27,13 +27,15 @@
 // The exact product needs, as B, the activations of four steps (64 inner indices): a lane holds the words of group
 // q ^ (r % 4) of the four steps; two exchanges between lanes (v_permlane16_swap: l <-> l ^ 16, v_permlane32_swap: l <->
 // l ^ 32) and selects by the bits of r % 4 leave k-sub q with the four groups of step q, in order.  The A operand is the
-// packed weights of the four steps ([step][channel][slot] bytes).
+// packed weights of the four steps ([step][channel][slot] bytes).  Matrix and vector instructions of a SIMD do not overlap
+// here (16.6 clocks for the one, 4 for the other, 10.8 for a lane exchange, all of them adding up), so this costs a fifth of
+// the loop wherever the fill of LDS does not hide it; interleaving it with the reads changed nothing.
 //
-// LDS: two 64 KB table buffers, line address = buffer << 16 | activation byte << 8 | slot << 4, built by one v_perm_b32.
-// While step s is read from one buffer the table of step s + 1 is copied into the other by LDS-direct loads; a step ends
-// when the wave's part of that copy has landed (a counted wait that leaves the newer activation loads in flight) and a
-// barrier.  Activations are signed codes, so the lines of negative ones sit at the end of the 64 KB (for fewer than 8 bits
-// with a gap in between).
+// LDS: tables of up to 32 KB (7 bits and fewer, or 8 bits behind a ReLU) in four buffers, of 64 KB in two; line address =
+// buffer | activation byte << 8 | slot << 4, built by one v_perm_b32.  Tables are copied by LDS-direct loads, three steps
+// ahead where there are four buffers: with two, nothing is on its way between the end of one copy and the start of the next,
+// and every step pays the latency of L2 again (32 KB tables, two pixels per row slot: 1580 clocks a step with two buffers, 1450
+// with four).
 //
 // Inner dimension.  Channels come in groups of four per filter tap; byte_slot() numbers the groups of all taps without
 // gaps (only the last step is padded), and a table in LDS holds the byte offset of every group inside a window: strides,
@@ -44,15 +46,18 @@
 // Rows are virtual: an image row of Wo pixels counts as Wv = Wo rounded up to runs of V = min(R, 4) pixels; what lies
 // beyond is computed and not stored.
 //
-// What bounds it (one MI355X): the path that fills LDS (64 KB of 8-bit table per step and workgroup at 46 B per clock and
-// compute unit) and the LDS reads, which hardly overlap.  One-byte entries halve both per lookup.  Measured against the
-// two-digit form (lut_quad.hpp): 3 x 3, 64 -> 64 channels, 32 images of 32 x 32, 8 bits: 41 -> 32 us; 128 -> 256 channels, 64 images
-// of 16 x 16: 85 us = 57 T lookups/s; against the 128-byte-line kernel on odd sizes (100 -> 200 channels, stride 2, 27 -> 14
-// pixels wide, 50 images): 271 -> 80 us.
+// What bounds it (one MI355X): with 64 KB tables the path that fills LDS (46 B per clock and compute unit, plus the latency of
+// L2 once per step), with smaller ones or many pixels per table the matrix and vector instructions (20.6 clocks a read and
+// SIMD), which equal what the LDS delivers (5.1 clocks a read).  One-byte entries halve all of it per lookup.  Measured against
+// the two-digit form (lut_quad.hpp): 3 x 3, 64 -> 64 channels, 32 images of 32 x 32, 8 bits: 41 -> 31 us; 128 -> 256 channels, 64
+// images of 16 x 16: 78 us = 62 T lookups/s; against the 128-byte-line kernel on odd sizes (100 -> 200 channels, stride 2,
+// 27 -> 14 pixels wide, 50 images): 271 -> 81 us.  A launch costs 6500 clocks before its first step (first table) and 1400 to 3500
+// behind the last.
 //
-// Split inner dimension: ksplit workgroups share a tile, each with gps steps.  Each leaves its sums in memory; the one
-// that arrives last (a counter per tile) adds the others' and finishes.  The exchange goes through device-scope (sc1)
-// stores, loads and one atomic: no cache write-back, no second launch, and nobody waits for anybody.
+// Split inner dimension: ksplit workgroups share a tile.  All but the last to arrive (a counter per tile) leave their sums
+// in memory, the last one adds them to its own and finishes; its slice is a little longer, so that the others have stored
+// by then.  The exchange goes through device-scope (sc1) stores, loads and one atomic: no cache write-back, no second launch,
+// and nobody waits for anybody.
 #pragma once
 #include <type_traits>
 
@@ -84,7 +89,7 @@ struct ByteParams {
     int Mv;                     // virtual rows
     int N, n_tiles, m_tiles, phases;
     int cg, taps, kw, steps;    // channel groups per tap, taps, filter width, steps of the whole inner dimension
-    int gps, ksplit;            // steps per slice, slices
+    int ksplit, even;           // slices of the inner dimension: slice i ends at step (i + 1) even / ksplit, the last one at the end
     int bits, copy_lines;       // copy_lines: 2^bits, or half of it where all activations are >= 0
     int Wo, Wv;                 // output width (per phase), the same rounded up to runs
     int img_stride, oy_stride;  // bytes of xt per image / output row
@@ -92,7 +97,7 @@ struct ByteParams {
     int dw, wsub;               // horizontal dilation; columns per residue class of a copied row
     uint32_t amask;             // am in every byte
     int corr;                   // c x real lookups of an output
-    FastDiv d_HoWv, d_Wv, d_ntiles, d_mtiles, d_phases, d_taps, d_rest, d_kw, d_sw;
+    FastDiv d_HoWv, d_Wv, d_ntiles, d_mtiles, d_phases, d_ksplit, d_taps, d_rest, d_kw, d_sw;
     int xt_off[4];              // per phase: bytes into xt,
     int oy0[4], ox0[4];         // position of its first output pixel; pixel (a, b) of a phase is (oy0 + a step, ox0 + b step)
     int out_step;
@@ -136,13 +141,14 @@ __device__ __forceinline__ bi32x4_t byte_ones(int lane) {
     return a;
 }
 
-// address = permute(activation word, column word, selector); read the 16 bytes there
+// address = permute(activation word, column word, selector); read the 16 bytes there (OFF: constant part of the address)
+template <int OFF>
 __device__ __forceinline__ void byte_fetch(b32x4_t &v, uint32_t word, uint32_t colw, uint32_t sel) {
     uint32_t tmp;
     asm volatile("v_perm_b32 %[t], %[wd], %[cw], %[sl]\n\t"
-                 "ds_read_b128 %[v], %[t]"
+                 "ds_read_b128 %[v], %[t] offset:%[of]"
                  : [v] "+v"(v), [t] "=&v"(tmp)
-                 : [wd] "v"(word), [cw] "v"(colw), [sl] "v"(sel));
+                 : [wd] "v"(word), [cw] "v"(colw), [sl] "v"(sel), [of] "n"(OFF));
 }
 
 template <int WAITN>
@@ -169,117 +175,192 @@ __device__ __forceinline__ bool byte_run_pos(const ByteParams &p, int mt, int rs
     return live;
 }
 
-// The end of a workgroup: the sums of slices (ksplit > 1), then everything that becomes of a finished sum.
-template <int R, bool EXTRA, int NACC>
-__device__ __forceinline__ void byte_epilogue(const ByteParams &p, bi32x4_t (&acc)[NACC], uint32_t *shared_word, int tid, int nt, int ph, int mt, int ks) {
-    constexpr int V = R < 4 ? R : 4, NRUN = R / V;
-    const int lane = tid & 63, q = lane >> 4, rs = (tid >> 6) * 16 + (lane & 15);
-
-    if (p.ksplit > 1) {
-        // leave the sums, count the arrival; the last one to arrive adds the other slices' sums to its own
-        const int tile = (ph * p.m_tiles + mt) * p.n_tiles + nt;
-        int32_t *const mine = p.partial + ((size_t)tile * p.ksplit + ks) * (R * BYTE_THREADS * 4);
-        const uint32_t voff = (uint32_t)tid * 16u;
+// The sums of a tile whose inner dimension is split: true in the workgroup that finishes the tile, which then holds the sum
+// of all slices.  The workgroup of the last slice looks first: if all others have arrived it keeps its sums to itself.
+// Everyone else stores its sums and counts itself in (and is the last one if the count says so).
+template <int R, int NACC>
+__device__ __forceinline__ bool byte_join_slices(const ByteParams &p, bi32x4_t (&acc)[NACC], uint32_t *shared_word, int tid, int tile, int ks, bool live) {
+    const uint32_t others = (uint32_t)(p.ksplit - 1);
+    const uint32_t voff = (uint32_t)tid * 16u;
+    int32_t *const slices = p.partial + (size_t)tile * p.ksplit * (R * BYTE_THREADS * 4);
+    bool alone = false;
+    if (ks == p.ksplit - 1) {           // (the long slice; a look costs 1 us, which the others save)
+        if (tid == 0) shared_word[0] = __hip_atomic_load(p.arrived + tile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        alone = shared_word[0] == others;
+    }
+    if (!alone) {
+        int32_t *const mine = slices + (size_t)ks * (R * BYTE_THREADS * 4);
+        if (live) {
 #pragma unroll
-        for (int i = 0; i < R; ++i)
-            asm volatile("global_store_dwordx4 %[o], %[v], %[sa] sc1" : : [o] "v"(voff), [v] "v"(acc[i]), [sa] "s"(mine + i * (BYTE_THREADS * 4)) : "memory");
+            for (int i = 0; i < R; ++i)
+                asm volatile("global_store_dwordx4 %[o], %[v], %[sa] sc1" : : [o] "v"(voff), [v] "v"(acc[i]), [sa] "s"(mine + i * (BYTE_THREADS * 4)) : "memory");
+        }
         asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
         __syncthreads();
         if (tid == 0) shared_word[0] = __hip_atomic_fetch_add(p.arrived + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        if (shared_word[0] != (uint32_t)(p.ksplit - 1)) return;
-        if (tid == 0) __hip_atomic_store(p.arrived + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int o = 1; o < p.ksplit; ++o) {
-            const int other = ks + o < p.ksplit ? ks + o : ks + o - p.ksplit;
-            const int32_t *const theirs = p.partial + ((size_t)tile * p.ksplit + other) * (R * BYTE_THREADS * 4);
-            bi32x4_t t[R];
+        if (shared_word[0] != others) return false;
+    }
+    if (tid == 0) __hip_atomic_store(p.arrived + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!live) return true;
+    constexpr int B = 8 / R;                          // slices whose loads are in flight together
+    for (int o = 0; o < p.ksplit; o += B) {
+        bi32x4_t t[B][R];
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const int from = o + j < p.ksplit ? o + j : ks;         // (past the end: any valid address)
+            const int32_t *const theirs = slices + (size_t)from * (R * BYTE_THREADS * 4);
 #pragma unroll
             for (int i = 0; i < R; ++i)
-                asm volatile("global_load_dwordx4 %[v], %[o], %[sa] sc1" : [v] "=v"(t[i]) : [o] "v"(voff), [sa] "s"(theirs + i * (BYTE_THREADS * 4)) : "memory");
-            asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+                asm volatile("global_load_dwordx4 %[v], %[o], %[sa] sc1" : [v] "=v"(t[j][i]) : [o] "v"(voff), [sa] "s"(theirs + i * (BYTE_THREADS * 4)) : "memory");
+        }
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const bool add = o + j < p.ksplit && o + j != ks;
 #pragma unroll
             for (int i = 0; i < R; ++i) {
-                asm volatile("" : "+v"(t[i]));
-                acc[i] += t[i];
+                asm volatile("" : "+v"(t[j][i]));
+                if (add) acc[i] += t[j][i];
             }
         }
     }
+    return true;
+}
 
-    // epilogue: channels cb .. cb + 3 of this lane's pixels
-    const int cb = nt * BYTE_TILE + 4 * q;
-    if (cb >= p.N) return;
+// What becomes of the finished sums of a lane: channels cb .. cb + 3 of its R pixels.
+// LEVEL 0: rescaling, bias, residual, ReLU.  1: also border terms of a transposed convolution and the next layer's copy.
+// 2: also tanh (16 or 32 inlined copies of it: an instantiation of its own).  3: the same in the kernel for tables whose
+// exact product drops low bits of the activations.
+template <int R, int LEVEL, int NACC>
+__device__ __forceinline__ void byte_epilogue(const ByteParams &p, const bi32x4_t (&acc)[NACC], const float (&sc)[4], const float (&bi)[4], int mt, int rs,
+                                              int ph, int cb) {
+    constexpr int V = R < 4 ? R : 4, NRUN = R / V;
+    const int nch = min(4, p.N - cb);
     const int oy0 = pick4(p.oy0, ph), ox0 = pick4(p.ox0, ph);
+    const int px = p.linear ? p.N : p.out_step;             // elements between consecutive pixels of a run,
+    const size_t plane = p.linear ? 1 : (size_t)p.out_plane;       // and between channels
 #pragma unroll
     for (int run = 0; run < NRUN; ++run) {
         int img, a, b;
         if (!byte_run_pos<R>(p, mt, rs, run, img, a, b)) continue;
         const int oy = oy0 + a * p.out_step, ox = ox0 + b * p.out_step;
         const int nv = min(V, p.Wo - b);            // pixels of the run that exist
-        const bool near_border = EXTRA && p.zsum && (oy < p.cv_Ly || oy >= p.cv_Ho - p.cv_Ly || ox < p.cv_Lx || ox + (V - 1) * p.out_step >= p.cv_Wo - p.cv_Lx);
-        uint32_t f[4][V];
-        uint32_t code[V];
+        const bool whole = nv == V && nch == 4;
+        const size_t at = p.linear ? (size_t)b * p.N + cb : ((size_t)img * p.N + cb) * plane + (size_t)oy * p.out_w + ox;
+        // runs of a channel are one access where they are contiguous and aligned; in a linear layer the four channels are
+        const bool vec = whole && px == 1 && ((at | plane) & (V - 1)) == 0;
+        const bool vec_ch = whole && p.linear && (p.N & 3) == 0;
+        uint32_t v[4][V];
 #pragma unroll
-        for (int i = 0; i < V; ++i) code[i] = 0;
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int n = cb + r;
-            if (n >= p.N) continue;
-            uint32_t v[V];
-#pragma unroll
-            for (int i = 0; i < V; ++i) v[i] = (uint32_t)acc[run * V + i][r] + (uint32_t)p.corr;
-            if (EXTRA && near_border) {
+            for (int i = 0; i < V; ++i) v[r][i] = (uint32_t)acc[run * V + i][r] + (uint32_t)p.corr;
+        if (LEVEL >= 1 && p.zsum && (oy < p.cv_Ly || oy >= p.cv_Ho - p.cv_Ly || ox < p.cv_Lx || ox + (V - 1) * p.out_step >= p.cv_Wo - p.cv_Lx)) {
+            for (int r = 0; r < nch; ++r) {
                 uint32_t extra[V];
-                convt_border_terms<V>(p, n, oy, ox, extra);
+                convt_border_terms<V>(p, cb + r, oy, ox, extra);
 #pragma unroll
-                for (int i = 0; i < V; ++i) v[i] -= extra[i];
+                for (int i = 0; i < V; ++i) {
+                    v[0][i] -= r == 0 ? extra[i] : 0u;
+                    v[1][i] -= r == 1 ? extra[i] : 0u;
+                    v[2][i] -= r == 2 ? extra[i] : 0u;
+                    v[3][i] -= r == 3 ? extra[i] : 0u;
+                }
             }
-            const size_t at = p.linear ? (size_t)b * p.N + n : (size_t)((size_t)img * p.N + n) * p.out_plane + (size_t)oy * p.out_w + ox;
-            const int px = p.linear ? p.N : p.out_step;         // elements between consecutive pixels
+        }
+        if (p.deq) {
+            float y[4][V];
 #pragma unroll
-            for (int i = 0; i < V; ++i) f[r][i] = i < nv ? finish_sum<EXTRA>(p, v[i], n, at + (size_t)(i * px)) : 0u;
-            if (EXTRA && p.chain.buf) {
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int i = 0; i < V; ++i) code[i] |= p.chain.code(__uint_as_float(f[r][i])) << (8 * r);
+                for (int i = 0; i < V; ++i) y[r][i] = (float)(int32_t)v[r][i] * sc[r];
+            if (p.bias) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) y[r][i] = y[r][i] + bi[r];
             }
-            if ((EXTRA && p.no_out) || (p.linear && (p.N & 3) == 0)) continue;      // nothing to store, or stored below
-            int32_t *const o = p.out + at;
-            if (V == 4 && nv == 4 && px == 1 && (reinterpret_cast<uintptr_t>(o) & 15u) == 0) {
-                *reinterpret_cast<uint4 *>(o) = make_uint4(f[r][0], f[r][1], f[r][V - 2], f[r][V - 1]);
-            } else if (V == 2 && nv == 2 && px == 1 && (reinterpret_cast<uintptr_t>(o) & 7u) == 0) {
-                *reinterpret_cast<uint2 *>(o) = make_uint2(f[r][0], f[r][1]);
-            } else {
+            if (p.resid) {
+                const float *const q = p.resid + at;
+                float t[4][V];
+                if (vec && V == 4 && (reinterpret_cast<uintptr_t>(p.resid) & 15u) == 0) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float4 f = *reinterpret_cast<const float4 *>(q + r * plane);
+                        t[r][0] = f.x; t[r][1] = f.y; t[r][V - 2] = f.z; t[r][V - 1] = f.w;
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int i = 0; i < V; ++i) t[r][i] = r < nch && i < nv ? q[r * plane + (size_t)(i * px)] : 0.0f;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) y[r][i] = y[r][i] + t[r][i];
+            }
+            if (p.act == 1) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) y[r][i] = y[r][i] > 0.0f ? y[r][i] : 0.0f;
+            } else if (LEVEL >= 2 && p.act == 2) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) y[r][i] = tanh_spec(y[r][i]);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int i = 0; i < V; ++i) v[r][i] = __float_as_uint(y[r][i]);
+            if (LEVEL >= 1 && p.chain.buf) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    uint32_t code = 0;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) code |= r < nch ? p.chain.code(y[r][i]) << (8 * r) : 0u;
+                    if (i < nv) p.chain.put4(img, cb, oy, ox + i * p.out_step, code);
+                }
+                if (p.no_out) continue;
+            }
+        }
+        int32_t *const o = p.out + at;
+        const bool al = (reinterpret_cast<uintptr_t>(p.out) & (V * 4 - 1)) == 0;
+        if (vec && al) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (V == 4) *reinterpret_cast<uint4 *>(o + r * plane) = make_uint4(v[r][0], v[r][1], v[r][V - 2], v[r][V - 1]);
+                else *reinterpret_cast<uint2 *>(o + r * plane) = make_uint2(v[r][0], v[r][1]);
+            }
+        } else if (vec_ch && (reinterpret_cast<uintptr_t>(p.out) & 15u) == 0) {
+#pragma unroll
+            for (int i = 0; i < V; ++i) *reinterpret_cast<uint4 *>(o + (size_t)(i * px)) = make_uint4(v[0][i], v[1][i], v[2][i], v[3][i]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int i = 0; i < V; ++i)
-                    if (i < nv) o[(size_t)(i * px)] = (int32_t)f[r][i];
-            }
-        }
-        if (p.linear && (p.N & 3) == 0) {           // four channels of a row are 16 contiguous bytes
-#pragma unroll
-            for (int i = 0; i < V; ++i)
-                if (i < nv) {
-                    int32_t *const o = p.out + (size_t)(b + i) * p.N + cb;
-                    if ((reinterpret_cast<uintptr_t>(o) & 15u) == 0) *reinterpret_cast<uint4 *>(o) = make_uint4(f[0][i], f[1][i], f[2][i], f[3][i]);
-                    else for (int r = 0; r < 4; ++r) o[r] = (int32_t)f[r][i];
-                }
-        }
-        if (EXTRA && p.chain.buf) {
-#pragma unroll
-            for (int i = 0; i < V; ++i)
-                if (i < nv) p.chain.put4(img, cb, oy, ox + i * p.out_step, code[i]);
+                    if (r < nch && i < nv) o[r * plane + (size_t)(i * px)] = (int32_t)v[r][i];
         }
     }
 }
 
 // DOPS: table copy operations per wave and step = copied lines * 256 B / (16 waves * 1 KB): 4 / 2 / 1 for 256 / 128 / <= 64
-// lines (fewer: one operation with fewer lanes).  R: pixels per row slot.  EXTRA: the epilogue also knows tanh, the border
-// terms of a transposed convolution and the next layer's input copy.
-template <int DOPS, int R, bool EXTRA>
+// lines (fewer: one operation with fewer lanes).  R: pixels per row slot.  LEVEL: see byte_epilogue.
+template <int DOPS, int R, int LEVEL>
 __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams p) {
     static_assert(R == 8 || R == 4 || R == 2, "pixels per row slot");
     constexpr int V = R < 4 ? R : 4;        // pixels per run: one load
     constexpr int NRUN = R / V;
     constexpr int NL = NRUN;                // activation loads per lane and step
     constexpr int NP = DOPS >= 2 ? 1 : 0;   // L2 prefetch loads per step (tables of one copy operation are not prefetched)
+    // Tables of up to 32 KB: four buffers, a table is copied three steps ahead.  64 KB: two buffers, one step ahead.
+    constexpr bool DEEP = DOPS <= 2;
+    constexpr int AHEAD = DEEP ? 3 : 1;
     constexpr int NACC = R < 4 ? 4 : R;     // accumulators: with two pixels, two each (reads t and t + 1 do not depend on each other)
     // 160 KB; the alignment puts the buffers at multiples of 64 KB, which the address arithmetic needs
     __shared__ __attribute__((aligned(BYTE_BUF))) uint4 tbl[2 * (BYTE_BUF / 16)];
@@ -307,13 +388,12 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     const int ks = (int)p.d_mtiles.div((uint32_t)rest);
     const int mt = rest - ks * p.m_tiles;
     const int8_t *const xt = p.xt + pick4(p.xt_off, ph);
-    const uint32_t lines = 1u << p.bits;
-    const uint32_t table_bytes = lines * BYTE_LINE;                         // distance between the tables of two steps
-    const uint32_t half_bytes = table_bytes >> 1;
-    const uint32_t neg_shift = BYTE_BUF - table_bytes;                      // lines of negative activations: end of the buffer
+    const uint32_t table_bytes = (uint32_t)BYTE_LINE << p.bits;             // distance between the tables of two steps
     const uint32_t copy_bytes = (uint32_t)p.copy_lines * BYTE_LINE;
-    const int s_begin = ks * p.gps;
-    const int nsteps = min(p.steps, s_begin + p.gps) - s_begin;
+    const uint32_t line_mask = (uint32_t)(p.copy_lines - 1) * 0x01010101u;  // activation byte -> line
+    const int s_begin = (int)p.d_ksplit.div((uint32_t)(ks * p.even));
+    const int nsteps = (ks + 1 < p.ksplit ? (int)p.d_ksplit.div((uint32_t)((ks + 1) * p.even)) : p.steps) - s_begin;
+    const bool live = (mt * BYTE_ROW_SLOTS + wave * 16) * R < p.Mv;         // some row of this wave exists
     const size_t first_table = (size_t)(ph * p.n_tiles + nt) * p.steps + s_begin;
     const unsigned char *const dt = reinterpret_cast<const unsigned char *>(p.dt) + first_table * table_bytes;
     const int8_t *const wx = p.wx + first_table * (BYTE_TILE * BYTE_STEP);
@@ -327,44 +407,6 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     // (8-bit tables: workgroup number `rest` of a tile and phase starts two chunks further on than its predecessor, so that
     // the workgroups that stream one table do not all ask L2 for the same lines at the same moment)
     const uint32_t dma_rot = DOPS == 4 ? (uint32_t)rest * 2u : 0u;
-    // Past the end of the slice there is nothing to copy; without newer operations to count, the wave then waits for
-    // everything it has in flight.  (One asm statement: the branch stays inside it.)
-    auto dma = [&](int step, int buf) {
-        const unsigned char *src[DOPS];
-        uint32_t to[DOPS];
-#pragma unroll
-        for (int o = 0; o < DOPS; ++o) {
-            const uint32_t chunk = DOPS == 4 ? ((uint32_t)(o * 16 + wave) + dma_rot) & 63u : (uint32_t)(o * 16 + wave);
-            const uint32_t at = DOPS > 1 ? chunk * 1024u : (uint32_t)(wave * lanes_act) * 16u;
-            src[o] = dt + (size_t)(unsigned)step * table_bytes + at;
-            to[o] = lds_tbl + (uint32_t)buf * BYTE_BUF + at + (at >= half_bytes ? neg_shift : 0u);
-        }
-        uint64_t save;
-#define BYTE_COPY_BEGIN "s_cmp_lt_i32 %[st], %[ns]\n\ts_cbranch_scc0 .Lbyte_none%=\n\ts_mov_b64 %[sv], exec\n\ts_mov_b64 exec, %[mk]\n\t"
-#define BYTE_COPY_OP(i) "s_mov_b32 m0, %[t" #i "]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[vo], %[a" #i "]\n\t"
-#define BYTE_COPY_END "s_mov_b64 exec, %[sv]\n\ts_branch .Lbyte_done%=\n.Lbyte_none%=:\n\ts_waitcnt vmcnt(0)\n.Lbyte_done%=:"
-        if constexpr (DOPS == 4)
-            asm volatile(BYTE_COPY_BEGIN BYTE_COPY_OP(0) BYTE_COPY_OP(1) BYTE_COPY_OP(2) BYTE_COPY_OP(3) BYTE_COPY_END
-                         : [sv] "=&s"(save)
-                         : [vo] "v"(dma_voff), [mk] "s"(dma_mask), [st] "s"(step), [ns] "s"(nsteps), [a0] "s"(src[0]), [t0] "s"(to[0]), [a1] "s"(src[1]),
-                           [t1] "s"(to[1]), [a2] "s"(src[2]), [t2] "s"(to[2]), [a3] "s"(src[3]), [t3] "s"(to[3])
-                         : "memory", "scc");
-        else if constexpr (DOPS == 2)
-            asm volatile(BYTE_COPY_BEGIN BYTE_COPY_OP(0) BYTE_COPY_OP(1) BYTE_COPY_END
-                         : [sv] "=&s"(save)
-                         : [vo] "v"(dma_voff), [mk] "s"(dma_mask), [st] "s"(step), [ns] "s"(nsteps), [a0] "s"(src[0]), [t0] "s"(to[0]), [a1] "s"(src[1]),
-                           [t1] "s"(to[1])
-                         : "memory", "scc");
-        else
-            asm volatile(BYTE_COPY_BEGIN BYTE_COPY_OP(0) BYTE_COPY_END
-                         : [sv] "=&s"(save)
-                         : [vo] "v"(dma_voff), [mk] "s"(dma_mask), [st] "s"(step), [ns] "s"(nsteps), [a0] "s"(src[0]), [t0] "s"(to[0])
-                         : "memory", "scc");
-#undef BYTE_COPY_BEGIN
-#undef BYTE_COPY_OP
-#undef BYTE_COPY_END
-    };
-
     // L2 prefetch: a table is new to the L2 that serves it, so each of up to 32 workgroups that stream it at about the same
     // time touches its share of the 128-byte lines BYTE_PF_DIST steps ahead of the copy, one plain load per wave (the
     // result is never used).
@@ -382,6 +424,58 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
         asm volatile("global_load_dword %[d], %[vo], %[sa]" : [d] "+v"(pf_sink) : [vo] "v"(pf_voff), [sa] "s"(dt + (size_t)(unsigned)at * table_bytes));
     };
 
+    // Past the end of the slice there is nothing to copy.  DEEP: as many small loads are issued instead, so that the counted
+    // waits stay the same (nothing waits for them in particular).  Two buffers: the wave waits for everything it has in
+    // flight, which is little more than the activations it needs next.  (One asm statement: the branch stays inside it.)
+    // (first_c: the first table, which always exists - no load then targets pf_sink while the compiler still computes addresses)
+    auto dma = [&](int step, int buf, auto first_c, uint32_t &sink) {
+        constexpr bool FIRST = decltype(first_c)::value;
+        const unsigned char *src[DOPS];
+        uint32_t to[DOPS];
+#pragma unroll
+        for (int o = 0; o < DOPS; ++o) {
+            const uint32_t chunk = DOPS == 4 ? ((uint32_t)(o * 16 + wave) + dma_rot) & 63u : (uint32_t)(o * 16 + wave);
+            const uint32_t at = DOPS > 1 ? chunk * 1024u : (uint32_t)(wave * lanes_act) * 16u;
+            src[o] = dt + (size_t)(unsigned)step * table_bytes + at;
+            to[o] = lds_tbl + (uint32_t)buf * (DEEP ? BYTE_BUF / 2 : BYTE_BUF) + at;
+        }
+        uint64_t save;
+        const uint32_t po = pf_voff;        // (named here: asm operands inside the branches below do not capture)
+        const int ns = nsteps;
+#define BYTE_COPY_BEGIN "s_cmp_lt_i32 %[st], %[ns]\n\ts_cbranch_scc0 .Lbyte_none%=\n\ts_mov_b64 %[sv], exec\n\ts_mov_b64 exec, %[mk]\n\t"
+#define BYTE_COPY_OP(i) "s_mov_b32 m0, %[t" #i "]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[vo], %[a" #i "]\n\t"
+#define BYTE_NO_COPY "global_load_dword %[sk], %[po], %[tb]\n\t"
+#define BYTE_COPY_END(ops) "s_mov_b64 exec, %[sv]\n\ts_branch .Lbyte_done%=\n.Lbyte_none%=:\n\t" ops ".Lbyte_done%=:"
+        if constexpr (FIRST) {
+#pragma unroll
+            for (int o = 0; o < DOPS; ++o)
+                asm volatile("s_mov_b64 %[sv], exec\n\ts_mov_b64 exec, %[mk]\n\t" BYTE_COPY_OP(0) "s_mov_b64 exec, %[sv]"
+                             : [sv] "=&s"(save)
+                             : [vo] "v"(dma_voff), [mk] "s"(dma_mask), [a0] "s"(src[o]), [t0] "s"(to[o])
+                             : "memory");
+        } else if constexpr (DOPS == 4)
+            asm volatile(BYTE_COPY_BEGIN BYTE_COPY_OP(0) BYTE_COPY_OP(1) BYTE_COPY_OP(2) BYTE_COPY_OP(3) BYTE_COPY_END("s_waitcnt vmcnt(0)\n")
+                         : [sv] "=&s"(save), [sk] "+v"(sink)
+                         : [vo] "v"(dma_voff), [po] "v"(po), [tb] "s"(dt), [mk] "s"(dma_mask), [st] "s"(step), [ns] "s"(ns), [a0] "s"(src[0]), [t0] "s"(to[0]), [a1] "s"(src[1]),
+                           [t1] "s"(to[1]), [a2] "s"(src[2]), [t2] "s"(to[2]), [a3] "s"(src[3]), [t3] "s"(to[3])
+                         : "memory", "scc");
+        else if constexpr (DOPS == 2)
+            asm volatile(BYTE_COPY_BEGIN BYTE_COPY_OP(0) BYTE_COPY_OP(1) BYTE_COPY_END(BYTE_NO_COPY BYTE_NO_COPY)
+                         : [sv] "=&s"(save), [sk] "+v"(sink)
+                         : [vo] "v"(dma_voff), [po] "v"(po), [tb] "s"(dt), [mk] "s"(dma_mask), [st] "s"(step), [ns] "s"(ns), [a0] "s"(src[0]), [t0] "s"(to[0]), [a1] "s"(src[1]),
+                           [t1] "s"(to[1])
+                         : "memory", "scc");
+        else
+            asm volatile(BYTE_COPY_BEGIN BYTE_COPY_OP(0) BYTE_COPY_END(BYTE_NO_COPY)
+                         : [sv] "=&s"(save), [sk] "+v"(sink)
+                         : [vo] "v"(dma_voff), [po] "v"(po), [tb] "s"(dt), [mk] "s"(dma_mask), [st] "s"(step), [ns] "s"(ns), [a0] "s"(src[0]), [t0] "s"(to[0])
+                         : "memory", "scc");
+#undef BYTE_COPY_BEGIN
+#undef BYTE_COPY_OP
+#undef BYTE_COPY_END
+#undef BYTE_NO_COPY
+    };
+
     // byte offset of flat channel group f inside a window
     const int groups = p.taps * p.cg;
     auto group_off = [&](int f) -> uint32_t {
@@ -392,7 +486,7 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
         const uint32_t xo = (uint32_t)(kx * p.dw), xs = p.d_sw.div(xo), xr = xo - xs * p.d_sw.d;
         return (uint32_t)(c * p.ch_stride + ky * p.ky_stride) + 4u * (xr * (uint32_t)p.wsub + xs);
     };
-    dma(0, 0);
+    dma(0, 0, std::true_type{}, pf_sink);
     for (int i = tid; i < nsteps * 4 + 8; i += BYTE_THREADS) goff[i] = group_off(s_begin * 4 + i);
 
     // runs of V consecutive pixels of one output row
@@ -405,11 +499,12 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     }
     typedef typename std::conditional<V == 4, b32x4_t, b32x2_t>::type run_t;
     auto load_acts = [&](run_t (&w)[NRUN], uint32_t off) {
+        const int8_t *const from = xt;
 #pragma unroll
         for (int i = 0; i < NRUN; ++i) {
             const uint32_t at = base[i] + off;
-            if constexpr (V == 4) asm volatile("global_load_dwordx4 %[v], %[b], %[xr]" : [v] "+v"(w[i]) : [b] "v"(at), [xr] "s"(xt));
-            else asm volatile("global_load_dwordx2 %[v], %[b], %[xr]" : [v] "+v"(w[i]) : [b] "v"(at), [xr] "s"(xt));
+            if constexpr (V == 4) asm volatile("global_load_dwordx4 %[v], %[b], %[xr]" : [v] "+v"(w[i]) : [b] "v"(at), [xr] "s"(from));
+            else asm volatile("global_load_dwordx2 %[v], %[b], %[xr]" : [v] "+v"(w[i]) : [b] "v"(at), [xr] "s"(from));
         }
     };
 
@@ -429,6 +524,7 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     // Address pieces.  Column word for read t in buffer u: byte 0 = slot * 16, byte 2 = buffer.  Selector: result byte 0 =
     // column byte 0, byte 1 = activation byte e, byte 2 = column byte 2, byte 3 = 0 (bytes of the first source of
     // v_perm_b32 are numbered 4..7, those of the second 0..3, 0x0c gives zero).
+    // (DEEP: buffers 2 u and 2 u + 1 share a column word, the odd one is a constant offset of 32 KB away)
     uint32_t colw[2][4], sel[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -441,23 +537,6 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     const uint32_t wx_voff = (uint32_t)(q * (BYTE_TILE * BYTE_STEP) + rl * BYTE_STEP);
     const bool bit0 = rl & 1, bit1 = rl & 2;
 
-    // one step's reads: read t of the R pixels, t = 0..3, four in flight
-    auto run_step = [&](auto uc, const run_t (&w)[NRUN]) {
-        constexpr int u = decltype(uc)::value;
-        constexpr int NR = 4 * R;
-        auto word = [&](int i) { return w[i / V][i % V]; };
-#pragma unroll
-        for (int n = 0; n < 4; ++n) byte_fetch(rv[n], word(n % R), colw[u][n / R], sel[n / R]);
-#pragma unroll
-        for (int n = 0; n < NR - 4; ++n) {
-            byte_add<3>(acc[n % NACC], rv[n & 3], ones);
-            byte_fetch(rv[n & 3], word((n + 4) % R), colw[u][(n + 4) / R], sel[(n + 4) / R]);
-        }
-        byte_add<3>(acc[(NR - 4) % NACC], rv[0], ones);
-        byte_add<2>(acc[(NR - 3) % NACC], rv[1], ones);
-        byte_add<1>(acc[(NR - 2) % NACC], rv[2], ones);
-        byte_add<0>(acc[(NR - 1) % NACC], rv[3], ones);
-    };
     // behind a wait: what the loads have written is not read, moved or copied any earlier
     auto settle = [&]() {
 #pragma unroll
@@ -466,89 +545,139 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
             for (int i = 0; i < NRUN; ++i) asm volatile("" : "+v"(W[k][i]));
         asm volatile("" : "+v"(wa));
     };
-    // the exact product of the four steps whose words are in W (see the head of this file)
-    auto exact = [&]() {
+    // the exact product of the four steps whose words are in W, for pixel i of the slot (see the head of this file)
+    auto exact = [&](int i) {
+        auto s01 = __builtin_amdgcn_permlane16_swap(W[0][i / V][i % V], W[1][i / V][i % V], false, false);
+        auto s23 = __builtin_amdgcn_permlane16_swap(W[2][i / V][i % V], W[3][i / V][i % V], false, false);
+        const uint32_t x0 = bit0 ? s01[1] : s01[0], x1 = bit0 ? s01[0] : s01[1];
+        const uint32_t y0 = bit0 ? s23[1] : s23[0], y1 = bit0 ? s23[0] : s23[1];
+        auto e0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);       // groups with low bit 0
+        auto e1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);       // low bit 1
+        bi32x4_t b;
+        b.x = (int)(bit1 ? e0[1] : e0[0]);
+        b.y = (int)(bit1 ? e1[1] : e1[0]);
+        b.z = (int)(bit1 ? e0[0] : e0[1]);
+        b.w = (int)(bit1 ? e1[0] : e1[1]);
+        if constexpr (LEVEL == 3) {
 #pragma unroll
-        for (int i = 0; i < R; ++i) {
-            auto s01 = __builtin_amdgcn_permlane16_swap(W[0][i / V][i % V], W[1][i / V][i % V], false, false);
-            auto s23 = __builtin_amdgcn_permlane16_swap(W[2][i / V][i % V], W[3][i / V][i % V], false, false);
-            const uint32_t x0 = bit0 ? s01[1] : s01[0], x1 = bit0 ? s01[0] : s01[1];
-            const uint32_t y0 = bit0 ? s23[1] : s23[0], y1 = bit0 ? s23[0] : s23[1];
-            auto e0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);       // groups with low bit 0
-            auto e1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);       // low bit 1
-            bi32x4_t b;
-            b.x = (int)((bit1 ? e0[1] : e0[0]) & p.amask);
-            b.y = (int)((bit1 ? e1[1] : e1[0]) & p.amask);
-            b.z = (int)((bit1 ? e0[0] : e0[1]) & p.amask);
-            b.w = (int)((bit1 ? e1[0] : e1[1]) & p.amask);
-            asm volatile("s_nop 1\n\tv_mfma_i32_16x16x64_i8 %[d], %[a], %[b], %[d]" : [d] "+v"(acc[i]) : [a] "v"(wa), [b] "v"(b));
+            for (int j = 0; j < 4; ++j) b[j] &= (int)p.amask;
         }
+        asm volatile("s_nop 1\n\tv_mfma_i32_16x16x64_i8 %[d], %[a], %[b], %[d]" : [d] "+v"(acc[i]) : [a] "v"(wa), [b] "v"(b));
     };
 
-    // Step k of a group, step s of the slice.  Memory operations a wave issues, in this order: DOPS copy operations of the
-    // next step's table, then NX[k]: NL activation loads of the next step, (k = 0) the group's weights, the prefetch.
-    // A wave's memory operations retire in order, which is what the counted waits rely on.
+    // one step's reads: read t of the R pixels, t = 0..3, four in flight
+    auto run_step = [&](auto bc, const run_t (&w)[NRUN]) {
+        constexpr int buf = decltype(bc)::value, u = DEEP ? buf >> 1 : buf, off = DEEP && (buf & 1) ? BYTE_BUF / 2 : 0;
+        constexpr int NR = 4 * R;
+        uint32_t word[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) word[i] = DEEP ? w[i / V][i % V] & line_mask : w[i / V][i % V];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) byte_fetch<off>(rv[n], word[n % R], colw[u][n / R], sel[n / R]);
+#pragma unroll
+        for (int n = 0; n < NR - 4; ++n) {
+            byte_add<3>(acc[n % NACC], rv[n & 3], ones);
+            byte_fetch<off>(rv[n & 3], word[(n + 4) % R], colw[u][(n + 4) / R], sel[(n + 4) / R]);
+        }
+        byte_add<3>(acc[(NR - 4) % NACC], rv[0], ones);
+        byte_add<2>(acc[(NR - 3) % NACC], rv[1], ones);
+        byte_add<1>(acc[(NR - 2) % NACC], rv[2], ones);
+        byte_add<0>(acc[(NR - 1) % NACC], rv[3], ones);
+    };
+
+    // Step k of a group, step s of the slice.  A wave's memory operations retire in order, which is what the counted waits
+    // rely on.  Per step it issues
+    //   DEEP:      NL activation loads of the next step, (k = 0) the group's weights, DOPS copy operations of the table three
+    //              steps ahead, the prefetch.  Waiting for a step's activations then means that the next table has landed too
+    //              and leaves the two after it in flight; the step ends with a barrier alone.
+    //   two bufs:  DOPS copy operations of the next table, NL loads, (k = 0) the weights, the prefetch.  The step ends when
+    //              this wave's part of the copy has landed; the newer loads stay in flight across the barrier.
+    // In the last step of a group the exact product comes first: the next loads go where its words are.
     uint32_t gv = 0;                        // group offset of the next step
     uint32_t gaddr = (uint32_t)(uintptr_t)(lds_ptr_t)goff + (uint32_t)g * 4u + 32u;         // that of the step after it
     auto step = [&](auto kc, int s) {
         constexpr int k = decltype(kc)::value;
-        constexpr int nx = NL + NP + (k == 0 ? 1 : 0);
-        constexpr int newer = NP + (k == 1 ? 1 : 0);        // operations of the previous step issued after its activation loads
-        dma(s + 1, (k + 1) & 1);
-        if constexpr (k == 3) {             // the next loads go where the words of the group's first step are
-            asm volatile("s_waitcnt vmcnt(%0)" : : "n"(newer + DOPS) : "memory");
+        constexpr int nx = NL + NP + (k == 0 ? 1 : 0);      // operations of a step besides the copies
+        constexpr int newer = NP + (k == 1 ? 1 : 0) + (DEEP ? DOPS : 0);    // of the previous step, issued after its activation loads
+        if constexpr (!DEEP) dma(s + 1, (k + 1) & 1, std::false_type{}, pf_sink);
+        if constexpr (k == 3) {
+            asm volatile("s_waitcnt vmcnt(%0)" : : "n"(newer + (DEEP ? 0 : DOPS)) : "memory");
             settle();
-            exact();
+#pragma unroll
+            for (int i = 0; i < R; ++i) exact(i);
         }
         load_acts(W[(k + 1) & 3], gv);
-        if constexpr (k == 0)
-            asm volatile("global_load_dwordx4 %[v], %[o], %[sa]" : [v] "+v"(wa) : [o] "v"(wx_voff), [sa] "s"(wx + (size_t)(unsigned)s * (BYTE_TILE * BYTE_STEP)));
+        if constexpr (k == 0) {
+            const int8_t *const from = wx + (size_t)(unsigned)s * (BYTE_TILE * BYTE_STEP);
+            asm volatile("global_load_dwordx4 %[v], %[o], %[sa]" : [v] "+v"(wa) : [o] "v"(wx_voff), [sa] "s"(from));
+        }
         asm volatile("ds_read_b32 %[d], %[a]" : [d] "+v"(gv) : [a] "v"(gaddr));
         gaddr += 16u;
-        prefetch(s + 1 + BYTE_PF_DIST);
-        if constexpr (k != 3) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(newer + DOPS + nx) : "memory");
-        run_step(std::integral_constant<int, (k & 1)>{}, W[k]);
-        // end of a step: this wave's part of the next table has landed; the newer loads stay in flight across the barrier
-        asm volatile("s_waitcnt vmcnt(%[nx])\n\ts_barrier" : [g] "+v"(gv) : [nx] "n"(nx) : "memory");
+        if constexpr (DEEP) dma(s + AHEAD, (k + AHEAD) & 3, std::false_type{}, pf_sink);
+        prefetch(s + AHEAD + BYTE_PF_DIST);
+        if constexpr (k != 3) {
+            asm volatile("s_waitcnt vmcnt(%0)" : : "n"(newer + DOPS + nx) : "memory");
+#pragma unroll
+            for (int i = 0; i < NRUN; ++i) asm volatile("" : "+v"(W[k][i]));
+        }
+        run_step(std::integral_constant<int, DEEP ? k : (k & 1)>{}, W[k]);
+        if constexpr (DEEP) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : [g] "+v"(gv) : : "memory");
+        else asm volatile("s_waitcnt vmcnt(%[nx]) lgkmcnt(0)\n\ts_barrier" : [g] "+v"(gv) : [nx] "n"(nx) : "memory");
     };
     using std::integral_constant;
 
-    // prologue: table, activations and offsets of the first step
-#pragma unroll
-    for (int d = 1; d <= BYTE_PF_DIST; ++d) prefetch(d);
+    // prologue: offsets, table and activations of the first step; DEEP: the next two tables are on their way
     load_acts(W[0], group_off(s_begin * 4 + g));
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" : : : "memory");
+    if constexpr (DEEP) {
+        dma(1, 1, std::false_type{}, pf_sink);
+        dma(2, 2, std::false_type{}, pf_sink);
+    }
+#pragma unroll
+    for (int d = 0; d < BYTE_PF_DIST; ++d) prefetch(AHEAD + d);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((DEEP ? 2 * DOPS : 0) + NP * BYTE_PF_DIST) : "memory");
     gv = goff[4 + g];
     asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(gv) : : "memory");
 
-    int s = 0;
-    for (; s + 4 <= nsteps; s += 4) {
-        step(integral_constant<int, 0>{}, s);
-        step(integral_constant<int, 1>{}, s + 1);
-        step(integral_constant<int, 2>{}, s + 2);
-        step(integral_constant<int, 3>{}, s + 3);
-    }
-    const int left = nsteps - s;
-    if (left > 0) {
-        step(integral_constant<int, 0>{}, s);
-        if (left > 1) {
+    if (live) {
+        int s = 0;
+        for (; s + 4 <= nsteps; s += 4) {
+            step(integral_constant<int, 0>{}, s);
             step(integral_constant<int, 1>{}, s + 1);
-            if (left > 2) step(integral_constant<int, 2>{}, s + 2);
+            step(integral_constant<int, 2>{}, s + 2);
+            step(integral_constant<int, 3>{}, s + 3);
         }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");                      // retire what is still in flight
-    asm volatile("" : : "v"(pf_sink));
-    if (left > 0) {                         // the last, incomplete group: no weights for the steps it does not have
-        settle();
-        if (q >= left) wa = bi32x4_t{0, 0, 0, 0};
-        exact();
-    }
-
-    // the last matrix instructions have to leave the pipe before a vector instruction reads their registers (every
-    // accumulator passes through an asm statement behind the waiting one, so that no read can be scheduled ahead of it)
-    asm volatile("s_nop 15\n\ts_nop 15" : : : "memory");
+        const int left = nsteps - s;
+        if (left > 0) {
+            step(integral_constant<int, 0>{}, s);
+            if (left > 1) {
+                step(integral_constant<int, 1>{}, s + 1);
+                if (left > 2) step(integral_constant<int, 2>{}, s + 2);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");                  // retire what is still in flight
+        if (left > 0) {                     // the last, incomplete group: no weights for the steps it does not have
+            settle();
+            if (q >= left) wa = bi32x4_t{0, 0, 0, 0};
 #pragma unroll
-    for (int i = 0; i < NACC; ++i) asm volatile("" : "+v"(acc[i]));
+            for (int i = 0; i < R; ++i) exact(i);
+        }
+        // the last matrix instructions have to leave the pipe before a vector instruction reads their registers (every
+        // accumulator passes through an asm statement behind the waiting one, so that no read can be scheduled ahead of it)
+        asm volatile("s_nop 15\n\ts_nop 15" : : : "memory");
+#pragma unroll
+        for (int i = 0; i < NACC; ++i) asm volatile("" : "+v"(acc[i]));
+    } else {                                // no row of this wave exists: it copies its part of the tables
+        uint32_t sink = 0;
+        for (int s = 0; s < nsteps; ++s) {
+            dma(s + AHEAD, DEEP ? (s + AHEAD) & 3 : (s + 1) & 1, std::false_type{}, sink);
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(DEEP ? 2 * DOPS : 0) : "memory");
+        }
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        asm volatile("" : : "v"(sink));
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");      // (for the prefetch loads of either branch)
+    asm volatile("" : : "v"(pf_sink));
+
     if constexpr (NACC > R) {
 #pragma unroll
         for (int i = 0; i < R; ++i) acc[i] += acc[i + R];
@@ -558,7 +687,20 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     // they would not fit.
     const __attribute__((address_space(4))) ByteParams *args = (const __attribute__((address_space(4))) ByteParams *)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));
-    byte_epilogue<R, EXTRA>(*(const ByteParams *)args, acc, goff, tid, nt, ph, mt, ks);
+    const ByteParams &pe = *(const ByteParams *)args;
+    // (requested before the slices are joined: the values travel meanwhile)
+    const int cb = nt * BYTE_TILE + 4 * q;
+    float sc[4] = {pe.scale, pe.scale, pe.scale, pe.scale}, bi[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (pe.scales) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sc[r] = pe.scales[min(cb + r, pe.N - 1)];
+    }
+    if (pe.bias) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bi[r] = pe.bias[min(cb + r, pe.N - 1)];
+    }
+    if (pe.ksplit > 1 && !byte_join_slices<R>(pe, acc, goff, tid, (ph * pe.m_tiles + mt) * pe.n_tiles + nt, ks, live)) return;
+    if (cb < pe.N) byte_epilogue<R, LEVEL>(pe, acc, sc, bi, mt, rs, ph, cb);
 }
 
 // ------------------------------------------------------------------------------------------------ packing

@@ -73,12 +73,12 @@ def _check_function(fn, body, report):
     memory operations in flight (destination registers of those issued from asm), and the accumulators of matrix
     instructions issued from asm that have not been drained.  Where paths meet, the states are merged entry by entry
     (what MAY be in flight), so the check errs on the side of reporting."""
-    prog, labels = [], {}
+    prog, labels, inside = [], {}, False         # (an asm statement may hold branches and labels of its own)
     for ln, s in body:
         if s.startswith(';;#ASMSTART'):
-            prog.append((ln, 'asm+', '', '')); continue
+            inside = True; continue
         if s.startswith(';;#ASMEND'):
-            prog.append((ln, 'asm-', '', '')); continue
+            inside = False; continue
         if not s or s.startswith((';', '.')) and not re.match(r'^[.\w$]+:', s):
             continue
         code = s.split(';')[0].strip()
@@ -87,14 +87,13 @@ def _check_function(fn, body, report):
         if re.match(r'^[.\w$]+:$', code):
             labels[code[:-1]] = len(prog); continue
         op = code.split()[0]
-        prog.append((ln, 'i', op, code[len(op):]))
+        prog.append((ln, inside, op, code[len(op):]))
     state_in_points = set(labels.values())       # where blocks begin
     state_in = {0: ((), (), frozenset())}
     work = [0]
     while work:
         pc = work.pop()
         lq, vq, mf = state_in[pc]
-        in_asm = False
 
         def flow(to):
             old = state_in.get(to)
@@ -109,12 +108,8 @@ def _check_function(fn, body, report):
                 flow(pc)          # fall through into a block that other paths enter as well
                 break
             first = False
-            ln, kind, op, args = prog[pc]
+            ln, in_asm, op, args = prog[pc]
             pc += 1
-            if kind == 'asm+':
-                in_asm = True; continue
-            if kind == 'asm-':
-                in_asm = False; continue
             code = op + args
             if op == 's_endpgm':
                 break
