@@ -8,6 +8,8 @@
 // distribution reaches), which the vector L1 and the L2 serve.  The function form evaluates the multiplier in the
 // vector ALU and needs no memory at all; it covers operands of up to 16 bits.
 //
+// Tables of 9 to 12 bits that are an exact product plus an error of 16 bits are served by lut_cols.hpp instead.
+//
 // One kernel template serves both: lanes along the GEMM rows (output pixels), NT output channels per lane; per inner index
 // the lane loads one activation and the NT weight words arrive through scalar loads (pre-packed [K][Npad] int32: element
 // offset of the weight's table row, or the weight itself for the function form).  No LDS.
