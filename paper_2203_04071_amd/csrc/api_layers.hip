@@ -172,12 +172,8 @@ int run_rows(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *ou
         HIP_TRY(hipGetLastError());
         return ADAPT_OK;
     }
-    // tile shape: prefer 16 outputs per lane; shrink the tile until the grid covers the chip
-    const int cu = device_cus();
-    int NT = 16, MT = 1024;
-    auto wgs = [&](int nt, int mt) { return (long long)((g.M + mt - 1) / mt) * ((g.N + nt - 1) / nt) * ngroups; };
-    while (MT > 64 && (MT / 2 >= g.M || (wgs(NT, MT) < cu && Ktot / (adapt::ROWS_THREADS / (MT / 2)) >= 16))) MT /= 2;
-    if ((wgs(NT, MT) < cu && g.N > 8) || (ngroups > 1 && g.N <= 8)) NT = 8;
+    const RowsShape shape = rows_shape(g.M, g.N, Ktot, ngroups, device_cus());
+    int NT = shape.NT, MT = shape.MT;
     if (lstm) { NT = lstm->kind == 2 ? 6 : (lstm->kind == 3 ? 2 : 8); MT = 64; }    // the cell epilogue sits in the split-K reduction: all gates of two units
     const int KS = adapt::ROWS_THREADS / MT;
     const int Npad = prepacked ? prepacked_npad : ((g.N + NT - 1) / NT) * NT;
@@ -953,7 +949,8 @@ int with_temp_tables(const adapt_lut *lut, const int8_t *w, const LinesShape &q,
 }
 
 // The lines path pays K*N*2^b table entries of packing and streams them once per 128*R rows:
-// worth it from a few thousand rows on.
+// worth it from a few thousand rows on.  (With tables of the byte form, linear layers with fewer rows go by an estimate
+// instead: byte_pays.  Convolutions with plain weights do not: below 4096 pixels both kinds took the same time, 28 to 50 us.)
 constexpr int LINES_MIN_ROWS = 4096;
 
 int check_lut(const adapt_lut *lut, const char *who) {
@@ -1047,12 +1044,15 @@ int adapt_approx_linear(const adapt_lut *lut, const int8_t *a_dev, const int8_t 
     g.mode = adapt::MODE_GEMM; g.M = M; g.N = N; g.Cin = K; g.taps = 1; g.kw = 1;
     g.H = 1; g.W = 1; g.Wo = 1; g.HoWo = 1; g.sh = g.sw = g.dh = g.dw = 1; g.ph = g.pw = 0;
     g.kstride = 1; g.img_stride = K;
-    if (M >= LINES_MIN_ROWS && K >= 8 && lut->byte_form) {
+    if (lut->byte_form && K >= 8) {
         const ByteShape q = byte_shape(lut->bits, N, K, 1, 1);
-        if (byte_packable(q, (size_t)4 << 30) && (long long)q.cg * 4 * (M + 4) < 0x7fffff00LL)
-            return with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
+        if (byte_packable(q, (size_t)4 << 30) && (long long)q.cg * 4 * (M + 4) < 0x7fffff00LL && (M >= LINES_MIN_ROWS || byte_call_pays(lut, q, M, true))) {
+            rc = with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
                 return byte_linear(lut, t, q, a_dev, acc_dev, M, (hipStream_t)stream, nullptr, nullptr);
             });
+            if (rc != ADAPT_ERR_OUT_OF_MEMORY || M >= LINES_MIN_ROWS) return rc;        // (no room for tables: the whole-table kernel needs little)
+            (void)hipGetLastError();
+        }
     }
     if (M >= LINES_MIN_ROWS && K >= 8) {
         const LinesShape q = lines_shape(0, lut->bits, N, K, 1, 1);
@@ -1437,7 +1437,7 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
         return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: bad argument", who);
     int k = 0, rpw = 0, ks = 1, st = 0, wg = 0;
     const bool phased = kind == 2 && kh % stride == 0 && kw % stride == 0;
-    if (rows < LINES_MIN_ROWS && kind == 0) {
+    if (kind == 0 && rows < LINES_MIN_ROWS && (storage != 2 || !byte_pays(byte_shape(bits, Cout, Cin, 1, 1), bits, 0, rows, false, cu))) {
         k = -1;                                 // whole-table kernel (lut_rows_kernel)
     } else if (kind == 2 && !phased) {
         k = -1;
@@ -1465,6 +1465,19 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
     return ADAPT_OK;
 }
 
+// Whether M rows of a packed linear layer go to the whole-table kernel: too few to amortise streaming the derived tables.  (A
+// call that is being recorded and that has not run at this size before may not allocate what the byte kernel needs.)
+static bool linear_on_rows(const adapt_weights *h, int M, hipStream_t s) {
+    if (M >= LINES_MIN_ROWS) return false;
+    if (!h->byte_form) return true;
+    const ByteShape q = byte_shape_of(h);
+    if (!byte_call_pays(h->lut, q, M, false)) return true;
+    if (h->ws.bytes >= byte_linear_bytes(q, h->bits, M)) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
+}
+
 int adapt_approx_linear_packed(const adapt_weights *h, const int8_t *a_dev, int32_t *acc_dev, int M, void *stream) {
     int rc = check_weights(h, 0, "adapt_approx_linear_packed");
     if (rc) return rc;
@@ -1473,14 +1486,20 @@ int adapt_approx_linear_packed(const adapt_weights *h, const int8_t *a_dev, int3
     if (!a_dev || !acc_dev) return fail(ADAPT_ERR_INVALID_ARGUMENT, "adapt_approx_linear_packed: NULL pointer");
     if ((long long)M * h->Cp >= 0x7fffff00LL || (long long)M * h->N > 0x7fffffffLL)
         return fail(ADAPT_ERR_UNSUPPORTED, "adapt_approx_linear_packed: tensor with more than 2^31-1 elements");
-    if (M < LINES_MIN_ROWS) {       // too few rows to amortise streaming the derived tables: whole-table kernel
+    bool rows = linear_on_rows(h, M, (hipStream_t)stream);
+    if (h->byte_form && !rows) {
+        rc = byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), a_dev, acc_dev, M, (hipStream_t)stream, &h->ws, nullptr);
+        if (rc != ADAPT_ERR_OUT_OF_MEMORY || M >= LINES_MIN_ROWS) return rc;
+        (void)hipGetLastError();
+        rows = true;                // (no room for the copy: the whole-table kernel needs none)
+    }
+    if (rows) {
         Geometry g{};
         g.mode = adapt::MODE_GEMM; g.M = M; g.N = h->N; g.Cin = h->Cin; g.taps = 1; g.kw = 1;
         g.H = 1; g.W = 1; g.Wo = 1; g.HoWo = 1; g.sh = g.sw = g.dh = g.dw = 1; g.ph = g.pw = 0;
         g.kstride = 1; g.img_stride = h->Cin;
         return run_rows(h->lut, a_dev, nullptr, acc_dev, g, (hipStream_t)stream, h->wofs_dev, h->wofs_npad);
     }
-    if (h->byte_form) return byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), a_dev, acc_dev, M, (hipStream_t)stream, &h->ws, nullptr);
     return lines_linear(h->bits, h->storage, shape_of(h), h->dt_dev, a_dev, acc_dev, M, (hipStream_t)stream, &h->ws, nullptr, h);
 }
 
@@ -1542,7 +1561,14 @@ int adapt_linear_layer_f32(const adapt_weights *h, const float *x_dev, float *y_
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: tensor with more than 2^31-1 elements", who);
     hipStream_t s = (hipStream_t)stream;
     int32_t *out = reinterpret_cast<int32_t *>(y_dev);
-    if (M < LINES_MIN_ROWS) {
+    bool rows = linear_on_rows(h, M, s);
+    if (h->byte_form && !rows) {
+        rc = byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), nullptr, out, M, s, &h->ws, &io);
+        if (rc != ADAPT_ERR_OUT_OF_MEMORY || M >= LINES_MIN_ROWS) return rc;
+        (void)hipGetLastError();
+        rows = true;                // (no room for copy and partial sums: the whole-table kernel needs less)
+    }
+    if (rows) {
         int8_t *q = nullptr;
         if ((rc = quantize_into_ws(h, io, (size_t)M * h->Cin, s, &q))) return rc;
         Geometry g{};
@@ -1551,7 +1577,6 @@ int adapt_linear_layer_f32(const adapt_weights *h, const float *x_dev, float *y_
         g.kstride = 1; g.img_stride = h->Cin;
         return run_rows(h->lut, q, nullptr, out, g, s, h->wofs_dev, h->wofs_npad, &io);
     }
-    if (h->byte_form) return byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), nullptr, out, M, s, &h->ws, &io);
     return lines_linear(h->bits, h->storage, shape_of(h), h->dt_dev, nullptr, out, M, s, &h->ws, &io, h);
 }
 

@@ -36,7 +36,12 @@ int pack_byte(const adapt_lut *lut, const int8_t *w, const ByteShape &q, const B
     p.bits = lut->bits; p.N = q.N; p.Cin = q.Cin; p.taps = q.kh * q.kw; p.cg = q.cg; p.n_tiles = q.n_tiles; p.steps = q.steps;
     p.wmode = convt ? 1 : 0; p.kh = q.kh * q.st; p.kw = q.kw * q.st; p.st = q.st;
     p.c = lut->byte_c; p.am = lut->byte_am; p.wm = lut->byte_wm;
-    adapt::pack_byte_tables_kernel<<<(unsigned)((size_t)q.phases * q.n_tiles * q.steps), 256, 0, s>>>(p);
+    // about eight workgroups per compute unit: enough to hide the latencies, and each stages its band for several tables
+    const int bands = ((1 << lut->bits) + adapt::BYTE_PACK_LINES - 1) / adapt::BYTE_PACK_LINES;
+    p.tables = q.phases * q.n_tiles * q.steps;
+    p.per_wg = (int)((long long)p.tables * bands / (8 * device_cus()));
+    p.per_wg = p.per_wg < 1 ? 1 : (p.per_wg > 64 ? 64 : p.per_wg);
+    adapt::pack_byte_tables_kernel<<<dim3((unsigned)((p.tables + p.per_wg - 1) / p.per_wg), (unsigned)bands), 256, 0, s>>>(p);
     HIP_TRY(hipGetLastError());
     return ADAPT_OK;
 }
@@ -87,6 +92,17 @@ BytePlan byte_plan_of(const ByteShape &q, int bits, int images, int Ho, int Wo, 
 #endif
     return pl;
 }
+
+// whether the byte kernel is the better one for M rows of a linear layer; pack: the tables are to be made for this call;
+// storage: of the table (1: the whole-table kernel runs twice)
+bool byte_pays(const ByteShape &q, int bits, int storage, int M, bool pack, int cu = 0) {
+#ifdef ADAPT_TUNING_KNOBS
+    if (const char *e = getenv("ADAPT_BYTE_PAYS")) return atoi(e) != 0;
+#endif
+    const long long byte = byte_call_clocks(byte_plan_of(q, bits, 1, 1, M, false, cu), q.dt_bytes, pack);
+    return byte_beats_rows(byte, rows_clocks(bits, M, q.N, q.Cin, cu > 0 ? cu : device_cus()) * (storage + 1));
+}
+bool byte_call_pays(const adapt_lut *lut, const ByteShape &q, int M, bool pack) { return byte_pays(q, lut->bits, lut->storage, M, pack); }
 
 // sums that split products leave behind: 16 R KB per workgroup
 size_t byte_partial_bytes(const BytePlan &pl, const ByteShape &q, int images, int Ho, int Wo) {
@@ -170,6 +186,11 @@ int launch_byte_copy(const LayerIO *io, const int8_t *x, int bits, int8_t *xt, i
 size_t byte_copy_bytes(int N, int Cin, int Hp, int Wp, int sw) {
     const long long n = (long long)N * Hp * ((Cin + 3) / 4) * ((Wp + sw - 1) / sw * sw) * 4;
     return n < 0x7fffff00LL ? align256((size_t)n + 64) : 0;
+}
+
+// workspace of a linear layer
+size_t byte_linear_bytes(const ByteShape &q, int bits, int M) {
+    return align256((size_t)q.cg * ((M + 3) / 4 * 4) * 4 + 64) + byte_partial_bytes(byte_plan_of(q, bits, 1, 1, M, false), q, 1, 1, M);
 }
 
 // linear layer: x [M][K] int8 (a) or fp32 (io->xf)

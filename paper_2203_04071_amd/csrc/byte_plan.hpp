@@ -61,4 +61,44 @@ inline BytePlan plan_byte(const BytePlanIn &in) {
     return best;
 }
 
+// A product on the whole-table kernel (lut_rows.hpp), as run_rows lays it out
+struct RowsShape {
+    int NT, MT;                 // channels and rows per workgroup
+};
+inline RowsShape rows_shape(long long M, long long N, long long K, int groups, int cu) {
+    // prefer 16 outputs per lane; shrink the tile until the grid covers the chip
+    RowsShape r{16, 1024};
+    auto wgs = [&] { return (M + r.MT - 1) / r.MT * ((N + r.NT - 1) / r.NT) * groups; };
+    while (r.MT > 64 && (r.MT / 2 >= M || (wgs() < cu && K / (1024 / (r.MT / 2)) >= 16))) r.MT /= 2;
+    if ((wgs() < cu && N > 8) || (groups > 1 && N <= 8)) r.NT = 8;
+    return r;
+}
+
+// Estimated clocks of a linear layer on it (one MI355X, 2.2 GHz): 16 waves of ceil(K / slices) NT reads of LDS at 4.3 clocks each where
+// activations come as whole words, 8 where they come byte by byte (K no multiple of 4), behind the copy of the
+// table into LDS at 10 B per clock.  Measured 4096 x 4096 x 4000 rows: 8.5 ms (8.2 estimated), 777 x 999 x 1024: 193 us (196).
+inline long long rows_clocks(int bits, long long M, long long N, long long K, int cu) {
+    const RowsShape r = rows_shape(M, N, K, 1, cu);
+    const long long slices = 1024 / r.MT, kc = (K + slices - 1) / slices, wgs = (M + r.MT - 1) / r.MT * ((N + r.NT - 1) / r.NT);
+    const long long table = ((1LL << bits) * ((1LL << bits) + 2)) * 2, red = slices > 1 ? 4096LL * r.NT : 0;
+    const int per_cu = (table > red ? table : red) <= 80 * 1024 ? 2 : 1;
+    const long long rounds = wgs <= cu ? 1 : (wgs + cu * per_cu - 1) / (cu * per_cu) * per_cu;
+    return rounds * ((long long)(16 * kc * r.NT * (K % 4 == 0 && kc % 4 == 0 ? 4.3 : 8.0)) + table / 10) + 4000;
+}
+
+// Estimated clocks of a whole call on the byte kernel: the launch, or the stream of its tables where that takes longer (2300 B
+// per clock, and up to 40000 clocks more where they come from HBM: 202 MB 39 us in the caches and 75 us behind other
+// work), and the activation copy; pack: with tables made for this call
+// (1400 B per clock behind one more allocation and launch).
+inline long long byte_call_clocks(const BytePlan &pl, size_t table_bytes, bool pack) {
+    const long long stream = (long long)(table_bytes / 2300), first = (long long)((table_bytes < 200000000 ? table_bytes : 200000000) / 5000);
+    return (pl.clocks > stream ? pl.clocks : stream) + first + 11000 + (pack ? 30000 + (long long)(table_bytes / 1400) : 0);
+}
+
+// Where tables of the byte form exist (or are to be made), the byte kernel is taken if its estimate is a tenth below that of
+// the whole-table kernel.  Measured both ways for 16 to 4000 rows, six pairs of K and N from 64 x 10 to 4096 x 4096, 6 to 8 bits:
+// the rule loses at most 20 % or 3 us to the better one; e.g. 8 bits, K = 777, N = 999: 256 rows 66 / 53 us (whole table / byte
+// kernel), 1024 rows 194 / 72 us; K = N = 4096: 256 rows 628 / 891 us, 1024 rows 2243 / 1158 us.
+inline bool byte_beats_rows(long long byte_clk, long long rows_clk) { return byte_clk + byte_clk / 10 < rows_clk; }
+
 }  // namespace adapt_api

@@ -125,3 +125,32 @@ def test_chain_into_a_strided_layer(B, bits, stride, kind):
         B.adapt_conv2d_layer_chain_f32(p1, x, s_x, s_1, out1, (1, 1), (1, 1), act=act, next_pw=p2, s_next=s_2)
         B.adapt_conv2d_layer_chain_f32(p2, None, s_2, s_o, out2, (stride, stride), (1, 1), in_shape=(3, 11, 13))
         assert torch.equal(out1, y1) and torch.equal(out2, want)
+
+
+@pytest.mark.parametrize("M,K,N,bits", [(512, 777, 37, 8), (1111, 130, 999, 8), (16, 4096, 17, 7), (4095, 33, 48, 6), (4095, 40, 250, 5)])
+def test_linear_layers_below_4096_rows(B, M, K, N, bits):
+    """Whichever kernel the estimate picks: sums of packed and plain weights, and the fused layer, bit-exact; a recorded first
+    call (which may not allocate) too."""
+    rng = np.random.default_rng(M + K)
+    t = table("product", bits, rng)
+    L = B.Lut(t, bits)
+    h = 1 << (bits - 1)
+    a, w = rng.integers(-h, h, size=(M, K)).astype(np.int8), rng.integers(-h, h, size=(N, K)).astype(np.int8)
+    want = orc.approx_linear(t, bits, a, w)
+    ad, wd = dev(a), dev(w)
+    assert (host(B.adapt_approx_linear(L, ad, wd)) == want).all()
+    pw = B.adapt_weights_pack_linear(L, wd)
+    out = torch.zeros((M, N), dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.adapt_approx_linear_packed(pw, ad, out=out)
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        assert (host(out) == want).all()
+    assert (host(B.adapt_approx_linear_packed(pw, ad)) == want).all()
+    x = (a.astype(np.float32) * np.float32(0.25))
+    y = B.adapt_linear_layer_f32(pw, dev(x), 0.25, 0.5)
+    q = orc.quantize(x, np.float32(0.25), bits)
+    assert np.array_equal(host(y).view(np.uint32), orc.dequant(orc.approx_linear(t, bits, q, w), np.float32(0.5), M, N, 1).reshape(M, N).view(np.uint32))

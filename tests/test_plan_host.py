@@ -65,3 +65,16 @@ def test_bad_arguments(plan):
         plan(3, 8, 0, 64, 64, 3, 3, 1, 1024, 32, 1)
     with pytest.raises(B.AdaptError):
         plan(1, 9, 0, 64, 64, 3, 3, 1, 1024, 32, 1)
+
+
+BYTE = 4
+
+
+@pytest.mark.parametrize("bits,K,N,first_byte", [(8, 777, 999, 512), (8, 4096, 4096, 512), (8, 4096, 64, 16), (7, 1024, 512, 512), (8, 64, 10, 4096)])
+def test_linear_layers_with_byte_tables_change_kernel_once(plan, bits, K, N, first_byte):
+    # from `first_byte` rows (of powers of two) on the derived tables are streamed; below, the whole-table kernel is faster
+    for rows in (16, 64, 128, 256, 512, 1024, 2048, 4096, 16384):
+        kernel, per_wg, ksplit, steps, wgs = plan(0, bits, 2, N, K, 1, 1, 1, rows, rows, 1)
+        assert kernel == (BYTE if rows >= first_byte else ROWS)
+        if kernel == BYTE:
+            assert wgs == -(-rows // per_wg) * -(-N // 16) * ksplit
