@@ -95,10 +95,10 @@ inline long long byte_call_clocks(const BytePlan &pl, size_t table_bytes, bool p
     return (pl.clocks > stream ? pl.clocks : stream) + first + 11000 + (pack ? 30000 + (long long)(table_bytes / 1400) : 0);
 }
 
-// Where tables of the byte form exist (or are to be made), the byte kernel is taken if its estimate is a tenth below that of
+// Where tables of the byte form exist (or are to be made), the byte kernel is taken if its estimate times 1.2 is below that of
 // the whole-table kernel.  Measured both ways for 16 to 4000 rows, six pairs of K and N from 64 x 10 to 4096 x 4096, 6 to 8 bits:
 // the rule loses at most 20 % or 3 us to the better one; e.g. 8 bits, K = 777, N = 999: 256 rows 66 / 53 us (whole table / byte
 // kernel), 1024 rows 194 / 72 us; K = N = 4096: 256 rows 628 / 891 us, 1024 rows 2243 / 1158 us.
-inline bool byte_beats_rows(long long byte_clk, long long rows_clk) { return byte_clk + byte_clk / 10 < rows_clk; }
+inline bool byte_beats_rows(long long byte_clk, long long rows_clk) { return byte_clk + byte_clk / 5 < rows_clk; }
 
 }  // namespace adapt_api

@@ -70,7 +70,7 @@ def test_bad_arguments(plan):
 BYTE = 4
 
 
-@pytest.mark.parametrize("bits,K,N,first_byte", [(8, 777, 999, 512), (8, 4096, 4096, 512), (8, 4096, 64, 16), (7, 1024, 512, 512), (8, 64, 10, 4096)])
+@pytest.mark.parametrize("bits,K,N,first_byte", [(8, 777, 999, 512), (8, 4096, 4096, 1024), (8, 4096, 64, 16), (7, 1024, 512, 512), (8, 64, 10, 4096)])
 def test_linear_layers_with_byte_tables_change_kernel_once(plan, bits, K, N, first_byte):
     # from `first_byte` rows (of powers of two) on the derived tables are streamed; below, the whole-table kernel is faster
     for rows in (16, 64, 128, 256, 512, 1024, 2048, 4096, 16384):
