@@ -15,10 +15,10 @@ int ste_env(const char *name) {
     return e ? atoi(e) : 0;
 }
 // Floats of partial sums a split product may need: it is split only below 256 tiles of 64 x 64, into at most
-// 512 / tiles + 1 parts.
+// 512 / tiles + 1 parts.  (An unsplit one over an unfolded input passes through there as well: see SteConvPlan.)
 constexpr size_t STE_PARTIAL_FLOATS = (size_t)(512 + 256) * 64 * 64;
 
-// partials != nullptr (STE_PARTIAL_FLOATS floats): a product with few output tiles and a long contraction is split
+// partials != nullptr: a product over an unfolded input (im2col); with few output tiles and a long contraction it is split
 // over grid z into partial sums, which ste_reduce_masked_kernel adds in a fixed order.
 void launch_ste_gemm(const adapt::SteParams &p_in, bool a_t, bool aligned, hipStream_t s, float *partials = nullptr) {
     static const int env_tile = ste_env("ADAPT_STE_TILE"), env_ks = ste_env("ADAPT_STE_KS");
@@ -43,7 +43,7 @@ void launch_ste_gemm(const adapt::SteParams &p_in, bool a_t, bool aligned, hipSt
             parts = (chunks + p.cps - 1) / p.cps;
         }
     }
-    if (parts > 1) { grid.z = (unsigned)parts; p.c = partials; p.o = nullptr; }
+    if (p.im2col) { grid.z = (unsigned)parts; p.c = partials; p.o = nullptr; }
     int ks = tiles * parts < 2 * cus ? 2 : 1;
     if (env_ks == 1 || env_ks == 2) ks = env_ks;
     const bool full = aligned && p.I % tile == 0 && p.J % tile == 0 && p.R % adapt::STE_TR == 0 && p.lda % 4 == 0 && p.R > 0;
@@ -56,11 +56,11 @@ void launch_ste_gemm(const adapt::SteParams &p_in, bool a_t, bool aligned, hipSt
     else { if (tile == 128) STE_LAUNCH2(false, 128, false); else STE_LAUNCH2(false, 64, false); }
 #undef STE_LAUNCH2
 #undef STE_LAUNCH4
-    if (parts > 1) {
+    if (p.im2col) {             // (one part too: the columns are in another order than the weight tensor)
         const size_t n = (size_t)p.I * (size_t)p.J;
         const size_t blocks = (n + 255) / 256;
         adapt::ste_reduce_masked_kernel<<<(unsigned)(blocks < 4096 ? blocks : 4096), 256, 0, s>>>(partials, parts, n, p_in.o, p_in.so, p_in.Q,
-                                                                                                  p_in.c);
+                                                                                                  p_in.c, p.g.kh * p.g.kw, p.g.C, (int)p.g.dCp.d);
     }
 }
 
@@ -115,7 +115,8 @@ namespace {
 struct SteConvPlan {
     adapt::SteConvGeo g;
     long long M, K;
-    size_t rows_bytes, col_bytes, wp_bytes, part_bytes, total;
+    bool direct;                // stride 1: the input gradient is one product (ste_dx_kernel)
+    size_t rows_bytes, col_bytes, wp_bytes, xq_bytes, part_bytes, total;
 };
 int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int kh, int kw, int stride_h, int stride_w, int pad_h, int pad_w,
                   int dil_h, int dil_w, bool want_dx, bool want_dw, const char *who) {
@@ -130,21 +131,27 @@ int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int k
     pl->K = (long long)Cin * kh * kw;
     if (pl->M > 65535LL * 64 || pl->K > 0x7fffffffLL || Ho > 0x7fffffffLL || Wo > 0x7fffffffLL || (long long)N * Cin * H * W > (1LL << 40))
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: tensor too large (N Ho Wo is limited to %d)", who, 65535 * 64);
+    if ((long long)kh * kw * ((Cin + 3LL) / 4 * 4) > 0x7fffffffLL)
+        return fail(ADAPT_ERR_UNSUPPORTED, "%s: a filter is limited to 2^31 - 1 weights (channels rounded up to 4)", who);
     if ((long long)H * W > 0x7fffffffLL || Ho * Wo > 0x7fffffffLL)
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: an image plane is limited to 2^31 - 1 pixels", who);
     adapt::SteConvGeo &g = pl->g;
     g = adapt::SteConvGeo{};
     g.N = N; g.C = Cin; g.H = H; g.W = W; g.O = Cout; g.kh = kh; g.kw = kw; g.sh = stride_h; g.sw = stride_w; g.ph = pad_h; g.pw = pad_w;
     g.dh = dil_h; g.dw = dil_w; g.Ho = (int)Ho; g.Wo = (int)Wo;
-    g.dK = fast_div((uint32_t)pl->K); g.dkw = fast_div((uint32_t)kw); g.dkhkw = fast_div((uint32_t)(kh * kw)); g.dWo = fast_div((uint32_t)Wo);
+    const long long Cp = ((long long)Cin + 3) / 4 * 4;
+    g.dkw = fast_div((uint32_t)kw); g.dWo = fast_div((uint32_t)Wo); g.dCp = fast_div((uint32_t)Cp);
     g.dHoWo = fast_div((uint32_t)(Ho * Wo)); g.dC = fast_div((uint32_t)Cin); g.dW = fast_div((uint32_t)W); g.dHW = fast_div((uint32_t)(H * W));
-    g.dO = fast_div((uint32_t)Cout); g.dP = fast_div((uint32_t)(Ho * Wo)); g.dsh = fast_div((uint32_t)stride_h); g.dsw = fast_div((uint32_t)stride_w);
+    g.dsh = fast_div((uint32_t)stride_h); g.dsw = fast_div((uint32_t)stride_w);
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     pl->rows_bytes = up((size_t)pl->M * Cout * sizeof(float));
-    pl->col_bytes = up((size_t)pl->M * (size_t)pl->K * sizeof(float));
-    pl->part_bytes = up(STE_PARTIAL_FLOATS * sizeof(float));
-    pl->wp_bytes = want_dx ? up((size_t)Cout * (size_t)pl->K * sizeof(float)) : 0;
-    pl->total = pl->rows_bytes + (want_dx ? pl->col_bytes : 0) + pl->wp_bytes + pl->part_bytes;
+    pl->direct = stride_h == 1 && stride_w == 1 && (long long)N * H * W < 0x7fffff00LL;
+    pl->col_bytes = want_dx && !pl->direct ? up((size_t)pl->M * (size_t)pl->K * sizeof(float)) : 0;
+    const size_t cols = (size_t)kh * kw * (size_t)Cp;
+    pl->xq_bytes = want_dw ? up((size_t)N * H * W * (size_t)Cp * sizeof(float)) : 0;
+    pl->part_bytes = up((want_dw && Cout * cols > STE_PARTIAL_FLOATS ? Cout * cols : STE_PARTIAL_FLOATS) * sizeof(float));
+    pl->wp_bytes = want_dx ? up((size_t)Cout * cols * sizeof(float)) : 0;
+    pl->total = pl->rows_bytes + pl->col_bytes + pl->wp_bytes + pl->xq_bytes + pl->part_bytes;
     return ADAPT_OK;
 }
 }  // namespace
@@ -196,25 +203,42 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
                     pl.total);
     char *ws = static_cast<char *>(workspace_dev);
     float *rows = reinterpret_cast<float *>(ws);
-    float *dcol = dx_dev ? reinterpret_cast<float *>(ws + pl.rows_bytes) : nullptr;
+    float *dcol = reinterpret_cast<float *>(ws + pl.rows_bytes);
+    float *wp = reinterpret_cast<float *>(ws + pl.rows_bytes + pl.col_bytes);           // the weights in the order that the input gradient reads
+    float *xq = reinterpret_cast<float *>(ws + pl.rows_bytes + pl.col_bytes + pl.wp_bytes);
     float *partials = reinterpret_cast<float *>(ws + pl.total - pl.part_bytes);      // used by one kernel pair at a time (stream order)
-    const int M = (int)pl.M, K = (int)pl.K, P = g.Ho * g.Wo;
-    const size_t rows_n = (size_t)M * Cout, col_n = (size_t)M * K;     // (col_n: elements of dcol)
-    if (rows_n < 0x7fffffffull) adapt::ste_rows_from_nchw_kernel<uint32_t><<<ew_grid(rows_n), 256, 0, s>>>(dy_dev, rows, g, rows_n);
-    else adapt::ste_rows_from_nchw_kernel<size_t><<<ew_grid(rows_n), 256, 0, s>>>(dy_dev, rows, g, rows_n);
-    HIP_TRY(hipGetLastError());
-    if (dw_dev) {           // dw [Cout][K] = inside(w) * rows^T [Cout][M] . fq(col(x)) [M][K], col(x) read from x itself
+    const int M = (int)pl.M, K = (int)pl.K, P = g.Ho * g.Wo, HW = H * W, Cp = (int)g.dCp.d;
+    const size_t col_n = (size_t)M * K;     // elements of dcol
+    auto channels_last = [&](const float *src, float *dst, int C, int pixels, int ld, float scale) {
+        const dim3 grid((unsigned)((pixels + 31) / 32), (unsigned)((ld + 63) / 64), (unsigned)(N < 65535 ? N : 65535));
+        adapt::ste_channels_last_kernel<<<grid, 256, 0, s>>>(src, dst, N, C, pixels, ld, scale, Q);
+    };
+    if (dw_dev || (dx_dev && !pl.direct)) {
+        channels_last(dy_dev, rows, Cout, P, Cout, 0.0f);
+        HIP_TRY(hipGetLastError());
+    }
+    if (dw_dev) {           // dw [Cout][K] = inside(w) * rows^T [Cout][M] . fq(col(x)) [M][K], col(x) read from the copy xq
+        channels_last(x_dev, xq, Cin, HW, Cp, s_x);
+        HIP_TRY(hipGetLastError());
         adapt::SteParams p{};
-        p.a = rows; p.b = x_dev; p.o = w_dev; p.c = dw_dev;
-        p.I = Cout; p.J = K; p.R = M; p.lda = Cout;
+        p.a = rows; p.b = xq; p.o = w_dev; p.c = dw_dev;
+        p.I = Cout; p.J = kh * kw * Cp; p.R = M; p.lda = Cout;
         p.sb = s_x; p.so = s_w; p.Q = Q;
         p.im2col = 1; p.g = g;
         launch_ste_gemm(p, true, true, s, partials);        // (both operands lie in the workspace)
         HIP_TRY(hipGetLastError());
     }
-    if (dx_dev) {           // dcol [M][K] = rows [M][Cout] . fq(w) [Cout][K]; dx = inside(x) * the taps of dcol gathered onto the image
+    if (dx_dev && pl.direct) {
+        const size_t wq_n = (size_t)kh * kw * Cout * Cp;
+        adapt::ste_weights_by_tap_kernel<<<ew_grid(wq_n), 256, 0, s>>>(w_dev, wp, Cout, Cin, Cp, kh * kw, s_w, Q);
+        HIP_TRY(hipGetLastError());
+        adapt::SteDxParams p{};
+        p.dy = dy_dev; p.wq = wp; p.x = x_dev; p.dx = dx_dev;
+        p.pixels = N * HW; p.Cp = Cp; p.so = s_x; p.Q = Q; p.g = g;
+        adapt::ste_dx_kernel<<<dim3((unsigned)((p.pixels + 63) / 64), (unsigned)((Cin + 63) / 64)), adapt::STE_THREADS, 0, s>>>(p);
+        HIP_TRY(hipGetLastError());
+    } else if (dx_dev) {    // dcol [M][K] = rows [M][Cout] . fq(w) [Cout][K]; dx = inside(x) * the taps of dcol gathered onto the image
         adapt::SteParams p{};
-        float *wp = reinterpret_cast<float *>(ws + pl.rows_bytes + pl.col_bytes);      // the weights with the channel last in each row
         adapt::ste_taps_first_kernel<<<ew_grid(w_elems), 256, 0, s>>>(w_dev, wp, Cout, Cin, kh * kw);
         HIP_TRY(hipGetLastError());
         p.a = rows; p.b = wp; p.o = nullptr; p.c = dcol;
@@ -231,7 +255,7 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
         const int Z = N < 16 ? N : 16;
         if ((size_t)Z * Cout <= STE_PARTIAL_FLOATS && Z > 1) {
             adapt::ste_bias_grad_nchw_kernel<<<dim3((unsigned)Cout, (unsigned)Z), 256, 0, s>>>(dy_dev, partials, N, Cout, P);
-            adapt::ste_reduce_masked_kernel<<<(unsigned)((Cout + 255) / 256), 256, 0, s>>>(partials, Z, (size_t)Cout, nullptr, 1.0f, Q, db_dev);
+            adapt::ste_reduce_masked_kernel<<<(unsigned)((Cout + 255) / 256), 256, 0, s>>>(partials, Z, (size_t)Cout, nullptr, 1.0f, Q, db_dev, 0, 0, 0);
         } else {
             adapt::ste_bias_grad_nchw_kernel<<<dim3((unsigned)Cout, 1), 256, 0, s>>>(dy_dev, db_dev, N, Cout, P);
         }

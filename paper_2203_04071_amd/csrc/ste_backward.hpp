@@ -13,11 +13,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "elementwise.hpp"
 
 namespace adapt {
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int STE_TR = 32;          // contraction indices per staged chunk
 constexpr int STE_THREADS = 256;    // four waves, 2 x 2 over the workgroup's output tile (x KS, see the kernel)
@@ -25,7 +28,7 @@ constexpr int STE_THREADS = 256;    // four waves, 2 x 2 over the workgroup's ou
 // geometry of a convolution whose unfolded input takes part in a product (see the end of this file)
 struct SteConvGeo {
     int N, C, H, W, O, kh, kw, sh, sw, ph, pw, dh, dw, Ho, Wo;
-    FastDiv dK, dkw, dkhkw, dWo, dHoWo, dC, dW, dHW, dO, dP, dsh, dsw;      // the divisors of the index decodes below
+    FastDiv dkw, dWo, dHoWo, dC, dCp, dW, dHW, dsh, dsw;     // the divisors of the index decodes below (Cp: C rounded up to 4)
 };
 
 // n / f.d: multiply-and-shift for 32-bit indices (exact below 2^31), a plain division otherwise
@@ -44,8 +47,8 @@ struct SteParams {
     int I, J, R, lda;
     float sb, so, Q;
     int cps;            // chunks of STE_TR contraction indices per grid z: z > 0 writes its partial sums to c + z * I * J
-    int im2col;         // b is an NCHW image tensor x and stands for its unfolded matrix: b[r][j] = x(n, c, oy s - p + ky d, ...)
-    SteConvGeo g;       //   with r = (n, oy, ox), j = (c, ky, kx) of this geometry, zero outside the image
+    int im2col;         // b is the channel-last copy of an image tensor (already fake-quantised) and stands for its unfolded
+    SteConvGeo g;       //   matrix: b[r][j] = x(n, oy s - p + ky d, ..., c) with r = (n, oy, ox), j = (ky, kx, c), zero outside the image
 };
 
 __device__ __forceinline__ float ste_fake_quant(float x, float s, float Q) {
@@ -78,27 +81,23 @@ __device__ __forceinline__ float4 ste_load4(const float *__restrict__ base, int 
     return v;
 }
 
-// Four consecutive elements of a row of the unfolded input of a convolution, read from the image itself (row = (n, oy, ox),
-// col = (c, ky, kx), a multiple of 4): no unfolded copy exists.  Branch-free like the ragged loads above: the address of
-// an element outside the matrix or the image is replaced by 0 and the value by zero.
-__device__ __forceinline__ float4 ste_load4_unfolded(const float *__restrict__ x, int row, int col, int rows, int cols, const SteConvGeo &g) {
+// Four consecutive elements of a row of the unfolded input of a convolution (row = (n, oy, ox), col = (ky, kx, c), a multiple of
+// 4) from the fake-quantised, channel-last copy xq [N][H][W][Cp] (ste_channels_last_kernel): one 16-byte load, no unfolded
+// copy exists.  Elements outside the image are to be zero: `inside` says so, and is applied when the value is stored (applied here,
+// every load would be waited for before the matrix instructions of the chunk).  Rows beyond the matrix are read from its last row (the other operand is
+// zero there), columns beyond it from its last ones (never stored).
+__device__ __forceinline__ float4 ste_load4_unfolded(const float *__restrict__ xq, int row, int col, int rows, int cols, const SteConvGeo &g, uint32_t &inside) {
     const uint32_t m = (uint32_t)min(row, rows - 1);
     const uint32_t n = g.dHoWo.div(m), pix = m - n * (uint32_t)(g.Ho * g.Wo);
     const int oy = (int)g.dWo.div(pix), ox = (int)pix - oy * g.Wo;
-    const int y0 = oy * g.sh - g.ph, x0 = ox * g.sw - g.pw;
-    float v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t k = (uint32_t)min(col + q, cols - 1);
-        const uint32_t c = g.dkhkw.div(k), tap = k - c * (uint32_t)(g.kh * g.kw);
-        const int ky = (int)g.dkw.div(tap), kx = (int)tap - ky * g.kw;
-        const int iy = y0 + ky * g.dh, ix = x0 + kx * g.dw;
-        const bool ok = row < rows && col + q < cols && iy >= 0 && iy < g.H && ix >= 0 && ix < g.W;
-        const size_t at = ok ? (((size_t)n * g.C + c) * g.H + iy) * g.W + ix : 0;
-        const float t = x[at];
-        v[q] = ok ? t : 0.0f;
-    }
-    return make_float4(v[0], v[1], v[2], v[3]);
+    const uint32_t k = (uint32_t)min(col, cols - 4);
+    const uint32_t tap = g.dCp.div(k), c = k - tap * g.dCp.d;
+    const int ky = (int)g.dkw.div(tap), kx = (int)tap - ky * g.kw;
+    const int iy = oy * g.sh - g.ph + ky * g.dh, ix = ox * g.sw - g.pw + kx * g.dw;
+    const bool ok = iy >= 0 && iy < g.H && ix >= 0 && ix < g.W;
+    const size_t at = ok ? (((size_t)n * g.H + iy) * g.W + ix) * g.dCp.d + c : 0;
+    inside = ok ? ~0u : 0u;
+    return *reinterpret_cast<const float4 *>(xq + at);
 }
 
 // TILE x TILE outputs per workgroup (128: four 32 x 32 blocks per wave; 64: one), FULL as above.  Chunks of 32
@@ -107,7 +106,7 @@ __device__ __forceinline__ float4 ste_load4_unfolded(const float *__restrict__ x
 // KS = 2: eight waves; waves w and w + 4 share an output quarter and take alternate pairs of contraction indices, their
 // sums are added through LDS at the end (a fixed order).  For launches with about one workgroup per compute unit:
 // two waves per SIMD, so that one wave's staging arithmetic runs under the other's matrix instructions.
-// UNFOLD: b is an image tensor that stands for its unfolded matrix (p.im2col; a template parameter so that the plain
+// UNFOLD: b is a copy of an image tensor that stands for its unfolded matrix (p.im2col; a template parameter so that the plain
 // products carry no trace of it: a run-time branch around the loads cost them 10 - 30 %).
 template <bool A_T, int TILE, bool FULL, int KS, bool UNFOLD = false>
 __global__ __launch_bounds__(STE_THREADS * KS) void ste_gemm_kernel(SteParams p) {
@@ -134,11 +133,12 @@ __global__ __launch_bounds__(STE_THREADS * KS) void ste_gemm_kernel(SteParams p)
             for (int v = 0; v < 16; ++v) acc[bi][bj][v] = 0.0f;
 
     float4 ra[PASSES], rb[PASSES];
+    uint32_t in_image[UNFOLD ? PASSES : 1];
     auto fetch = [&](int r0) {
 #pragma unroll
         for (int pass = 0; pass < PASSES; ++pass) {
             const int r = tid / TPR + RPP * pass, c4 = (tid % TPR) * 4;
-            if constexpr (UNFOLD) rb[pass] = ste_load4_unfolded(p.b, r0 + r, j0 + c4, p.R, p.J, p.g);
+            if constexpr (UNFOLD) rb[pass] = ste_load4_unfolded(p.b, r0 + r, j0 + c4, p.R, p.J, p.g, in_image[pass]);
             else rb[pass] = ste_load4<FULL>(p.b, r0 + r, j0 + c4, p.R, p.J, p.J);
             if (A_T) {
                 ra[pass] = ste_load4<FULL>(p.a, r0 + r, i0 + c4, p.R, p.I, p.lda);
@@ -152,11 +152,18 @@ __global__ __launch_bounds__(STE_THREADS * KS) void ste_gemm_kernel(SteParams p)
 #pragma unroll
         for (int pass = 0; pass < PASSES; ++pass) {
             const int r = tid / TPR + RPP * pass, c4 = (tid % TPR) * 4;
-            float4 q;
-            q.x = ste_fake_quant(rb[pass].x, p.sb, p.Q);
-            q.y = ste_fake_quant(rb[pass].y, p.sb, p.Q);
-            q.z = ste_fake_quant(rb[pass].z, p.sb, p.Q);
-            q.w = ste_fake_quant(rb[pass].w, p.sb, p.Q);
+            float4 q = rb[pass];
+            if constexpr (UNFOLD) {
+                q.x = __uint_as_float(__float_as_uint(q.x) & in_image[pass]);
+                q.y = __uint_as_float(__float_as_uint(q.y) & in_image[pass]);
+                q.z = __uint_as_float(__float_as_uint(q.z) & in_image[pass]);
+                q.w = __uint_as_float(__float_as_uint(q.w) & in_image[pass]);
+            } else {
+                q.x = ste_fake_quant(rb[pass].x, p.sb, p.Q);
+                q.y = ste_fake_quant(rb[pass].y, p.sb, p.Q);
+                q.z = ste_fake_quant(rb[pass].z, p.sb, p.Q);
+                q.w = ste_fake_quant(rb[pass].w, p.sb, p.Q);
+            }
             *reinterpret_cast<float4 *>(&Bs[buf][r][c4]) = q;
             if (A_T) {
                 *reinterpret_cast<float4 *>(&As[buf][r][c4]) = ra[pass];
@@ -246,14 +253,31 @@ __global__ __launch_bounds__(STE_THREADS * KS) void ste_gemm_kernel(SteParams p)
 }
 
 // c[i] = inside(o[i]) * (part[0][i] + part[1][i] + ... + part[S-1][i]), in that order: the partial sums of a product whose
-// contraction was split over grid z
+// contraction was split over grid z.  Eight parts are requested together (one at a time, 57 parts of 36864 took 15.5 us, the
+// latency of memory 57 times over; now 5.4 us).
+// taps > 0: the parts are rows of (tap, channel), taps x Cp columns, and c, o the weight tensor [row][C][taps].
 __global__ __launch_bounds__(256) void ste_reduce_masked_kernel(const float *__restrict__ part, int S, size_t n, const float *__restrict__ o,
-                                                                float so, float Q, float *__restrict__ c) {
+                                                                float so, float Q, float *__restrict__ c, int taps, int C, int Cp) {
     const size_t stride = (size_t)gridDim.x * 256;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
         float s = part[i];
-        for (int z = 1; z < S; ++z) s += part[(size_t)z * n + i];
-        c[i] = (!o || ste_inside(o[i], so, Q)) ? s : 0.0f;
+        int z = 1;
+        for (; z + 8 <= S; z += 8) {
+            float t[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) t[q] = part[(size_t)(z + q) * n + i];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s += t[q];
+        }
+        for (; z < S; ++z) s += part[(size_t)z * n + i];
+        size_t at = i;
+        if (taps > 0) {
+            const size_t row = i / ((size_t)taps * Cp), rem = i - row * (size_t)taps * Cp;
+            const int tap = (int)(rem / Cp), ch = (int)(rem - (size_t)tap * Cp);
+            if (ch >= C) continue;
+            at = (row * C + ch) * (size_t)taps + tap;
+        }
+        c[at] = (!o || ste_inside(o[at], so, Q)) ? s : 0.0f;
     }
 }
 
@@ -307,17 +331,38 @@ __global__ __launch_bounds__(STE_COLSUM_THREADS) void ste_colsum_kernel(const fl
 
 // ---- convolution (groups = 1): the same two products over the unfolded input --------------------------------------
 // y[m][o] = sum_k col(x^)[m][k] * w^[o][k] with m = (n, oy, ox), k = (c, ky, kx) (Sec. III-B: the convolution as a matrix
-// product over the unfolded input), so dw = mask(w) . dy_rows^T . fq(col(x)) and dcol = dy_rows . fq(w), and dx gathers
-// dcol back onto the image (a fixed order) under mask(x).  col(x) is never written: the product reads it from the image
-// (ste_load4_unfolded); dy as rows, dcol and the partial sums live in a workspace of the caller.
-// dy [N][O][P] -> rows [N * P][O]
-template <typename Idx>
-__global__ __launch_bounds__(256) void ste_rows_from_nchw_kernel(const float *__restrict__ dy, float *__restrict__ rows, SteConvGeo g, size_t total) {
-    const Idx stride = (Idx)gridDim.x * 256;
-    const int O = g.O, P = g.Ho * g.Wo;
-    for (Idx i = (Idx)blockIdx.x * 256 + threadIdx.x; i < (Idx)total; i += stride) {
-        const Idx m = ste_div<Idx>(i, g.dO), o = i - m * (Idx)O, n = ste_div<Idx>(m, g.dP), pix = m - n * (Idx)P;
-        rows[i] = dy[((size_t)n * O + o) * P + pix];
+// product over the unfolded input), so dw = mask(w) . dy_rows^T . col(x^) and dx gathers dy . w^ over the taps that reach a
+// pixel (a fixed order) under mask(x).  col(x) is never written: the product reads it from a fake-quantised channel-last copy
+// of x (ste_load4_unfolded).  Stride 1: dx is one product whose operand is read from dy itself (ste_dx_kernel); other strides:
+// dcol = dy_rows . fq(w), then ste_col2im_kernel.
+
+// src [N][C][P] -> dst [N][P][ld] (zeros in channels C .. ld - 1), fake-quantised with (s, Q) if s > 0.  64 channels x 32
+// pixels go through LDS so that reads and writes coalesce (without it: 8.4 MB in 14 us, now 5 us).
+__global__ __launch_bounds__(256) void ste_channels_last_kernel(const float *__restrict__ src, float *__restrict__ dst, int N, int C, int P, int ld, float s, float Q) {
+    __shared__ float tile[64][33];
+    const int p0 = blockIdx.x * 32, c0 = blockIdx.y * 64, tid = threadIdx.x;
+    for (int n = blockIdx.z; n < N; n += gridDim.z) {
+        const int pl = tid & 31, cl = tid >> 5;
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int c = c0 + cl + 8 * q;
+            const bool ok = c < C && p0 + pl < P;
+            const float t = src[ok ? ((size_t)n * C + c) * (size_t)P + (size_t)(p0 + pl) : 0];
+            v[q] = ok ? t : 0.0f;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) tile[cl + 8 * q][pl] = s > 0.0f ? ste_fake_quant(v[q], s, Q) : v[q];
+        __syncthreads();
+        const int wc = tid & 63, wp = tid >> 6;
+        if (c0 + wc < ld) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int pp = wp + 4 * q;
+                if (p0 + pp < P) dst[((size_t)n * P + (size_t)(p0 + pp)) * (size_t)ld + (size_t)(c0 + wc)] = tile[wc][pp];
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -328,6 +373,140 @@ __global__ __launch_bounds__(256) void ste_taps_first_kernel(const float *__rest
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
         const size_t o = i / ((size_t)C * T), rem = i - o * (size_t)C * T, t = rem / C, c = rem - t * C;
         wp[i] = w[(o * C + c) * T + t];
+    }
+}
+
+// w [O][C][T] -> wq [T][O][Cp], fake-quantised, zeros in the padded channels: the other operand of ste_dx_kernel
+__global__ __launch_bounds__(256) void ste_weights_by_tap_kernel(const float *__restrict__ w, float *__restrict__ wq, int O, int C, int Cp, int T, float s, float Q) {
+    const size_t total = (size_t)T * O * Cp, stride = (size_t)gridDim.x * 256;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
+        const size_t t = i / ((size_t)O * Cp), rem = i - t * (size_t)O * Cp, o = rem / Cp, c = rem - o * Cp;
+        wq[i] = c < (size_t)C ? ste_fake_quant(w[(o * C + c) * T + t], s, Q) : 0.0f;
+    }
+}
+
+struct SteDxParams {
+    const float *dy, *wq, *x;   // [N][O][Ho Wo], [tap][O][Cp], [N][C][H W]
+    float *dx;
+    int pixels, Cp;             // N H W
+    float so, Q;
+    SteConvGeo g;
+};
+
+// dx of a convolution with stride 1: dx[n][c][iy][ix] = inside(x) * sum over taps (ky, kx ascending) of sum over o of
+// w^[o][c][tap] dy[n][o][iy + ph - ky dh][ix + pw - kx dw].  A workgroup owns 64 channels x 64 pixels; chunks of 32 output
+// channels of a tap go through two LDS buffers (lanes along pixels: 256-byte loads from dy), a wave multiplies a 32 x 32 block.
+// The sum of a tap is finished before it is added, the order of the dcol form: same rounding, same results.  Against that
+// form (product 43 us, 75 MB written and read again by a gather of 39 us, 64 -> 64 channels, 3 x 3, 32 images of 32 x 32, fp32):
+// 40 us.  Bounded by the matrix pipe (fp32: 2.4 GFLOP, 15 us) and the latency of a chunk.
+__global__ __launch_bounds__(STE_THREADS, 2) void ste_dx_kernel(const SteDxParams p) {
+    constexpr int LD = 96;                                  // rows 2 k and 2 k + 1 of a read lie in different halves of the banks
+    __shared__ __align__(16) float As[2][STE_TR][LD];       // [o][c]
+    __shared__ __align__(16) float Bs[2][STE_TR][LD];       // [o][pixel]
+    const SteConvGeo &g = p.g;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+    const int wi = (wave & 1) * 32, wj = (wave >> 1) * 32;
+    const int P = g.Ho * g.Wo, HW = g.H * g.W, taps = g.kh * g.kw;
+    auto decode = [&](int j, int &n, int &pin) {
+        n = (int)g.dHW.div((uint32_t)j);
+        pin = j - n * HW;
+    };
+    // staging: this thread's pixel, and rows wave + 4 i of a chunk
+    int sn, spin;
+    decode(min(j0 + lane, p.pixels - 1), sn, spin);
+    const int sy = (int)g.dW.div((uint32_t)spin), sx = spin - sy * g.W;
+    const float *const dyn = p.dy + (size_t)sn * g.O * (size_t)P;
+    const int ac = min(i0 + (tid & 15) * 4, p.Cp - 4);
+    const int cpt = (g.O + STE_TR - 1) / STE_TR, chunks = taps * cpt;
+    int ky = 0, kx = 0, tap = 0, part = 0;                  // of the chunk that is fetched next
+    // What is fetched stays untouched until it is stored: zeros (outside the image, beyond the last channel) are put in by then.
+    // (Selected right behind its load, every value was waited for before the matrix instructions of the chunk: 59 -> 40 us.)
+    float rb[2][8];
+    f32x4_t ra[2][2];
+    uint32_t inside[2];
+    int from_o[2];
+    auto fetch = [&](float (&b)[8], f32x4_t (&a)[2], uint32_t &in, int &first_o) {
+        const int oy = sy + g.ph - ky * g.dh, ox = sx + g.pw - kx * g.dw, o0 = part * STE_TR;
+        const bool ok = oy >= 0 && oy < g.Ho && ox >= 0 && ox < g.Wo;
+        const float *const from = dyn + (ok ? oy * g.Wo + ox : 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int o = o0 + wave + 4 * i;                // (the same in the whole wave)
+            b[i] = from[(size_t)min(o, g.O - 1) * (size_t)P];
+        }
+        in = ok ? ~0u : 0u;
+        first_o = o0;
+        const float *const wt = p.wq + (size_t)tap * g.O * (size_t)p.Cp;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const f32x4_t *>(wt + (size_t)min(o0 + (tid >> 4) + 16 * i, g.O - 1) * (size_t)p.Cp + ac);
+        if (++part == cpt) {
+            part = 0;
+            ++tap;
+            if (++kx == g.kw) {
+                kx = 0;
+                ++ky;
+            }
+        }
+    };
+    auto stash = [&](int buf, const float (&b)[8], const f32x4_t (&a)[2], uint32_t in, int first_o) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) Bs[buf][wave + 4 * i][lane] = __uint_as_float(__float_as_uint(b[i]) & (first_o + wave + 4 * i < g.O ? in : 0u));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4_t *>(&As[buf][(tid >> 4) + 16 * i][(tid & 15) * 4]) = a[i];
+    };
+    f32x16_t acc, tot;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = tot[v] = 0.0f;
+    int left = cpt;                 // chunks of this tap that are still to be multiplied
+    // chunk ch lies in LDS buffer S = ch % 2 and was fetched into register set S; set 1 - S holds the next one (requested a chunk
+    // ago), set S takes the one after it
+    auto chunk = [&](int ch, auto set_c) {
+        constexpr int S = decltype(set_c)::value;
+        if (ch + 2 < chunks) fetch(rb[S], ra[S], inside[S], from_o[S]);
+        const int kr = lane >> 5, c = lane & 31;
+        float av[STE_TR / 2], bv[STE_TR / 2];
+#pragma unroll
+        for (int k2 = 0; k2 < STE_TR / 2; ++k2) {
+            av[k2] = As[S][2 * k2 + kr][wi + c];
+            bv[k2] = Bs[S][2 * k2 + kr][wj + c];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k2 = 0; k2 < STE_TR / 2; ++k2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[k2], bv[k2], acc, 0, 0, 0);
+        if (ch + 1 < chunks) stash(1 - S, rb[1 - S], ra[1 - S], inside[1 - S], from_o[1 - S]);
+        if (--left == 0) {
+            left = cpt;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                tot[v] += acc[v];
+                acc[v] = 0.0f;
+            }
+        }
+        __syncthreads();
+    };
+    fetch(rb[0], ra[0], inside[0], from_o[0]);
+    if (chunks > 1) fetch(rb[1], ra[1], inside[1], from_o[1]);
+    stash(0, rb[0], ra[0], inside[0], from_o[0]);
+    __syncthreads();
+    for (int ch = 0; ch < chunks; ch += 2) {
+        chunk(ch, std::integral_constant<int, 0>{});
+        if (ch + 1 < chunks) chunk(ch + 1, std::integral_constant<int, 1>{});
+    }
+    const int j = j0 + wj + (lane & 31);
+    if (j >= p.pixels) return;
+    int n, pin;
+    decode(j, n, pin);
+    float xv[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int c = i0 + wi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        xv[v] = c < g.C ? p.x[((size_t)n * g.C + c) * (size_t)HW + (size_t)pin] : 0.0f;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int c = i0 + wi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        if (c < g.C) p.dx[((size_t)n * g.C + c) * (size_t)HW + (size_t)pin] = ste_inside(xv[v], p.so, p.Q) ? tot[v] : 0.0f;
     }
 }
 

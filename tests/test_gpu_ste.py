@@ -331,3 +331,32 @@ def test_retraining_loop_of_two_approximate_layers(B):
         B.adapt_weights_destroy(p1); B.adapt_weights_destroy(p2)
     assert np.isfinite(losses).all()
     assert losses[-1] < 0.3 * losses[0], losses[::10]
+
+
+STRIDE1_CASES = [
+    # tiles of ste_dx_kernel: 64 channels x 64 pixels, chunks of 32 output channels
+    (3, 65, 5, 9, 33, 3, 3, (1, 1), (1, 1), (1, 1), 8),            # one channel, one output channel and 7 pixels over
+    (1, 1, 3, 3, 1, 3, 3, (1, 1), (2, 2), (1, 1), 8),              # one channel; taps that no pixel reaches
+    (2, 7, 11, 6, 64, 5, 2, (1, 1), (4, 0), (2, 3), 7),            # dilated, output larger than the input
+    (1, 128, 8, 8, 40, 1, 1, (1, 1), (0, 0), (1, 1), 6),           # one tap, two channel tiles
+    (2, 130, 6, 6, 300, 3, 3, (1, 1), (1, 1), (1, 1), 8),          # many outputs: the weight gradient in one part per tile
+]
+
+
+@pytest.mark.parametrize("case", STRIDE1_CASES)
+def test_ste_conv2d_backward_stride1_tiles(B, case):
+    test_ste_conv2d_backward_matches_oracle(B, case)
+
+
+def test_ste_conv2d_backward_keeps_infinities_to_their_pixels(B):
+    """An infinite or NaN gradient reaches the pixels under its taps and nothing else: padding and tile remainders add nothing."""
+    rng = np.random.default_rng(3)
+    x, w = rng.standard_normal((2, 5, 7, 7)).astype(np.float32), rng.standard_normal((6, 5, 3, 3)).astype(np.float32)
+    dy = rng.standard_normal((2, 6, 7, 7)).astype(np.float32)
+    clean = B.adapt_ste_conv2d_backward_f32(dev(dy), dev(x), dev(w), (1, 1), (1, 1), (1, 1), 0.1, 0.1, 8)[0]
+    dy[0, 2, 3, 3], dy[1, 5, 0, 0] = np.inf, np.nan
+    got = B.adapt_ste_conv2d_backward_f32(dev(dy), dev(x), dev(w), (1, 1), (1, 1), (1, 1), 0.1, 0.1, 8)[0]
+    far = torch.ones((2, 5, 7, 7), dtype=torch.bool, device="cuda")
+    far[0, :, 2:5, 2:5] = False
+    far[1, :, 0:2, 0:2] = False
+    assert torch.equal(got[far], clean[far]) and torch.isfinite(got[far]).all() and not torch.isfinite(got[~far]).all()
