@@ -1,8 +1,53 @@
 // C ABI, part 1: error text, table handles, quantiser / dequantiser, calibrators, the fp32 operations between layers.
 #include "api_common.hpp"
 
+#include <mutex>
+
 namespace adapt_api {
 thread_local char g_err[512] = "";
+
+namespace {
+constexpr int SCRATCH_DEVICES = 64;
+std::mutex g_scratch_lock;
+struct ScratchPool {
+    std::atomic<int> state{0};      // 0: not asked for yet, 1: there is one, 2: the device has none
+    hipMemPool_t pool = nullptr;
+} g_scratch[SCRATCH_DEVICES];
+}  // namespace
+
+hipMemPool_t scratch_pool() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= SCRATCH_DEVICES) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    ScratchPool &sp = g_scratch[dev];
+    if (sp.state.load(std::memory_order_acquire) == 0) {
+        std::lock_guard<std::mutex> lock(g_scratch_lock);
+        if (sp.state.load(std::memory_order_relaxed) == 0) {
+            hipMemPoolProps props{};
+            props.allocType = hipMemAllocationTypePinned;
+            props.location.type = hipMemLocationTypeDevice;
+            props.location.id = dev;
+            uint64_t keep = SCRATCH_KEEP;
+            hipMemPool_t pool = nullptr;
+            bool ok = hipMemPoolCreate(&pool, &props) == hipSuccess;
+            if (ok && hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+                (void)hipMemPoolDestroy(pool);
+                ok = false;
+            }
+            if (!ok) (void)hipGetLastError();
+            sp.pool = ok ? pool : nullptr;
+            sp.state.store(ok ? 1 : 2, std::memory_order_release);
+        }
+    }
+    return sp.pool;
+}
+
+void trim_scratch() {
+    for (ScratchPool &sp : g_scratch)
+        if (sp.state.load(std::memory_order_acquire) == 1 && hipMemPoolTrimTo(sp.pool, 0) != hipSuccess) (void)hipGetLastError();
+}
 }
 using namespace adapt_api;
 
@@ -112,6 +157,7 @@ int adapt_lut_destroy(adapt_lut *lut) {
         if (lut->lut16_dev[j]) (void)hipFree(lut->lut16_dev[j]);
     }
     delete lut;
+    trim_scratch();
     return ADAPT_OK;
 }
 

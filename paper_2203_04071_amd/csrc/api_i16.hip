@@ -116,6 +116,7 @@ int adapt_lut16_destroy(adapt_lut16 *lut) {
     if (lut->t_dev) (void)hipFree(lut->t_dev);
     if (lut->e_dev) (void)hipFree(lut->e_dev);
     delete lut;
+    trim_scratch();
     return ADAPT_OK;
 }
 
