@@ -479,9 +479,9 @@ def network_roofline(cfg_id, bits, macs, ms_per_step, ceilings, model_peak, gnet
         dom, bound = "lut_rows_kernel (recurrent step: product + cell, 100 launches)", "lds_gather16 (recurrence) + lds_read (input products)"
     else:
         t = 2.0 * macs / lds
-        dom = {3: "lut_quad_kernel (stride-1 layers; the 32- and 64-channel ones in slices + reduce_partials_kernel); 19 layers of 13 - 23 us",
-               5: "lut_quad_kernel<%d, 8, true>" % (2 if bits == 8 else 1),
-               6: "lut_grouped_tiled_kernel + lut_quad_kernel"}[cfg_id]
+        dom = {3: "lut_byte_kernel (19 layers of 11 - 20 us; the 32- and 64-channel ones in slices joined in the kernel)",
+               5: "lut_byte_kernel<%d, 8, 1>" % (2 if bits == 8 else 1),
+               6: "lut_grouped_tiled_kernel + lut_byte_kernel"}[cfg_id]
         bound = "lds_read"
     return dict(bound=bound, achieved=macs / (ms_per_step * 1e-3) / 1e12, peak=macs / t / 1e12, unit="Tlookup/s", frac=t / (ms_per_step * 1e-3),
                 traffic=None, bound_us=t * 1e6, dominant_kernel=dom, covers="the whole network step (every kernel, launch gaps included)",
