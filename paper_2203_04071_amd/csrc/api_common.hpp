@@ -67,11 +67,16 @@ constexpr uint64_t SCRATCH_KEEP = 256ull << 20;
 hipMemPool_t scratch_pool();        // of the current device; nullptr: there is none (defined in api_core.hip)
 void trim_scratch();
 
-inline hipError_t dbg_malloc_async(void **p, size_t bytes, hipStream_t s) {
+// whether calls on this stream are being recorded, or may be (the question has no answer)
+inline bool is_capturing(hipStream_t s) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    hipMemPool_t pool = nullptr;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
-    else if (st == hipStreamCaptureStatusNone) pool = scratch_pool();
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+inline hipError_t dbg_malloc_async(void **p, size_t bytes, hipStream_t s) {
+    hipMemPool_t pool = is_capturing(s) ? nullptr : scratch_pool();
     hipError_t e = pool ? hipMallocFromPoolAsync(p, bytes, pool, s) : hipMallocAsync(p, bytes, s);
     if (e == hipSuccess) e = dbg_poison(*p, bytes, s);
     return e;
@@ -85,27 +90,61 @@ inline hipError_t dbg_malloc(void **p, size_t bytes) {
     return e;
 }
 
-// Scratch memory of one call.  Plain entry points take it from the stream-ordered allocator and give it back in stream
-// order; a packed-weights handle keeps one grow-only buffer, so that its calls allocate nothing once they have run at
-// their largest size (they can then be recorded into a HIP graph).
+// Scratch memory of one call: the activation copy, and the partial sums of a product whose inner dimension is split.  Plain
+// entry points take it from the stream-ordered allocator and give it back in stream order; a packed-weights handle keeps one
+// grow-only buffer of each, so that its calls allocate nothing once they have run at their largest size (they can then be
+// recorded into a HIP graph).  How much partial sums need depends on the plan and does not grow with the size, so that buffer
+// is reserved for every product of up to part_rows rows.
 struct Workspace {
     void *ptr = nullptr;
     size_t bytes = 0;
+    void *part = nullptr;
+    size_t part_bytes = 0;
+    long long part_rows = 0;
 };
+
+inline int ws_grow(void **buf, size_t *have, size_t bytes) {
+    if (*have >= bytes) return ADAPT_OK;
+    if (*buf) HIP_TRY(hipFree(*buf));       // waits for the device: no earlier call still uses it
+    *buf = nullptr;
+    *have = 0;
+    HIP_TRY(dbg_malloc(buf, bytes));
+    *have = bytes;
+    return ADAPT_OK;
+}
 
 inline int ws_get(Workspace *cache, size_t bytes, hipStream_t s, void **out) {
     if (!cache) {
         HIP_TRY(dbg_malloc_async(out, bytes, s));
         return ADAPT_OK;
     }
-    if (cache->bytes < bytes) {
-        if (cache->ptr) HIP_TRY(hipFree(cache->ptr));       // waits for the device: no earlier call still uses it
-        cache->ptr = nullptr;
-        cache->bytes = 0;
-        HIP_TRY(dbg_malloc(&cache->ptr, bytes));
-        cache->bytes = bytes;
-    }
+    if (int rc = ws_grow(&cache->ptr, &cache->bytes, bytes)) return rc;
     *out = cache->ptr;
+    return ADAPT_OK;
+}
+
+// room in a handle for the partial sums of every product of up to `rows` rows; reserve(): the bytes these need
+template <typename Reserve>
+inline int ws_reserve_partials(Workspace *cache, long long rows, Reserve &&reserve) {
+    if (rows <= cache->part_rows) return ADAPT_OK;
+    const size_t bytes = reserve();
+    if (cache->part_bytes < bytes) cache->part_rows = 0;
+    if (int rc = ws_grow(&cache->part, &cache->part_bytes, bytes)) return rc;
+    cache->part_rows = rows;
+    return ADAPT_OK;
+}
+
+// both: copy_bytes at *mem and part_bytes (of a product of `rows` rows) at *part; given back together by ws_put(*mem)
+template <typename Reserve>
+inline int ws_get_both(Workspace *cache, size_t copy_bytes, size_t part_bytes, long long rows, Reserve &&reserve, hipStream_t s, void **mem, int32_t **part) {
+    if (!cache) {
+        if (int rc = ws_get(nullptr, copy_bytes + part_bytes, s, mem)) return rc;
+        *part = part_bytes ? reinterpret_cast<int32_t *>(static_cast<char *>(*mem) + copy_bytes) : nullptr;
+        return ADAPT_OK;
+    }
+    if (int rc = ws_get(cache, copy_bytes, s, mem)) return rc;
+    if (int rc = ws_reserve_partials(cache, rows, reserve)) return rc;
+    *part = part_bytes ? static_cast<int32_t *>(cache->part) : nullptr;
     return ADAPT_OK;
 }
 

@@ -516,12 +516,6 @@ LinesPlan plan_product(const LinesShape &q, int bits, int storage, int M, int ph
     return pl;
 }
 
-// bytes of partial sums a call needs from its workspace (0 without a split of the inner dimension): ksplit copies of
-// the output for reduce_partials_kernel
-size_t plan_partial_bytes(const LinesPlan &pl, size_t out_elems) {
-    return pl.ksplit > 1 ? (size_t)pl.ksplit * out_elems * sizeof(int32_t) : 0;
-}
-
 // bytes of one phase's tables in the quad order
 size_t quad_table_bytes(const LinesShape &q, int bits) {
     return (size_t)q.n_tiles * q.kh * q.kw * (q.Cp / adapt::QUAD_STEP) * ((size_t)adapt::QUAD_LINE_BYTES << bits);
@@ -712,12 +706,13 @@ int lines_linear(int bits, int storage, const LinesShape &q, uint4 *const dt[2],
     c.phases.resize(1);
     c.out_elems = (size_t)M * q.N; c.out_channels = (size_t)q.N; c.out_inner = 1;
     c.plan = plan_product(q, bits, storage, M, 1, M, 1, wh && wh->dtq_dev);
-    const size_t part_bytes = plan_partial_bytes(c.plan, c.out_elems);
+    const size_t part_bytes = lines_partial_bytes(c.plan, c.out_elems);
     const size_t copy_bytes = (((size_t)M * Kp + 64 + 255) / 256) * 256;
+    auto reserve = [&] { return lines_partial_reserve(device_cus(), c.out_elems); };
     if (c.plan.xmajor) {
         // x-major copy: one image of one row of M pixels with K channels; a lane's 8 rows x 4 inner indices are 32
         // contiguous bytes instead of 8 words that are a whole matrix row apart
-        int wrc = ws_get(ws, copy_bytes + part_bytes, s, (void **)&tmp);
+        int wrc = ws_get_both(ws, copy_bytes, part_bytes, M, reserve, s, (void **)&tmp, &c.partial);
         if (wrc) return wrc;
         dim3 grid((unsigned)((M + 63) / 64), (unsigned)((Kp / 4 + 15) / 16));
         if (from_f32) adapt::rows_to_xmajor_kernel<<<grid, 256, 0, s>>>(srcf, tmp, M, K, Kp);
@@ -729,8 +724,9 @@ int lines_linear(int bits, int storage, const LinesShape &q, uint4 *const dt[2],
         c.out_plane = 1; c.out_sy = 0; c.out_sx = q.N;
         if (c.plan.kernel == LK_QUAD) { c.dt_quad = wh->dtq_dev; c.quad_c = wh->dtq_c; }
     } else {
-        if (Kp != K || from_f32 || part_bytes) {
-            int wrc = ws_get(ws, copy_bytes + part_bytes, s, (void **)&tmp);
+        // (nothing is needed otherwise; a handle makes room all the same, for smaller products that do, unless the call is recorded)
+        if (Kp != K || from_f32 || part_bytes || (ws && ws->part_rows < M && !is_capturing(s))) {
+            int wrc = ws_get_both(ws, copy_bytes, part_bytes, M, reserve, s, (void **)&tmp, &c.partial);
             if (wrc) return wrc;
         }
         if (Kp != K || from_f32) {
@@ -746,7 +742,6 @@ int lines_linear(int bits, int storage, const LinesShape &q, uint4 *const dt[2],
         c.xmajor = 0; c.ch_stride = 0;
         c.out_plane = 1; c.out_sy = 0; c.out_sx = 0;
     }
-    if (part_bytes) c.partial = reinterpret_cast<int32_t *>(tmp + copy_bytes);
     bool finished = false;
     int rc = run_lines(bits, storage, q, dt, xt, c, out, s, io, true, nullptr, &finished);
     rc = ws_put(ws, tmp, s, rc);
@@ -766,21 +761,23 @@ int lines_conv2d(int bits, int storage, const LinesShape &q, uint4 *const dt[2],
     const LinesPlan plan = plan_product(q, bits, storage, M, 1, Wo, sw, wh && wh->dtq_dev);
     const int xmajor = plan.xmajor;
     const size_t out_elems = (size_t)M * q.N;
-    const size_t part_bytes = plan_partial_bytes(plan, out_elems);
+    const size_t part_bytes = lines_partial_bytes(plan, out_elems);
     const size_t copy_bytes = ((xt_bytes + 64 + 255) / 256) * 256;
     int8_t *xt = nullptr;
+    int32_t *partial = nullptr;
     {
         if (input_ready) {      // the layer before wrote the copy (adapt_conv2d_chain_prepare fixed its place and layout)
-            if (!ws || !ws->ptr || ws->bytes < copy_bytes + part_bytes || !wh || wh->chain_in.xmajor != xmajor)
+            if (!ws || !ws->ptr || ws->bytes < copy_bytes || ws->part_rows < M || !wh || wh->chain_in.xmajor != xmajor)
                 return fail(ADAPT_ERR_INVALID_ARGUMENT, "chained convolution: the input buffer was not prepared for this geometry");
             xt = static_cast<int8_t *>(ws->ptr);
+            partial = static_cast<int32_t *>(ws->part);
         } else {
             if (wh && wh->chain_in.valid) {     // an ordinary call with another geometry ends the prepared state
                 const auto &ci = wh->chain_in;
                 if (ci.N != N || ci.H != H || ci.W != W || ci.sh != sh || ci.sw != sw || ci.ph != ph || ci.pw != pw || ci.dh != dh || ci.dw != dw)
                     wh->chain_in.valid = false;
             }
-            int wrc = ws_get(ws, copy_bytes + part_bytes, s, (void **)&xt);
+            int wrc = ws_get_both(ws, copy_bytes, part_bytes, M, [&] { return lines_partial_reserve(device_cus(), out_elems); }, s, (void **)&xt, &partial);
             if (wrc) return wrc;
             int prc = launch_pad(io, x, bits, xt, N, q.Cin, H, W, ph, pw, Cp, xmajor, s);
             if (prc) return ws_put(ws, xt, s, prc);
@@ -797,7 +794,7 @@ int lines_conv2d(int bits, int storage, const LinesShape &q, uint4 *const dt[2],
     c.out_plane = Ho * Wo; c.out_sy = Wo; c.out_sx = 1;
     c.phases.resize(1);
     c.out_elems = out_elems; c.out_channels = (size_t)q.N; c.out_inner = (size_t)Ho * Wo;
-    if (part_bytes) c.partial = reinterpret_cast<int32_t *>(xt + copy_bytes);
+    if (part_bytes) c.partial = partial;
     if (plan.kernel == LK_QUAD) { c.dt_quad = wh->dtq_dev; c.quad_c = wh->dtq_c; }
     c.nonneg_in = input_ready && wh && wh->chain_in.nonneg;
     bool finished = false;
@@ -830,16 +827,18 @@ int lines_conv_transpose2d(int bits, int storage, const LinesShape &q, uint4 *co
     const LinesPlan plan = plan_product(q, bits, storage, M, st * st, Qx, 1, wh && wh->dtq_dev);
     const int xmajor = plan.xmajor;
     const size_t out_elems = (size_t)N * q.N * Ho * Wo;
-    const size_t part_bytes = plan_partial_bytes(plan, out_elems);
+    const size_t part_bytes = lines_partial_bytes(plan, out_elems);
     const size_t copy_bytes = ((xt_bytes + 64 + 255) / 256) * 256;
     int8_t *xt = nullptr;
+    int32_t *partial = nullptr;
     if (input_ready) {          // the layer before wrote the copy (adapt_conv_transpose2d_chain_prepare fixed its place and layout)
-        if (!ws || !ws->ptr || ws->bytes < copy_bytes + part_bytes || !wh || wh->chain_in.xmajor != xmajor)
+        if (!ws || !ws->ptr || ws->bytes < copy_bytes || ws->part_rows < M || !wh || wh->chain_in.xmajor != xmajor)
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "chained transposed convolution: the input buffer was not prepared for this geometry");
         xt = static_cast<int8_t *>(ws->ptr);
+        partial = static_cast<int32_t *>(ws->part);
     } else {
         if (wh) wh->chain_in.valid = false;     // (an ordinary call overwrites a prepared copy)
-        int wrc = ws_get(ws, copy_bytes + part_bytes, s, (void **)&xt);
+        int wrc = ws_get_both(ws, copy_bytes, part_bytes, M, [&] { return lines_partial_reserve(device_cus(), out_elems); }, s, (void **)&xt, &partial);
         if (wrc) return wrc;
         int prc = launch_pad(io, x, bits, xt, N, q.Cin, H, W, Ty - 1, Tx - 1, Cp, xmajor, s);
         if (prc) return ws_put(ws, xt, s, prc);
@@ -868,7 +867,7 @@ int lines_conv_transpose2d(int bits, int storage, const LinesShape &q, uint4 *co
     const int Ly = kh - st - pad > 0 ? kh - st - pad : 0, Lx = kw - st - pad > 0 ? kw - st - pad : 0;
     const bool border = Ly > 0 || Lx > 0;       // then the sums are corrected before they can be rescaled
     c.out_elems = out_elems; c.out_channels = (size_t)q.N; c.out_inner = (size_t)Ho * Wo;
-    if (part_bytes) c.partial = reinterpret_cast<int32_t *>(xt + copy_bytes);
+    if (part_bytes) c.partial = partial;
     const bool quad = plan.kernel == LK_QUAD;
     if (quad) { c.dt_quad = wh->dtq_dev; c.quad_c = wh->dtq_c; }
     c.nonneg_in = input_ready && wh && wh->chain_in.nonneg;
@@ -1206,11 +1205,10 @@ static adapt::ChainOut chain_out_of(const adapt_weights *next, float s_next) {
 static int byte_chain_prepare(const adapt_weights *h, size_t copy_bytes, int N, int Ho, int Wo, hipStream_t s) {
     if (!copy_bytes) return fail(ADAPT_ERR_UNSUPPORTED, "chain prepare: input copy of 2 GiB or more");
     const ByteShape q = byte_shape_of(h);
-    // (the producer decides whether the codes are known to be >= 0, which may change the plan)
-    const size_t p0 = byte_partial_bytes(byte_plan_of(q, h->bits, N, Ho, Wo, false), q, N, Ho, Wo);
-    const size_t p1 = byte_partial_bytes(byte_plan_of(q, h->bits, N, Ho, Wo, true), q, N, Ho, Wo);
+    const BytePartials sums(q, h->bits, BytePlan{}, N, Ho, Wo);
     void *xt = nullptr;
-    int rc = ws_get(&h->ws, copy_bytes + (p0 > p1 ? p0 : p1), s, &xt);
+    int32_t *partial = nullptr;
+    int rc = ws_get_both(&h->ws, copy_bytes, 0, sums.rows, [&] { return sums.reserve(); }, s, &xt, &partial);
     if (rc) return rc;
     adapt::fill_u32_kernel<<<ew_grid(copy_bytes / 4), 256, 0, s>>>(static_cast<uint32_t *>(xt), 0u, copy_bytes / 4);
     HIP_TRY(hipGetLastError());
@@ -1391,6 +1389,7 @@ int adapt_weights_destroy(adapt_weights *h) {
     for (int j = 0; j < 2; ++j)
         if (h->dt_dev[j]) (void)hipFree(h->dt_dev[j]);
     if (h->ws.ptr) (void)hipFree(h->ws.ptr);
+    if (h->ws.part) (void)hipFree(h->ws.part);
     if (h->wofs_dev) (void)hipFree(h->wofs_dev);
     if (h->wofs1_dev) (void)hipFree(h->wofs1_dev);
     if (h->dtq_dev) (void)hipFree(h->dtq_dev);
@@ -1465,17 +1464,29 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
     return ADAPT_OK;
 }
 
-// Whether M rows of a packed linear layer go to the whole-table kernel: too few to amortise streaming the derived tables.  (A
-// call that is being recorded and that has not run at this size before may not allocate what the byte kernel needs.)
+// Room in a byte-form handle for linear layers of up to M rows, whichever kernel they take
+static int byte_linear_reserve(const adapt_weights *h, const ByteShape &q, int M, hipStream_t s) {
+    const BytePartials sums(q, h->bits, BytePlan{}, 1, 1, M);
+    void *mem = nullptr;
+    int32_t *partial = nullptr;
+    return ws_get_both(&h->ws, byte_linear_copy_bytes(q, M), 0, sums.rows, [&] { return sums.reserve(); }, s, &mem, &partial);
+}
+
+// Whether M rows of a packed linear layer go to the whole-table kernel: too few to amortise streaming the derived tables.  A
+// call that has not run at this size before makes room here, also where it then needs none, so that smaller ones find it; one that
+// is being recorded, or that finds no memory, takes the whole-table kernel instead.
 static bool linear_on_rows(const adapt_weights *h, int M, hipStream_t s) {
     if (M >= LINES_MIN_ROWS) return false;
     if (!h->byte_form) return true;
     const ByteShape q = byte_shape_of(h);
-    if (!byte_call_pays(h->lut, q, M, false)) return true;
-    if (h->ws.bytes >= byte_linear_bytes(q, h->bits, M)) return false;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
-    return st != hipStreamCaptureStatusNone;
+    if (h->ws.part_rows < (M + 3) / 4 * 4 || h->ws.bytes < byte_linear_copy_bytes(q, M)) {
+        if (is_capturing(s)) return true;
+        if (byte_linear_reserve(h, q, M, s) != ADAPT_OK) {
+            (void)hipGetLastError();
+            return true;
+        }
+    }
+    return !byte_call_pays(h->lut, q, M, false);
 }
 
 int adapt_approx_linear_packed(const adapt_weights *h, const int8_t *a_dev, int32_t *acc_dev, int M, void *stream) {
@@ -1678,9 +1689,10 @@ int adapt_conv2d_chain_prepare(const adapt_weights *h, int N, int H, int W, int 
     const int xmajor = plan.xmajor;
     const size_t xt_bytes = (size_t)N * (H + 2 * pad_h) * (W + 2 * pad_w) * q.Cp;
     const size_t copy_bytes = ((xt_bytes + 64 + 255) / 256) * 256;
-    const size_t part_bytes = plan_partial_bytes(plan, (size_t)M * q.N);
     int8_t *xt = nullptr;
-    if ((rc = ws_get(&h->ws, copy_bytes + part_bytes, (hipStream_t)stream, (void **)&xt))) return rc;
+    int32_t *partial = nullptr;
+    if ((rc = ws_get_both(&h->ws, copy_bytes, 0, M, [&] { return lines_partial_reserve(device_cus(), (size_t)M * q.N); }, (hipStream_t)stream, (void **)&xt, &partial)))
+        return rc;
     adapt::fill_u32_kernel<<<ew_grid(copy_bytes / 4), 256, 0, (hipStream_t)stream>>>(reinterpret_cast<uint32_t *>(xt), 0u, copy_bytes / 4);
     HIP_TRY(hipGetLastError());
     ci.xmajor = xmajor; ci.valid = true;
@@ -1829,9 +1841,10 @@ int adapt_conv_transpose2d_chain_prepare(const adapt_weights *h, int N, int H, i
     const int xmajor = plan.xmajor;
     const size_t xt_bytes = (size_t)N * (H + 2 * (Ty - 1)) * (W + 2 * (Tx - 1)) * q.Cp;
     const size_t copy_bytes = ((xt_bytes + 64 + 255) / 256) * 256;
-    const size_t part_bytes = plan_partial_bytes(plan, (size_t)N * q.N * Ho * Wo);
     int8_t *xt = nullptr;
-    if ((rc = ws_get(&h->ws, copy_bytes + part_bytes, (hipStream_t)stream, (void **)&xt))) return rc;
+    int32_t *partial = nullptr;
+    if ((rc = ws_get_both(&h->ws, copy_bytes, 0, M, [&] { return lines_partial_reserve(device_cus(), (size_t)N * q.N * Ho * Wo); }, (hipStream_t)stream, (void **)&xt, &partial)))
+        return rc;
     adapt::fill_u32_kernel<<<ew_grid(copy_bytes / 4), 256, 0, (hipStream_t)stream>>>(reinterpret_cast<uint32_t *>(xt), 0u, copy_bytes / 4);
     HIP_TRY(hipGetLastError());
     ci.xmajor = xmajor; ci.valid = true;

@@ -77,11 +77,15 @@ struct ByteCall {
     int cv_Ho = 0, cv_Wo = 0, cv_H = 0, cv_W = 0, cv_kh = 0, cv_kw = 0, cv_s = 1, cv_pad = 0, cv_Ly = 0, cv_Lx = 0;
 };
 
-BytePlan byte_plan_of(const ByteShape &q, int bits, int images, int Ho, int Wo, bool nonneg, int cu = 0) {
+BytePlanIn byte_plan_in(const ByteShape &q, int bits, int images, int Ho, int Wo, bool nonneg, int cu = 0) {
     BytePlanIn in;
     in.rows4 = (long long)images * Ho * ((Wo + 3) / 4 * 4); in.rows2 = (long long)images * Ho * ((Wo + 1) / 2 * 2);
     in.tiles = q.n_tiles * q.phases; in.steps = q.steps; in.copy_lines = (1 << bits) >> (nonneg ? 1 : 0); in.cu = cu > 0 ? cu : device_cus();
-    BytePlan pl = plan_byte(in);
+    return in;
+}
+
+BytePlan byte_plan_of(const ByteShape &q, int bits, int images, int Ho, int Wo, bool nonneg, int cu = 0) {
+    BytePlan pl = plan_byte(byte_plan_in(q, bits, images, Ho, Wo, nonneg, cu));
 #ifdef ADAPT_TUNING_KNOBS
     if (const char *e = getenv("ADAPT_BYTE_PLAN")) {        // "R,ksplit": tuning experiments only (not compiled into the product)
         int R = 0, ks = 0;
@@ -104,14 +108,25 @@ bool byte_pays(const ByteShape &q, int bits, int storage, int M, bool pack, int 
 }
 bool byte_call_pays(const adapt_lut *lut, const ByteShape &q, int M, bool pack) { return byte_pays(q, lut->bits, lut->storage, M, pack); }
 
-// sums that split products leave behind: 16 R KB per workgroup
-size_t byte_partial_bytes(const BytePlan &pl, const ByteShape &q, int images, int Ho, int Wo) {
-    if (pl.ksplit <= 1) return 0;
-    const int V = pl.R < 4 ? pl.R : 4;
-    const long long rows = (long long)images * Ho * ((Wo + V - 1) / V * V);
-    const long long tiles = (rows + 256 * pl.R - 1) / (256 * pl.R) * q.n_tiles * (q.phases < 4 ? q.phases : 4);
-    return (size_t)tiles * pl.ksplit * pl.R * adapt::BYTE_THREADS * 16;
-}
+// room for the sums that the slices of a split product leave behind: `bytes` for this one, reserve() for all that are no larger
+struct BytePartials {
+    const ByteShape &q;
+    int bits;
+    long long rows;
+    size_t bytes;
+    BytePartials(const ByteShape &shape, int operand_bits, const BytePlan &pl, int images, int Ho, int Wo) : q(shape), bits(operand_bits) {
+        const BytePlanIn in = byte_plan_in(q, bits, images, Ho, Wo, false);
+        rows = in.rows4;
+        bytes = byte_partial_bytes(pl.R, pl.ksplit, pl.R >= 4 ? in.rows4 : in.rows2, launch_tiles());
+    }
+    long long launch_tiles() const { return (long long)q.n_tiles * (q.phases < 4 ? q.phases : 4); }
+    // (whether all activations are known to be >= 0 changes the plan, and is only known call by call)
+    size_t reserve() const {
+        const BytePlanIn all = byte_plan_in(q, bits, 1, 1, 1, false), half = byte_plan_in(q, bits, 1, 1, 1, true);
+        const size_t a = byte_partial_reserve(all, rows, launch_tiles()), h = byte_partial_reserve(half, rows, launch_tiles());
+        return a > h ? a : h;
+    }
+};
 
 int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, const BytePlan &pl, const ByteCall &c, const int8_t *xt, int32_t *partial,
              int32_t *out, hipStream_t s, const LayerIO *io) {
@@ -188,20 +203,20 @@ size_t byte_copy_bytes(int N, int Cin, int Hp, int Wp, int sw) {
     return n < 0x7fffff00LL ? align256((size_t)n + 64) : 0;
 }
 
-// workspace of a linear layer
-size_t byte_linear_bytes(const ByteShape &q, int bits, int M) {
-    return align256((size_t)q.cg * ((M + 3) / 4 * 4) * 4 + 64) + byte_partial_bytes(byte_plan_of(q, bits, 1, 1, M, false), q, 1, 1, M);
-}
+// activation copy of a linear layer
+size_t byte_linear_copy_bytes(const ByteShape &q, int M) { return align256((size_t)q.cg * ((M + 3) / 4 * 4) * 4 + 64); }
 
 // linear layer: x [M][K] int8 (a) or fp32 (io->xf)
 int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, const int8_t *a, int32_t *out, int M, hipStream_t s, Workspace *ws,
                 const LayerIO *io) {
     const int Mp = (M + 3) / 4 * 4;
     const BytePlan pl = byte_plan_of(q, lut->bits, 1, 1, M, false);
-    const size_t copy_bytes = align256((size_t)q.cg * Mp * 4 + 64);
+    const size_t copy_bytes = byte_linear_copy_bytes(q, M);
     if (copy_bytes > 0x7fffff00u) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: tensor with more than 2^31-1 elements");
+    const BytePartials sums(q, lut->bits, pl, 1, 1, M);
     unsigned char *mem = nullptr;
-    int rc = ws_get(ws, copy_bytes + byte_partial_bytes(pl, q, 1, 1, M), s, (void **)&mem);
+    int32_t *partial = nullptr;
+    int rc = ws_get_both(ws, copy_bytes, sums.bytes, sums.rows, [&] { return sums.reserve(); }, s, (void **)&mem, &partial);
     if (rc) return rc;
     int8_t *xt = reinterpret_cast<int8_t *>(mem);
     const dim3 grid((unsigned)((M + 63) / 64), (unsigned)((q.cg + 15) / 16));
@@ -213,20 +228,21 @@ int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
     ByteCall c;
     c.images = 1; c.Ho = 1; c.Wo = M; c.linear = true;
     c.img_stride = 0; c.oy_stride = 0; c.ch_stride = 4 * Mp; c.ky_stride = 0; c.wsub = Mp;
-    rc = run_byte(lut, t, q, pl, c, xt, reinterpret_cast<int32_t *>(mem + copy_bytes), out, s, io);
+    rc = run_byte(lut, t, q, pl, c, xt, partial, out, s, io);
     return ws_put(ws, mem, s, rc);
 }
 
 // what lies in a prepared handle's workspace, or a fresh copy of x in it
 template <typename Copy>
-int byte_input(size_t copy_bytes, size_t part_bytes, Workspace *ws, bool input_ready, hipStream_t s, unsigned char **mem, Copy &&copy) {
+int byte_input(size_t copy_bytes, const BytePartials &sums, Workspace *ws, bool input_ready, hipStream_t s, unsigned char **mem, int32_t **partial, Copy &&copy) {
     if (input_ready) {
-        if (!ws || !ws->ptr || ws->bytes < copy_bytes + part_bytes)
+        if (!ws || !ws->ptr || ws->bytes < copy_bytes || ws->part_rows < sums.rows)
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "chained layer: the input buffer was not prepared for this geometry");
         *mem = static_cast<unsigned char *>(ws->ptr);
+        *partial = static_cast<int32_t *>(ws->part);
         return ADAPT_OK;
     }
-    int rc = ws_get(ws, copy_bytes + part_bytes, s, (void **)mem);
+    int rc = ws_get_both(ws, copy_bytes, sums.bytes, sums.rows, [&] { return sums.reserve(); }, s, (void **)mem, partial);
     if (rc) return rc;
     if ((rc = copy(reinterpret_cast<int8_t *>(*mem)))) return ws_put(ws, *mem, s, rc);
     return ADAPT_OK;
@@ -246,8 +262,10 @@ int byte_conv2d(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
         if (ci.N != N || ci.H != H || ci.W != W || ci.sh != sh || ci.sw != sw || ci.ph != ph || ci.pw != pw || ci.dh != dh || ci.dw != dw)
             wh->chain_in.valid = false;
     }
+    const BytePartials sums(q, lut->bits, pl, N, Ho, Wo);
     unsigned char *mem = nullptr;
-    int rc = byte_input(copy_bytes, byte_partial_bytes(pl, q, N, Ho, Wo), ws, input_ready, s, &mem, [&](int8_t *xt) {
+    int32_t *partial = nullptr;
+    int rc = byte_input(copy_bytes, sums, ws, input_ready, s, &mem, &partial, [&](int8_t *xt) {
         return launch_byte_copy(io, x, lut->bits, xt, N, q.Cin, H, W, ph, pw, sw, wsub, s);
     });
     if (rc) return rc;
@@ -256,7 +274,7 @@ int byte_conv2d(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
     c.ch_stride = row; c.img_stride = Hp * q.cg * row; c.oy_stride = sh * q.cg * row; c.ky_stride = dh * q.cg * row;
     c.dw = dw; c.sw = sw; c.wsub = wsub;
     c.out_plane = Ho * Wo; c.out_w = Wo;
-    rc = run_byte(lut, t, q, pl, c, reinterpret_cast<int8_t *>(mem), reinterpret_cast<int32_t *>(mem + copy_bytes), out, s, io);
+    rc = run_byte(lut, t, q, pl, c, reinterpret_cast<int8_t *>(mem), partial, out, s, io);
     return ws_put(ws, mem, s, rc);
 }
 
@@ -274,8 +292,10 @@ int byte_conv_transpose2d(const adapt_lut *lut, const ByteTables &t, const ByteS
     c.nonneg = input_ready && wh && wh->chain_in.nonneg;
     const BytePlan pl = byte_plan_of(q, lut->bits, N, c.Ho, c.Wo, c.nonneg);
     if (!input_ready && wh) wh->chain_in.valid = false;     // (an ordinary call overwrites a prepared copy)
+    const BytePartials sums(q, lut->bits, pl, N, c.Ho, c.Wo);
     unsigned char *mem = nullptr;
-    int rc = byte_input(copy_bytes, byte_partial_bytes(pl, q, N, c.Ho, c.Wo), ws, input_ready, s, &mem, [&](int8_t *xt) {
+    int32_t *partial = nullptr;
+    int rc = byte_input(copy_bytes, sums, ws, input_ready, s, &mem, &partial, [&](int8_t *xt) {
         return launch_byte_copy(io, x, lut->bits, xt, N, q.Cin, H, W, Ty - 1, Tx - 1, 1, Wp, s);
     });
     if (rc) return rc;
@@ -294,7 +314,7 @@ int byte_conv_transpose2d(const adapt_lut *lut, const ByteTables &t, const ByteS
     const int Ly = kh - st - pad > 0 ? kh - st - pad : 0, Lx = kw - st - pad > 0 ? kw - st - pad : 0;
     if (Ly > 0 || Lx > 0) c.zsum = zsum;
     c.cv_Ho = Ho; c.cv_Wo = Wo; c.cv_H = H; c.cv_W = W; c.cv_kh = kh; c.cv_kw = kw; c.cv_s = st; c.cv_pad = pad; c.cv_Ly = Ly; c.cv_Lx = Lx;
-    rc = run_byte(lut, t, q, pl, c, reinterpret_cast<int8_t *>(mem), reinterpret_cast<int32_t *>(mem + copy_bytes), out, s, io);
+    rc = run_byte(lut, t, q, pl, c, reinterpret_cast<int8_t *>(mem), partial, out, s, io);
     return ws_put(ws, mem, s, rc);
 }
 

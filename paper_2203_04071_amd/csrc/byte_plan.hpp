@@ -1,6 +1,7 @@
 // How a product on the byte kernel (lut_byte.hpp) is spread over the chip: pixels per row slot and slices of the inner
 // dimension.  Host code only (no device calls).
 #pragma once
+#include <stddef.h>
 
 namespace adapt_api {
 
@@ -59,6 +60,36 @@ inline BytePlan plan_byte(const BytePlanIn &in) {
         }
     }
     return best;
+}
+
+// Bytes of the sums that the slices of a split product leave behind: 16 R KB per workgroup (launch_tiles: channel tiles x phases
+// of one launch).
+inline size_t byte_partial_bytes(int R, int ksplit, long long rows, long long launch_tiles) {
+    return ksplit > 1 ? (size_t)((rows + 256 * R - 1) / (256 * R) * launch_tiles * ksplit) * R * 16384 : 0;
+}
+
+// The most that any product of up to `rows4` virtual rows needs of them, whatever its plan.  A plan splits the inner dimension
+// where there are few tiles, so fewer rows often need more (8 bits, K = 777, N = 999: 4.7 MB for 6000 rows, 36 MB for
+// 4000): a buffer that has to last for all smaller products is sized by this bound, which only grows with the rows.  For every R and
+// number of row tiles t: the slices that the estimate chooses there.  One row tile: the fewer rows, the cheaper a slice, so those of
+// one row; with 8 or 4 pixels per row slot only from half a tile on (below, half as many pixels make one tile too, and are cheaper).
+// in: tiles, steps, copy_lines and cu count.
+inline size_t byte_partial_reserve(BytePlanIn in, long long rows4, long long launch_tiles) {
+    size_t most = 0;
+    for (int R = 2; R <= 8; R *= 2)
+        for (long long t = 1; t * in.tiles <= in.cu && t * in.tiles <= 1024; ++t) {
+            if (rows4 <= (t > 1 ? (t - 1) * 256 * R : (R > 2 ? 128 * R : 0))) break;
+            in.rows4 = in.rows2 = t > 1 ? t * 256 * R : 1;
+            int slices = 1;
+            long long least = 0;
+            for (int ks = 1; ks <= 32 && ks <= in.steps && t * in.tiles * ks <= 2LL * in.cu; ++ks) {
+                const long long c = byte_plan_clocks(in, R, ks);
+                if (ks == 1 || c < least) { least = c; slices = ks; }
+            }
+            const size_t bytes = byte_partial_bytes(R, slices, in.rows4, launch_tiles);
+            most = bytes > most ? bytes : most;
+        }
+    return most;
 }
 
 // A product on the whole-table kernel (lut_rows.hpp), as run_rows lays it out

@@ -2,6 +2,7 @@
 // per lane, whether the inner dimension is split over workgroups, and the layout of the activation copy.  Host code only
 // (no device calls), so that the decisions can be enumerated without a GPU.
 #pragma once
+#include <stddef.h>
 
 namespace adapt_api {
 
@@ -127,6 +128,16 @@ inline LinesPlan plan_lines(const PlanIn &in) {
     pl.xmajor = (pl.R == 8 && in.Wo % 4 == 0 && M % 8 == 0 && in.sw == 1 && in.k_cc % 4 == 0) ? 1 : 0;
     pl.kernel = pl.xmajor ? LK_XMAJOR : (in.k_cc % 4 == 0 ? LK_FAST : LK_GENERIC);
     return pl;
+}
+
+// bytes of the partial sums of a split product with out_elems outputs
+inline size_t lines_partial_bytes(const LinesPlan &pl, size_t out_elems) { return pl.ksplit > 1 ? (size_t)pl.ksplit * out_elems * 4 : 0; }
+
+// The most that any product of up to out_elems outputs needs of them, whatever its plan: at most 16 slices, and at most cu
+// workgroups of 1024 rows x 8 channels.  (Larger products are split less, so a buffer sized for the plan of one does not hold the sums of smaller ones.)
+inline size_t lines_partial_reserve(int cu, size_t out_elems) {
+    const size_t few = 16 * out_elems, chip = (size_t)cu * 1024 * 8;
+    return (few < chip ? few : chip) * 4;
 }
 
 }  // namespace adapt_api

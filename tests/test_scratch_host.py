@@ -1,0 +1,74 @@
+"""Room for partial sums (host code only: the plan headers, compiled for the CPU).  Smaller products are split more, so what
+one product needs is no measure for what a smaller one needs; what a handle reserves has to be."""
+import os
+import subprocess
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2203_04071_amd", "csrc")
+
+PROGRAM = r'''
+#include <cstdio>
+#include <cstdlib>
+#include "byte_plan.hpp"
+#include "lines_plan.hpp"
+using namespace adapt_api;
+
+static int bad(const char *what, long long a, long long b, long long c, long long d) {
+    std::printf("%s: %lld %lld %lld %lld\n", what, a, b, c, d);
+    return 1;
+}
+
+int main() {
+    int shrinks = 0;        // how often a larger product needs less: what makes the reservation necessary
+    const int cu = 256;
+    const struct { int n_tiles, phases, steps; } byte_shapes[] = {{63, 1, 49}, {32, 1, 32}, {4, 1, 36}, {2, 1, 18}, {1, 1, 9}, {13, 1, 57}, {16, 1, 144},
+                                                                 {4, 1, 256}, {1, 4, 16}, {16, 4, 128}, {1, 9, 20}, {1, 64, 3}, {256, 1, 256}, {1, 1, 2040}};
+    for (const auto &q : byte_shapes)
+        for (int lines = 4; lines <= 256; lines *= 4) {
+            const long long launch = (long long)q.n_tiles * (q.phases < 4 ? q.phases : 4);
+            BytePlanIn in{0, 0, q.n_tiles * q.phases, q.steps, lines, cu};
+            size_t held = 0, before = 0;
+            for (long long rows = 1; rows < 300000; rows += rows < 9000 ? 7 : 997) {
+                in.rows4 = (rows + 3) / 4 * 4;
+                const size_t room = byte_partial_reserve(in, in.rows4, launch);
+                if (room < held) return bad("byte: the room shrinks", q.n_tiles, q.steps, lines, rows);
+                held = room;
+                // image rows of any width: between rows4 / 4 * 2 and rows4 rows in runs of two
+                for (long long rows2 : {(rows + 1) / 2 * 2, in.rows4, in.rows4 / 2}) {
+                    in.rows2 = rows2;
+                    const BytePlan pl = plan_byte(in);
+                    const size_t need = byte_partial_bytes(pl.R, pl.ksplit, pl.R >= 4 ? in.rows4 : in.rows2, launch);
+                    if (need > room) return bad("byte: more than the room", q.n_tiles, q.steps, lines, rows);
+                    shrinks += need < before;
+                    before = need;
+                }
+            }
+        }
+    const struct { int n_tiles, phases, cc, taps, quad_steps; } line_shapes[] = {{8, 1, 8, 9, 36}, {8, 1, 8, 9, 0}, {2, 1, 2, 9, 9}, {25, 1, 13, 9, 0}, {125, 1, 100, 1, 0},
+                                                                                 {4, 4, 16, 4, 32}, {1, 4, 4, 1, 0}, {256, 1, 64, 1, 0}, {1, 1, 512, 1, 256}};
+    for (const auto &q : line_shapes)
+        for (int Wo : {1, 7, 8, 32})
+            for (int sw = 1; sw <= 2; ++sw) {
+                size_t held = 0;
+                for (int lines = 1; lines < 40000; lines += lines < 600 ? 1 : 131) {
+                    const int M = lines * Wo;
+                    const size_t out = (size_t)M * q.phases * q.n_tiles * 8;        // (the last tile full: the most outputs)
+                    const LinesPlan pl = plan_lines(PlanIn{M, q.n_tiles * q.phases, q.cc, q.taps, Wo, sw, q.quad_steps, 8, cu});
+                    const size_t room = lines_partial_reserve(cu, out);
+                    if (room < held) return bad("lines: the room shrinks", q.n_tiles, q.taps, Wo, M);
+                    if (lines_partial_bytes(pl, out) > room) return bad("lines: more than the room", q.n_tiles, q.taps, Wo, M);
+                    held = room;
+                }
+            }
+    std::printf("ok %d\n", shrinks);
+    return shrinks > 0 ? 0 : 1;
+}
+'''
+
+
+def test_room_for_partial_sums_covers_every_smaller_product(tmp_path):
+    src = tmp_path / "room.cpp"
+    src.write_text(PROGRAM)
+    exe = tmp_path / "room"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-include", "initializer_list", "-I", CSRC, str(src), "-o", str(exe)], check=True, timeout=120)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
