@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/adapt_mi355.h"
+#include "byte_form.hpp"
 #include "elementwise.hpp"
 
 namespace adapt_api {
@@ -188,7 +189,5 @@ struct adapt_lut {
     int img_bytes;          // per image, multiple of 16
     uint16_t *img_dev[2];   // [0] = only / low half, [1] = high half
     uint16_t *lut16_dev[2]; // same halves, plain [a & mask][w & mask] order (source of the derived line tables)
-    // byte form (lut_byte.hpp): T[a][w] = (a & byte_am) * (w & byte_wm) + byte_c + an error of one byte, if there is one
-    bool byte_form;
-    int byte_c, byte_am, byte_wm;
+    adapt_api::ByteForm byte;   // for the byte kernel, if the table has such a form
 };

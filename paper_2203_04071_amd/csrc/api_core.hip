@@ -51,32 +51,6 @@ void trim_scratch() {
 }
 using namespace adapt_api;
 
-// The byte form of a table (see struct adapt_lut): the exact product of the operands, or of the operands without their low
-// ta / tw bits (multipliers that drop them), leaves an error that spans at most 255.  The first pair that does is taken.
-static void find_byte_form(adapt_lut *l, const int32_t *table) {
-    l->byte_form = false;
-    l->byte_c = 0; l->byte_am = l->byte_wm = -1;
-    if (l->storage != 0) return;
-    const int n = 1 << l->bits, H = n >> 1;
-    for (int sum = 0; sum <= 6; ++sum)
-        for (int ta = sum < 3 ? sum : 3; ta >= 0; --ta) {
-            const int tw = sum - ta;
-            if (tw > 3) break;
-            const int am = -(1 << ta), wm = -(1 << tw);
-            int lo = 0x7fffffff, hi = -0x7fffffff;
-            for (int a = -H; a < H && hi - lo <= 255; ++a)
-                for (int w = -H; w < H; ++w) {
-                    const int e = table[(size_t)(a + H) * n + (w + H)] - (a & am) * (w & wm);
-                    lo = e < lo ? e : lo;
-                    hi = e > hi ? e : hi;
-                }
-            if (hi - lo > 255) continue;
-            l->byte_form = true;
-            l->byte_c = lo + 128; l->byte_am = am; l->byte_wm = wm;
-            return;
-        }
-}
-
 extern "C" {
 
 const char *adapt_last_error(void) { return g_err; }
@@ -108,7 +82,7 @@ int adapt_lut_create(adapt_lut **out, int bits, const int32_t *table_host) {
     l->storage = (lo >= -32768 && hi <= 32767) ? 0 : 1;
     l->rs = n + 2;
     l->img_bytes = ((n * l->rs * 2 + 15) / 16) * 16;
-    find_byte_form(l, table_host);
+    l->byte = l->storage == 0 ? find_byte_form(bits, table_host) : ByteForm{};
     l->img_dev[0] = l->img_dev[1] = nullptr;
     l->lut16_dev[0] = l->lut16_dev[1] = nullptr;
     if (hipGetDevice(&l->device) != hipSuccess) {

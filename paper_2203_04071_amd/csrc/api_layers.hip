@@ -991,7 +991,7 @@ int convt_any(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *a
               int kw, int stride, int pad, hipStream_t s) {
     const int Ho = (H - 1) * stride - 2 * pad + kh, Wo = (W - 1) * stride - 2 * pad + kw;
     const long long M = (long long)N * Ho * Wo;
-    if (convt_phases_ok(H, W, kh, kw, stride, pad) && M >= LINES_MIN_ROWS && stride <= 8 && lut->byte_form) {
+    if (convt_phases_ok(H, W, kh, kw, stride, pad) && M >= LINES_MIN_ROWS && stride <= 8 && lut->byte.found) {
         const ByteShape q = byte_shape(lut->bits, Cout, Cin, kh, kw, stride);
         if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * (q.kh - 1), W + 2 * (q.kw - 1), 1))
             return with_temp_byte_tables(lut, w, q, true, s, [&](const ByteTables &t) {
@@ -1043,7 +1043,7 @@ int adapt_approx_linear(const adapt_lut *lut, const int8_t *a_dev, const int8_t 
     g.mode = adapt::MODE_GEMM; g.M = M; g.N = N; g.Cin = K; g.taps = 1; g.kw = 1;
     g.H = 1; g.W = 1; g.Wo = 1; g.HoWo = 1; g.sh = g.sw = g.dh = g.dw = 1; g.ph = g.pw = 0;
     g.kstride = 1; g.img_stride = K;
-    if (lut->byte_form && K >= 8) {
+    if (lut->byte.found && K >= 8) {
         const ByteShape q = byte_shape(lut->bits, N, K, 1, 1);
         if (byte_packable(q, (size_t)4 << 30) && (long long)q.cg * 4 * (M + 4) < 0x7fffff00LL && (M >= LINES_MIN_ROWS || byte_call_pays(lut, q, M, true))) {
             rc = with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
@@ -1112,7 +1112,7 @@ int adapt_approx_conv2d(const adapt_lut *lut, const int8_t *x_dev, const int8_t 
     g.H = H; g.W = W; g.Wo = (int)Wo; g.HoWo = (int)(Ho * Wo);
     g.sh = stride_h; g.sw = stride_w; g.ph = pad_h; g.pw = pad_w; g.dh = dil_h; g.dw = dil_w;
     g.kstride = H * W; g.img_stride = Cin * H * W; g.groups = groups;
-    if (groups == 1 && g.M >= LINES_MIN_ROWS && lut->byte_form) {
+    if (groups == 1 && g.M >= LINES_MIN_ROWS && lut->byte.found) {
         const ByteShape q = byte_shape(lut->bits, Cout, Cin, kh, kw);
         if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * pad_h, W + 2 * pad_w, stride_w))
             return with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
@@ -1226,7 +1226,7 @@ static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t 
     if ((long long)N * Cin * kh * kw > 0x7fffffffLL) return fail(ADAPT_ERR_UNSUPPORTED, "%s: more than 2^31-1 weights", who);
     const LinesShape q = lines_shape(kind, lut->bits, N, Cin, kh, kw, lut->storage == 0);
     const ByteShape bq = byte_shape(lut->bits, N, Cin, kh, kw);
-    const bool byte_form = lut->byte_form && byte_packable(bq, (size_t)64 << 30);
+    const bool byte_form = lut->byte.found && byte_packable(bq, (size_t)64 << 30);
     if (!byte_form && q.dt_bytes * (size_t)(lut->storage + 1) > ((size_t)64 << 30))
         return fail(ADAPT_ERR_OUT_OF_MEMORY, "%s: packed tables would need %zu bytes", who, q.dt_bytes * (size_t)(lut->storage + 1));
     adapt_weights *h = new (std::nothrow) adapt_weights();
@@ -1349,7 +1349,7 @@ int adapt_weights_pack_conv_transpose2d(adapt_weights **out, const adapt_lut *lu
         const LinesShape q = convt_phase_shape(lut->bits, Cout, Cin, kh, kw, stride);
         const size_t all = q.dt_bytes * stride * stride;
         const ByteShape bq = byte_shape(lut->bits, Cout, Cin, kh, kw, stride);
-        if (lut->byte_form && byte_packable(bq, (size_t)64 << 30)) {
+        if (lut->byte.found && byte_packable(bq, (size_t)64 << 30)) {
             h->Cp = q.Cp; h->Cc = q.Cc; h->n_tiles = q.n_tiles;
             e = dbg_malloc((void **)&h->zsum_dev, (size_t)Cout * kh * kw * sizeof(int32_t));
             if (e == hipSuccess) {

@@ -35,7 +35,7 @@ int pack_byte(const adapt_lut *lut, const int8_t *w, const ByteShape &q, const B
     p.lut16 = lut->lut16_dev[0]; p.w = w; p.dt = t.dt; p.wx = t.wx; p.arrived = t.arrived;
     p.bits = lut->bits; p.N = q.N; p.Cin = q.Cin; p.taps = q.kh * q.kw; p.cg = q.cg; p.n_tiles = q.n_tiles; p.steps = q.steps;
     p.wmode = convt ? 1 : 0; p.kh = q.kh * q.st; p.kw = q.kw * q.st; p.st = q.st;
-    p.c = lut->byte_c; p.am = lut->byte_am; p.wm = lut->byte_wm;
+    p.c = lut->byte.c; p.am = lut->byte.am; p.wm = lut->byte.wm;
     // about eight workgroups per compute unit: enough to hide the latencies, and each stages its band for several tables
     const int bands = ((1 << lut->bits) + adapt::BYTE_PACK_LINES - 1) / adapt::BYTE_PACK_LINES;
     p.tables = q.phases * q.n_tiles * q.steps;
@@ -141,8 +141,8 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
     p.cg = q.cg; p.taps = q.kh * q.kw; p.kw = q.kw; p.steps = q.steps; p.ksplit = pl.ksplit; p.even = pl.even;
     p.bits = bits; p.copy_lines = (1 << bits) >> (c.nonneg ? 1 : 0);
     p.img_stride = c.img_stride; p.oy_stride = c.oy_stride; p.ch_stride = c.ch_stride; p.ky_stride = c.ky_stride; p.dw = c.dw; p.wsub = c.wsub;
-    p.amask = (uint32_t)(lut->byte_am & 0xff) * 0x01010101u;
-    p.corr = (int)(uint32_t)((long long)q.kh * q.kw * q.Cin * lut->byte_c);
+    p.amask = (uint32_t)(lut->byte.am & 0xff) * 0x01010101u;
+    p.corr = (int)(uint32_t)((long long)q.kh * q.kw * q.Cin * lut->byte.c);
     p.d_HoWv = fast_div((uint32_t)(c.Ho * p.Wv)); p.d_Wv = fast_div((uint32_t)p.Wv);
     p.d_ntiles = fast_div((uint32_t)q.n_tiles); p.d_mtiles = fast_div((uint32_t)p.m_tiles); p.d_ksplit = fast_div((uint32_t)p.ksplit);
     p.d_taps = fast_div((uint32_t)p.taps); p.d_rest = fast_div((uint32_t)((q.cg & 3) ? q.cg & 3 : 1)); p.d_kw = fast_div((uint32_t)q.kw);
@@ -157,7 +157,7 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
     p.zsum = c.zsum; p.cv_s = fast_div((uint32_t)c.cv_s);
     p.cv_Ho = c.cv_Ho; p.cv_Wo = c.cv_Wo; p.cv_H = c.cv_H; p.cv_W = c.cv_W; p.cv_kh = c.cv_kh; p.cv_kw = c.cv_kw; p.cv_pad = c.cv_pad;
     p.cv_Ly = c.cv_Ly; p.cv_Lx = c.cv_Lx;
-    const int level = lut->byte_am != -1 ? 3 : p.act == 2 ? 2 : (p.zsum || p.chain.buf ? 1 : 0);
+    const int level = lut->byte.am != -1 ? 3 : p.act == 2 ? 2 : (p.zsum || p.chain.buf ? 1 : 0);
     if (p.ksplit > 1 && !partial) return fail(ADAPT_ERR_HIP, "byte path: no room for partial sums");
     const int n_phases = (int)c.xt_off.size();
     const size_t tables = (size_t)q.n_tiles * q.steps;          // of one phase
