@@ -1215,6 +1215,8 @@ static int byte_chain_prepare(const adapt_weights *h, size_t copy_bytes, int N, 
     return ADAPT_OK;
 }
 
+constexpr size_t PACK_LIMIT = (size_t)64 << 30;     // bytes of derived tables in one order that a handle may hold
+
 static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t *w_dev, int kind, int N, int Cin, int kh,
                         int kw, void *stream, const char *who) {
     if (!out) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: out is NULL", who);
@@ -1226,8 +1228,8 @@ static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t 
     if ((long long)N * Cin * kh * kw > 0x7fffffffLL) return fail(ADAPT_ERR_UNSUPPORTED, "%s: more than 2^31-1 weights", who);
     const LinesShape q = lines_shape(kind, lut->bits, N, Cin, kh, kw, lut->storage == 0);
     const ByteShape bq = byte_shape(lut->bits, N, Cin, kh, kw);
-    const bool byte_form = lut->byte.found && byte_packable(bq, (size_t)64 << 30);
-    if (!byte_form && q.dt_bytes * (size_t)(lut->storage + 1) > ((size_t)64 << 30))
+    const bool byte_form = lut->byte.found && byte_packable(bq, PACK_LIMIT);
+    if (!byte_form && q.dt_bytes * (size_t)(lut->storage + 1) > PACK_LIMIT)
         return fail(ADAPT_ERR_OUT_OF_MEMORY, "%s: packed tables would need %zu bytes", who, q.dt_bytes * (size_t)(lut->storage + 1));
     adapt_weights *h = new (std::nothrow) adapt_weights();
     if (!h) return fail(ADAPT_ERR_OUT_OF_MEMORY, "%s: host allocation failed", who);
@@ -1349,7 +1351,7 @@ int adapt_weights_pack_conv_transpose2d(adapt_weights **out, const adapt_lut *lu
         const LinesShape q = convt_phase_shape(lut->bits, Cout, Cin, kh, kw, stride);
         const size_t all = q.dt_bytes * stride * stride;
         const ByteShape bq = byte_shape(lut->bits, Cout, Cin, kh, kw, stride);
-        if (lut->byte.found && byte_packable(bq, (size_t)64 << 30)) {
+        if (lut->byte.found && byte_packable(bq, PACK_LIMIT)) {
             h->Cp = q.Cp; h->Cc = q.Cc; h->n_tiles = q.n_tiles;
             e = dbg_malloc((void **)&h->zsum_dev, (size_t)Cout * kh * kw * sizeof(int32_t));
             if (e == hipSuccess) {
@@ -1360,7 +1362,7 @@ int adapt_weights_pack_conv_transpose2d(adapt_weights **out, const adapt_lut *lu
                     return rc;
                 }
             }
-        } else if (all * (size_t)(lut->storage + 1) > ((size_t)64 << 30)) {
+        } else if (all * (size_t)(lut->storage + 1) > PACK_LIMIT) {
             h->phased = false;      // too large to hold: this handle keeps to the plain form
         } else {
             h->Cp = q.Cp; h->Cc = q.Cc; h->n_tiles = q.n_tiles; h->dt_bytes = all;
@@ -1435,13 +1437,15 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
         rows < 1 || Wo < 1 || sw < 1)
         return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: bad argument", who);
     int k = 0, rpw = 0, ks = 1, st = 0, wg = 0;
-    const bool phased = kind == 2 && kh % stride == 0 && kw % stride == 0;
-    if (kind == 0 && rows < LINES_MIN_ROWS && (storage != 2 || !byte_pays(byte_shape(bits, Cout, Cin, 1, 1), bits, 0, rows, false, cu))) {
+    const bool phased = kind == 2 && kh % stride == 0 && kw % stride == 0 && stride <= 8;
+    const ByteShape bq = byte_shape(bits, Cout, Cin, kh, kw, phased ? stride : 1);
+    if (storage == 2 && !byte_packable(bq, PACK_LIMIT)) storage = 0;        // (such a handle keeps the other tables)
+    if (kind == 0 && rows < LINES_MIN_ROWS && (storage != 2 || !byte_pays(bq, bits, 0, rows, false, cu))) {
         k = -1;                                 // whole-table kernel (lut_rows_kernel)
     } else if (kind == 2 && !phased) {
         k = -1;
     } else if (storage == 2) {                  // lut_byte_kernel
-        const ByteShape q = byte_shape(bits, Cout, Cin, kh, kw, kind == 2 ? stride : 1);
+        const ByteShape &q = bq;
         const int lines = rows / Wo;            // image rows of the output
         const BytePlan pl = byte_plan_of(q, bits, 1, lines > 0 ? lines : 1, Wo, false, cu);
         const int V = pl.R < 4 ? pl.R : 4;

@@ -154,3 +154,14 @@ def test_linear_layers_below_4096_rows(B, M, K, N, bits):
     y = B.adapt_linear_layer_f32(pw, dev(x), 0.25, 0.5)
     q = orc.quantize(x, np.float32(0.25), bits)
     assert np.array_equal(host(y).view(np.uint32), orc.dequant(orc.approx_linear(t, bits, q, w), np.float32(0.5), M, N, 1).reshape(M, N).view(np.uint32))
+
+
+@pytest.mark.parametrize("K", [32640, 32641])
+def test_longest_inner_dimension(B, K):
+    """The last length whose group offsets fit, and the first that takes the other tables."""
+    rng = np.random.default_rng(K)
+    t = table("product", 6, rng)
+    L = B.Lut(t, 6)
+    a, w = wl.random_i8(rng, (4100, K), 6), wl.random_i8(rng, (3, K), 6)
+    pw = B.adapt_weights_pack_linear(L, dev(w))
+    assert (host(B.adapt_approx_linear_packed(pw, dev(a))) == orc.approx_linear(t, 6, a, w, threads=4)).all()

@@ -78,3 +78,15 @@ def test_linear_layers_with_byte_tables_change_kernel_once(plan, bits, K, N, fir
         assert kernel == (BYTE if rows >= first_byte else ROWS)
         if kernel == BYTE:
             assert wgs == -(-rows // per_wg) * -(-N // 16) * ksplit
+
+
+def test_handles_whose_inner_dimension_is_too_long_for_the_byte_kernel(plan):
+    # its table of group offsets holds 2040 steps of 16 inner indices; longer products keep the other tables
+    assert plan(0, 8, 2, 64, 32640, 1, 1, 1, 8192, 8192, 1)[::3] == (BYTE, 2040)
+    for K in (32641, 32644, 40000):
+        assert plan(0, 8, 2, 64, K, 1, 1, 1, 8192, 8192, 1) == plan(0, 8, 0, 64, K, 1, 1, 1, 8192, 8192, 1)
+        assert plan(0, 8, 2, 64, K, 1, 1, 1, 1024, 1024, 1)[0] == ROWS
+    # transposed: a phase counts, and strides above 8 have none
+    assert plan(2, 8, 2, 64, 4080, 4, 4, 2, 4096, 32, 1)[0] == plan(2, 8, 2, 64, 8160, 4, 4, 2, 4096, 32, 1)[0] == BYTE
+    assert plan(2, 8, 2, 64, 8164, 4, 4, 2, 4096, 32, 1) == plan(2, 8, 0, 64, 8164, 4, 4, 2, 4096, 32, 1)
+    assert plan(2, 8, 2, 16, 16, 18, 18, 9, 4096, 32, 1)[0] == ROWS
