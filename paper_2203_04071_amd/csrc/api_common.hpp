@@ -13,6 +13,7 @@
 #include "../../include/adapt_mi355.h"
 #include "byte_form.hpp"
 #include "elementwise.hpp"
+#include "scratch.hpp"
 
 namespace adapt_api {
 
@@ -47,48 +48,6 @@ inline unsigned ew_grid(size_t work_items) {
 inline unsigned red_grid(size_t n) {
     const size_t g = (n + adapt::RED_THREADS * 4 - 1) / (adapt::RED_THREADS * 4);
     return (unsigned)(g < 1 ? 1 : (g > adapt::RED_BLOCKS ? adapt::RED_BLOCKS : g));
-}
-
-// Debugging aid: with ADAPT_POISON_ALLOC set in the environment every device allocation of the library is filled with
-// 0xA5 bytes before use, so that code which relies on fresh memory being zero shows up in the tests.
-inline bool poison_on() {
-    static const bool v = getenv("ADAPT_POISON_ALLOC") != nullptr;
-    return v;
-}
-inline hipError_t dbg_poison(void *p, size_t bytes, hipStream_t s) {
-    if (!poison_on() || !p || bytes < 4) return hipSuccess;
-    adapt::fill_u32_kernel<<<4096, 256, 0, s>>>(static_cast<uint32_t *>(p), 0xA5A5A5A5u, bytes / 4);
-    return hipGetLastError();
-}
-// Scratch memory of calls comes from a pool of the library's own, one per device, that keeps up to SCRATCH_KEEP bytes between
-// calls: the device's default pool gives everything back at every synchronisation, and a program that waits for each result
-// then pays for mapping the memory again (waiting after every call: 12-bit 3 x 3 layer 291 -> 218 us, retraining step 299 -> 250 us).
-// trim_scratch (called when a multiplier table is destroyed) gives back what no call uses.  A call that is being recorded allocates through the default pool, as a node of the graph.
-constexpr uint64_t SCRATCH_KEEP = 256ull << 20;
-hipMemPool_t scratch_pool();        // of the current device; nullptr: there is none (defined in api_core.hip)
-void trim_scratch();
-
-// whether calls on this stream are being recorded, or may be (the question has no answer)
-inline bool is_capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;
-}
-
-inline hipError_t dbg_malloc_async(void **p, size_t bytes, hipStream_t s) {
-    hipMemPool_t pool = is_capturing(s) ? nullptr : scratch_pool();
-    hipError_t e = pool ? hipMallocFromPoolAsync(p, bytes, pool, s) : hipMallocAsync(p, bytes, s);
-    if (e == hipSuccess) e = dbg_poison(*p, bytes, s);
-    return e;
-}
-inline hipError_t dbg_malloc(void **p, size_t bytes) {
-    hipError_t e = hipMalloc(p, bytes);
-    if (e == hipSuccess && poison_on()) {
-        e = dbg_poison(*p, bytes, nullptr);
-        if (e == hipSuccess) e = hipDeviceSynchronize();
-    }
-    return e;
 }
 
 // Scratch memory of one call: the activation copy, and the partial sums of a product whose inner dimension is split.  Plain

@@ -1,52 +1,17 @@
 // C ABI, part 1: error text, table handles, quantiser / dequantiser, calibrators, the fp32 operations between layers.
 #include "api_common.hpp"
 
-#include <mutex>
-
 namespace adapt_api {
 thread_local char g_err[512] = "";
 
-namespace {
-constexpr int SCRATCH_DEVICES = 64;
-std::mutex g_scratch_lock;
-struct ScratchPool {
-    std::atomic<int> state{0};      // 0: not asked for yet, 1: there is one, 2: the device has none
-    hipMemPool_t pool = nullptr;
-} g_scratch[SCRATCH_DEVICES];
-}  // namespace
-
-hipMemPool_t scratch_pool() {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= SCRATCH_DEVICES) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    ScratchPool &sp = g_scratch[dev];
-    if (sp.state.load(std::memory_order_acquire) == 0) {
-        std::lock_guard<std::mutex> lock(g_scratch_lock);
-        if (sp.state.load(std::memory_order_relaxed) == 0) {
-            hipMemPoolProps props{};
-            props.allocType = hipMemAllocationTypePinned;
-            props.location.type = hipMemLocationTypeDevice;
-            props.location.id = dev;
-            uint64_t keep = SCRATCH_KEEP;
-            hipMemPool_t pool = nullptr;
-            bool ok = hipMemPoolCreate(&pool, &props) == hipSuccess;
-            if (ok && hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
-                (void)hipMemPoolDestroy(pool);
-                ok = false;
-            }
-            if (!ok) (void)hipGetLastError();
-            sp.pool = ok ? pool : nullptr;
-            sp.state.store(ok ? 1 : 2, std::memory_order_release);
-        }
-    }
-    return sp.pool;
+bool poison_on() {
+    static const bool on = getenv("ADAPT_POISON_ALLOC") != nullptr;
+    return on;
 }
-
-void trim_scratch() {
-    for (ScratchPool &sp : g_scratch)
-        if (sp.state.load(std::memory_order_acquire) == 1 && hipMemPoolTrimTo(sp.pool, 0) != hipSuccess) (void)hipGetLastError();
+hipError_t dbg_poison(void *p, size_t bytes, hipStream_t s) {
+    if (!p || bytes < 4) return hipSuccess;
+    adapt::fill_u32_kernel<<<4096, 256, 0, s>>>(static_cast<uint32_t *>(p), 0xA5A5A5A5u, bytes / 4);
+    return hipGetLastError();
 }
 }
 using namespace adapt_api;

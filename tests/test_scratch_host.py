@@ -72,3 +72,111 @@ def test_room_for_partial_sums_covers_every_smaller_product(tmp_path):
     subprocess.run(["g++", "-O1", "-std=c++17", "-include", "initializer_list", "-I", CSRC, str(src), "-o", str(exe)], check=True, timeout=120)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+# The allocation functions against a device with 1000 MB: what the library's pool keeps, and what the default pool holds, is
+# in nobody else's way.
+MEMORY = r'''
+#define __HIP_PLATFORM_AMD__
+#include "scratch.hpp"
+#include <cstdio>
+#include <map>
+using namespace adapt_api;
+
+static const size_t MB = (size_t)1 << 20, CAPACITY = 1000 * MB;
+static size_t used, kept[2];                    // by allocations; by pools without a user (0: the library's, 1: the default one)
+static int pools_made, fail_pools, trims, device;
+static bool capturing;
+static std::map<void *, std::pair<size_t, int>> live;
+static char *next_address = (char *)0x1000;
+
+static hipError_t take(void **p, size_t bytes, int pool) {
+    const size_t reuse = pool >= 0 ? (kept[pool] < bytes ? kept[pool] : bytes) : 0;
+    if (used + kept[0] + kept[1] - reuse + bytes > CAPACITY) return hipErrorOutOfMemory;
+    if (pool >= 0) kept[pool] -= reuse;
+    used += bytes;
+    *p = next_address += 256;
+    live[*p] = {bytes, pool};
+    return hipSuccess;
+}
+static void give(void *p) {
+    const auto it = live.find(p);
+    used -= it->second.first;
+    if (it->second.second >= 0) kept[it->second.second] += it->second.first;
+    live.erase(it);
+}
+extern "C" {
+hipError_t hipMalloc(void **p, size_t bytes) { return take(p, bytes, -1); }
+hipError_t hipMallocAsync(void **p, size_t bytes, hipStream_t) {
+    kept[1] = 0;                                // (the default pool gives back at the next synchronisation)
+    return take(p, bytes, 1);
+}
+hipError_t hipMallocFromPoolAsync(void **p, size_t bytes, hipMemPool_t, hipStream_t) { return take(p, bytes, 0); }
+hipError_t hipMemPoolCreate(hipMemPool_t *pool, const hipMemPoolProps *) {
+    if (fail_pools-- > 0) return hipErrorOutOfMemory;
+    *pool = (hipMemPool_t)(size_t)++pools_made;
+    return hipSuccess;
+}
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
+hipError_t hipMemPoolDestroy(hipMemPool_t) { return hipSuccess; }
+hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) { ++trims; kept[0] = 0; return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = device; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st) {
+    *st = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+}
+namespace adapt_api {
+bool poison_on() { return false; }
+hipError_t dbg_poison(void *, size_t, hipStream_t) { return hipSuccess; }
+}
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+
+int main() {
+    void *a = nullptr, *b = nullptr, *c = nullptr;
+@BODY@
+    return 0;
+}
+'''
+
+
+def run_memory(tmp_path, body):
+    src, exe = tmp_path / "memory.cpp", tmp_path / "memory"
+    src.write_text(MEMORY.replace("@BODY@", body))
+    subprocess.run(["g++", "-O1", "-std=c++17", "-pthread", "-w", "-I", CSRC, "-I", "/opt/rocm/include", str(src), "-o", str(exe)], check=True, timeout=120)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_scratch_that_is_kept_refuses_nothing(tmp_path):
+    run_memory(tmp_path, r'''
+    // a handle's allocation finds the memory that the pool keeps
+    CHECK(dbg_malloc_async(&a, 250 * MB, nullptr) == hipSuccess);
+    give(a);
+    CHECK(kept[0] == 250 * MB);
+    CHECK(dbg_malloc(&b, 900 * MB) == hipSuccess && trims == 1);
+    // too much is still too much
+    CHECK(dbg_malloc(&c, 200 * MB) == hipErrorOutOfMemory);
+    CHECK(dbg_malloc_async(&c, 200 * MB, nullptr) == hipErrorOutOfMemory);
+    give(b);
+    // scratch that the library's pool cannot have comes from the default pool
+    CHECK(dbg_malloc_async(&a, 200 * MB, nullptr) == hipSuccess);
+    give(a);
+    kept[1] = 700 * MB;
+    CHECK(dbg_malloc_async(&a, 600 * MB, nullptr) == hipSuccess && live[a].second == 1);
+    give(a);
+    // recorded calls allocate through the default pool
+    capturing = true;
+    CHECK(dbg_malloc_async(&a, MB, nullptr) == hipSuccess && live[a].second == 1);
+''')
+
+
+def test_a_pool_that_could_not_be_made_is_tried_again(tmp_path):
+    run_memory(tmp_path, r'''
+    fail_pools = 1;
+    CHECK(dbg_malloc_async(&a, MB, nullptr) == hipSuccess && live[a].second == 1 && pools_made == 0);
+    CHECK(dbg_malloc_async(&b, MB, nullptr) == hipSuccess && live[b].second == 0 && pools_made == 1);
+    CHECK(dbg_malloc_async(&c, MB, nullptr) == hipSuccess && pools_made == 1);
+''')
