@@ -85,18 +85,20 @@ int adapt_lut_create(adapt_lut **out, int bits, const int32_t *table_host) {
                         "adapt_lut_create: device image: %s", hipGetErrorString(e));
         }
     }
+    scratch_table_made(l->device);
     *out = l;
     return ADAPT_OK;
 }
 
 int adapt_lut_destroy(adapt_lut *lut) {
     if (!lut) return ADAPT_OK;
+    const int device = lut->device;
     for (int j = 0; j < 2; ++j) {
         if (lut->img_dev[j]) (void)hipFree(lut->img_dev[j]);
         if (lut->lut16_dev[j]) (void)hipFree(lut->lut16_dev[j]);
     }
     delete lut;
-    trim_scratch();
+    scratch_table_gone(device);
     return ADAPT_OK;
 }
 

@@ -71,6 +71,7 @@ int adapt_lut16_create(adapt_lut16 **out, int bits, const int32_t *table_host) {
         (void)hipGetLastError();
         return fail(e == hipErrorOutOfMemory ? ADAPT_ERR_OUT_OF_MEMORY : ADAPT_ERR_HIP, "adapt_lut16_create: %s", hipGetErrorString(e));
     }
+    scratch_table_made(l->device);
     *out = l;
     return ADAPT_OK;
 }
@@ -107,16 +108,18 @@ int adapt_lut16_create_from_func(adapt_lut16 **out, int kind, int param, int bit
         return fail(e == hipErrorOutOfMemory ? ADAPT_ERR_OUT_OF_MEMORY : ADAPT_ERR_HIP, "adapt_lut16_create_from_func: %s",
                     hipGetErrorString(e));
     }
+    scratch_table_made(l->device);
     *out = l;
     return ADAPT_OK;
 }
 
 int adapt_lut16_destroy(adapt_lut16 *lut) {
     if (!lut) return ADAPT_OK;
+    const int device = lut->device;
     if (lut->t_dev) (void)hipFree(lut->t_dev);
     if (lut->e_dev) (void)hipFree(lut->e_dev);
     delete lut;
-    trim_scratch();
+    scratch_table_gone(device);
     return ADAPT_OK;
 }
 

@@ -17,11 +17,13 @@ hipError_t dbg_poison(void *p, size_t bytes, hipStream_t s);
 // Scratch memory of calls comes from a pool of the library's own, one per device, that keeps up to SCRATCH_KEEP bytes between
 // calls: the device's default pool gives everything back at every synchronisation, and a program that waits for each result
 // then pays for mapping the memory again (waiting after every call: 12-bit 3 x 3 layer 291 -> 218 us, retraining step 299 -> 250 us).
-// What no call uses is given back when a multiplier table is destroyed, and when an allocation of the library finds no memory.  A call that is being recorded allocates through the default pool, as a node of the graph.
+// What no call uses is given back when the last multiplier table on the device is destroyed, and when an allocation of the
+// library finds no memory (and by the runtime at every hipFree of the process: the next call maps its scratch anew, 199 MB in 130 us).  A call that is being recorded allocates through the default pool, as a node of the graph.
 constexpr uint64_t SCRATCH_KEEP = 256ull << 20;
 constexpr int SCRATCH_DEVICES = 64;
 struct ScratchPool {
     std::atomic<hipMemPool_t> pool{nullptr};
+    std::atomic<int> tables{0};     // multiplier tables on this device
 };
 inline ScratchPool g_scratch[SCRATCH_DEVICES];
 inline std::mutex g_scratch_lock;
@@ -64,8 +66,13 @@ inline void trim_scratch(ScratchPool *sp) {
     if (pool && hipMemPoolTrimTo(pool, 0) != hipSuccess) (void)hipGetLastError();
 }
 
-inline void trim_scratch() {
-    for (ScratchPool &sp : g_scratch) trim_scratch(&sp);
+// a multiplier table (of either kind) was made on a device, is gone
+inline void scratch_table_made(int dev) {
+    if (ScratchPool *sp = scratch_of(dev)) sp->tables.fetch_add(1, std::memory_order_relaxed);
+}
+inline void scratch_table_gone(int dev) {
+    ScratchPool *sp = scratch_of(dev);
+    if (sp && sp->tables.fetch_sub(1, std::memory_order_acq_rel) == 1) trim_scratch(sp);
 }
 
 // whether calls on this stream are being recorded, or may be (the question has no answer)

@@ -180,3 +180,23 @@ def test_a_pool_that_could_not_be_made_is_tried_again(tmp_path):
     CHECK(dbg_malloc_async(&b, MB, nullptr) == hipSuccess && live[b].second == 0 && pools_made == 1);
     CHECK(dbg_malloc_async(&c, MB, nullptr) == hipSuccess && pools_made == 1);
 ''')
+
+
+def test_scratch_is_kept_until_the_last_table_of_its_device_is_gone(tmp_path):
+    run_memory(tmp_path, r'''
+    scratch_table_made(0);
+    scratch_table_made(0);
+    scratch_table_made(1);
+    CHECK(dbg_malloc_async(&a, 100 * MB, nullptr) == hipSuccess);
+    give(a);
+    scratch_table_gone(1);          // another device's, which has no pool
+    scratch_table_gone(0);
+    CHECK(trims == 0 && kept[0] == 100 * MB);
+    scratch_table_gone(0);
+    CHECK(trims == 1 && kept[0] == 0);
+    scratch_table_made(0);
+    CHECK(dbg_malloc_async(&a, 100 * MB, nullptr) == hipSuccess);
+    give(a);
+    scratch_table_gone(0);
+    CHECK(trims == 2);
+''')
