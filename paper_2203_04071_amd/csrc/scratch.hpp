@@ -16,10 +16,11 @@ hipError_t dbg_poison(void *p, size_t bytes, hipStream_t s);
 
 // Scratch memory of calls comes from a pool of the library's own, one per device, that keeps up to SCRATCH_KEEP bytes between
 // calls: the device's default pool gives everything back at every synchronisation, and a program that waits for each result
-// then pays for mapping the memory again (waiting after every call: 12-bit 3 x 3 layer 291 -> 218 us, retraining step 299 -> 250 us).
+// then pays for mapping the memory again (waiting after every call: 12-bit 3 x 3 layer 291 -> 218 us, retraining step 299 -> 250 us;
+// with tables of 268 MB made for the call, 2000 rows 1024 -> 1024, 8 bits: 588 -> 202 us, 412 us by the whole-table kernel).
 // What no call uses is given back when the last multiplier table on the device is destroyed, and when an allocation of the
 // library finds no memory (and by the runtime at every hipFree of the process: the next call maps its scratch anew, 199 MB in 130 us).  A call that is being recorded allocates through the default pool, as a node of the graph.
-constexpr uint64_t SCRATCH_KEEP = 256ull << 20;
+constexpr uint64_t SCRATCH_KEEP = 1ull << 30;
 constexpr int SCRATCH_DEVICES = 64;
 struct ScratchPool {
     std::atomic<hipMemPool_t> pool{nullptr};

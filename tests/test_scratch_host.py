@@ -87,6 +87,7 @@ static const size_t MB = (size_t)1 << 20, CAPACITY = 1000 * MB;
 static size_t used, kept[2];                    // by allocations; by pools without a user (0: the library's, 1: the default one)
 static int pools_made, fail_pools, trims, device;
 static bool capturing;
+static uint64_t threshold;
 static std::map<void *, std::pair<size_t, int>> live;
 static char *next_address = (char *)0x1000;
 
@@ -117,7 +118,7 @@ hipError_t hipMemPoolCreate(hipMemPool_t *pool, const hipMemPoolProps *) {
     *pool = (hipMemPool_t)(size_t)++pools_made;
     return hipSuccess;
 }
-hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *v) { threshold = *(uint64_t *)v; return hipSuccess; }
 hipError_t hipMemPoolDestroy(hipMemPool_t) { return hipSuccess; }
 hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) { ++trims; kept[0] = 0; return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = device; return hipSuccess; }
@@ -199,4 +200,12 @@ def test_scratch_is_kept_until_the_last_table_of_its_device_is_gone(tmp_path):
     give(a);
     scratch_table_gone(0);
     CHECK(trims == 2);
+''')
+
+
+def test_scratch_of_a_retraining_step_stays_mapped(tmp_path):
+    run_memory(tmp_path, r'''
+    // a 1024 x 1024 linear layer on plain weights, 8 bits: its tables and weights, partial sums, the activation copy of 8192 rows
+    CHECK(dbg_malloc_async(&a, MB, nullptr) == hipSuccess);
+    CHECK(threshold >= 1024ull * 1024 * (256 + 1) + 67 * MB + 8192ull * 1024);
 ''')
