@@ -158,6 +158,9 @@ void launch_cols_bits(const adapt::ColsParams &p, unsigned grid, int NR, hipStre
     else adapt::lut_cols_kernel<BITS, 1><<<grid, adapt::COLS_THREADS, 0, s>>>(p);
 }
 
+// residue classes of the columns of the activation copy: the horizontal stride, where the window moves at all
+int cols_classes(const adapt::BigParams &g) { return g.conv && g.Wo == 1 ? 1 : g.sw; }
+
 // Plan of a product on the columns kernel (g as in run_big); NR == 0 where offsets would not fit 32 bits.  Every product of a
 // table with columns goes there: whole layers take 30 to 210 us against 45 to 1730 us of the gathering kernel, from 64 pixels
 // and 5 -> 9 channels (37 against 45 us) to 32 images of 32 x 32 pixels and 64 -> 64 channels, 3 x 3 (12 bits: 207 against 1730
@@ -180,8 +183,8 @@ ColsPlan cols_plan_of(const adapt_lut16 *lut, const adapt::BigParams &g) {
     }
 #endif
     // 32-bit offsets into the copy and its virtual rows
-    const long long Hp = g.H + 2LL * g.ph, Wp = g.W + 2LL * g.pw;
-    const long long copy = g.conv ? (long long)images * Hp * ((g.Cin + 1) / 2) * ((Wp + g.sw - 1) / g.sw * g.sw) : (long long)((g.Cin + 1) / 2) * ((g.M + 3) / 4 * 4);
+    const long long Hp = g.H + 2LL * g.ph, Wp = g.W + 2LL * g.pw, sw = cols_classes(g);
+    const long long copy = g.conv ? (long long)images * Hp * ((g.Cin + 1) / 2) * ((Wp + sw - 1) / sw * sw) : (long long)((g.Cin + 1) / 2) * ((g.M + 3) / 4 * 4);
     const long long packed = in.n_tiles * (in.pairs + 8) * adapt::COLS_NT;
     if (copy >= 0x1fffff00LL || in.runs * 4 + 8192 >= 0x7fffffffLL || packed >= 0x10000000LL) pl.NR = 0;
     return pl;
@@ -192,7 +195,7 @@ int run_cols(const adapt_lut16 *lut, const ColsPlan &pl, const int16_t *x, const
              const BigLayer *layer, bool *no_room) {
     const int cp = (g.Cin + 1) / 2, KP = 1 << (12 - lut->bits), h = 1 << (lut->bits - 1);
     const int images = g.conv ? g.M / g.HoWo : 1, Ho = g.conv ? g.HoWo / g.Wo : 1, Wo = g.conv ? g.Wo : g.M;
-    const int Hp = g.H + 2 * g.ph, Wp = g.W + 2 * g.pw, wsub = (Wp + g.sw - 1) / g.sw, Mp = (g.M + 3) / 4 * 4;
+    const int Hp = g.H + 2 * g.ph, Wp = g.W + 2 * g.pw, sw = cols_classes(g), wsub = (Wp + sw - 1) / sw, Mp = (g.M + 3) / 4 * 4;
     adapt::ColsParams p{};
     p.pairs = g.taps * cp; p.cp = cp; p.kw = g.kw; p.stages = (p.pairs + KP - 1) / KP;
     p.N = g.N; p.n_tiles = (g.N + adapt::COLS_NT - 1) / adapt::COLS_NT;
@@ -201,7 +204,7 @@ int run_cols(const adapt_lut16 *lut, const ColsPlan &pl, const int16_t *x, const
     p.m_tiles = (p.Mv / 4 + per_wg - 1) / per_wg; p.ksplit = pl.ksplit;
     const size_t tiles = (size_t)p.m_tiles * p.n_tiles;
     if (tiles * p.ksplit > 0x7fffffffull) return fail(ADAPT_ERR_UNSUPPORTED, "too many workgroups");
-    const size_t copy_words = g.conv ? (size_t)images * Hp * cp * g.sw * wsub : (size_t)cp * Mp;
+    const size_t copy_words = g.conv ? (size_t)images * Hp * cp * sw * wsub : (size_t)cp * Mp;
     const size_t copy_bytes = (copy_words * 4 + 64 + 255) / 256 * 256, words_bytes = ((size_t)p.n_tiles * p.stages * KP * 32 + 255) / 256 * 256;
     const size_t n_arrived = p.ksplit > 1 ? tiles : 0;
     const size_t part_bytes = p.ksplit > 1 ? tiles * p.ksplit * pl.NR * 4 * adapt::COLS_THREADS * 16 : 0;
@@ -218,8 +221,8 @@ int run_cols(const adapt_lut16 *lut, const ColsPlan &pl, const int16_t *x, const
     p.partial = reinterpret_cast<int32_t *>(mem + copy_bytes + words_bytes);
     p.arrived = reinterpret_cast<uint32_t *>(mem + copy_bytes + words_bytes + part_bytes);
     if (g.conv) {
-        p.ch_stride = g.sw * wsub; p.img_stride = Hp * cp * p.ch_stride; p.oy_stride = g.sh * cp * p.ch_stride; p.ky_stride = g.dh * cp * p.ch_stride;
-        p.dw = g.dw; p.sw = g.sw; p.wsub = wsub;
+        p.ch_stride = sw * wsub; p.img_stride = Hp * cp * p.ch_stride; p.oy_stride = g.sh * cp * p.ch_stride; p.ky_stride = g.dh * cp * p.ch_stride;
+        p.dw = g.dw; p.sw = sw; p.wsub = wsub;
     } else {
         p.ch_stride = Mp; p.dw = 1; p.sw = 1; p.wsub = Mp; p.linear = 1;
     }
@@ -236,7 +239,7 @@ int run_cols(const adapt_lut16 *lut, const ColsPlan &pl, const int16_t *x, const
     const adapt::ColsF32 sf{layer ? layer->xf : nullptr, layer ? layer->s_x : 1.0f, layer ? layer->Q : 0.0f};
     if (g.conv) {
         const unsigned blocks = (unsigned)((copy_words + 255) / 256);
-        const adapt::FastDiv a = fast_div((uint32_t)wsub), b = fast_div((uint32_t)g.sw), c = fast_div((uint32_t)cp), d = fast_div((uint32_t)Hp);
+        const adapt::FastDiv a = fast_div((uint32_t)wsub), b = fast_div((uint32_t)sw), c = fast_div((uint32_t)cp), d = fast_div((uint32_t)Hp);
         if (layer) adapt::cols_copy_kernel<<<blocks, 256, 0, s>>>(sf, xt, g.Cin, g.H, g.W, g.ph, g.pw, a, b, c, d, (uint32_t)copy_words);
         else adapt::cols_copy_kernel<<<blocks, 256, 0, s>>>(si, xt, g.Cin, g.H, g.W, g.ph, g.pw, a, b, c, d, (uint32_t)copy_words);
     } else {

@@ -1114,7 +1114,7 @@ int adapt_approx_conv2d(const adapt_lut *lut, const int8_t *x_dev, const int8_t 
     g.kstride = H * W; g.img_stride = Cin * H * W; g.groups = groups;
     if (groups == 1 && g.M >= LINES_MIN_ROWS && lut->byte.found) {
         const ByteShape q = byte_shape(lut->bits, Cout, Cin, kh, kw);
-        if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * pad_h, W + 2 * pad_w, stride_w))
+        if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * pad_h, W + 2 * pad_w, byte_col_classes(stride_w, Wo)))
             return with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
                 return byte_conv2d(lut, t, q, x_dev, acc_dev, N, H, W, (int)Ho, (int)Wo, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w,
                                    (hipStream_t)stream, nullptr);
@@ -1195,7 +1195,7 @@ static adapt::ChainOut chain_out_of(const adapt_weights *next, float s_next) {
     o.ph = ci.ph; o.pw = ci.pw;
     o.scale = s_next; o.Q = (float)((1 << (next->bits - 1)) - 1); o.mask = (1u << next->bits) - 1u;
     if (next->byte_form) {
-        const int sw = next->kind == 1 ? ci.sw : 1, wsub = (o.Wp + sw - 1) / sw;
+        const int sw = next->kind == 1 ? byte_col_classes(ci.sw, (o.Wp - (long long)ci.dw * (next->kw - 1) - 1) / ci.sw + 1) : 1, wsub = (o.Wp + sw - 1) / sw;
         o.xmajor = 1; o.Cp = (next->Cin + 3) / 4 * 4; o.Wp = sw * wsub; o.wsub = (uint32_t)wsub; o.dsw = fast_div((uint32_t)sw); o.mask = 0xffu;
     }
     return o;
@@ -1681,7 +1681,7 @@ int adapt_conv2d_chain_prepare(const adapt_weights *h, int N, int H, int W, int 
     ci.N = N; ci.H = H; ci.W = W; ci.sh = stride_h; ci.sw = stride_w; ci.ph = pad_h; ci.pw = pad_w; ci.dh = dil_h; ci.dw = dil_w;
     ci.xmajor = 1; ci.nonneg = false;
     if (h->byte_form) {
-        if ((rc = byte_chain_prepare(h, byte_copy_bytes(N, h->Cin, H + 2 * pad_h, W + 2 * pad_w, stride_w), N, (int)g.Ho, (int)g.Wo, (hipStream_t)stream)))
+        if ((rc = byte_chain_prepare(h, byte_copy_bytes(N, h->Cin, H + 2 * pad_h, W + 2 * pad_w, byte_col_classes(stride_w, g.Wo)), N, (int)g.Ho, (int)g.Wo, (hipStream_t)stream)))
             return rc;
         ci.valid = true;
         return ADAPT_OK;

@@ -197,7 +197,11 @@ int launch_byte_copy(const LayerIO *io, const int8_t *x, int bits, int8_t *xt, i
     return ADAPT_OK;
 }
 
-// bytes of a convolution's copy (padded image Hp x Wp), 0 if it does not fit 32-bit offsets
+// Residue classes of the columns of a convolution's copy: the horizontal stride, where it matters.  (With one output column the window
+// never moves; classes of a stride beyond the image would be mostly empty, up to billions of words per row.)
+int byte_col_classes(int sw, long long Wo) { return Wo > 1 ? sw : 1; }
+
+// bytes of a convolution's copy (padded image Hp x Wp, sw residue classes), 0 if it does not fit 32-bit offsets
 size_t byte_copy_bytes(int N, int Cin, int Hp, int Wp, int sw) {
     const long long n = (long long)N * Hp * ((Cin + 3) / 4) * ((Wp + sw - 1) / sw * sw) * 4;
     return n < 0x7fffff00LL ? align256((size_t)n + 64) : 0;
@@ -251,8 +255,8 @@ int byte_input(size_t copy_bytes, const BytePartials &sums, Workspace *ws, bool 
 int byte_conv2d(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, const int8_t *x, int32_t *out, int N, int H, int W, int Ho, int Wo, int sh,
                 int sw, int ph, int pw, int dh, int dw, hipStream_t s, Workspace *ws, const LayerIO *io = nullptr, const adapt_weights *wh = nullptr,
                 bool input_ready = false) {
-    const int Hp = H + 2 * ph, Wp = W + 2 * pw, wsub = (Wp + sw - 1) / sw;
-    const size_t copy_bytes = byte_copy_bytes(N, q.Cin, Hp, Wp, sw);
+    const int csw = byte_col_classes(sw, Wo), Hp = H + 2 * ph, Wp = W + 2 * pw, wsub = (Wp + csw - 1) / csw;
+    const size_t copy_bytes = byte_copy_bytes(N, q.Cin, Hp, Wp, csw);
     if (!copy_bytes) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: tensor with more than 2^31-1 elements");
     ByteCall c;
     c.nonneg = input_ready && wh && wh->chain_in.nonneg;
@@ -266,13 +270,13 @@ int byte_conv2d(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
     unsigned char *mem = nullptr;
     int32_t *partial = nullptr;
     int rc = byte_input(copy_bytes, sums, ws, input_ready, s, &mem, &partial, [&](int8_t *xt) {
-        return launch_byte_copy(io, x, lut->bits, xt, N, q.Cin, H, W, ph, pw, sw, wsub, s);
+        return launch_byte_copy(io, x, lut->bits, xt, N, q.Cin, H, W, ph, pw, csw, wsub, s);
     });
     if (rc) return rc;
-    const int row = 4 * sw * wsub;          // bytes of one channel group of one padded row
+    const int row = 4 * csw * wsub;         // bytes of one channel group of one padded row
     c.images = N; c.Ho = Ho; c.Wo = Wo;
     c.ch_stride = row; c.img_stride = Hp * q.cg * row; c.oy_stride = sh * q.cg * row; c.ky_stride = dh * q.cg * row;
-    c.dw = dw; c.sw = sw; c.wsub = wsub;
+    c.dw = dw; c.sw = csw; c.wsub = wsub;
     c.out_plane = Ho * Wo; c.out_w = Wo;
     rc = run_byte(lut, t, q, pl, c, reinterpret_cast<int8_t *>(mem), partial, out, s, io);
     return ws_put(ws, mem, s, rc);

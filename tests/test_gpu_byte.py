@@ -165,3 +165,27 @@ def test_longest_inner_dimension(B, K):
     a, w = wl.random_i8(rng, (4100, K), 6), wl.random_i8(rng, (3, K), 6)
     pw = B.adapt_weights_pack_linear(L, dev(w))
     assert (host(B.adapt_approx_linear_packed(pw, dev(a))) == orc.approx_linear(t, 6, a, w, threads=4)).all()
+
+
+@pytest.mark.parametrize("sw", [7, 1 << 26, (1 << 31) - 1])
+def test_one_output_column_under_any_stride(B, sw):
+    """The horizontal stride does not matter where the window never moves: packed and plain weights, and a chained input."""
+    rng = np.random.default_rng(sw)
+    t = table("product", 7, rng)
+    L = B.Lut(t, 7)
+    x, w = wl.random_i8(rng, (64, 5, 66, 6), 7), wl.random_i8(rng, (9, 5, 3, 5), 7)
+    want = orc.approx_conv2d(t, 7, x, w, (1, 7), (0, 0), (1, 1), threads=4)
+    assert want.shape == (64, 9, 64, 1)
+    pw = B.adapt_weights_pack_conv2d(L, dev(w))
+    assert (host(B.adapt_approx_conv2d_packed(pw, dev(x), (1, sw), (0, 0))) == want).all()
+    assert (host(B.adapt_approx_conv2d(L, dev(x), dev(w), (1, sw), (0, 0))) == want).all()
+    w1 = wl.random_i8(rng, (5, 5, 1, 1), 7)
+    p1 = B.adapt_weights_pack_conv2d(L, dev(w1))
+    B.adapt_conv2d_chain_prepare(pw, 64, 66, 6, (1, sw), (0, 0))
+    xf = dev(x.astype(np.float32))
+    y1 = B.adapt_conv2d_layer_f32(p1, xf, 1.0, 0.01)
+    ref = B.adapt_conv2d_layer_f32(pw, y1, 0.5, 0.1, (1, sw))
+    out1, out2 = torch.empty_like(y1), torch.empty_like(ref)
+    B.adapt_conv2d_layer_chain_f32(p1, xf, 1.0, 0.01, out1, next_pw=pw, s_next=0.5)
+    B.adapt_conv2d_layer_chain_f32(pw, None, 0.5, 0.1, out2, (1, sw), in_shape=(64, 66, 6))
+    assert torch.equal(out1, y1) and torch.equal(out2, ref)

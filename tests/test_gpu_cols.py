@@ -93,3 +93,17 @@ def test_codes_wrap_like_the_gathering_kernel(B):
         lut = table(10, span, rng)
         got = host(B.adapt_approx_linear_i16(B.Lut16(10, table=lut), dev(a), dev(w)))
         assert (got == orc.approx_linear_i16(lut, 10, wrapped, w, threads=4)).all()
+
+
+def test_one_output_column_under_a_large_stride(B):
+    """The horizontal stride does not matter where the window never moves."""
+    rng = np.random.default_rng(3)
+    h = 1 << 9
+    v = np.arange(-h, h, dtype=np.int64)
+    t = (v[:, None] * v[None, :] + rng.integers(-1000, 1000, size=(2 * h, 2 * h))).astype(np.int32)
+    L = B.Lut16(10, table=t)
+    x, w = rng.integers(-h, h, size=(3, 5, 20, 6)).astype(np.int16), rng.integers(-h, h, size=(6, 5, 3, 5)).astype(np.int16)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    want = B.adapt_approx_conv2d_i16(L, xd[..., :5].contiguous(), wd)
+    for sw in (4, 1 << 20, (1 << 31) - 1):
+        assert torch.equal(B.adapt_approx_conv2d_i16(L, xd, wd, (1, sw)), want)
