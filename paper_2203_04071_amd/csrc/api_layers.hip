@@ -993,7 +993,8 @@ int convt_any(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *a
     const long long M = (long long)N * Ho * Wo;
     if (convt_phases_ok(H, W, kh, kw, stride, pad) && M >= LINES_MIN_ROWS && stride <= 8 && lut->byte.found) {
         const ByteShape q = byte_shape(lut->bits, Cout, Cin, kh, kw, stride);
-        if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * (q.kh - 1), W + 2 * (q.kw - 1), 1))
+        if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * (q.kh - 1), W + 2 * (q.kw - 1), 1) &&
+            byte_rows_ok((long long)N * (Ho / stride), Wo / stride))
             return with_temp_byte_tables(lut, w, q, true, s, [&](const ByteTables &t) {
                 int32_t *zsum = nullptr;
                 HIP_TRY(dbg_malloc_async((void **)&zsum, (size_t)Cout * kh * kw * sizeof(int32_t), s));
@@ -1114,7 +1115,8 @@ int adapt_approx_conv2d(const adapt_lut *lut, const int8_t *x_dev, const int8_t 
     g.kstride = H * W; g.img_stride = Cin * H * W; g.groups = groups;
     if (groups == 1 && g.M >= LINES_MIN_ROWS && lut->byte.found) {
         const ByteShape q = byte_shape(lut->bits, Cout, Cin, kh, kw);
-        if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * pad_h, W + 2 * pad_w, byte_col_classes(stride_w, Wo)))
+        if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * pad_h, W + 2 * pad_w, byte_col_classes(stride_w, Wo)) &&
+            byte_rows_ok((long long)N * Ho, Wo))
             return with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
                 return byte_conv2d(lut, t, q, x_dev, acc_dev, N, H, W, (int)Ho, (int)Wo, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w,
                                    (hipStream_t)stream, nullptr);
@@ -1203,7 +1205,7 @@ static adapt::ChainOut chain_out_of(const adapt_weights *next, float s_next) {
 
 // room for and zeroes in the input copy of a handle in the byte form (all the layer before does not write stays zero)
 static int byte_chain_prepare(const adapt_weights *h, size_t copy_bytes, int N, int Ho, int Wo, hipStream_t s) {
-    if (!copy_bytes) return fail(ADAPT_ERR_UNSUPPORTED, "chain prepare: input copy of 2 GiB or more");
+    if (!copy_bytes) return fail(ADAPT_ERR_UNSUPPORTED, "chain prepare: input copy of 4 GiB or more");
     const ByteShape q = byte_shape_of(h);
     const BytePartials sums(q, h->bits, BytePlan{}, N, Ho, Wo);
     void *xt = nullptr;

@@ -67,10 +67,11 @@ int with_temp_byte_tables(const adapt_lut *lut, const int8_t *w, const ByteShape
 // activation side of one product
 struct ByteCall {
     int images, Ho, Wo;             // output of one phase (linear: 1, 1, M)
-    int img_stride, oy_stride, ch_stride, ky_stride;    // bytes of the copy
+    uint32_t img_stride, oy_stride, ch_stride, ky_stride;       // bytes of the copy
     int dw = 1, sw = 1, wsub;
     bool linear = false;
-    std::vector<int> xt_off{0}, oy0{0}, ox0{0};         // per phase
+    std::vector<uint32_t> xt_off{0};                    // per phase
+    std::vector<int> oy0{0}, ox0{0};
     int out_step = 1, out_plane = 1, out_w = 0;
     bool nonneg = false;
     const int32_t *zsum = nullptr;
@@ -128,6 +129,9 @@ struct BytePartials {
     }
 };
 
+// virtual rows are counted in 31 bits (image rows of one pixel count as four)
+bool byte_rows_ok(long long image_rows, long long Wo) { return image_rows * ((Wo + 3) / 4 * 4) + 4096 <= 0x7fffffffLL; }
+
 int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, const BytePlan &pl, const ByteCall &c, const int8_t *xt, int32_t *partial,
              int32_t *out, hipStream_t s, const LayerIO *io) {
     const int bits = lut->bits, R = pl.R, V = R < 4 ? R : 4;
@@ -135,7 +139,7 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
     p.xt = xt; p.out = out; p.partial = partial; p.arrived = t.arrived;
     p.Wo = c.Wo; p.Wv = (c.Wo + V - 1) / V * V;
     const long long Mv = (long long)c.images * c.Ho * p.Wv;
-    if (Mv + 4096 > 0x7fffffffLL) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: more than 2^31 rows");
+    if (!byte_rows_ok((long long)c.images * c.Ho, c.Wo)) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: more than 2^31 rows");
     p.Mv = (int)Mv;
     p.N = q.N; p.n_tiles = q.n_tiles; p.m_tiles = (int)((Mv + 256 * R - 1) / (256 * R));
     p.cg = q.cg; p.taps = q.kh * q.kw; p.kw = q.kw; p.steps = q.steps; p.ksplit = pl.ksplit; p.even = pl.even;
@@ -178,6 +182,10 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
     return ADAPT_OK;
 }
 
+// Copies are addressed by unsigned 32-bit byte offsets.  (They hold at most twice what the callers' limit of 2^31 bytes is taken from:
+// the channels rounded up to four, not eight, and less than a stride's worth of columns more per row.)
+constexpr long long BYTE_MAX_COPY = 0xfffffe00LL;
+
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
 // int8 or fp32 activations -> the copy of byte_copy_kernel
@@ -204,7 +212,7 @@ int byte_col_classes(int sw, long long Wo) { return Wo > 1 ? sw : 1; }
 // bytes of a convolution's copy (padded image Hp x Wp, sw residue classes), 0 if it does not fit 32-bit offsets
 size_t byte_copy_bytes(int N, int Cin, int Hp, int Wp, int sw) {
     const long long n = (long long)N * Hp * ((Cin + 3) / 4) * ((Wp + sw - 1) / sw * sw) * 4;
-    return n < 0x7fffff00LL ? align256((size_t)n + 64) : 0;
+    return n <= BYTE_MAX_COPY ? align256((size_t)n + 64) : 0;
 }
 
 // activation copy of a linear layer
@@ -216,7 +224,7 @@ int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
     const int Mp = (M + 3) / 4 * 4;
     const BytePlan pl = byte_plan_of(q, lut->bits, 1, 1, M, false);
     const size_t copy_bytes = byte_linear_copy_bytes(q, M);
-    if (copy_bytes > 0x7fffff00u) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: tensor with more than 2^31-1 elements");
+    if ((long long)q.cg * Mp * 4 > BYTE_MAX_COPY) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: tensor with more than 2^31-1 elements");
     const BytePartials sums(q, lut->bits, pl, 1, 1, M);
     unsigned char *mem = nullptr;
     int32_t *partial = nullptr;
@@ -231,7 +239,7 @@ int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
     if (e != hipSuccess) return ws_put(ws, mem, s, fail(ADAPT_ERR_HIP, "activation copy: %s", hipGetErrorString(e)));
     ByteCall c;
     c.images = 1; c.Ho = 1; c.Wo = M; c.linear = true;
-    c.img_stride = 0; c.oy_stride = 0; c.ch_stride = 4 * Mp; c.ky_stride = 0; c.wsub = Mp;
+    c.img_stride = 0; c.oy_stride = 0; c.ch_stride = 4u * (uint32_t)Mp; c.ky_stride = 0; c.wsub = Mp;
     rc = run_byte(lut, t, q, pl, c, xt, partial, out, s, io);
     return ws_put(ws, mem, s, rc);
 }
@@ -273,9 +281,10 @@ int byte_conv2d(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
         return launch_byte_copy(io, x, lut->bits, xt, N, q.Cin, H, W, ph, pw, csw, wsub, s);
     });
     if (rc) return rc;
-    const int row = 4 * csw * wsub;         // bytes of one channel group of one padded row
+    const uint32_t row = 4u * (uint32_t)csw * (uint32_t)wsub;      // bytes of one channel group of one padded row
     c.images = N; c.Ho = Ho; c.Wo = Wo;
-    c.ch_stride = row; c.img_stride = Hp * q.cg * row; c.oy_stride = sh * q.cg * row; c.ky_stride = dh * q.cg * row;
+    const uint32_t line = (uint32_t)q.cg * row;                     // and of a whole padded row
+    c.ch_stride = row; c.img_stride = (uint32_t)Hp * line; c.oy_stride = (uint32_t)sh * line; c.ky_stride = (uint32_t)dh * line;
     c.dw = dw; c.sw = csw; c.wsub = wsub;
     c.out_plane = Ho * Wo; c.out_w = Wo;
     rc = run_byte(lut, t, q, pl, c, reinterpret_cast<int8_t *>(mem), partial, out, s, io);
@@ -303,15 +312,15 @@ int byte_conv_transpose2d(const adapt_lut *lut, const ByteTables &t, const ByteS
         return launch_byte_copy(io, x, lut->bits, xt, N, q.Cin, H, W, Ty - 1, Tx - 1, 1, Wp, s);
     });
     if (rc) return rc;
-    const int row = 4 * Wp;
-    c.ch_stride = row; c.img_stride = Hp * q.cg * row; c.oy_stride = c.ky_stride = q.cg * row; c.wsub = Wp;
+    const uint32_t row = 4u * (uint32_t)Wp, line = (uint32_t)q.cg * row;
+    c.ch_stride = row; c.img_stride = (uint32_t)Hp * line; c.oy_stride = c.ky_stride = line; c.wsub = Wp;
     c.out_step = st; c.out_plane = Ho * Wo; c.out_w = Wo;
     c.xt_off.clear(); c.oy0.clear(); c.ox0.clear();
     for (int ry = 0; ry < st; ++ry)
         for (int rx = 0; rx < st; ++rx) {
             // first window of the phase: see lines_conv_transpose2d
             const int qy0 = pad > ry ? (pad - ry + st - 1) / st : 0, qx0 = pad > rx ? (pad - rx + st - 1) / st : 0;
-            c.xt_off.push_back(qy0 * c.oy_stride + qx0 * 4);
+            c.xt_off.push_back((uint32_t)qy0 * c.oy_stride + (uint32_t)qx0 * 4u);
             c.oy0.push_back(st * qy0 + ry - pad);
             c.ox0.push_back(st * qx0 + rx - pad);
         }

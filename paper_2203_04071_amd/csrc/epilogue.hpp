@@ -29,7 +29,7 @@ struct ChainOut {
     // element (image, channel c, row oy, column ox) of the producing layer's fp32 output y
     __device__ __forceinline__ void put(int img, int c, int oy, int ox, float y) const {
         const uint32_t q = (uint32_t)quant1(y, scale, Q) & mask;
-        // (a copy is smaller than 2^31 bytes: 32-bit offsets)
+        // (a copy is smaller than 2^32 bytes: 32-bit offsets)
         const uint32_t row = (uint32_t)img * (uint32_t)Hp + (uint32_t)(oy + ph), col = col_pos((uint32_t)(ox + pw));
         const uint32_t a = xmajor ? ((row * (uint32_t)(Cp >> 2) + (uint32_t)(c >> 2)) * (uint32_t)Wp + col) * 4u + (uint32_t)(c & 3)
                                   : (row * (uint32_t)Wp + col) * (uint32_t)Cp + (uint32_t)c;

@@ -80,7 +80,7 @@ typedef uint32_t b32x2_t __attribute__((ext_vector_type(2)));
 typedef int bi32x4_t __attribute__((ext_vector_type(4)));
 
 struct ByteParams {
-    const int8_t *xt;           // activation copy (signed codes), smaller than 2^31 bytes
+    const int8_t *xt;           // activation copy (signed codes), smaller than 2^32 bytes
     const uint4 *dt;            // derived tables [phase][n_tile][step][line][slot] x 16 B
     const int8_t *wx;           // weights of the exact product [phase][n_tile][step][channel][slot]
     int32_t *out;
@@ -92,13 +92,13 @@ struct ByteParams {
     int ksplit, even;           // slices of the inner dimension: slice i ends at step (i + 1) even / ksplit, the last one at the end
     int bits, copy_lines;       // copy_lines: 2^bits, or half of it where all activations are >= 0
     int Wo, Wv;                 // output width (per phase), the same rounded up to runs
-    int img_stride, oy_stride;  // bytes of xt per image / output row
-    int ch_stride, ky_stride;   // bytes of xt per channel group / filter row
+    uint32_t img_stride, oy_stride;     // bytes of xt per image / output row
+    uint32_t ch_stride, ky_stride;      // bytes of xt per channel group / filter row
     int dw, wsub;               // horizontal dilation; columns per residue class of a copied row
     uint32_t amask;             // am in every byte
     int corr;                   // c x real lookups of an output
     FastDiv d_HoWv, d_Wv, d_ntiles, d_mtiles, d_phases, d_ksplit, d_taps, d_rest, d_kw, d_sw;
-    int xt_off[4];              // per phase: bytes into xt,
+    uint32_t xt_off[4];         // per phase: bytes into xt,
     int oy0[4], ox0[4];         // position of its first output pixel; pixel (a, b) of a phase is (oy0 + a step, ox0 + b step)
     int out_step;
     int linear;                 // output [M][N] instead of [img][N][rows][out_w]
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
         byte_slot(f, p.taps, p.cg, [&](int v) { return (int)p.d_taps.div((uint32_t)v); }, [&](int v) { return (int)p.d_rest.div((uint32_t)v); }, &tap, &c);
         const int ky = (int)p.d_kw.div((uint32_t)tap), kx = tap - ky * p.kw;
         const uint32_t xo = (uint32_t)(kx * p.dw), xs = p.d_sw.div(xo), xr = xo - xs * p.d_sw.d;
-        return (uint32_t)(c * p.ch_stride + ky * p.ky_stride) + 4u * (xr * (uint32_t)p.wsub + xs);
+        return (uint32_t)c * p.ch_stride + (uint32_t)ky * p.ky_stride + 4u * (xr * (uint32_t)p.wsub + xs);
     };
     dma(0, 0, std::true_type{}, pf_sink);
     for (int i = tid; i < nsteps * 4 + 8; i += BYTE_THREADS) goff[i] = group_off(s_begin * 4 + i);
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     for (int i = 0; i < NRUN; ++i) {
         int img, a, b;
         byte_run_pos<R>(p, mt, rs, i, img, a, b);
-        base[i] = (uint32_t)(img * p.img_stride + a * p.oy_stride + b * 4);
+        base[i] = (uint32_t)img * p.img_stride + (uint32_t)a * p.oy_stride + (uint32_t)b * 4u;
     }
     typedef typename std::conditional<V == 4, b32x4_t, b32x2_t>::type run_t;
     auto load_acts = [&](run_t (&w)[NRUN], uint32_t off) {

@@ -189,3 +189,29 @@ def test_one_output_column_under_any_stride(B, sw):
     B.adapt_conv2d_layer_chain_f32(p1, xf, 1.0, 0.01, out1, next_pw=pw, s_next=0.5)
     B.adapt_conv2d_layer_chain_f32(pw, None, 0.5, 0.1, out2, (1, sw), in_shape=(64, 66, 6))
     assert torch.equal(out1, y1) and torch.equal(out2, ref)
+
+
+def test_activation_copy_beyond_two_gigabytes(B):
+    """8 channels under stride 2 on three columns: an input of just under 2^31 elements, whose copy takes four words per row and
+    channel group.  Compared with the same layer on parts of the batch; the copy a producer writes, too."""
+    N, H = 8000, 11180
+    assert N * H * 3 * 8 < 0x7fffff00 < N * H * 4 * 8
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randint(-128, 128, (N, 8, H, 3), generator=gen, device="cuda", dtype=torch.int8)
+    w = torch.randint(-128, 128, (1, 8, 1, 1), generator=gen, device="cuda", dtype=torch.int8)
+    L = B.Lut(table("product", 8, np.random.default_rng(1)), 8)
+    pw = B.adapt_weights_pack_conv2d(L, w)
+    got = B.adapt_approx_conv2d_packed(pw, x, (1, 2))
+    for n in (0, 3999, N - 500):
+        assert torch.equal(got[n:n + 500], B.adapt_approx_conv2d(L, x[n:n + 500], w, (1, 2)))
+    # the input as a layer's output: 1 channel -> 8 channels, written into the copy alone
+    del x, got
+    p1 = B.adapt_weights_pack_conv2d(L, torch.randint(-128, 128, (8, 1, 1, 1), generator=gen, device="cuda", dtype=torch.int8))
+    xf = torch.randn((N, 1, H, 3), generator=gen, device="cuda")
+    B.adapt_conv2d_chain_prepare(pw, N, H, 3, (1, 2))
+    B.adapt_conv2d_layer_chain_f32(p1, xf, 0.02, 1e-3, None, next_pw=pw, s_next=0.1)
+    out = torch.empty((N, 1, H, 2), dtype=torch.float32, device="cuda")
+    B.adapt_conv2d_layer_chain_f32(pw, None, 0.1, 1e-3, out, (1, 2), in_shape=(N, H, 3))
+    for n in (0, 3999, N - 500):
+        y = B.adapt_conv2d_layer_f32(p1, xf[n:n + 500], 0.02, 1e-3)
+        assert torch.equal(out[n:n + 500], B.adapt_conv2d_layer_f32(pw, y, 0.1, 1e-3, (1, 2)))
