@@ -50,61 +50,46 @@ inline unsigned red_grid(size_t n) {
     return (unsigned)(g < 1 ? 1 : (g > adapt::RED_BLOCKS ? adapt::RED_BLOCKS : g));
 }
 
-// Scratch memory of one call: the activation copy, and the partial sums of a product whose inner dimension is split.  Plain
+// Scratch memory of one call: the partial sums of a product whose inner dimension is split, and the activation copy.  Plain
 // entry points take it from the stream-ordered allocator and give it back in stream order; a packed-weights handle keeps one
-// grow-only buffer of each, so that its calls allocate nothing once they have run at their largest size (they can then be
-// recorded into a HIP graph).  How much partial sums need depends on the plan and does not grow with the size, so that buffer
-// is reserved for every product of up to part_rows rows.
+// grow-only buffer, so that its calls allocate nothing once they have run at their largest size (they can then be
+// recorded into a HIP graph).  How much partial sums need depends on the plan and does not grow with the size, so that part of
+// the buffer is reserved for every product of up to part_rows rows.
 struct Workspace {
-    void *ptr = nullptr;
-    size_t bytes = 0;
-    void *part = nullptr;
-    size_t part_bytes = 0;
+    void *mem = nullptr;        // partial sums, the copy behind them (one allocation: a handle's first call waits for it)
+    size_t part_bytes = 0, copy_bytes = 0;
     long long part_rows = 0;
+    void *copy() const { return mem ? static_cast<char *>(mem) + part_bytes : nullptr; }
+    bool holds(size_t copy, long long rows) const { return mem && copy_bytes >= copy && part_rows >= rows; }
 };
 
-inline int ws_grow(void **buf, size_t *have, size_t bytes) {
-    if (*have >= bytes) return ADAPT_OK;
-    if (*buf) HIP_TRY(hipFree(*buf));       // waits for the device: no earlier call still uses it
-    *buf = nullptr;
-    *have = 0;
-    HIP_TRY(dbg_malloc(buf, bytes));
-    *have = bytes;
-    return ADAPT_OK;
-}
-
-inline int ws_get(Workspace *cache, size_t bytes, hipStream_t s, void **out) {
+// copy_bytes at *copy and part_bytes at *part for a product of `rows` rows; reserve(): the bytes of partial sums that products of up to
+// `rows` rows need.  Given back by ws_put(*copy).
+template <typename Reserve>
+inline int ws_get(Workspace *cache, size_t copy_bytes, size_t part_bytes, long long rows, Reserve &&reserve, hipStream_t s, void **copy, int32_t **part) {
     if (!cache) {
-        HIP_TRY(dbg_malloc_async(out, bytes, s));
+        HIP_TRY(dbg_malloc_async(copy, copy_bytes + part_bytes, s));
+        *part = part_bytes ? reinterpret_cast<int32_t *>(static_cast<char *>(*copy) + copy_bytes) : nullptr;
         return ADAPT_OK;
     }
-    if (int rc = ws_grow(&cache->ptr, &cache->bytes, bytes)) return rc;
-    *out = cache->ptr;
-    return ADAPT_OK;
-}
-
-// room in a handle for the partial sums of every product of up to `rows` rows; reserve(): the bytes these need
-template <typename Reserve>
-inline int ws_reserve_partials(Workspace *cache, long long rows, Reserve &&reserve) {
-    if (rows <= cache->part_rows) return ADAPT_OK;
-    const size_t bytes = reserve();
-    if (cache->part_bytes < bytes) cache->part_rows = 0;
-    if (int rc = ws_grow(&cache->part, &cache->part_bytes, bytes)) return rc;
-    cache->part_rows = rows;
-    return ADAPT_OK;
-}
-
-// both: copy_bytes at *mem and part_bytes (of a product of `rows` rows) at *part; given back together by ws_put(*mem)
-template <typename Reserve>
-inline int ws_get_both(Workspace *cache, size_t copy_bytes, size_t part_bytes, long long rows, Reserve &&reserve, hipStream_t s, void **mem, int32_t **part) {
-    if (!cache) {
-        if (int rc = ws_get(nullptr, copy_bytes + part_bytes, s, mem)) return rc;
-        *part = part_bytes ? reinterpret_cast<int32_t *>(static_cast<char *>(*mem) + copy_bytes) : nullptr;
-        return ADAPT_OK;
+    if (!cache->holds(copy_bytes, rows)) {
+        Workspace w = *cache;
+        if (rows > w.part_rows) {
+            const size_t bytes = (reserve() + 255) / 256 * 256;
+            w.part_bytes = bytes > w.part_bytes ? bytes : w.part_bytes;
+            w.part_rows = rows;
+        }
+        w.copy_bytes = copy_bytes > w.copy_bytes ? copy_bytes : w.copy_bytes;
+        if (!w.mem || w.part_bytes > cache->part_bytes || w.copy_bytes > cache->copy_bytes) {
+            if (w.mem) HIP_TRY(hipFree(w.mem));     // waits for the device: no earlier call still uses it
+            *cache = Workspace{};
+            w.mem = nullptr;
+            HIP_TRY(dbg_malloc(&w.mem, w.part_bytes + w.copy_bytes));
+        }
+        *cache = w;
     }
-    if (int rc = ws_get(cache, copy_bytes, s, mem)) return rc;
-    if (int rc = ws_reserve_partials(cache, rows, reserve)) return rc;
-    *part = part_bytes ? static_cast<int32_t *>(cache->part) : nullptr;
+    *copy = cache->copy();
+    *part = part_bytes ? static_cast<int32_t *>(cache->mem) : nullptr;
     return ADAPT_OK;
 }
 

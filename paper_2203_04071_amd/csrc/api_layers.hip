@@ -55,6 +55,7 @@ struct adapt_weights {
     int32_t *zsum_dev;      // [Cout][kh * kw] sums of T[0][w] over the input channels
     int8_t *w8_dev;         // copy of the weights for the geometries the phase form does not cover
     const adapt_lut *lut;   // the table handle (must outlive this handle), for those geometries
+    mutable int rows_without_room = 0;      // linear, byte form: rows of calls that needed none of it
     mutable Workspace ws;   // padded activation copy of the latest call
     // convolutions: the geometry for which the workspace was prepared to receive its input copy from the layer before
     // (adapt_conv2d_chain_prepare): borders and padded channels zeroed, layout fixed
@@ -712,7 +713,7 @@ int lines_linear(int bits, int storage, const LinesShape &q, uint4 *const dt[2],
     if (c.plan.xmajor) {
         // x-major copy: one image of one row of M pixels with K channels; a lane's 8 rows x 4 inner indices are 32
         // contiguous bytes instead of 8 words that are a whole matrix row apart
-        int wrc = ws_get_both(ws, copy_bytes, part_bytes, M, reserve, s, (void **)&tmp, &c.partial);
+        int wrc = ws_get(ws, copy_bytes, part_bytes, M, reserve, s, (void **)&tmp, &c.partial);
         if (wrc) return wrc;
         dim3 grid((unsigned)((M + 63) / 64), (unsigned)((Kp / 4 + 15) / 16));
         if (from_f32) adapt::rows_to_xmajor_kernel<<<grid, 256, 0, s>>>(srcf, tmp, M, K, Kp);
@@ -726,7 +727,7 @@ int lines_linear(int bits, int storage, const LinesShape &q, uint4 *const dt[2],
     } else {
         // (nothing is needed otherwise; a handle makes room all the same, for smaller products that do, unless the call is recorded)
         if (Kp != K || from_f32 || part_bytes || (ws && ws->part_rows < M && !is_capturing(s))) {
-            int wrc = ws_get_both(ws, copy_bytes, part_bytes, M, reserve, s, (void **)&tmp, &c.partial);
+            int wrc = ws_get(ws, copy_bytes, part_bytes, M, reserve, s, (void **)&tmp, &c.partial);
             if (wrc) return wrc;
         }
         if (Kp != K || from_f32) {
@@ -767,17 +768,17 @@ int lines_conv2d(int bits, int storage, const LinesShape &q, uint4 *const dt[2],
     int32_t *partial = nullptr;
     {
         if (input_ready) {      // the layer before wrote the copy (adapt_conv2d_chain_prepare fixed its place and layout)
-            if (!ws || !ws->ptr || ws->bytes < copy_bytes || ws->part_rows < M || !wh || wh->chain_in.xmajor != xmajor)
+            if (!ws || !ws->holds(copy_bytes, M) || !wh || wh->chain_in.xmajor != xmajor)
                 return fail(ADAPT_ERR_INVALID_ARGUMENT, "chained convolution: the input buffer was not prepared for this geometry");
-            xt = static_cast<int8_t *>(ws->ptr);
-            partial = static_cast<int32_t *>(ws->part);
+            xt = static_cast<int8_t *>(ws->copy());
+            partial = static_cast<int32_t *>(ws->mem);
         } else {
             if (wh && wh->chain_in.valid) {     // an ordinary call with another geometry ends the prepared state
                 const auto &ci = wh->chain_in;
                 if (ci.N != N || ci.H != H || ci.W != W || ci.sh != sh || ci.sw != sw || ci.ph != ph || ci.pw != pw || ci.dh != dh || ci.dw != dw)
                     wh->chain_in.valid = false;
             }
-            int wrc = ws_get_both(ws, copy_bytes, part_bytes, M, [&] { return lines_partial_reserve(device_cus(), out_elems); }, s, (void **)&xt, &partial);
+            int wrc = ws_get(ws, copy_bytes, part_bytes, M, [&] { return lines_partial_reserve(device_cus(), out_elems); }, s, (void **)&xt, &partial);
             if (wrc) return wrc;
             int prc = launch_pad(io, x, bits, xt, N, q.Cin, H, W, ph, pw, Cp, xmajor, s);
             if (prc) return ws_put(ws, xt, s, prc);
@@ -832,13 +833,13 @@ int lines_conv_transpose2d(int bits, int storage, const LinesShape &q, uint4 *co
     int8_t *xt = nullptr;
     int32_t *partial = nullptr;
     if (input_ready) {          // the layer before wrote the copy (adapt_conv_transpose2d_chain_prepare fixed its place and layout)
-        if (!ws || !ws->ptr || ws->bytes < copy_bytes || ws->part_rows < M || !wh || wh->chain_in.xmajor != xmajor)
+        if (!ws || !ws->holds(copy_bytes, M) || !wh || wh->chain_in.xmajor != xmajor)
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "chained transposed convolution: the input buffer was not prepared for this geometry");
-        xt = static_cast<int8_t *>(ws->ptr);
-        partial = static_cast<int32_t *>(ws->part);
+        xt = static_cast<int8_t *>(ws->copy());
+        partial = static_cast<int32_t *>(ws->mem);
     } else {
         if (wh) wh->chain_in.valid = false;     // (an ordinary call overwrites a prepared copy)
-        int wrc = ws_get_both(ws, copy_bytes, part_bytes, M, [&] { return lines_partial_reserve(device_cus(), out_elems); }, s, (void **)&xt, &partial);
+        int wrc = ws_get(ws, copy_bytes, part_bytes, M, [&] { return lines_partial_reserve(device_cus(), out_elems); }, s, (void **)&xt, &partial);
         if (wrc) return wrc;
         int prc = launch_pad(io, x, bits, xt, N, q.Cin, H, W, Ty - 1, Tx - 1, Cp, xmajor, s);
         if (prc) return ws_put(ws, xt, s, prc);
@@ -1192,7 +1193,7 @@ static ByteShape byte_shape_of(const adapt_weights *h) {
 static adapt::ChainOut chain_out_of(const adapt_weights *next, float s_next) {
     const auto &ci = next->chain_in;
     adapt::ChainOut o{};
-    o.buf = static_cast<int8_t *>(next->ws.ptr);
+    o.buf = static_cast<int8_t *>(next->ws.copy());
     o.xmajor = ci.xmajor; o.Hp = ci.H + 2 * ci.ph; o.Wp = ci.W + 2 * ci.pw; o.Cp = next->Cp;
     o.ph = ci.ph; o.pw = ci.pw;
     o.scale = s_next; o.Q = (float)((1 << (next->bits - 1)) - 1); o.mask = (1u << next->bits) - 1u;
@@ -1210,7 +1211,7 @@ static int byte_chain_prepare(const adapt_weights *h, size_t copy_bytes, int N, 
     const BytePartials sums(q, h->bits, BytePlan{}, N, Ho, Wo);
     void *xt = nullptr;
     int32_t *partial = nullptr;
-    int rc = ws_get_both(&h->ws, copy_bytes, 0, sums.rows, [&] { return sums.reserve(); }, s, &xt, &partial);
+    int rc = ws_get(&h->ws, copy_bytes, 0, sums.rows, [&] { return sums.reserve(); }, s, &xt, &partial);
     if (rc) return rc;
     adapt::fill_u32_kernel<<<ew_grid(copy_bytes / 4), 256, 0, s>>>(static_cast<uint32_t *>(xt), 0u, copy_bytes / 4);
     HIP_TRY(hipGetLastError());
@@ -1392,8 +1393,7 @@ int adapt_weights_destroy(adapt_weights *h) {
     if (!h) return ADAPT_OK;
     for (int j = 0; j < 2; ++j)
         if (h->dt_dev[j]) (void)hipFree(h->dt_dev[j]);
-    if (h->ws.ptr) (void)hipFree(h->ws.ptr);
-    if (h->ws.part) (void)hipFree(h->ws.part);
+    if (h->ws.mem) (void)hipFree(h->ws.mem);
     if (h->wofs_dev) (void)hipFree(h->wofs_dev);
     if (h->wofs1_dev) (void)hipFree(h->wofs1_dev);
     if (h->dtq_dev) (void)hipFree(h->dtq_dev);
@@ -1470,29 +1470,32 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
     return ADAPT_OK;
 }
 
-// Room in a byte-form handle for linear layers of up to M rows, whichever kernel they take
-static int byte_linear_reserve(const adapt_weights *h, const ByteShape &q, int M, hipStream_t s) {
-    const BytePartials sums(q, h->bits, BytePlan{}, 1, 1, M);
+// Room in a byte-form handle for linear layers of up to M rows, and of up to those that went to the whole-table kernel before
+// (which then made none)
+static int byte_linear_reserve(const adapt_weights *h, int M, hipStream_t s) {
+    const ByteShape q = byte_shape_of(h);
+    const int rows = M > h->rows_without_room ? M : h->rows_without_room;
+    const size_t copy_bytes = byte_linear_copy_bytes(q, rows);
+    const BytePartials sums(q, h->bits, BytePlan{}, 1, 1, rows);
+    if (h->ws.holds(copy_bytes, sums.rows)) return ADAPT_OK;
+    if (is_capturing(s)) return ADAPT_ERR_UNSUPPORTED;
     void *mem = nullptr;
     int32_t *partial = nullptr;
-    return ws_get_both(&h->ws, byte_linear_copy_bytes(q, M), 0, sums.rows, [&] { return sums.reserve(); }, s, &mem, &partial);
+    const int rc = ws_get(&h->ws, copy_bytes, 0, sums.rows, [&] { return sums.reserve(); }, s, &mem, &partial);
+    if (rc) (void)hipGetLastError();
+    return rc;
 }
 
-// Whether M rows of a packed linear layer go to the whole-table kernel: too few to amortise streaming the derived tables.  A
-// call that has not run at this size before makes room here, also where it then needs none, so that smaller ones find it; one that
-// is being recorded, or that finds no memory, takes the whole-table kernel instead.
+// Whether M rows of a packed linear layer go to the whole-table kernel: too few to amortise streaming the derived tables, or no room
+// for what the byte kernel needs (out of memory; or the call is being recorded and nothing of this size has run before).
 static bool linear_on_rows(const adapt_weights *h, int M, hipStream_t s) {
     if (M >= LINES_MIN_ROWS) return false;
     if (!h->byte_form) return true;
-    const ByteShape q = byte_shape_of(h);
-    if (h->ws.part_rows < (M + 3) / 4 * 4 || h->ws.bytes < byte_linear_copy_bytes(q, M)) {
-        if (is_capturing(s)) return true;
-        if (byte_linear_reserve(h, q, M, s) != ADAPT_OK) {
-            (void)hipGetLastError();
-            return true;
-        }
+    if (!byte_call_pays(h->lut, byte_shape_of(h), M, false)) {
+        if (h->rows_without_room < M) h->rows_without_room = M;
+        return true;
     }
-    return !byte_call_pays(h->lut, q, M, false);
+    return byte_linear_reserve(h, M, s) != ADAPT_OK;
 }
 
 int adapt_approx_linear_packed(const adapt_weights *h, const int8_t *a_dev, int32_t *acc_dev, int M, void *stream) {
@@ -1556,8 +1559,10 @@ static int layer_io(LayerIO *io, const adapt_weights *h, const float *x_dev, con
 }
 
 // int8 copy of fp32 activations in the handle's workspace, for the whole-table kernel
-static int quantize_into_ws(const adapt_weights *h, const LayerIO &io, size_t n, hipStream_t s, int8_t **q) {
-    int rc = ws_get(&h->ws, n + 64, s, (void **)q);
+static int quantize_into_ws(const adapt_weights *h, const LayerIO &io, int M, size_t n, hipStream_t s, int8_t **q) {
+    if (h->byte_form && h->kind == 0) (void)byte_linear_reserve(h, M, s);       // (or this buffer would move under a recorded call later)
+    int32_t *partial = nullptr;
+    int rc = ws_get(&h->ws, n + 64, 0, 0, [] { return (size_t)0; }, s, (void **)q, &partial);
     if (rc) return rc;
     const int vec = (aligned16(io.xf) && aligned16(*q)) ? 1 : 0;
     adapt::quantize_kernel<<<ew_grid(n / 16 + 1), adapt::EW_THREADS, 0, s>>>(io.xf, *q, n, io.s_x, io.Q, vec);
@@ -1587,7 +1592,7 @@ int adapt_linear_layer_f32(const adapt_weights *h, const float *x_dev, float *y_
     }
     if (rows) {
         int8_t *q = nullptr;
-        if ((rc = quantize_into_ws(h, io, (size_t)M * h->Cin, s, &q))) return rc;
+        if ((rc = quantize_into_ws(h, io, M, (size_t)M * h->Cin, s, &q))) return rc;
         Geometry g{};
         g.mode = adapt::MODE_GEMM; g.M = M; g.N = h->N; g.Cin = h->Cin; g.taps = 1; g.kw = 1;
         g.H = 1; g.W = 1; g.Wo = 1; g.HoWo = 1; g.sh = g.sw = g.dh = g.dw = 1; g.ph = g.pw = 0;
@@ -1644,7 +1649,7 @@ static int conv2d_layer(const adapt_weights *h, const float *x_dev, float *y_dev
         if ((rc = check_weights(next, 1, who))) return rc;
         if (next == h) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: a layer cannot chain into itself (one workspace per handle)", who);
         const auto &ci = next->chain_in;
-        if (!ci.valid || ci.N != N || ci.H != g.Ho || ci.W != g.Wo || next->Cin != h->N || !next->ws.ptr)
+        if (!ci.valid || ci.N != N || ci.H != g.Ho || ci.W != g.Wo || next->Cin != h->N || !next->ws.mem)
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: the next layer was not prepared for this layer's output", who);
         if (!(s_next > 0.0f)) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: s_next must be > 0", who);
         io.chain = chain_out_of(next, s_next);
@@ -1697,7 +1702,7 @@ int adapt_conv2d_chain_prepare(const adapt_weights *h, int N, int H, int W, int 
     const size_t copy_bytes = ((xt_bytes + 64 + 255) / 256) * 256;
     int8_t *xt = nullptr;
     int32_t *partial = nullptr;
-    if ((rc = ws_get_both(&h->ws, copy_bytes, 0, M, [&] { return lines_partial_reserve(device_cus(), (size_t)M * q.N); }, (hipStream_t)stream, (void **)&xt, &partial)))
+    if ((rc = ws_get(&h->ws, copy_bytes, 0, M, [&] { return lines_partial_reserve(device_cus(), (size_t)M * q.N); }, (hipStream_t)stream, (void **)&xt, &partial)))
         return rc;
     adapt::fill_u32_kernel<<<ew_grid(copy_bytes / 4), 256, 0, (hipStream_t)stream>>>(reinterpret_cast<uint32_t *>(xt), 0u, copy_bytes / 4);
     HIP_TRY(hipGetLastError());
@@ -1743,7 +1748,7 @@ int adapt_conv2d_grouped_layer_f32(const adapt_lut *lut, const float *x_dev, con
     if (next) {
         if ((rc = check_weights(next, 1, who))) return rc;
         const auto &ci = next->chain_in;
-        if (!ci.valid || ci.N != N || ci.H != Ho || ci.W != Wo || next->Cin != Cout || !next->ws.ptr)
+        if (!ci.valid || ci.N != N || ci.H != Ho || ci.W != Wo || next->Cin != Cout || !next->ws.mem)
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: the next layer was not prepared for this layer's output", who);
         if (!(s_next > 0.0f)) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: s_next must be > 0", who);
         io.chain = chain_out_of(next, s_next);
@@ -1803,7 +1808,7 @@ int adapt_conv_transpose2d_layer_f32(const adapt_weights *h, const float *x_dev,
                                           pad, s, &h->ws, &io, h);
     }
     int8_t *q8 = nullptr;
-    if ((rc = quantize_into_ws(h, io, (size_t)N * h->Cin * H * W, s, &q8))) return rc;
+    if ((rc = quantize_into_ws(h, io, 0, (size_t)N * h->Cin * H * W, s, &q8))) return rc;
     return convt_rows(h->lut, q8, h->w8_dev, out, N, h->Cin, H, W, h->N, h->kh, h->kw, h->stride, pad, s, h, &io);
 }
 
@@ -1849,7 +1854,7 @@ int adapt_conv_transpose2d_chain_prepare(const adapt_weights *h, int N, int H, i
     const size_t copy_bytes = ((xt_bytes + 64 + 255) / 256) * 256;
     int8_t *xt = nullptr;
     int32_t *partial = nullptr;
-    if ((rc = ws_get_both(&h->ws, copy_bytes, 0, M, [&] { return lines_partial_reserve(device_cus(), (size_t)N * q.N * Ho * Wo); }, (hipStream_t)stream, (void **)&xt, &partial)))
+    if ((rc = ws_get(&h->ws, copy_bytes, 0, M, [&] { return lines_partial_reserve(device_cus(), (size_t)N * q.N * Ho * Wo); }, (hipStream_t)stream, (void **)&xt, &partial)))
         return rc;
     adapt::fill_u32_kernel<<<ew_grid(copy_bytes / 4), 256, 0, (hipStream_t)stream>>>(reinterpret_cast<uint32_t *>(xt), 0u, copy_bytes / 4);
     HIP_TRY(hipGetLastError());
@@ -1892,7 +1897,7 @@ int adapt_conv_transpose2d_layer_chain_f32(const adapt_weights *h, const float *
         if ((rc = check_weights(next, next->kind, who))) return rc;
         if (next == h) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: a layer cannot chain into itself (one workspace per handle)", who);
         const auto &ci = next->chain_in;
-        if (!ci.valid || ci.N != N || ci.H != Ho || ci.W != Wo || next->Cin != h->N || !next->ws.ptr)
+        if (!ci.valid || ci.N != N || ci.H != Ho || ci.W != Wo || next->Cin != h->N || !next->ws.mem)
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: the next layer was not prepared for this layer's output", who);
         if (!(s_next > 0.0f)) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: s_next must be > 0", who);
         io.chain = chain_out_of(next, s_next);
@@ -1908,7 +1913,7 @@ int adapt_conv_transpose2d_layer_chain_f32(const adapt_weights *h, const float *
     } else {
         if (!y_dev) return fail(ADAPT_ERR_UNSUPPORTED, "%s: this geometry finishes its sums in a separate pass over the output: y_dev is needed", who);
         int8_t *q8 = nullptr;
-        if ((rc = quantize_into_ws(h, io, (size_t)N * h->Cin * H * W, s, &q8))) return rc;
+        if ((rc = quantize_into_ws(h, io, 0, (size_t)N * h->Cin * H * W, s, &q8))) return rc;
         rc = convt_rows(h->lut, q8, h->w8_dev, out, N, h->Cin, H, W, h->N, h->kh, h->kw, h->stride, pad, s, h, &io);
     }
     if (rc == ADAPT_OK && next) next->chain_in.nonneg = act == 1;

@@ -228,7 +228,7 @@ int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
     const BytePartials sums(q, lut->bits, pl, 1, 1, M);
     unsigned char *mem = nullptr;
     int32_t *partial = nullptr;
-    int rc = ws_get_both(ws, copy_bytes, sums.bytes, sums.rows, [&] { return sums.reserve(); }, s, (void **)&mem, &partial);
+    int rc = ws_get(ws, copy_bytes, sums.bytes, sums.rows, [&] { return sums.reserve(); }, s, (void **)&mem, &partial);
     if (rc) return rc;
     int8_t *xt = reinterpret_cast<int8_t *>(mem);
     const dim3 grid((unsigned)((M + 63) / 64), (unsigned)((q.cg + 15) / 16));
@@ -248,13 +248,13 @@ int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
 template <typename Copy>
 int byte_input(size_t copy_bytes, const BytePartials &sums, Workspace *ws, bool input_ready, hipStream_t s, unsigned char **mem, int32_t **partial, Copy &&copy) {
     if (input_ready) {
-        if (!ws || !ws->ptr || ws->bytes < copy_bytes || ws->part_rows < sums.rows)
+        if (!ws || !ws->holds(copy_bytes, sums.rows))
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "chained layer: the input buffer was not prepared for this geometry");
-        *mem = static_cast<unsigned char *>(ws->ptr);
-        *partial = static_cast<int32_t *>(ws->part);
+        *mem = static_cast<unsigned char *>(ws->copy());
+        *partial = static_cast<int32_t *>(ws->mem);
         return ADAPT_OK;
     }
-    int rc = ws_get_both(ws, copy_bytes, sums.bytes, sums.rows, [&] { return sums.reserve(); }, s, (void **)mem, partial);
+    int rc = ws_get(ws, copy_bytes, sums.bytes, sums.rows, [&] { return sums.reserve(); }, s, (void **)mem, partial);
     if (rc) return rc;
     if ((rc = copy(reinterpret_cast<int8_t *>(*mem)))) return ws_put(ws, *mem, s, rc);
     return ADAPT_OK;
