@@ -1047,9 +1047,11 @@ int adapt_approx_linear(const adapt_lut *lut, const int8_t *a_dev, const int8_t 
     g.kstride = 1; g.img_stride = K;
     if (lut->byte.found && K >= 8) {
         const ByteShape q = byte_shape(lut->bits, N, K, 1, 1);
-        if (byte_packable(q, (size_t)4 << 30) && (long long)q.cg * 4 * (M + 4) < 0x7fffff00LL && (M >= LINES_MIN_ROWS || byte_call_pays(lut, q, M, true))) {
+        BytePlan pl;
+        if (byte_packable(q, (size_t)4 << 30) && (long long)q.cg * 4 * (M + 4) < 0x7fffff00LL && (M >= LINES_MIN_ROWS || byte_call_pays(lut, q, M, true, &pl))) {
+            if (M >= LINES_MIN_ROWS) pl = byte_plan_of(q, lut->bits, 1, 1, M, false);
             rc = with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
-                return byte_linear(lut, t, q, a_dev, acc_dev, M, (hipStream_t)stream, nullptr, nullptr);
+                return byte_linear(lut, t, q, a_dev, acc_dev, M, (hipStream_t)stream, nullptr, nullptr, pl);
             });
             if (rc != ADAPT_ERR_OUT_OF_MEMORY || M >= LINES_MIN_ROWS) return rc;        // (no room for tables: the whole-table kernel needs little)
             (void)hipGetLastError();
@@ -1441,8 +1443,9 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
     int k = 0, rpw = 0, ks = 1, st = 0, wg = 0;
     const bool phased = kind == 2 && kh % stride == 0 && kw % stride == 0 && stride <= 8;
     const ByteShape bq = byte_shape(bits, Cout, Cin, kh, kw, phased ? stride : 1);
+    BytePlan found;
     if (storage == 2 && !byte_packable(bq, PACK_LIMIT)) storage = 0;        // (such a handle keeps the other tables)
-    if (kind == 0 && rows < LINES_MIN_ROWS && (storage != 2 || !byte_pays(bq, bits, 0, rows, false, cu))) {
+    if (kind == 0 && rows < LINES_MIN_ROWS && (storage != 2 || !byte_pays(bq, bits, 0, rows, false, cu, &found))) {
         k = -1;                                 // whole-table kernel (lut_rows_kernel)
     } else if (kind == 2 && !phased) {
         k = -1;
@@ -1487,11 +1490,15 @@ static int byte_linear_reserve(const adapt_weights *h, int M, hipStream_t s) {
 }
 
 // Whether M rows of a packed linear layer go to the whole-table kernel: too few to amortise streaming the derived tables, or no room
-// for what the byte kernel needs (out of memory; or the call is being recorded and nothing of this size has run before).
-static bool linear_on_rows(const adapt_weights *h, int M, hipStream_t s) {
-    if (M >= LINES_MIN_ROWS) return false;
+// for what the byte kernel needs (out of memory; or the call is being recorded and nothing of this size has run before).  *plan: the
+// byte kernel's, where it runs.
+static bool linear_on_rows(const adapt_weights *h, int M, hipStream_t s, BytePlan *plan) {
+    if (M >= LINES_MIN_ROWS) {
+        if (h->byte_form) *plan = byte_plan_of(byte_shape_of(h), h->bits, 1, 1, M, false);
+        return false;
+    }
     if (!h->byte_form) return true;
-    if (!byte_call_pays(h->lut, byte_shape_of(h), M, false)) {
+    if (!byte_call_pays(h->lut, byte_shape_of(h), M, false, plan)) {
         if (h->rows_without_room < M) h->rows_without_room = M;
         return true;
     }
@@ -1506,9 +1513,10 @@ int adapt_approx_linear_packed(const adapt_weights *h, const int8_t *a_dev, int3
     if (!a_dev || !acc_dev) return fail(ADAPT_ERR_INVALID_ARGUMENT, "adapt_approx_linear_packed: NULL pointer");
     if ((long long)M * h->Cp >= 0x7fffff00LL || (long long)M * h->N > 0x7fffffffLL)
         return fail(ADAPT_ERR_UNSUPPORTED, "adapt_approx_linear_packed: tensor with more than 2^31-1 elements");
-    bool rows = linear_on_rows(h, M, (hipStream_t)stream);
+    BytePlan plan;
+    bool rows = linear_on_rows(h, M, (hipStream_t)stream, &plan);
     if (h->byte_form && !rows) {
-        rc = byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), a_dev, acc_dev, M, (hipStream_t)stream, &h->ws, nullptr);
+        rc = byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), a_dev, acc_dev, M, (hipStream_t)stream, &h->ws, nullptr, plan);
         if (rc != ADAPT_ERR_OUT_OF_MEMORY || M >= LINES_MIN_ROWS) return rc;
         (void)hipGetLastError();
         rows = true;                // (no room for the copy: the whole-table kernel needs none)
@@ -1583,9 +1591,10 @@ int adapt_linear_layer_f32(const adapt_weights *h, const float *x_dev, float *y_
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: tensor with more than 2^31-1 elements", who);
     hipStream_t s = (hipStream_t)stream;
     int32_t *out = reinterpret_cast<int32_t *>(y_dev);
-    bool rows = linear_on_rows(h, M, s);
+    BytePlan plan;
+    bool rows = linear_on_rows(h, M, s, &plan);
     if (h->byte_form && !rows) {
-        rc = byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), nullptr, out, M, s, &h->ws, &io);
+        rc = byte_linear(h->lut, byte_tables_of(h), byte_shape_of(h), nullptr, out, M, s, &h->ws, &io, plan);
         if (rc != ADAPT_ERR_OUT_OF_MEMORY || M >= LINES_MIN_ROWS) return rc;
         (void)hipGetLastError();
         rows = true;                // (no room for copy and partial sums: the whole-table kernel needs less)

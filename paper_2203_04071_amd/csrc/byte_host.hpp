@@ -99,15 +99,22 @@ BytePlan byte_plan_of(const ByteShape &q, int bits, int images, int Ho, int Wo, 
 }
 
 // whether the byte kernel is the better one for M rows of a linear layer; pack: the tables are to be made for this call;
-// storage: of the table (1: the whole-table kernel runs twice)
-bool byte_pays(const ByteShape &q, int bits, int storage, int M, bool pack, int cu = 0) {
+// storage: of the table (1: the whole-table kernel runs twice); *plan: the byte kernel's, where it is
+bool byte_pays(const ByteShape &q, int bits, int storage, int M, bool pack, int cu, BytePlan *plan) {
 #ifdef ADAPT_TUNING_KNOBS
-    if (const char *e = getenv("ADAPT_BYTE_PAYS")) return atoi(e) != 0;
+    if (const char *e = getenv("ADAPT_BYTE_PAYS")) {
+        *plan = byte_plan_of(q, bits, 1, 1, M, false, cu);
+        return atoi(e) != 0;
+    }
 #endif
-    const long long byte = byte_call_clocks(byte_plan_of(q, bits, 1, 1, M, false, cu), q.dt_bytes, pack);
-    return byte_beats_rows(byte, rows_clocks(bits, M, q.N, q.Cin, cu > 0 ? cu : device_cus()) * (storage + 1));
+    const long long rows = rows_clocks(bits, M, q.N, q.Cin, cu > 0 ? cu : device_cus()) * (storage + 1);
+    if (!byte_beats_rows(byte_call_clocks_floor(q.steps, 1 << bits, q.dt_bytes, pack), rows)) return false;
+    *plan = byte_plan_of(q, bits, 1, 1, M, false, cu);
+    return byte_beats_rows(byte_call_clocks(*plan, q.dt_bytes, pack), rows);
 }
-bool byte_call_pays(const adapt_lut *lut, const ByteShape &q, int M, bool pack) { return byte_pays(q, lut->bits, lut->storage, M, pack); }
+bool byte_call_pays(const adapt_lut *lut, const ByteShape &q, int M, bool pack, BytePlan *plan) {
+    return byte_pays(q, lut->bits, lut->storage, M, pack, 0, plan);
+}
 
 // room for the sums that the slices of a split product leave behind: `bytes` for this one, reserve() for all that are no larger
 struct BytePartials {
@@ -218,11 +225,10 @@ size_t byte_copy_bytes(int N, int Cin, int Hp, int Wp, int sw) {
 // activation copy of a linear layer
 size_t byte_linear_copy_bytes(const ByteShape &q, int M) { return align256((size_t)q.cg * ((M + 3) / 4 * 4) * 4 + 64); }
 
-// linear layer: x [M][K] int8 (a) or fp32 (io->xf)
+// linear layer: x [M][K] int8 (a) or fp32 (io->xf); pl: byte_plan_of its shape
 int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, const int8_t *a, int32_t *out, int M, hipStream_t s, Workspace *ws,
-                const LayerIO *io) {
+                const LayerIO *io, const BytePlan &pl) {
     const int Mp = (M + 3) / 4 * 4;
-    const BytePlan pl = byte_plan_of(q, lut->bits, 1, 1, M, false);
     const size_t copy_bytes = byte_linear_copy_bytes(q, M);
     if ((long long)q.cg * Mp * 4 > BYTE_MAX_COPY) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: tensor with more than 2^31-1 elements");
     const BytePartials sums(q, lut->bits, pl, 1, 1, M);

@@ -126,6 +126,13 @@ inline long long byte_call_clocks(const BytePlan &pl, size_t table_bytes, bool p
     return (pl.clocks > stream ? pl.clocks : stream) + first + 11000 + (pack ? 30000 + (long long)(table_bytes / 1400) : 0);
 }
 
+// A bound below that estimate, whatever the plan, without a search for one (64 rows, K = 256, N = 128: 0.01 instead of 0.65 us on the
+// host, of a call of 20 us).
+inline long long byte_call_clocks_floor(int steps, int copy_lines, size_t table_bytes, bool pack) {
+    const int slice = steps < 32 ? 1 : steps / 32;
+    return byte_call_clocks(BytePlan{2, 1, 0, slice * byte_step_clocks(2, copy_lines) + 8000 + 2 * 350}, table_bytes, pack);
+}
+
 // Where tables of the byte form exist (or are to be made), the byte kernel is taken if its estimate times 1.2 is below that of
 // the whole-table kernel.  Measured both ways for 16 to 4000 rows, six pairs of K and N from 64 x 10 to 4096 x 4096, 6 to 8 bits:
 // the rule loses at most 20 % or 3 us to the better one; e.g. 8 bits, K = 777, N = 999: 256 rows 66 / 53 us (whole table / byte

@@ -37,6 +37,9 @@ int main() {
                     in.rows2 = rows2;
                     const BytePlan pl = plan_byte(in);
                     const size_t need = byte_partial_bytes(pl.R, pl.ksplit, pl.R >= 4 ? in.rows4 : in.rows2, launch);
+                    for (bool pack : {false, true})         // (the choice of the kernel may stop at the bound)
+                        if (byte_call_clocks_floor(in.steps, lines, rows * 64, pack) > byte_call_clocks(pl, rows * 64, pack))
+                            return bad("byte: the floor is above the estimate", q.n_tiles, q.steps, lines, rows);
                     if (need > room) return bad("byte: more than the room", q.n_tiles, q.steps, lines, rows);
                     shrinks += need < before;
                     before = need;
