@@ -210,7 +210,8 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
     const int M = (int)pl.M, K = (int)pl.K, P = g.Ho * g.Wo, HW = H * W, Cp = (int)g.dCp.d;
     const size_t col_n = (size_t)M * K;     // elements of dcol
     auto channels_last = [&](const float *src, float *dst, int C, int pixels, int ld, float scale) {
-        const dim3 grid((unsigned)((pixels + 31) / 32), (unsigned)((ld + 63) / 64), (unsigned)(N < 65535 ? N : 65535));
+        const long long blocks = (pixels + 31LL) / 32;
+        const dim3 grid((unsigned)(blocks < (1 << 22) ? blocks : (1 << 22)), (unsigned)((ld + 63) / 64), (unsigned)(N < 65535 ? N : 65535));
         adapt::ste_channels_last_kernel<<<grid, 256, 0, s>>>(src, dst, N, C, pixels, ld, scale, Q);
     };
     if (dw_dev || (dx_dev && !pl.direct)) {

@@ -340,8 +340,15 @@ __global__ __launch_bounds__(STE_COLSUM_THREADS) void ste_colsum_kernel(const fl
 // pixels go through LDS so that reads and writes coalesce (without it: 8.4 MB in 14 us, now 5 us).
 __global__ __launch_bounds__(256) void ste_channels_last_kernel(const float *__restrict__ src, float *__restrict__ dst, int N, int C, int P, int ld, float s, float Q) {
     __shared__ float tile[64][33];
-    const int p0 = blockIdx.x * 32, c0 = blockIdx.y * 64, tid = threadIdx.x;
-    for (int n = blockIdx.z; n < N; n += gridDim.z) {
+    const int c0 = blockIdx.y * 64, tid = threadIdx.x, blocks = (int)((P + 31LL) / 32);
+    // (planes beyond the grid: a launch is limited to 2^32 threads)
+    for (int n = blockIdx.z, b = blockIdx.x; n < N; b += gridDim.x) {
+        if (b >= blocks) {
+            b = (int)blockIdx.x - (int)gridDim.x;
+            n += gridDim.z;
+            continue;
+        }
+        const int p0 = b * 32;
         const int pl = tid & 31, cl = tid >> 5;
         float v[8];
 #pragma unroll

@@ -360,3 +360,17 @@ def test_ste_conv2d_backward_keeps_infinities_to_their_pixels(B):
     far[0, :, 2:5, 2:5] = False
     far[1, :, 0:2, 0:2] = False
     assert torch.equal(got[far], clean[far]) and torch.isfinite(got[far]).all() and not torch.isfinite(got[~far]).all()
+
+
+def test_conv2d_backward_of_an_image_of_half_a_billion_pixels(B):
+    """One channel under a stride of 64: a plane with more pixels than one launch has threads for, eight of which share a pixel."""
+    k = 23171
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randint(-9, 10, (1, 1, k, k), generator=gen, device="cuda", dtype=torch.float32)
+    w = torch.full((1, 1, 1, 1), 5.0, device="cuda")
+    dy = torch.randint(-9, 10, (1, 1, 363, 363), generator=gen, device="cuda").float()
+    dx, dw, db = B.adapt_ste_conv2d_backward_f32(dy, x, w, (64, 64), (0, 0), (1, 1), 1.0, 1.0, 4)
+    # 4 bits: codes up to 7, beyond them the clamp stops the gradient; whole numbers, every sum below 2^24: exact in any order
+    assert dw.item() == (dy * x[..., ::64, ::64].clamp(-7, 7)).double().sum().item() and db.item() == dy.double().sum().item()
+    assert torch.equal(dx[..., ::64, ::64], torch.where(x[..., ::64, ::64].abs() <= 7, dy * 5.0, 0.0))
+    assert dx.count_nonzero() == dx[..., ::64, ::64].count_nonzero()
