@@ -19,8 +19,9 @@ int ste_env(const char *name) {
 constexpr size_t STE_PARTIAL_FLOATS = (size_t)(512 + 256) * 64 * 64;
 
 // partials != nullptr: a product over an unfolded input (im2col); with few output tiles and a long contraction it is split
-// over grid z into partial sums, which ste_reduce_masked_kernel adds in a fixed order.
-void launch_ste_gemm(const adapt::SteParams &p_in, bool a_t, bool aligned, hipStream_t s, float *partials = nullptr) {
+// over grid z into partial sums, which ste_reduce_masked_kernel adds in a fixed order (its columns are taps tap0 .. of a filter of
+// all_taps).
+void launch_ste_gemm(const adapt::SteParams &p_in, bool a_t, bool aligned, hipStream_t s, float *partials = nullptr, int tap0 = 0, int all_taps = 0) {
     static const int env_tile = ste_env("ADAPT_STE_TILE"), env_ks = ste_env("ADAPT_STE_KS");
     adapt::SteParams p = p_in;
     const int cus = device_cus();
@@ -60,7 +61,7 @@ void launch_ste_gemm(const adapt::SteParams &p_in, bool a_t, bool aligned, hipSt
         const size_t n = (size_t)p.I * (size_t)p.J;
         const size_t blocks = (n + 255) / 256;
         adapt::ste_reduce_masked_kernel<<<(unsigned)(blocks < 4096 ? blocks : 4096), 256, 0, s>>>(partials, parts, n, p_in.o, p_in.so, p_in.Q,
-                                                                                                  p_in.c, p.g.kh * p.g.kw, p.g.C, (int)p.g.dCp.d);
+                                                                                                  p_in.c, p.g.kh * p.g.kw, p.g.C, (int)p.g.dCp.d, tap0, all_taps);
     }
 }
 
@@ -112,10 +113,13 @@ int adapt_ste_linear_backward_f32(const float *dy_dev, const float *x_dev, const
 }  // extern "C"
 
 namespace {
+constexpr long long MAX_COLS = 0x3fffff00;         // of one product: 31-bit columns, and four threads per column in a launch of less than 2^32
+
 struct SteConvPlan {
     adapt::SteConvGeo g;
     long long M, K;
     bool direct;                // stride 1: the input gradient is one product (ste_dx_kernel)
+    int dw_rows;                // filter rows per product of the weight gradient: all, unless there are more than MAX_COLS columns (tap, channel rounded up to 4)
     size_t rows_bytes, col_bytes, wp_bytes, xq_bytes, part_bytes, total;
 };
 int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int kh, int kw, int stride_h, int stride_w, int pad_h, int pad_w,
@@ -131,8 +135,6 @@ int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int k
     pl->K = (long long)Cin * kh * kw;
     if (pl->M > 65535LL * 64 || pl->K > 0x7fffffffLL || Ho > 0x7fffffffLL || Wo > 0x7fffffffLL || (long long)N * Cin * H * W > (1LL << 40))
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: tensor too large (N Ho Wo is limited to %d)", who, 65535 * 64);
-    if ((long long)kh * kw * ((Cin + 3LL) / 4 * 4) > 0x7fffffffLL)
-        return fail(ADAPT_ERR_UNSUPPORTED, "%s: a filter is limited to 2^31 - 1 weights (channels rounded up to 4)", who);
     if ((long long)H * W > 0x7fffffffLL || Ho * Wo > 0x7fffffffLL)
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: an image plane is limited to 2^31 - 1 pixels", who);
     adapt::SteConvGeo &g = pl->g;
@@ -145,11 +147,16 @@ int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int k
     g.dsh = fast_div((uint32_t)stride_h); g.dsw = fast_div((uint32_t)stride_w);
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     pl->rows_bytes = up((size_t)pl->M * Cout * sizeof(float));
-    pl->direct = stride_h == 1 && stride_w == 1 && (long long)N * H * W < 0x7fffff00LL;
+    const long long row_cols = (long long)kw * Cp;
+    if (want_dw && row_cols > 0x7fffff00LL)
+        return fail(ADAPT_ERR_UNSUPPORTED, "%s: a filter row is limited to 2^31 - 256 weights (channels rounded up to 4)", who);
+    pl->dw_rows = (int)(kh * row_cols <= MAX_COLS ? kh : (row_cols < MAX_COLS ? MAX_COLS / row_cols : 1));
+    pl->direct = stride_h == 1 && stride_w == 1 && (long long)N * H * W < 0x7fffff00LL && kh * row_cols <= MAX_COLS;
     pl->col_bytes = want_dx && !pl->direct ? up((size_t)pl->M * (size_t)pl->K * sizeof(float)) : 0;
     const size_t cols = (size_t)kh * kw * (size_t)Cp;
     pl->xq_bytes = want_dw ? up((size_t)N * H * W * (size_t)Cp * sizeof(float)) : 0;
-    pl->part_bytes = up((want_dw && Cout * cols > STE_PARTIAL_FLOATS ? Cout * cols : STE_PARTIAL_FLOATS) * sizeof(float));
+    const size_t dw_cols = (size_t)pl->dw_rows * (size_t)row_cols;
+    pl->part_bytes = up((want_dw && Cout * dw_cols > STE_PARTIAL_FLOATS ? Cout * dw_cols : STE_PARTIAL_FLOATS) * sizeof(float));
     pl->wp_bytes = want_dx ? up((size_t)Cout * cols * sizeof(float)) : 0;
     pl->total = pl->rows_bytes + pl->col_bytes + pl->wp_bytes + pl->xq_bytes + pl->part_bytes;
     return ADAPT_OK;
@@ -223,11 +230,16 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
         HIP_TRY(hipGetLastError());
         adapt::SteParams p{};
         p.a = rows; p.b = xq; p.o = w_dev; p.c = dw_dev;
-        p.I = Cout; p.J = kh * kw * Cp; p.R = M; p.lda = Cout;
+        p.I = Cout; p.R = M; p.lda = Cout;
         p.sb = s_x; p.so = s_w; p.Q = Q;
         p.im2col = 1; p.g = g;
-        launch_ste_gemm(p, true, true, s, partials);        // (both operands lie in the workspace)
-        HIP_TRY(hipGetLastError());
+        for (int ky = 0; ky < kh; ky += pl.dw_rows) {
+            p.g.kh = kh - ky < pl.dw_rows ? kh - ky : pl.dw_rows;
+            p.g.ph = g.ph - ky * g.dh;
+            p.J = p.g.kh * kw * Cp;
+            launch_ste_gemm(p, true, true, s, partials, ky * kw, kh * kw);          // (both operands lie in the workspace)
+            HIP_TRY(hipGetLastError());
+        }
     }
     if (dx_dev && pl.direct) {
         const size_t wq_n = (size_t)kh * kw * Cout * Cp;
@@ -256,7 +268,7 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
         const int Z = N < 16 ? N : 16;
         if ((size_t)Z * Cout <= STE_PARTIAL_FLOATS && Z > 1) {
             adapt::ste_bias_grad_nchw_kernel<<<dim3((unsigned)Cout, (unsigned)Z), 256, 0, s>>>(dy_dev, partials, N, Cout, P);
-            adapt::ste_reduce_masked_kernel<<<(unsigned)((Cout + 255) / 256), 256, 0, s>>>(partials, Z, (size_t)Cout, nullptr, 1.0f, Q, db_dev, 0, 0, 0);
+            adapt::ste_reduce_masked_kernel<<<(unsigned)((Cout + 255) / 256), 256, 0, s>>>(partials, Z, (size_t)Cout, nullptr, 1.0f, Q, db_dev, 0, 0, 0, 0, 0);
         } else {
             adapt::ste_bias_grad_nchw_kernel<<<dim3((unsigned)Cout, 1), 256, 0, s>>>(dy_dev, db_dev, N, Cout, P);
         }

@@ -255,9 +255,10 @@ __global__ __launch_bounds__(STE_THREADS * KS) void ste_gemm_kernel(SteParams p)
 // c[i] = inside(o[i]) * (part[0][i] + part[1][i] + ... + part[S-1][i]), in that order: the partial sums of a product whose
 // contraction was split over grid z.  Eight parts are requested together (one at a time, 57 parts of 36864 took 15.5 us, the
 // latency of memory 57 times over; now 5.4 us).
-// taps > 0: the parts are rows of (tap, channel), taps x Cp columns, and c, o the weight tensor [row][C][taps].
+// taps > 0: the parts are rows of (tap, channel), taps x Cp columns, and c, o the weight tensor [row][C][all_taps], of which these
+// are taps tap0 .. tap0 + taps - 1.
 __global__ __launch_bounds__(256) void ste_reduce_masked_kernel(const float *__restrict__ part, int S, size_t n, const float *__restrict__ o,
-                                                                float so, float Q, float *__restrict__ c, int taps, int C, int Cp) {
+                                                                float so, float Q, float *__restrict__ c, int taps, int C, int Cp, int tap0, int all_taps) {
     const size_t stride = (size_t)gridDim.x * 256;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
         float s = part[i];
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(256) void ste_reduce_masked_kernel(const float *__r
             const size_t row = i / ((size_t)taps * Cp), rem = i - row * (size_t)taps * Cp;
             const int tap = (int)(rem / Cp), ch = (int)(rem - (size_t)tap * Cp);
             if (ch >= C) continue;
-            at = (row * C + ch) * (size_t)taps + tap;
+            at = (row * C + ch) * (size_t)all_taps + tap0 + tap;
         }
         c[at] = (!o || ste_inside(o[at], so, Q)) ? s : 0.0f;
     }

@@ -374,3 +374,16 @@ def test_conv2d_backward_of_an_image_of_half_a_billion_pixels(B):
     assert dw.item() == (dy * x[..., ::64, ::64].clamp(-7, 7)).double().sum().item() and db.item() == dy.double().sum().item()
     assert torch.equal(dx[..., ::64, ::64], torch.where(x[..., ::64, ::64].abs() <= 7, dy * 5.0, 0.0))
     assert dx.count_nonzero() == dx[..., ::64, ::64].count_nonzero()
+
+
+def test_conv2d_backward_of_a_filter_of_half_a_billion_taps(B):
+    """One channel: the taps fit 31 bits, the columns that the weight gradient's product has for them (four per tap) do not."""
+    k = 23171
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randint(-9, 10, (1, 1, k, k), generator=gen, device="cuda", dtype=torch.float32)
+    w = torch.randint(-9, 10, (1, 1, k, k), generator=gen, device="cuda", dtype=torch.float32)
+    dy = torch.full((1, 1, 1, 1), 3.0, device="cuda")
+    _, dw, db = B.adapt_ste_conv2d_backward_f32(dy, x, w, (1, 1), (0, 0), (1, 1), 1.0, 1.0, 4, want=("dw", "db"))
+    # 4 bits: codes up to 7, beyond them the clamp stops the gradient
+    assert torch.equal(dw, torch.where(w.abs() <= 7, 3.0 * x.clamp(-7, 7), 0.0))
+    assert db.item() == 3.0
