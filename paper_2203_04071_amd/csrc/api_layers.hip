@@ -777,6 +777,7 @@ int lines_conv2d(int bits, int storage, const LinesShape &q, uint4 *const dt[2],
                 const auto &ci = wh->chain_in;
                 if (ci.N != N || ci.H != H || ci.W != W || ci.sh != sh || ci.sw != sw || ci.ph != ph || ci.pw != pw || ci.dh != dh || ci.dw != dw)
                     wh->chain_in.valid = false;
+                wh->chain_in.nonneg = false;        // (and any other leaves its own copy there)
             }
             int wrc = ws_get(ws, copy_bytes, part_bytes, M, [&] { return lines_partial_reserve(device_cus(), out_elems); }, s, (void **)&xt, &partial);
             if (wrc) return wrc;

@@ -279,6 +279,7 @@ int byte_conv2d(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
         const auto &ci = wh->chain_in;
         if (ci.N != N || ci.H != H || ci.W != W || ci.sh != sh || ci.sw != sw || ci.ph != ph || ci.pw != pw || ci.dh != dh || ci.dw != dw)
             wh->chain_in.valid = false;
+        wh->chain_in.nonneg = false;        // (and any other leaves its own copy there)
     }
     const BytePartials sums(q, lut->bits, pl, N, Ho, Wo);
     unsigned char *mem = nullptr;

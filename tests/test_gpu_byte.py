@@ -215,3 +215,20 @@ def test_activation_copy_beyond_two_gigabytes(B):
     for n in (0, 3999, N - 500):
         y = B.adapt_conv2d_layer_f32(p1, xf[n:n + 500], 0.02, 1e-3)
         assert torch.equal(out[n:n + 500], B.adapt_conv2d_layer_f32(pw, y, 0.1, 1e-3, (1, 2)))
+
+
+@pytest.mark.parametrize("bits,kind", [(8, "product"), (7, "dropped"), (8, "beyond")])
+def test_ordinary_call_between_a_relu_producer_and_a_chained_call(B, bits, kind):
+    """A prepared handle that ran on its own input holds codes of both signs, whatever the producer before had said."""
+    rng = np.random.default_rng(bits)
+    t = table(kind, bits, rng)
+    L = B.Lut(t, bits)
+    p1 = B.adapt_weights_pack_conv2d(L, dev(wl.random_i8(rng, (16, 16, 1, 1), bits)))
+    p2 = B.adapt_weights_pack_conv2d(L, dev(wl.random_i8(rng, (16, 16, 3, 3), bits)))
+    x, x2 = (dev(rng.standard_normal((8, 16, 16, 16)).astype(np.float32)) for _ in range(2))
+    out = torch.empty((8, 16, 16, 16), dtype=torch.float32, device="cuda")
+    B.adapt_conv2d_chain_prepare(p2, 8, 16, 16, (1, 1), (1, 1))
+    B.adapt_conv2d_layer_chain_f32(p1, x, 0.05, 1e-3, torch.empty_like(out), act=B.ACT_RELU, next_pw=p2, s_next=0.1)
+    want = B.adapt_conv2d_layer_f32(p2, x2, 0.05, 1e-3, (1, 1), (1, 1))
+    B.adapt_conv2d_layer_chain_f32(p2, None, 0.05, 1e-3, out, (1, 1), (1, 1), in_shape=(8, 16, 16))
+    assert torch.equal(out, want)
