@@ -28,10 +28,16 @@
  *     was current when they were created.
  *   - Two calls that overlap in time on different streams are safe for the plain
  *     entry points (workspaces are allocated per call in stream order).  A packed
- *     weights handle owns a grow-only workspace: calls with the SAME handle must not
- *     overlap in time; once a handle has run at its largest input size its calls
+ *     weights handle owns a grow-only workspace and the counters by which split
+ *     products find their last workgroup: calls with the SAME handle must not
+ *     overlap in time, whatever their size or data type - from several streams or
+ *     threads, order them (events, or one stream).  Overlapping calls mix their sums
+ *     without an error.  Once a handle has run at its largest input size its calls
  *     allocate nothing and may be recorded into a HIP graph (which a later call
- *     at a larger size, re-allocating the workspace, would invalidate).
+ *     at a larger size, re-allocating the workspace, would invalidate; smaller ones
+ *     never move it).  (Linear layers on int8 codes below 4096 rows may need none of
+ *     it at one size and some at a smaller one: the first call that does makes room
+ *     for all sizes so far, or runs without it when it is being recorded.)
  *   - Environment variables the library reads (debugging and measurement aids; results never depend on them):
  *     ADAPT_POISON_ALLOC   any value: every device allocation the library makes is filled with 0xA5 bytes before
  *                          use, so that code relying on fresh memory being zero shows up in tests.
@@ -183,8 +189,8 @@ int adapt_approx_conv_transpose2d(const adapt_lut *lut, const int8_t *x_dev, con
  * spanning at most 255 are stored as that error, one byte per entry, beside the weights: K * N * (2^b + 1)
  * bytes, K and N rounded up to the kernel's tiles.  Other tables take two orders (128-byte lines; 256-byte lines
  * of two-digit entries), 2 * K * N * 2^b * 2 bytes (the first order twice, and only that, for entries
- * beyond int16).  Everything is made by the pack call, nothing is added to a handle later, so a handle
- * may be used from several threads.  The handle is tied to the device, the table contents and the weight values at pack time; w_dev may be freed
+ * beyond int16).  All tables are made by the pack call; what later calls share
+ * is the handle's workspace and counters, so they have to be ordered (see the general rules), from whichever thread they come.  The handle is tied to the device, the table contents and the weight values at pack time; w_dev may be freed
  * once the stream has passed the call.  The handle keeps a pointer to `lut`: the table handle must stay alive as long
  * as the weights handle is used (short linear layers run on the whole-table kernel with pre-packed row offsets).  The packed entry points give the same integers as the plain
  * ones; they skip the per-call packing that the plain entry points do for long matrices.
