@@ -232,3 +232,100 @@ def test_ordinary_call_between_a_relu_producer_and_a_chained_call(B, bits, kind)
     want = B.adapt_conv2d_layer_f32(p2, x2, 0.05, 1e-3, (1, 1), (1, 1))
     B.adapt_conv2d_layer_chain_f32(p2, None, 0.05, 1e-3, out, (1, 1), (1, 1), in_shape=(8, 16, 16))
     assert torch.equal(out, want)
+
+
+def bits_equal(a, b):
+    return np.array_equal(np.ascontiguousarray(a).view(np.uint32), np.ascontiguousarray(b).view(np.uint32))
+
+
+FORMS = [(8, "product"), (8, "dropped"), (7, "dropped"), (8, "one_side"), (6, "one_side")]
+
+
+def finish(acc, s_out, bias, resid, act):
+    n, c, hw = acc.shape[0], acc.shape[1], int(np.prod(acc.shape[2:], dtype=np.int64))
+    y = orc.dequant(acc, s_out, n, c, hw, bias).reshape(acc.shape)
+    if resid is not None:
+        y = orc.add(y, resid).reshape(acc.shape)
+    return (orc.relu(y) if act == 1 else orc.tanh(y) if act == 2 else y).reshape(acc.shape)
+
+
+@pytest.mark.parametrize("bits,kind", FORMS)
+@pytest.mark.parametrize("act", [0, 1, 2])
+def test_fused_layers_on_every_form(B, bits, kind, act):
+    """Bias, residual, ReLU and tanh in the epilogue, tables whose exact product drops operand bits among them: a convolution with
+    few pixels (slices) and one with ragged runs, a linear layer, a transposed convolution with border terms."""
+    rng = np.random.default_rng(bits + act)
+    t = table(kind, bits, rng)
+    L = B.Lut(t, bits)
+    s_x, s_out = np.float32(0.02), np.float32(2e-4)
+    for N, Cin, H, W, Cout, k, st in ((1, 40, 8, 8, 24, 3, 1), (5, 7, 11, 13, 18, 3, 2), (40, 6, 20, 20, 16, 1, 1)):
+        x, w = rng.standard_normal((N, Cin, H, W)).astype(np.float32), wl.random_i8(rng, (Cout, Cin, k, k), bits)
+        acc = orc.approx_conv2d(t, bits, orc.quantize(x, s_x, bits), w, (st, st), (k // 2, k // 2), threads=4)
+        bias, resid = rng.standard_normal(Cout).astype(np.float32), rng.standard_normal(acc.shape).astype(np.float32)
+        pw = B.adapt_weights_pack_conv2d(L, dev(w))
+        got = B.adapt_conv2d_layer_f32(pw, dev(x), s_x, s_out, (st, st), (k // 2, k // 2), bias=dev(bias), act=act, residual=dev(resid))
+        assert bits_equal(host(got), finish(acc, s_out, bias, resid, act)), (Cin, Cout)
+    x, w = rng.standard_normal((4097, 33)).astype(np.float32), wl.random_i8(rng, (21, 33), bits)
+    acc, bias = orc.approx_linear(t, bits, orc.quantize(x, s_x, bits), w, threads=4), rng.standard_normal(21).astype(np.float32)
+    got = B.adapt_linear_layer_f32(B.adapt_weights_pack_linear(L, dev(w)), dev(x), s_x, s_out, dev(bias), act)
+    assert bits_equal(host(got), finish(acc, s_out, bias, None, act))
+    assert (host(B.adapt_approx_linear(L, dev(orc.quantize(x, s_x, bits)), dev(w))) == acc).all()
+    for N, Cin, H, W, Cout, k, st, pad in ((3, 7, 5, 6, 9, 4, 2, 1), (9, 20, 9, 13, 33, 4, 2, 0), (2, 5, 7, 7, 8, 6, 3, 0)):
+        x, w = rng.standard_normal((N, Cin, H, W)).astype(np.float32), wl.random_i8(rng, (Cin, Cout, k, k), bits)
+        q = orc.quantize(x, s_x, bits)
+        acc, bias = orc.approx_conv_transpose2d(t, bits, q, w, st, pad, threads=4), rng.standard_normal(Cout).astype(np.float32)
+        pw = B.adapt_weights_pack_conv_transpose2d(L, dev(w), st)
+        assert (host(B.adapt_approx_conv_transpose2d_packed(pw, dev(q), pad)) == acc).all()
+        got = B.adapt_conv_transpose2d_layer_f32(pw, dev(x), s_x, s_out, pad, dev(bias), act)
+        assert bits_equal(host(got), finish(acc, s_out, bias, None, act)), (k, st, pad)
+
+
+@pytest.mark.parametrize("bits,kind", FORMS)
+@pytest.mark.parametrize("first", ["conv", "transposed", "depthwise", "grouped"])
+def test_chains_between_forms(B, bits, kind, first):
+    """The copy that each kind of producer writes for a convolution that moves by 1 to 3 pixels (a transposed one: for such a
+    one too), behind a ReLU (half of every table) and without; 8 and 18 channels (whole words of the copy, and a last one that is not)."""
+    rng = np.random.default_rng(bits)
+    t = table(kind, bits, rng)
+    L = B.Lut(t, bits)
+    s_x, s_1, s_2, s_o = np.float32(0.03), np.float32(1e-3), np.float32(0.2), np.float32(1e-3)
+    for C in (8, 18):
+        x = rng.standard_normal((3, C, 11, 13)).astype(np.float32)
+        if first == "transposed":
+            x = x[:, :, :6, :7]
+        q = orc.quantize(x, s_x, bits)
+        if first == "conv":
+            w1 = wl.random_i8(rng, (C, C, 3, 3), bits)
+            p1, acc1 = B.adapt_weights_pack_conv2d(L, dev(w1)), orc.approx_conv2d(t, bits, q, w1, (1, 1), (1, 1), threads=4)
+            run = lambda out, act, p2: B.adapt_conv2d_layer_chain_f32(p1, dev(x), s_x, s_1, out, (1, 1), (1, 1), act=act, next_pw=p2, s_next=s_2)
+        elif first == "transposed":
+            w1 = wl.random_i8(rng, (C, C, 4, 4), bits)
+            p1, acc1 = B.adapt_weights_pack_conv_transpose2d(L, dev(w1), 2), orc.approx_conv_transpose2d(t, bits, q, w1, 2, 1, threads=4)
+            run = lambda out, act, p2: B.adapt_conv_transpose2d_layer_chain_f32(p1, dev(x), s_x, s_1, out, 1, act=act, next_pw=p2, s_next=s_2)
+        else:
+            g = C if first == "depthwise" else C // 2
+            w1 = wl.random_i8(rng, (C, C // g, 3, 3), bits)
+            acc1 = orc.approx_conv2d(t, bits, q, w1, (1, 1), (1, 1), (1, 1), g, threads=4)
+            run = lambda out, act, p2: out.copy_(B.adapt_conv2d_grouped_layer_f32(L, dev(x), dev(w1), s_x, s_1, (1, 1), (1, 1), groups=g, act=act,
+                                                                                  next_pw=p2, s_next=s_2))
+        _, _, H, W = acc1.shape
+        for st in (1, 2, 3) + ((0,) if first == "transposed" else ()):          # (0: the consumer is a transposed convolution, too)
+            w2 = wl.random_i8(rng, (C, 19, 4, 4) if st == 0 else (19, C, 3, 3), bits)
+            p2 = B.adapt_weights_pack_conv_transpose2d(L, dev(w2), 2) if st == 0 else B.adapt_weights_pack_conv2d(L, dev(w2))
+            if st == 0:
+                B.adapt_conv_transpose2d_chain_prepare(p2, 3, H, W, 1)
+            else:
+                B.adapt_conv2d_chain_prepare(p2, 3, H, W, (st, st), (1, 1))
+            for act in (1, 0, 1):
+                y = finish(acc1, s_1, None, None, act)
+                q2 = orc.quantize(y, s_2, bits)
+                acc2 = orc.approx_conv_transpose2d(t, bits, q2, w2, 2, 1, threads=4) if st == 0 else orc.approx_conv2d(t, bits, q2, w2, (st, st), (1, 1), threads=4)
+                out1 = torch.empty(acc1.shape, dtype=torch.float32, device="cuda")
+                out2 = torch.empty(acc2.shape, dtype=torch.float32, device="cuda")
+                run(out1, act, p2)
+                if st == 0:
+                    B.adapt_conv_transpose2d_layer_chain_f32(p2, None, s_2, s_o, out2, 1, in_shape=(3, H, W))
+                else:
+                    B.adapt_conv2d_layer_chain_f32(p2, None, s_2, s_o, out2, (st, st), (1, 1), in_shape=(3, H, W))
+                assert bits_equal(host(out1), y), (C, st, act)
+                assert bits_equal(host(out2), finish(acc2, s_o, None, None, 0)), (C, st, act)
