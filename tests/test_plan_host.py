@@ -1,5 +1,6 @@
 """Which kernel, rows per workgroup and split each layer of the five baseline configurations takes, on a 256-CU device,
-through the C ABI's plan query (host code only: no GPU needed).  A change of the launch planner shows up here."""
+through the C ABI's plan query (host code only: no GPU needed).  A change of the launch planner shows up here.  Storage 0: as an
+arbitrary table of 16-bit entries would run; storage 2: as the configurations' own tables do, which have a byte form."""
 import pytest
 
 QUAD, XMAJOR, FAST, GENERIC, ROWS = 3, 2, 1, 0, -1
@@ -90,3 +91,20 @@ def test_handles_whose_inner_dimension_is_too_long_for_the_byte_kernel(plan):
     assert plan(2, 8, 2, 64, 4080, 4, 4, 2, 4096, 32, 1)[0] == plan(2, 8, 2, 64, 8160, 4, 4, 2, 4096, 32, 1)[0] == BYTE
     assert plan(2, 8, 2, 64, 8164, 4, 4, 2, 4096, 32, 1) == plan(2, 8, 0, 64, 8164, 4, 4, 2, 4096, 32, 1)
     assert plan(2, 8, 2, 16, 16, 18, 18, 9, 4096, 32, 1)[0] == ROWS
+
+
+def test_layers_of_the_configurations_on_their_own_tables(plan):
+    # config 2: two slices of 18 steps; 1024 rows per workgroup
+    assert plan(1, 8, 2, 64, 64, 3, 3, 1, 32 * 32 * 32, 32, 1) == (BYTE, 1024, 2, 36, 256)
+    # config 3: every convolution fills the chip, the later stages by slices; the final linear layer stays on the whole table
+    for cout, cin, hw, stride, ksplit, steps in ((16, 3, 32, 1, 1, 3), (16, 16, 32, 1, 1, 9), (32, 16, 16, 2, 2, 9), (32, 32, 16, 1, 2, 18),
+                                                 (64, 32, 8, 2, 4, 18), (64, 64, 8, 1, 4, 36)):
+        assert plan(1, 8, 2, cout, cin, 3, 3, 1, 128 * hw * hw, hw, stride) == (BYTE, 512, ksplit, steps, 256)
+    assert plan(0, 8, 2, 10, 64, 1, 1, 1, 128, 128, 1)[0] == ROWS
+    # config 4: input products of all steps; one step of the recurrence
+    assert plan(0, 7, 2, 2048, 512, 1, 1, 1, 100 * 64, 100 * 64, 1) == (BYTE, 2048, 1, 32, 512)
+    assert plan(0, 7, 2, 2048, 512, 1, 1, 1, 64, 64, 1)[0] == ROWS
+    # config 5: 2048 rows per workgroup, the first layer in two slices
+    for bits in (6, 8):
+        for cin, cout, hw, ksplit in ((512, 256, 4, 2), (256, 128, 8, 1), (128, 64, 16, 1), (64, 3, 32, 1)):
+            assert plan(2, bits, 2, cout, cin, 4, 4, 2, 256 * hw * hw, hw, 1)[:4] == (BYTE, 2048, ksplit, 4 * cin // 16)
