@@ -27,7 +27,6 @@ sys.path.insert(0, ROOT)
 
 LDS_LANES_PER_CLK_PER_CU = 32      # 32 banks x 4 B: one 16-bit gather lane per bank per clock (the model peak named for this path)
 MODEL_CLOCK_GHZ = 2.4
-GATHER_LANES_PER_CLK_PER_CU = 4    # vector memory path: one 64-lane gather instruction per 16 clocks
 MITCHELL_OPS_PER_MAC = 15          # vector instructions per multiply-accumulate counted in the compiled function-form kernel (484 per 32)
 MODEL_CUS = 256
 HBM_PEAK_BYTES_PER_S = 8.0e12      # published HBM3E rate of MI355X
@@ -462,27 +461,25 @@ def cpu_baseline(cfg_id, bits, wl):
 
 def network_roofline(cfg_id, bits, macs, ms_per_step, ceilings, model_peak, gnet):
     """A whole network step priced against the measured ceilings: the time its lookups need at the rate of the resource
-    that bounds the kernel they run on (16-byte LDS reads for the derived-table kernels: 2 bytes per lookup; 16-bit LDS
-    gathers for the whole-table kernel: one per lookup), divided by the measured step time."""
+    that bounds the kernel they run on (16-byte LDS reads for the byte kernel: 1 byte per lookup; 16-bit LDS gathers for
+    the whole-table and the depthwise kernel: one per lookup), divided by the measured step time."""
     if not ceilings or cfg_id not in (3, 4, 5, 6, 7):
         return None
     lds = ceilings["lds_read_b128_TB_s"] * 1e12
     g16 = ceilings["lds_gather16_conflict_free_Tlookup_s"] * 1e12
-    if cfg_id == 4:
-        rec = 100 * 64 * 512 * 2048          # hidden-state products: one launch per time step on the whole-table kernel
-        proj = macs - rec                    # input products of all steps: one launch of the quad kernel
-        t = rec / g16 + 2.0 * proj / lds
-        dom, bound = "lut_rows_kernel (recurrent step: product + cell, 100 launches)", "lds_gather16 (recurrence) + lds_read (input products)"
-    elif cfg_id == 7:
-        rec = 100 * 64 * 512 * 1536
-        t = rec / g16 + 2.0 * (macs - rec) / lds
-        dom, bound = "lut_rows_kernel (recurrent step: product + cell, 100 launches)", "lds_gather16 (recurrence) + lds_read (input products)"
-    else:
-        t = 2.0 * macs / lds
-        dom = {3: "lut_byte_kernel (19 layers of 11 - 20 us; the 32- and 64-channel ones in slices joined in the kernel)",
-               5: "lut_byte_kernel<%d, 8, 1>" % (2 if bits == 8 else 1),
-               6: "lut_grouped_tiled_kernel + lut_byte_kernel"}[cfg_id]
-        bound = "lds_read"
+    gathered = {3: 128 * 64 * 10,                   # final linear layer
+                4: 100 * 64 * 512 * 2048,           # hidden-state products: one launch per time step
+                5: 256 * 100 * 8192,                # first layer: one input pixel
+                6: 32 * 1024 * 128 * 9,             # depthwise layer
+                7: 100 * 64 * 512 * 1536}[cfg_id]
+    t = gathered / g16 + (macs - gathered) / lds
+    dom = {3: "lut_byte_kernel (19 layers of 11 - 20 us; the 32- and 64-channel ones in slices joined in the kernel)",
+           4: "lut_rows_kernel (recurrent step: product + cell, 100 launches)",
+           5: "lut_byte_kernel<%d, 8, 1>" % (2 if bits == 8 else 1),
+           6: "lut_grouped_tiled_kernel + lut_byte_kernel",
+           7: "lut_rows_kernel (recurrent step: product + cell, 100 launches)"}[cfg_id]
+    bound = {4: "lds_gather16 (recurrence) + lds_read (input products)", 6: "lds_gather16 (depthwise) + lds_read (pointwise)",
+             7: "lds_gather16 (recurrence) + lds_read (input products)"}.get(cfg_id, "lds_read")
     return dict(bound=bound, achieved=macs / (ms_per_step * 1e-3) / 1e12, peak=macs / t / 1e12, unit="Tlookup/s", frac=t / (ms_per_step * 1e-3),
                 traffic=None, bound_us=t * 1e6, dominant_kernel=dom, covers="the whole network step (every kernel, launch gaps included)",
                 peak_source="what the step's lookups cost at the LDS rates measured by the probe kernels in this run", ceilings=ceilings)
@@ -541,7 +538,7 @@ def main():
         print(json.dumps({"copy_calibration_bytes": 64 << 20, "copies": 3}))
         return
     # ceilings of this device, measured now (headline and network configurations price their kernels against them)
-    ceilings = run_probes() if args.config <= 7 and not args.no_probes else None
+    ceilings = run_probes() if args.config <= 8 and not args.no_probes else None
     step, core, macs, name, _keep = build_step(args.config, args.bits, torch, B, gnet, wl, args.eager, "eager" if args.eager else ("graph" if args.graph else None))
 
     def timed(step_fn, steps, warmup, prewarm_ms):
@@ -577,7 +574,7 @@ def main():
         if ceilings:
             g = ceilings["lds_gather16_conflict_free_Tlookup_s"] * 1e12
             d.update(measured_conflict_free_gather_Tlookup_s=g / 1e12, frac_of_measured_gather=rate / g,
-                     note="a kernel on derived tables reads 16 bytes (8 entries) per LDS lane-access, so these two fractions are not "
+                     note="a kernel on derived tables reads 16 bytes (8 or 16 entries) per LDS lane-access, so these two fractions are not "
                           "bounded by 1 for it; its ceilings are the resources in roofline.resource_us")
         return d
 
@@ -602,17 +599,18 @@ def main():
         k_avg = float(kms.mean())
         achieved = macs / (k_avg * 1e-3)
         if args.config == 2 and ceilings:
-            # The product kernel of the headline layer (lut_quad_kernel), priced resource by resource: what one launch
-            # needs of each, divided by what the probes measured for it a moment ago.  The largest of these times is the
-            # bound; frac = that time / the kernel's measured time.
-            kern, rpw, ksplit, steps_k, wgs = B.adapt_plan_packed(1, 8, 0, 64, 64, 3, 3, 1, 32768, 32, 1)
-            if kern != 3:
-                raise SystemExit("bench.py: the headline layer is not planned on the quad kernel")
+            # The product kernel of the headline layer (lut_byte_kernel: its table is an exact product plus an error of one
+            # byte), priced resource by resource: what one launch needs of each, divided by what the probes measured for it
+            # a moment ago.  The largest of these times is the bound; frac = that time / the kernel's measured time.
+            kern, rpw, ksplit, steps_k, wgs = B.adapt_plan_packed(1, 8, 2, 64, 64, 3, 3, 1, 32768, 32, 1)
+            if kern != 4:
+                raise SystemExit("bench.py: the headline layer is not planned on the byte kernel")
             table_bytes = 256 << 8
-            lds_bytes = 2.0 * macs                                          # one 16-byte read per 8 lookups
+            lds_bytes = 1.0 * macs                                          # one 16-byte read per 16 lookups
             fill_bytes = float(wgs) * (steps_k / ksplit) * (table_bytes + rpw * 16)  # tables into LDS + activations into registers, per step
-            mfma_insts = macs / 512.0                                       # one matrix instruction per 64 reads
-            hbm_bytes = 32 * 34 * 34 * 64 + 8 * steps_k * table_bytes + 4.0 * 32 * 64 * 32 * 32      # padded copy + tables + fp32 output
+            mfma_insts = macs / 1024.0 * (1 + 1 / 16)                       # one matrix instruction per 64 reads; the exact product
+            hbm_bytes = 32 * 34 * 34 * 64 + 4 * steps_k * table_bytes + 4.0 * 32 * 64 * 32 * 32      # padded copy + tables + fp32 output
+            hbm_bytes += 2.0 * 64 * rpw * (wgs - wgs // ksplit)             # sums that slices leave behind (64 B per row), written and read
             res_us = dict(lds_read=lds_bytes / (ceilings["lds_read_b128_TB_s"] * 1e12) * 1e6,
                           l2_to_cu_fill=fill_bytes / (ceilings["l2_to_lds_TB_s"] * 1e12) * 1e6,
                           mfma=mfma_insts / (ceilings["mfma_i32_16x16x64_i8_Ginst_s"] * 1e9) * 1e6,
@@ -623,11 +621,11 @@ def main():
                                     "mfma": (mfma_insts * 32768, ceilings["mfma_i32_16x16x64_i8_Ginst_s"] * 1e9 * 32768 / 1e12, "TOP/s"),
                                     "hbm": (hbm_bytes, HBM_PEAK_BYTES_PER_S / 1e12, "TB/s")}[bound]
             if traffic is None:
-                traffic = traffic_by_kernel.get("lut_quad_kernel")
+                traffic = traffic_by_kernel.get("lut_byte_kernel")
             roof = dict(bound=bound, achieved=amount / (k_avg * 1e-3) / 1e12, peak=peak_v, unit=unit, frac=res_us[bound] / (k_avg * 1e3),
                         traffic=traffic, traffic_source=os.path.relpath(TRAFFIC_FILE, ROOT) if traffic is not None and args.traffic_bytes is None else None,
-                        kernel="lut_quad_kernel<4, %d, false>" % (rpw // 256), kernel_ms_avg=k_avg, kernel_ms_min=float(kms.min()),
-                        call_ms_avg=float(call_ms.mean()), call_traffic=(traffic + traffic_by_kernel["pad_channels_last"]) if traffic is not None and "pad_channels_last" in traffic_by_kernel else None,
+                        kernel="lut_byte_kernel<4, %d, 0>" % (rpw // 256), kernel_ms_avg=k_avg, kernel_ms_min=float(kms.min()),
+                        call_ms_avg=float(call_ms.mean()), call_traffic=(traffic + traffic_by_kernel["byte_copy_kernel"]) if traffic is not None and "byte_copy_kernel" in traffic_by_kernel else None,
                         covers="the product kernel alone, launched on an input copy made beforehand; call_ms_avg adds the call's quantise-and-copy kernel",
                         resource_us=res_us, algorithmic=dict(lds_bytes=lds_bytes, l2_to_cu_fill_bytes=fill_bytes, mfma_instructions=mfma_insts, hbm_bytes=hbm_bytes,
                                                              workgroups=wgs, steps=steps_k, rows_per_workgroup=rpw),
@@ -640,11 +638,15 @@ def main():
                         kernel_ms_avg=k_avg, kernel_ms_min=float(kms.min()), covers="every kernel of the call (products, bias gradient; convolution: also the unfolding and gathering kernels)",
                         peak_model="published dense fp32 matrix rate of MI355X")
         elif args.config == 8:
-            # a table beyond LDS is gathered through the vector memory path: 4 lane addresses per clock per compute unit
-            gpeak = cus * GATHER_LANES_PER_CLK_PER_CU * MODEL_CLOCK_GHZ * 1e9
-            roof = dict(bound="l1-gather", achieved=achieved / 1e12, peak=gpeak / 1e12, unit="Tlookup/s", frac=achieved / gpeak, traffic=traffic,
-                        kernel_ms_avg=k_avg, kernel_ms_min=float(kms.min()),
-                        peak_model=f"{cus} CUs x {GATHER_LANES_PER_CLK_PER_CU} gathered lanes/clk x {MODEL_CLOCK_GHZ} GHz; 1 lookup (4 B from device memory) per LUT-MAC")
+            # lut_cols_kernel: the columns of a stage are copied into LDS once per 8192 pixels and 4 channels (64 KB per pair of
+            # inner indices), and a lookup is a quarter of an 8-byte LDS read
+            fill_bytes, lds_bytes = 4.0 * 16 * (9 * 32) * 65536, 2.0 * macs
+            if ceilings:
+                t = {"l2_to_cu_fill": fill_bytes / (ceilings["l2_to_lds_TB_s"] * 1e12), "lds_read": lds_bytes / (ceilings["lds_read_b128_TB_s"] * 1e12)}
+                bound = max(t, key=t.get)
+                roof = dict(bound=bound, achieved=achieved / 1e12, peak=macs / t[bound] / 1e12, unit="Tlookup/s", frac=t[bound] / (k_avg * 1e-3), traffic=traffic,
+                            kernel_ms_avg=k_avg, kernel_ms_min=float(kms.min()), resource_us={k: v * 1e6 for k, v in t.items()},
+                            covers="every kernel of the call", peak_source="measured by the probe kernels in this run", ceilings=ceilings)
         elif args.config == 9:
             # the multiplier as a function: vector integer operations, 64 lanes per clock per compute unit
             apeak = cus * 64 * MODEL_CLOCK_GHZ * 1e9 / MITCHELL_OPS_PER_MAC
