@@ -162,9 +162,9 @@ void launch_cols_bits(const adapt::ColsParams &p, unsigned grid, int NR, hipStre
 int cols_classes(const adapt::BigParams &g) { return g.conv && g.Wo == 1 ? 1 : g.sw; }
 
 // Plan of a product on the columns kernel (g as in run_big); NR == 0 where offsets would not fit 32 bits.  Every product of a
-// table with columns goes there: whole layers take 30 to 210 us against 45 to 1730 us of the gathering kernel, from 64 pixels
-// and 5 -> 9 channels (37 against 45 us) to 32 images of 32 x 32 pixels and 64 -> 64 channels, 3 x 3 (12 bits: 207 against 1730
-// us, 9 bits: 131 against 1160 us).
+// table with columns goes there: whole layers take 30 to 200 us against 45 to 1730 us of the gathering kernel, from 64 pixels
+// and 5 -> 9 channels (37 against 45 us) to 32 images of 32 x 32 pixels and 64 -> 64 channels, 3 x 3 (12 bits: 196 against 1730
+// us, 9 bits: 121 against 1160 us).
 ColsPlan cols_plan_of(const adapt_lut16 *lut, const adapt::BigParams &g) {
     ColsPlanIn in;
     const int images = g.conv ? g.M / g.HoWo : 1, Wo = g.conv ? g.Wo : g.M;

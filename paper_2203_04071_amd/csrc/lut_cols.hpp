@@ -14,12 +14,12 @@
 // modulo the horizontal stride][column / stride], as in lut_byte.hpp: a run of four output pixels of a row is four consecutive
 // words for every stride.  Rows are virtual (an image row counts as Wo rounded up to runs of four).
 //
-// What bounds it (one MI355X; 3 x 3, 64 -> 64 channels, 32 images of 32 x 32, whole layer 207 us at 12 bits and 131 us at 9, against
-// 1700 and 1160 us of the gathering kernel): no unit by itself.  LDS is busy for 41 % of the time (7 clocks a read of 64 lanes,
-// half of them bank conflicts: 64 random entries), the vector ALU for at least 47 %; taking the columns' loads and stores out
-// saves 70 us at 12 bits, the exact product or the additions 12 us each.  8192 pixels per workgroup, because a column is
-// loaded and stored once per row tile (4096: 290 us at 12 bits) and larger ones would need more slices, whose sums cost as much
-// (8 slices instead of 4: 254 us).
+// What bounds it (one MI355X; 3 x 3, 64 -> 64 channels, 32 images of 32 x 32, whole layer 196 us at 12 bits and 121 us at 9, against
+// 1700 and 1160 us of the gathering kernel): no unit by itself.  LDS is busy for 39 % of the time (7 clocks a read of 64 lanes,
+// half of them bank conflicts: 64 random entries), the vector ALU for 48 %.  Timed when the layer took 207 us (it mapped its scratch
+// memory anew): taking the columns' loads and stores out saved 70 us at 12 bits, the exact product or the additions 12 us
+// each.  8192 pixels per workgroup, because a column is loaded and stored once per row tile (4096: 290 us at 12 bits) and larger
+// ones would need more slices, whose sums cost as much (8 slices instead of 4: 254 us).
 //
 // Split inner dimension: ksplit workgroups share a tile; all but the last to arrive leave their sums in memory, the last one
 // adds them to its own and finishes (the scheme of lut_byte.hpp).

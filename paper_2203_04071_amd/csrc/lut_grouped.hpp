@@ -113,8 +113,8 @@ constexpr int GROUPED_PF = 8;               // input elements a lane prefetches 
 constexpr int GROUPED_TOFF_SHIFT = 18;      // row offsets stay below 2^18 (255 rows of 516 bytes), tap offsets below 2^14
 
 // stage_table with all loads of a lane on their way before the first is stored (three of 16 bytes for tables of up to 7 bits, nine
-// for 8 bits): one latency of L2 instead of one per few loads.  Separable block, 128 channels, 32 images of 32 x 32, 8 bits: 45.2 ->
-// 43.1 us.  (In the whole-table kernel the registers it takes cost more than it gives: LSTM over 100 steps 1535 -> 1880 us.)
+// for 8 bits): one latency of L2 instead of one per few loads.  Separable block, 128 channels, 32 images of 32 x 32, 8 bits: 45.0 ->
+// 42.8 us.  (In the whole-table kernel the registers it takes cost more than it gives: LSTM over 100 steps 1535 -> 1880 us.)
 template <int U>
 __device__ __forceinline__ void stage_table_part(unsigned char *smem, const uint16_t *img, int n16, int tid) {
     typedef uint32_t words_t __attribute__((ext_vector_type(4)));
