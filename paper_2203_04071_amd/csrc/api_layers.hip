@@ -1569,7 +1569,8 @@ static int layer_io(LayerIO *io, const adapt_weights *h, const float *x_dev, con
 
 // int8 copy of fp32 activations in the handle's workspace, for the whole-table kernel
 static int quantize_into_ws(const adapt_weights *h, const LayerIO &io, int M, size_t n, hipStream_t s, int8_t **q) {
-    if (h->byte_form && h->kind == 0) (void)byte_linear_reserve(h, M, s);       // (or this buffer would move under a recorded call later)
+    // (a smaller call on the byte kernel must not move this buffer under a recorded one)
+    if (h->byte_form && h->kind == 0 && !byte_never_pays(byte_shape_of(h), h->bits, h->storage, M)) (void)byte_linear_reserve(h, M, s);
     int32_t *partial = nullptr;
     int rc = ws_get(&h->ws, n + 64, 0, 0, [] { return (size_t)0; }, s, (void **)q, &partial);
     if (rc) return rc;

@@ -112,6 +112,10 @@ bool byte_pays(const ByteShape &q, int bits, int storage, int M, bool pack, int 
     *plan = byte_plan_of(q, bits, 1, 1, M, false, cu);
     return byte_beats_rows(byte_call_clocks(*plan, q.dt_bytes, pack), rows);
 }
+// no linear layer of up to M rows on these (packed) tables runs on the byte kernel
+bool byte_never_pays(const ByteShape &q, int bits, int storage, int M) {
+    return !byte_beats_rows(byte_call_clocks_floor(q.steps, 1 << bits, q.dt_bytes, false), rows_clocks_up_to(bits, M, q.N, q.Cin, device_cus()) * (storage + 1));
+}
 bool byte_call_pays(const adapt_lut *lut, const ByteShape &q, int M, bool pack, BytePlan *plan) {
     return byte_pays(q, lut->bits, lut->storage, M, pack, 0, plan);
 }

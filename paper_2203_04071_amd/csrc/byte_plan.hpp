@@ -108,13 +108,28 @@ inline RowsShape rows_shape(long long M, long long N, long long K, int groups, i
 // Estimated clocks of a linear layer on it (one MI355X, 2.2 GHz): 16 waves of ceil(K / slices) NT reads of LDS at 4.3 clocks each where
 // activations come as whole words, 8 where they come byte by byte (K no multiple of 4), behind the copy of the
 // table into LDS at 10 B per clock.  Measured 4096 x 4096 x 4000 rows: 8.5 ms (8.2 estimated), 777 x 999 x 1024: 193 us (196).
-inline long long rows_clocks(int bits, long long M, long long N, long long K, int cu) {
-    const RowsShape r = rows_shape(M, N, K, 1, cu);
+inline long long rows_clocks_in(const RowsShape &r, int bits, long long M, long long N, long long K, int cu) {
     const long long slices = 1024 / r.MT, kc = (K + slices - 1) / slices, wgs = (M + r.MT - 1) / r.MT * ((N + r.NT - 1) / r.NT);
     const long long table = ((1LL << bits) * ((1LL << bits) + 2)) * 2, red = slices > 1 ? 4096LL * r.NT : 0;
     const int per_cu = (table > red ? table : red) <= 80 * 1024 ? 2 : 1;
     const long long rounds = wgs <= cu ? 1 : (wgs + cu * per_cu - 1) / (cu * per_cu) * per_cu;
     return rounds * ((long long)(16 * kc * r.NT * (K % 4 == 0 && kc % 4 == 0 ? 4.3 : 8.0)) + table / 10) + 4000;
+}
+
+inline long long rows_clocks(int bits, long long M, long long N, long long K, int cu) { return rows_clocks_in(rows_shape(M, N, K, 1, cu), bits, M, N, K, cu); }
+
+// A bound above that estimate for every number of rows up to M: in a given tile shape more rows only take longer, so the longest of
+// the shapes that any of them can get (64 rows per workgroup, or less than twice its rows; 16 channels only where the grid then covers
+// the chip)
+inline long long rows_clocks_up_to(int bits, long long M, long long N, long long K, int cu) {
+    long long most = 0;
+    for (int MT = 64; MT <= 1024 && (MT == 64 || MT / 2 < M); MT *= 2)
+        for (int NT = 8; NT <= 16; NT *= 2) {
+            if (NT == 16 && N > 8 && (M + MT - 1) / MT * ((N + 15) / 16) < cu) continue;
+            const long long c = rows_clocks_in(RowsShape{NT, MT}, bits, M, N, K, cu);
+            most = c > most ? c : most;
+        }
+    return most;
 }
 
 // Estimated clocks of a whole call on the byte kernel: the launch, or the stream of its tables where that takes longer (2300 B

@@ -62,6 +62,17 @@ int main() {
                     held = room;
                 }
             }
+    // the whole-table kernel's estimate for all smaller row counts, and what it says about them
+    for (int bits = 2; bits <= 8; bits += 2)
+        for (int K : {1, 16, 100, 256, 534, 777, 1024, 4096})
+            for (int N : {1, 8, 9, 64, 128, 300, 912, 2048, 4096}) {
+                long long most = 0;
+                for (int M = 1; M < 4096; M += M < 700 ? 1 : 11) {
+                    const long long c = rows_clocks(bits, M, N, K, cu), bound = rows_clocks_up_to(bits, M, N, K, cu);
+                    most = c > most ? c : most;
+                    if (most > bound) return bad("rows: the bound is below an estimate", bits, K, N, M);
+                }
+            }
     std::printf("ok %d\n", shrinks);
     return shrinks > 0 ? 0 : 1;
 }
