@@ -55,7 +55,8 @@ struct adapt_weights {
     int32_t *zsum_dev;      // [Cout][kh * kw] sums of T[0][w] over the input channels
     int8_t *w8_dev;         // copy of the weights for the geometries the phase form does not cover
     const adapt_lut *lut;   // the table handle (must outlive this handle), for those geometries
-    mutable int rows_without_room = 0;      // linear, byte form: rows of calls that needed none of it
+    mutable int rows_without_room = 0;      // linear, byte form: rows of calls that needed none of it,
+    mutable int rows_without_byte = 0;      // and up to which no call runs on the byte kernel
     mutable Workspace ws;   // padded activation copy of the latest call
     // convolutions: the geometry for which the workspace was prepared to receive its input copy from the layer before
     // (adapt_conv2d_chain_prepare): borders and padded channels zeroed, layout fixed
@@ -1475,13 +1476,17 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
 }
 
 // Room in a byte-form handle for linear layers of up to M rows, and of up to those that went to the whole-table kernel before
-// (which then made none)
-static int byte_linear_reserve(const adapt_weights *h, int M, hipStream_t s) {
+// (which then made none); if_any_runs: only if some of them may run on the byte kernel
+static int byte_linear_reserve(const adapt_weights *h, int M, hipStream_t s, bool if_any_runs) {
     const ByteShape q = byte_shape_of(h);
     const int rows = M > h->rows_without_room ? M : h->rows_without_room;
     const size_t copy_bytes = byte_linear_copy_bytes(q, rows);
     const BytePartials sums(q, h->bits, BytePlan{}, 1, 1, rows);
     if (h->ws.holds(copy_bytes, sums.rows)) return ADAPT_OK;
+    if (if_any_runs && byte_never_pays(q, h->bits, h->storage, rows)) {
+        h->rows_without_byte = rows;
+        return ADAPT_OK;
+    }
     if (is_capturing(s)) return ADAPT_ERR_UNSUPPORTED;
     void *mem = nullptr;
     int32_t *partial = nullptr;
@@ -1503,7 +1508,7 @@ static bool linear_on_rows(const adapt_weights *h, int M, hipStream_t s, BytePla
         if (h->rows_without_room < M) h->rows_without_room = M;
         return true;
     }
-    return byte_linear_reserve(h, M, s) != ADAPT_OK;
+    return byte_linear_reserve(h, M, s, false) != ADAPT_OK;
 }
 
 int adapt_approx_linear_packed(const adapt_weights *h, const int8_t *a_dev, int32_t *acc_dev, int M, void *stream) {
@@ -1570,7 +1575,8 @@ static int layer_io(LayerIO *io, const adapt_weights *h, const float *x_dev, con
 // int8 copy of fp32 activations in the handle's workspace, for the whole-table kernel
 static int quantize_into_ws(const adapt_weights *h, const LayerIO &io, int M, size_t n, hipStream_t s, int8_t **q) {
     // (a smaller call on the byte kernel must not move this buffer under a recorded one)
-    if (h->byte_form && h->kind == 0 && !byte_never_pays(byte_shape_of(h), h->bits, h->storage, M)) (void)byte_linear_reserve(h, M, s);
+    if (h->byte_form && h->kind == 0 && M > h->rows_without_byte)
+        (void)byte_linear_reserve(h, M, s, true);
     int32_t *partial = nullptr;
     int rc = ws_get(&h->ws, n + 64, 0, 0, [] { return (size_t)0; }, s, (void **)q, &partial);
     if (rc) return rc;

@@ -112,9 +112,11 @@ bool byte_pays(const ByteShape &q, int bits, int storage, int M, bool pack, int 
     *plan = byte_plan_of(q, bits, 1, 1, M, false, cu);
     return byte_beats_rows(byte_call_clocks(*plan, q.dt_bytes, pack), rows);
 }
-// no linear layer of up to M rows on these (packed) tables runs on the byte kernel
+// No linear layer of up to M rows on these (packed) tables runs on the byte kernel: what is cheapest for one row (more rows make every
+// plan dearer and rule some out) against the most that any of them takes on the other kernel
 bool byte_never_pays(const ByteShape &q, int bits, int storage, int M) {
-    return !byte_beats_rows(byte_call_clocks_floor(q.steps, 1 << bits, q.dt_bytes, false), rows_clocks_up_to(bits, M, q.N, q.Cin, device_cus()) * (storage + 1));
+    const long long one_row = byte_call_clocks(byte_plan_of(q, bits, 1, 1, 1, false), q.dt_bytes, false);
+    return !byte_beats_rows(one_row, rows_clocks_up_to(bits, M, q.N, q.Cin, device_cus()) * (storage + 1));
 }
 bool byte_call_pays(const adapt_lut *lut, const ByteShape &q, int M, bool pack, BytePlan *plan) {
     return byte_pays(q, lut->bits, lut->storage, M, pack, 0, plan);

@@ -33,9 +33,13 @@ int main() {
                 if (room < held) return bad("byte: the room shrinks", q.n_tiles, q.steps, lines, rows);
                 held = room;
                 // image rows of any width: between rows4 / 4 * 2 and rows4 rows in runs of two
+                BytePlanIn one = in;
+                one.rows4 = 4; one.rows2 = 2;
+                const long long one_row = plan_byte(one).clocks;
                 for (long long rows2 : {(rows + 1) / 2 * 2, in.rows4, in.rows4 / 2}) {
                     in.rows2 = rows2;
                     const BytePlan pl = plan_byte(in);
+                    if (rows2 >= 2 && pl.clocks < one_row) return bad("byte: cheaper than one row", q.n_tiles, q.steps, lines, rows);
                     const size_t need = byte_partial_bytes(pl.R, pl.ksplit, pl.R >= 4 ? in.rows4 : in.rows2, launch);
                     for (bool pack : {false, true})         // (the choice of the kernel may stop at the bound)
                         if (byte_call_clocks_floor(in.steps, lines, rows * 64, pack) > byte_call_clocks(pl, rows * 64, pack))
