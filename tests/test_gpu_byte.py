@@ -78,6 +78,24 @@ def test_convolution(B, bits, kind, case):
     assert (plain == want).all()
 
 
+@pytest.mark.parametrize("bits,kind", [(8, "product"), (8, "dropped"), (7, "product"), (6, "one_side")])
+@pytest.mark.parametrize("images,hw,steps", [(1, 12, range(1, 10)), (9, 64, range(1, 6)), (8, 256, (1, 2, 3, 5))])
+def test_every_remainder_of_a_group_of_steps(B, bits, kind, images, hw, steps):
+    """1 x 1 layers of 1, 2, .. steps of 16 inner indices (the last one ragged): the exact product takes them in pairs, copies and
+    activations in groups of four; few, more and many pixels, so that all numbers of pixels per row slot occur."""
+    rng = np.random.default_rng(17 * bits + images)
+    h = 1 << (bits - 1)
+    t = table(kind, bits, rng)
+    lut = B.Lut(t, bits)
+    for s in steps:
+        cin = 16 * s - 3 * (s % 2)
+        x = rng.integers(-h, h, size=(images, cin, hw, hw)).astype(np.int8)
+        w = rng.integers(-h, h, size=(16, cin, 1, 1)).astype(np.int8)
+        pw = B.adapt_weights_pack_conv2d(lut, dev(w))
+        got = host(B.adapt_approx_conv2d_packed(pw, dev(x), (1, 1), (0, 0)))
+        assert np.array_equal(got, orc.approx_conv2d(t, bits, x, w, (1, 1), (0, 0))), s
+
+
 @pytest.mark.parametrize("bits", [6, 8])
 @pytest.mark.parametrize("shape", [(4096, 1, 1), (4097, 15, 17), (4099, 130, 33), (9000, 64, 16), (5000, 517, 100)])
 def test_linear(B, bits, shape):
