@@ -174,7 +174,12 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
     p.zsum = c.zsum; p.cv_s = fast_div((uint32_t)c.cv_s);
     p.cv_Ho = c.cv_Ho; p.cv_Wo = c.cv_Wo; p.cv_H = c.cv_H; p.cv_W = c.cv_W; p.cv_kh = c.cv_kh; p.cv_kw = c.cv_kw; p.cv_pad = c.cv_pad;
     p.cv_Ly = c.cv_Ly; p.cv_Lx = c.cv_Lx;
-    const int level = lut->byte.am != -1 ? 3 : p.act == 2 ? 2 : (p.zsum || p.chain.buf ? 1 : 0);
+    p.edge_rows = p.edge_cols = 0;
+    if (p.zsum && c.cv_H >= q.kh - 1 && c.cv_W >= q.kw - 1) {       // border terms by class: where they fit behind the group offsets
+        const long long rows = 2 * q.kh - 1, cols = 2 * q.kw - 1;
+        if (rows * cols * adapt::BYTE_TILE + 4LL * q.steps + 8 <= adapt::BYTE_GOFF) { p.edge_rows = (int)rows; p.edge_cols = (int)cols; }
+    }
+    const int level = lut->byte.am != -1 ? 4 : p.act == 2 ? 3 : (p.zsum ? 2 : (p.chain.buf ? 1 : 0));
     if (p.ksplit > 1 && !partial) return fail(ADAPT_ERR_HIP, "byte path: no room for partial sums");
     const int n_phases = (int)c.xt_off.size();
     const size_t tables = (size_t)q.n_tiles * q.steps;          // of one phase

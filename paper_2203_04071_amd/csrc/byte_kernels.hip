@@ -7,7 +7,8 @@ namespace {
 
 template <int DOPS, int R>
 void launch(const adapt::ByteParams &p, unsigned grid, int level, hipStream_t s) {
-    if (level == 3) adapt::lut_byte_kernel<DOPS, R, 3><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
+    if (level == 4) adapt::lut_byte_kernel<DOPS, R, 4><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
+    else if (level == 3) adapt::lut_byte_kernel<DOPS, R, 3><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
     else if (level == 2) adapt::lut_byte_kernel<DOPS, R, 2><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
     else if (level == 1) adapt::lut_byte_kernel<DOPS, R, 1><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
     else adapt::lut_byte_kernel<DOPS, R, 0><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);

@@ -5,7 +5,7 @@
 
 namespace adapt_api {
 
-// R = 8, 4 or 2 pixels per row slot; level 0 .. 3: see adapt::byte_epilogue
+// R = 8, 4 or 2 pixels per row slot; level 0 .. 4: see adapt::byte_epilogue
 hipError_t launch_byte(const adapt::ByteParams &p, unsigned grid, int R, int level, hipStream_t s);
 
 }  // namespace adapt_api

@@ -77,6 +77,7 @@ constexpr int BYTE_STEP = 16;               // inner indices per step
 constexpr int BYTE_TILE = 16;               // output channels per tile
 constexpr int BYTE_ROW_SLOTS = 256;         // per workgroup
 constexpr int BYTE_MAX_STEPS = 2040;        // steps of a product (room for the group offsets of a slice in LDS)
+constexpr int BYTE_GOFF = (BYTE_MAX_STEPS + 8) * 4;         // words of that room; border terms lie at its end, where they fit
 constexpr int BYTE_MAX_TILES = 1024;        // output tiles of a launch that splits the inner dimension (arrival counters)
 
 typedef uint32_t b32x4_t __attribute__((ext_vector_type(4)));
@@ -117,7 +118,14 @@ struct ByteParams {
     const int32_t *zsum;        // transposed convolution with border terms (see LinesParams)
     FastDiv cv_s;
     int cv_Ho, cv_Wo, cv_H, cv_W, cv_kh, cv_kw, cv_pad, cv_Ly, cv_Lx;
+    int edge_rows, edge_cols;   // classes of border positions whose terms fit LDS (see byte_edge_class), or 0
 };
+
+// Rows (columns) of a transposed convolution's output by the window taps that have no input there.  Position q of a phase, of T taps
+// and H input rows (H >= T - 1), meets tap m if 0 <= q - m < H: class 1 + q below T - 1, T + q - H from H on, 0 (none missing) between;
+// 2 T - 1 classes.
+__host__ __device__ __forceinline__ int byte_edge_class(int q, int T, int H) { return q < T - 1 ? 1 + q : (q >= H ? T + q - H : 0); }
+__host__ __device__ __forceinline__ bool byte_edge_missing(int cls, int m, int T) { return cls > 0 && (cls < T ? m > cls - 1 : m <= cls - T); }
 
 // Flat channel group f of the inner dimension -> (tap, channel group of that tap).  Whole steps first, the taps of one
 // block of 16 channels one after the other (a workgroup then re-reads the same activation lines, shifted, in consecutive
@@ -247,13 +255,15 @@ __device__ __forceinline__ bool byte_join_slices(const ByteParams &p, bi32x4_t (
 }
 
 // What becomes of the finished sums of a lane: channels cb .. cb + 3 of its R pixels.
-// LEVEL 0: rescaling, bias, residual, ReLU.  1: also border terms of a transposed convolution and the next layer's copy.
-// 2: also tanh (16 or 32 inlined copies of it: an instantiation of its own).  3: the same in the kernel for tables whose
-// exact product drops low bits of the activations.
-template <int R, int LEVEL, int NACC>
+// LEVEL 0: rescaling, bias, residual, ReLU.  1: also the next layer's copy.  2: also border terms of a transposed convolution (an
+// instantiation of its own: its code costs the ordinary chained layers 0.2 us a launch).  3: also tanh (16 or 32 inlined copies of it).
+// 4: the same in the kernel for tables whose exact product drops low bits of the activations.
+// edge: the border terms of the tile's channels by class of the position, four words of 16 bytes each, in LDS (or nullptr).
+// NARROW: the lane holds R / 4 pixels of the slot, from pixel `first` on (channels 0 .. 3 of the tile), instead of all.
+template <int R, int LEVEL, bool NARROW, int NACC>
 __device__ __forceinline__ void byte_epilogue(const ByteParams &p, const bi32x4_t (&acc)[NACC], const float (&sc)[4], const float (&bi)[4], int mt, int rs,
-                                              int ph, int cb) {
-    constexpr int V = R < 4 ? R : 4, NRUN = R / V;
+                                              int ph, int cb, const uint4 *edge, int first) {
+    constexpr int V = NARROW ? R / 4 : (R < 4 ? R : 4), NRUN = NARROW ? 1 : R / V;
     const int nch = min(4, p.N - cb);
     const int oy0 = pick4(p.oy0, ph), ox0 = pick4(p.ox0, ph);
     const int px = p.linear ? p.N : p.out_step;             // elements between consecutive pixels of a run,
@@ -261,7 +271,8 @@ __device__ __forceinline__ void byte_epilogue(const ByteParams &p, const bi32x4_
 #pragma unroll
     for (int run = 0; run < NRUN; ++run) {
         int img, a, b;
-        if (!byte_run_pos<R>(p, mt, rs, run, img, a, b)) continue;
+        if (!byte_run_pos<R>(p, mt, rs, NARROW ? first >> 2 : run, img, a, b)) continue;
+        if (NARROW) b += first & 3;
         const int oy = oy0 + a * p.out_step, ox = ox0 + b * p.out_step;
         const int nv = min(V, p.Wo - b);            // pixels of the run that exist
         const bool whole = nv == V && nch == 4;
@@ -274,8 +285,18 @@ __device__ __forceinline__ void byte_epilogue(const ByteParams &p, const bi32x4_
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int i = 0; i < V; ++i) v[r][i] = (uint32_t)acc[run * V + i][r] + (uint32_t)p.corr;
-        if (LEVEL >= 1 && p.zsum && (oy < p.cv_Ly || oy >= p.cv_Ho - p.cv_Ly || ox < p.cv_Lx || ox + (V - 1) * p.out_step >= p.cv_Wo - p.cv_Lx)) {
-            for (int r = 0; r < nch; ++r) {
+        if (LEVEL >= 2 && p.zsum && (oy < p.cv_Ly || oy >= p.cv_Ho - p.cv_Ly || ox < p.cv_Lx || ox + (V - 1) * p.out_step >= p.cv_Wo - p.cv_Lx)) {
+            if (edge) {         // (class 0 holds zeros)
+                const int Ty = (p.edge_rows + 1) >> 1, Tx = (p.edge_cols + 1) >> 1;
+                const int cy = byte_edge_class((int)p.cv_s.div((uint32_t)(oy + p.cv_pad)), Ty, p.cv_H) * p.edge_cols;
+                const int qx = (int)p.cv_s.div((uint32_t)(ox + p.cv_pad));
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    // (pixels beyond the row are not stored: any class)
+                    const uint4 e = edge[(cy + min(byte_edge_class(qx + i, Tx, p.cv_W), p.edge_cols - 1)) * 4 + ((cb >> 2) & 3)];
+                    v[0][i] -= e.x; v[1][i] -= e.y; v[2][i] -= e.z; v[3][i] -= e.w;
+                }
+            } else for (int r = 0; r < nch; ++r) {
                 uint32_t extra[V];
                 convt_border_terms<V>(p, cb + r, oy, ox, extra);
 #pragma unroll
@@ -306,7 +327,7 @@ __device__ __forceinline__ void byte_epilogue(const ByteParams &p, const bi32x4_
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const float4 f = *reinterpret_cast<const float4 *>(q + r * plane);
-                        t[r][0] = f.x; t[r][1] = f.y; t[r][V - 2] = f.z; t[r][V - 1] = f.w;
+                        t[r][0] = f.x; t[r][V > 1 ? 1 : 0] = f.y; t[r][V > 2 ? V - 2 : 0] = f.z; t[r][V - 1] = f.w;
                     }
                 } else {
 #pragma unroll
@@ -324,7 +345,7 @@ __device__ __forceinline__ void byte_epilogue(const ByteParams &p, const bi32x4_
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
                     for (int i = 0; i < V; ++i) y[r][i] = y[r][i] > 0.0f ? y[r][i] : 0.0f;
-            } else if (LEVEL >= 2 && p.act == 2) {
+            } else if (LEVEL >= 3 && p.act == 2) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -350,8 +371,9 @@ __device__ __forceinline__ void byte_epilogue(const ByteParams &p, const bi32x4_
         if (vec && al) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                if (V == 4) *reinterpret_cast<uint4 *>(o + r * plane) = make_uint4(v[r][0], v[r][1], v[r][V - 2], v[r][V - 1]);
-                else *reinterpret_cast<uint2 *>(o + r * plane) = make_uint2(v[r][0], v[r][1]);
+                if (V == 4) *reinterpret_cast<uint4 *>(o + r * plane) = make_uint4(v[r][0], v[r][V > 1 ? 1 : 0], v[r][V > 2 ? V - 2 : 0], v[r][V - 1]);
+                else if (V == 2) *reinterpret_cast<uint2 *>(o + r * plane) = make_uint2(v[r][0], v[r][V - 1]);
+                else o[r * plane] = (int32_t)v[r][0];
             }
         } else if (vec_ch && (reinterpret_cast<uintptr_t>(p.out) & 15u) == 0) {
 #pragma unroll
@@ -381,7 +403,7 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     constexpr int NACC = R < 4 ? 4 : R;     // accumulators: with two pixels, two each (reads t and t + 1 do not depend on each other)
     // 160 KB; the alignment puts the buffers at multiples of 64 KB, which the address arithmetic needs
     __shared__ __attribute__((aligned(BYTE_BUF))) uint4 tbl[2 * (BYTE_BUF / 16)];
-    __shared__ uint32_t goff[(BYTE_MAX_STEPS + 8) * 4];
+    __shared__ __attribute__((aligned(16))) uint32_t goff[BYTE_GOFF];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -521,7 +543,7 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
         bi32x2_t b;
         b.x = (int)(bit3 ? s[1] : s[0]);
         b.y = (int)(bit3 ? s[0] : s[1]);
-        if constexpr (LEVEL == 3) {
+        if constexpr (LEVEL == 4) {
             b.x &= (int)p.amask;
             b.y &= (int)p.amask;
         }
@@ -612,6 +634,24 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     };
     using std::integral_constant;
 
+    // Border terms of the tile's 16 channels by class of the position: what the taps without an input there have added.  Read one by one
+    // in the epilogue, a lane's terms were up to 32 loads behind each other: 28000 - 44000 clocks of a workgroup with short
+    // rows.  (Their loads travel beside the first table's copy.)
+    if (LEVEL >= 2 && p.edge_cols) {
+        const int ec = p.edge_cols, Ty = (p.edge_rows + 1) >> 1, Tx = (ec + 1) >> 1, st = (int)p.cv_s.d;
+        const int ry = (int)((uint32_t)(pick4(p.oy0, ph) + p.cv_pad) - p.cv_s.div((uint32_t)(pick4(p.oy0, ph) + p.cv_pad)) * p.cv_s.d);
+        const int rx = (int)((uint32_t)(pick4(p.ox0, ph) + p.cv_pad) - p.cv_s.div((uint32_t)(pick4(p.ox0, ph) + p.cv_pad)) * p.cv_s.d);
+        for (int i = tid; i < p.edge_rows * ec * BYTE_TILE; i += BYTE_THREADS) {
+            const int cls = i / BYTE_TILE, cy = cls / ec, cx = cls - cy * ec;
+            const int32_t *const z = p.zsum + (size_t)min(nt * BYTE_TILE + i % BYTE_TILE, p.N - 1) * p.cv_kh * p.cv_kw;
+            uint32_t sum = 0;
+            for (int m = 0; m < Ty; ++m)
+                for (int n = 0; n < Tx; ++n)
+                    if (byte_edge_missing(cy, m, Ty) || byte_edge_missing(cx, n, Tx)) sum += (uint32_t)z[(ry + st * m) * p.cv_kw + rx + st * n];
+            goff[BYTE_GOFF - p.edge_rows * ec * BYTE_TILE + i] = sum;
+        }
+    }
+
     // prologue: offsets, table and activations of the first step; DEEP: the next two tables are on their way
     {
         const uint32_t off = group_off(s_begin * 4 + g);
@@ -695,7 +735,36 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
         for (int r = 0; r < 4; ++r) bi[r] = pe.bias[min(cb + r, pe.N - 1)];
     }
     if (pe.ksplit > 1 && !byte_join_slices<R>(pe, acc, goff, tid, (ph * pe.m_tiles + mt) * pe.n_tiles + nt, ks, live)) return;
-    if (cb < pe.N) byte_epilogue<R, LEVEL>(pe, acc, sc, bi, mt, rs, ph, cb);
+    const uint4 *const edge = LEVEL >= 2 && pe.edge_cols ? reinterpret_cast<const uint4 *>(goff + BYTE_GOFF - pe.edge_rows * pe.edge_cols * BYTE_TILE) : nullptr;
+    // At most four channels in the tile: a quarter of the lanes hold all of it.  With tanh (60 instructions a value) every lane takes a
+    // quarter of its column's pixels instead, through the LDS of the tables: 3 channels of 64 x 64, 33000 -> 8000 clocks.
+    if constexpr (LEVEL == 3 && R >= 4) {
+        if (pe.N - nt * BYTE_TILE <= 4) {
+            constexpr int P = R / 4;
+            if (!live) return;
+            uint4 *const col = tbl + rs * R;
+            if (q == 0) {
+#pragma unroll
+                for (int i = 0; i < R; ++i) col[i] = make_uint4((uint32_t)acc[i].x, (uint32_t)acc[i].y, (uint32_t)acc[i].z, (uint32_t)acc[i].w);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");        // (written and read by the same wave)
+            bi32x4_t mine[P];
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                const uint4 t = col[q * P + i];
+                mine[i] = bi32x4_t{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
+            }
+            float sc0[4] = {pe.scale, pe.scale, pe.scale, pe.scale}, bi0[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (pe.scales) sc0[r] = pe.scales[min(nt * BYTE_TILE + r, pe.N - 1)];
+                if (pe.bias) bi0[r] = pe.bias[min(nt * BYTE_TILE + r, pe.N - 1)];
+            }
+            byte_epilogue<R, LEVEL, true>(pe, mine, sc0, bi0, mt, rs, ph, nt * BYTE_TILE, edge, q * P);
+            return;
+        }
+    }
+    if (cb < pe.N) byte_epilogue<R, LEVEL, false>(pe, acc, sc, bi, mt, rs, ph, cb, edge, 0);
 }
 
 // ------------------------------------------------------------------------------------------------ packing

@@ -298,6 +298,29 @@ def test_fused_layers_on_every_form(B, bits, kind, act):
         assert bits_equal(host(got), finish(acc, s_out, bias, None, act)), (k, st, pad)
 
 
+@pytest.mark.parametrize("bits,kind", [(8, "product"), (7, "product"), (8, "dropped")])
+@pytest.mark.parametrize("act", [0, 2])
+@pytest.mark.parametrize("case", [
+    # N, Cin, H, W, Cout, k, stride, padding
+    (600, 3, 16, 16, 3, 4, 2, 1),           # at most four channels of a tile, many pixels per row slot
+    (40, 5, 9, 13, 20, 4, 2, 0),            # the same in the last tile, runs that end inside a row
+    (60, 4, 12, 10, 4, 6, 2, 2),            # three taps: 25 classes of border positions
+    (2, 6, 1, 9, 7, 6, 2, 0),               # fewer rows than taps: no classes
+    (3, 2, 1, 2, 5, 4, 2, 1),               # every position at a border
+    (2, 3, 5, 4, 6, 24, 2, 11)])            # more classes than LDS has room for
+def test_border_terms_and_narrow_tiles_of_transposed_layers(B, bits, kind, act, case):
+    N, Cin, H, W, Cout, k, st, pad = case
+    rng = np.random.default_rng(bits + act + sum(case))
+    t = table(kind, bits, rng)
+    x, w = rng.standard_normal((N, Cin, H, W)).astype(np.float32), wl.random_i8(rng, (Cin, Cout, k, k), bits)
+    s_x, s_out = np.float32(0.02), np.float32(2e-4)
+    q, bias = orc.quantize(x, s_x, bits), rng.standard_normal(Cout).astype(np.float32)
+    acc = orc.approx_conv_transpose2d(t, bits, q, w, st, pad, threads=4)
+    pw = B.adapt_weights_pack_conv_transpose2d(B.Lut(t, bits), dev(w), st)
+    assert (host(B.adapt_approx_conv_transpose2d_packed(pw, dev(q), pad)) == acc).all()
+    assert bits_equal(host(B.adapt_conv_transpose2d_layer_f32(pw, dev(x), s_x, s_out, pad, dev(bias), act)), finish(acc, s_out, bias, None, act))
+
+
 @pytest.mark.parametrize("bits,kind", FORMS)
 @pytest.mark.parametrize("first", ["conv", "transposed", "depthwise", "grouped"])
 def test_chains_between_forms(B, bits, kind, first):
