@@ -60,7 +60,7 @@ struct Workspace {
     size_t part_bytes = 0, copy_bytes = 0;
     long long part_rows = 0;
     void *copy() const { return mem ? static_cast<char *>(mem) + part_bytes : nullptr; }
-    bool holds(size_t copy, long long rows) const { return mem && copy_bytes >= copy && part_rows >= rows; }
+    bool holds(size_t copy, long long rows, size_t part = 0) const { return mem && copy_bytes >= copy && part_rows >= rows && part_bytes >= part; }
 };
 
 // copy_bytes at *copy and part_bytes at *part for a product of `rows` rows; reserve(): the bytes of partial sums that products of up to
@@ -72,12 +72,13 @@ inline int ws_get(Workspace *cache, size_t copy_bytes, size_t part_bytes, long l
         *part = part_bytes ? reinterpret_cast<int32_t *>(static_cast<char *>(*copy) + copy_bytes) : nullptr;
         return ADAPT_OK;
     }
-    if (!cache->holds(copy_bytes, rows)) {
+    if (!cache->holds(copy_bytes, rows, part_bytes)) {
         Workspace w = *cache;
-        if (rows > w.part_rows) {
-            const size_t bytes = (reserve() + 255) / 256 * 256;
+        if (rows > w.part_rows || part_bytes > w.part_bytes) {      // (what the call itself needs in any case)
+            size_t bytes = reserve();
+            bytes = ((part_bytes > bytes ? part_bytes : bytes) + 255) / 256 * 256;
             w.part_bytes = bytes > w.part_bytes ? bytes : w.part_bytes;
-            w.part_rows = rows;
+            w.part_rows = rows > w.part_rows ? rows : w.part_rows;
         }
         w.copy_bytes = copy_bytes > w.copy_bytes ? copy_bytes : w.copy_bytes;
         if (!w.mem || w.part_bytes > cache->part_bytes || w.copy_bytes > cache->copy_bytes) {

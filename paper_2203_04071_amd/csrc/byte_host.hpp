@@ -192,9 +192,11 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
             const int f = first + (i < p.phases ? i : 0);
             p.xt_off[i] = c.xt_off[f]; p.oy0[i] = c.oy0[f]; p.ox0[i] = c.ox0[f];
         }
-        const long long grid = (long long)p.m_tiles * q.n_tiles * p.phases * p.ksplit;
+        long long grid = (long long)p.m_tiles * q.n_tiles * p.phases * p.ksplit;
+        p.units = byte_by_units(q.n_tiles, p.m_tiles, p.phases, p.ksplit, device_cus()) ? q.n_tiles * p.ksplit : 0;
         if (grid > 0x7fffffffLL) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: grid too large");
         if (p.ksplit > 1 && grid / p.ksplit > adapt::BYTE_MAX_TILES) return fail(ADAPT_ERR_HIP, "byte path: more tiles than arrival counters");
+        if (p.units) grid = (long long)(p.units + 7) / 8 * 8 * p.m_tiles;
         HIP_TRY(launch_byte(p, (unsigned)grid, R, level, s));
     }
     return ADAPT_OK;
@@ -265,7 +267,7 @@ int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
 template <typename Copy>
 int byte_input(size_t copy_bytes, const BytePartials &sums, Workspace *ws, bool input_ready, hipStream_t s, unsigned char **mem, int32_t **partial, Copy &&copy) {
     if (input_ready) {
-        if (!ws || !ws->holds(copy_bytes, sums.rows))
+        if (!ws || !ws->holds(copy_bytes, sums.rows, sums.bytes))
             return fail(ADAPT_ERR_INVALID_ARGUMENT, "chained layer: the input buffer was not prepared for this geometry");
         *mem = static_cast<unsigned char *>(ws->copy());
         *partial = static_cast<int32_t *>(ws->mem);

@@ -29,10 +29,20 @@ inline int byte_last_slice(int steps, int ksplit) { return steps - (int)((long l
 // Estimated clocks of a launch, fitted to measured ones (3 x 3, 64 -> 64 channels, 32 images of 32 x 32, and 64 x 64 pixels of
 // one image; one MI355X).  Per step of a workgroup 432 R for the reads and the matrix instructions behind them, and the part
 // of the copies (table and activations, 54 B per clock) that these do not hide: R = 8 / 4 / 2 with 256 lines 3810 / 2420 /
-// 1950 measured, with 128 lines 3770 / 2140 / 1450, with 64 lines 3470 / 1900 / 1140.
+// 1950 measured, with 128 lines 3770 / 2140 / 1450, with 64 lines 3470 / 1900 / 1140.  (The loop has become faster since: 2930 / 2480 / 2060,
+// 2790 / 1780 / 1170, 2800 / 1270 / 950 on a part of the chip, less when all of it runs.  Of 19 layers under all plans, the plans chosen
+// by these numbers are the best or within 4 % of it but for one, those chosen by the new ones lose up to 20 %.)
 inline long long byte_step_clocks(int R, int copy_lines) {
     const double fill = (copy_lines * 256.0 + R * 4096.0) / 54.0;
     return 432LL * R + (long long)(fill * (R == 8 ? 0.225 : (R == 4 ? 0.45 : 0.72)));
+}
+
+// Whether the workgroups of a launch go to the XCDs by units (see lut_byte_kernel): where every XCD then gets as few workgroups as it would
+// get otherwise, and where the row tiles of a channel tile do not share an XCD anyway
+inline bool byte_by_units(int n_tiles, int m_tiles, int phases, int ksplit, int cu) {
+    if (phases != 1 || m_tiles == 1 || n_tiles % 8 == 0 || 8 % n_tiles == 0 || cu % 8 != 0) return false;
+    const long long units = (long long)n_tiles * ksplit, per_xcd = (units + 7) / 8 * m_tiles, wgs = units * m_tiles;
+    return (per_xcd + cu / 8 - 1) / (cu / 8) <= (wgs + cu - 1) / cu && per_xcd * 8 <= 0x7fffffffLL;
 }
 
 inline long long byte_plan_clocks(const BytePlanIn &in, int R, int ksplit) {

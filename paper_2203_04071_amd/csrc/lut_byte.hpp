@@ -96,6 +96,7 @@ struct ByteParams {
     int Mv;                     // virtual rows
     int N, n_tiles, m_tiles, phases;
     int cg, taps, kw, steps;    // channel groups per tap, taps, filter width, steps of the whole inner dimension
+    int units;                  // > 0: workgroups by units, see the kernel
     int ksplit, even;           // slices of the inner dimension: slice i ends at step (i + 1) even / ksplit, the last one at the end
     int bits, copy_lines;       // copy_lines: 2^bits, or half of it where all activations are >= 0
     int Wo, Wv;                 // output width (per phase), the same rounded up to runs
@@ -415,16 +416,26 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     // a tile's tables stay in one L2, with 4 / 2 / 1 tiles every 2nd / 4th / 8th workgroup of a tile shares an XCD
     // (xcd_span).  The phases of a transposed convolution vary fastest among the workgroups of one XCD, so that the pixels
     // they interleave meet in its L2.
+    // By units: a unit is the row tiles that read the same tables (a slice of a channel tile); unit u runs on XCD u % 8, its
+    // row tiles one behind the other.  Elsewhere (13 tiles, say) every XCD fetches most tables: 1111 rows, K = 777, N = 999, 8 bits:
+    // 75 -> 50 us; 100 -> 200 channels, stride 2, 27 -> 14 pixels wide, 50 images: 79 -> 64 us.
     const int wg = (int)p.d_ntiles.div(blockIdx.x);
-    const int nt = blockIdx.x - wg * p.n_tiles;
+    int nt = blockIdx.x - wg * p.n_tiles;
     int xcd_span = (p.n_tiles < 8 && 8 % p.n_tiles == 0) ? 8 / p.n_tiles : 1;
     if ((p.m_tiles * p.ksplit) % xcd_span) xcd_span = 1;
     const int wx_ = wg & (xcd_span - 1), wy = wg / xcd_span;
     const int wz = (int)p.d_phases.div((uint32_t)wy);
-    const int ph = wy - wz * p.phases;
+    int ph = wy - wz * p.phases;
     const int rest = wz * xcd_span + wx_;
-    const int ks = (int)p.d_mtiles.div((uint32_t)rest);
-    const int mt = rest - ks * p.m_tiles;
+    int ks = (int)p.d_mtiles.div((uint32_t)rest), mt = rest - ks * p.m_tiles;
+    if (p.units > 0) {
+        const int local = (int)(blockIdx.x >> 3), ul = (int)p.d_mtiles.div((uint32_t)local), unit = ul * 8 + (int)(blockIdx.x & 7);
+        if (unit >= p.units) return;
+        mt = local - ul * p.m_tiles;
+        ks = (int)p.d_ntiles.div((uint32_t)unit);
+        nt = unit - ks * p.n_tiles;
+        ph = 0;
+    }
     const int8_t *const xt = p.xt + pick4(p.xt_off, ph);
     const uint32_t table_bytes = (uint32_t)BYTE_LINE << p.bits;             // distance between the tables of two steps
     const uint32_t copy_bytes = (uint32_t)p.copy_lines * BYTE_LINE;

@@ -174,6 +174,19 @@ def test_linear_layers_below_4096_rows(B, M, K, N, bits):
     assert np.array_equal(host(y).view(np.uint32), orc.dequant(orc.approx_linear(t, bits, q, w), np.float32(0.5), M, N, 1).reshape(M, N).view(np.uint32))
 
 
+@pytest.mark.parametrize("bits", [8, 7])
+@pytest.mark.parametrize("images,cin,cout,hw,stride", [(50, 20, 200, 27, 2), (24, 36, 140, 20, 1), (40, 33, 72, 14, 1)])
+def test_channel_tiles_that_no_power_of_two_divides(B, bits, images, cin, cout, hw, stride):
+    """13, 9 and 5 channel tiles with several row tiles: workgroups are dealt to the XCDs by the tables they read, some have none."""
+    rng = np.random.default_rng(bits + cout)
+    t = table("product", bits, rng)
+    x, w = wl.random_i8(rng, (images, cin, hw, hw), bits), wl.random_i8(rng, (cout, cin, 3, 3), bits)
+    pw = B.adapt_weights_pack_conv2d(B.Lut(t, bits), dev(w))
+    want = orc.approx_conv2d(t, bits, x, w, (stride, stride), (1, 1), threads=4)
+    for _ in range(2):
+        assert (host(B.adapt_approx_conv2d_packed(pw, dev(x), (stride, stride), (1, 1))) == want).all()
+
+
 @pytest.mark.parametrize("K", [32640, 32641])
 def test_longest_inner_dimension(B, K):
     """The last length whose group offsets fit, and the first that takes the other tables."""
