@@ -61,8 +61,38 @@ void launch_ste_gemm(const adapt::SteParams &p_in, bool a_t, bool aligned, hipSt
         const size_t n = (size_t)p.I * (size_t)p.J;
         const size_t blocks = (n + 255) / 256;
         adapt::ste_reduce_masked_kernel<<<(unsigned)(blocks < 4096 ? blocks : 4096), 256, 0, s>>>(partials, parts, n, p_in.o, p_in.so, p_in.Q,
-                                                                                                  p_in.c, p.g.kh * p.g.kw, p.g.C, (int)p.g.dCp.d, tap0, all_taps);
+                                                                                                  p_in.c, p.g.kh * p.g.kw, p.g.C, (int)p.g.dCp.d, tap0, all_taps, 1.0f);
     }
+}
+
+// Weight gradient of a convolution on bf16 instructions (ste_dw16_kernel): partial sums as launch_ste_gemm makes them, 64 x 64 outputs
+// per workgroup and two workgroups per compute unit where the contraction is long enough.  o, so: mask; scale: of the sums.
+void launch_ste_dw16(const adapt::SteDwParams &p_in, const float *o, float so, float Q, float scale, float *dw, hipStream_t s, float *partials, int tap0, int all_taps) {
+    adapt::SteDwParams p = p_in;
+    const int cus = device_cus(), chunks = (p.R + adapt::STE_TR - 1) / adapt::STE_TR;
+    dim3 grid((unsigned)((p.J + 63) / 64), (unsigned)((p.I + 63) / 64), 1);
+    const long long tiles = (long long)grid.x * grid.y;
+    p.cps = chunks;
+    if (tiles < cus && chunks >= 8) {
+        int want = (int)((2 * cus + tiles - 1) / tiles);
+        if (want > chunks / 4) want = chunks / 4;
+        if (want >= 2) {
+            p.cps = (chunks + want - 1) / want;
+            grid.z = (unsigned)((chunks + p.cps - 1) / p.cps);
+        }
+    }
+    p.c = partials;
+    adapt::ste_dw16_kernel<<<grid, adapt::STE_THREADS, 0, s>>>(p);
+    const size_t n = (size_t)p.I * (size_t)p.J, blocks = (n + 255) / 256;
+    adapt::ste_reduce_masked_kernel<<<(unsigned)(blocks < 4096 ? blocks : 4096), 256, 0, s>>>(partials, (int)grid.z, n, o, so, Q, dw, p.g.kh * p.g.kw, p.g.C,
+                                                                                              (int)p.g.dCp.d, tap0, all_taps, scale);
+}
+
+// s = pow2 * rest with rest in [1, 2)
+void split_scale(float s, float *pow2, float *rest) {
+    int e;
+    *rest = 2.0f * frexpf(s, &e);
+    *pow2 = ldexpf(1.0f, e - 1);
 }
 
 }  // namespace
@@ -118,7 +148,8 @@ constexpr long long MAX_COLS = 0x3fffff00;         // of one product: 31-bit col
 struct SteConvPlan {
     adapt::SteConvGeo g;
     long long M, K;
-    bool direct;                // stride 1: the input gradient is one product (ste_dx_kernel)
+    bool direct;                // stride 1: the input gradient is one product (ste_dx_kernel, ste_dx16_kernel)
+    bool padded_weights;        // there is room for the weights as ste_dx16_kernel reads them
     int dw_rows;                // filter rows per product of the weight gradient: all, unless there are more than MAX_COLS columns (tap, channel rounded up to 4)
     size_t rows_bytes, col_bytes, wp_bytes, xq_bytes, part_bytes, total;
 };
@@ -146,7 +177,9 @@ int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int k
     g.dHoWo = fast_div((uint32_t)(Ho * Wo)); g.dC = fast_div((uint32_t)Cin); g.dW = fast_div((uint32_t)W); g.dHW = fast_div((uint32_t)(H * W));
     g.dsh = fast_div((uint32_t)stride_h); g.dsw = fast_div((uint32_t)stride_w);
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-    pl->rows_bytes = up((size_t)pl->M * Cout * sizeof(float));
+    // rows of the gradient: fp32, or three bf16 pieces of whole groups of four channels
+    const size_t row16 = (size_t)(((long long)Cout + 3) / 4 * 4) * 6, row32 = (size_t)Cout * sizeof(float);
+    pl->rows_bytes = up((size_t)pl->M * (want_dw && row16 > row32 ? row16 : row32));
     const long long row_cols = (long long)kw * Cp;
     if (want_dw && row_cols > 0x7fffff00LL)
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: a filter row is limited to 2^31 - 256 weights (channels rounded up to 4)", who);
@@ -157,7 +190,11 @@ int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int k
     pl->xq_bytes = want_dw ? up((size_t)N * H * W * (size_t)Cp * sizeof(float)) : 0;
     const size_t dw_cols = (size_t)pl->dw_rows * (size_t)row_cols;
     pl->part_bytes = up((want_dw && Cout * dw_cols > STE_PARTIAL_FLOATS ? Cout * dw_cols : STE_PARTIAL_FLOATS) * sizeof(float));
-    pl->wp_bytes = want_dx ? up((size_t)Cout * cols * sizeof(float)) : 0;
+    // weights for the input gradient: fp32 [taps][Cout][Cp], or bf16 with Cout rounded up to 32 and the channels to 64
+    const size_t wp16 = pl->direct ? (size_t)kh * kw * (((size_t)Cout + 31) / 32 * 32) * (((size_t)Cin + 63) / 64 * 64) * 2 : 0, wp32 = (size_t)Cout * cols * sizeof(float);
+    // (the padding of narrow layers is not worth gigabytes for filters of millions of taps)
+    pl->padded_weights = pl->direct && (wp16 <= wp32 * 4 || wp16 <= ((size_t)64 << 20));
+    pl->wp_bytes = want_dx ? up(pl->padded_weights && wp16 > wp32 ? wp16 : wp32) : 0;
     pl->total = pl->rows_bytes + pl->col_bytes + pl->wp_bytes + pl->xq_bytes + pl->part_bytes;
     return ADAPT_OK;
 }
@@ -221,11 +258,41 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
         const dim3 grid((unsigned)(blocks < (1 << 22) ? blocks : (1 << 22)), (unsigned)((ld + 63) / 64), (unsigned)(N < 65535 ? N : 65535));
         adapt::ste_channels_last_kernel<<<grid, 256, 0, s>>>(src, dst, N, C, pixels, ld, scale, Q);
     };
-    if (dw_dev || (dx_dev && !pl.direct)) {
+    // Codes of up to 9 bits are bf16 numbers: both products on bf16 instructions (a scale whose power of two is not a normal number, or
+    // leaves none to the codes, takes the fp32 form).  64 -> 64 channels, 3 x 3, 32 images of 32 x 32: weight gradient 43 -> 28 us,
+    // input gradient 42 -> 28 us, with errors against 64 bits of 0.4 to 0.9 of the fp32 form (2-norms of 4e-8 to 2e-7 over 14 layers).
+    const bool codes16 = bits <= 9;
+    const bool dw16 = codes16 && s_x > 1e-30f && s_x < 1e30f, dx16 = codes16 && s_w > 1e-30f && s_w < 1e30f;
+    if (dw_dev && dw16) {
+        const int lda = (Cout + 3) / 4 * 4;
+        const size_t plane = (size_t)M * lda;
+        uint16_t *const pieces = reinterpret_cast<uint16_t *>(rows), *const codes = reinterpret_cast<uint16_t *>(xq);
+        float pow2, rest;
+        split_scale(s_x, &pow2, &rest);
+        auto copy16 = [&](const float *src, uint16_t *dst, int C, int pixels, int ld, float scale, float factor) {
+            const long long blocks = (pixels + 31LL) / 32;
+            const dim3 grid((unsigned)(blocks < (1 << 22) ? blocks : (1 << 22)), (unsigned)((ld + 63) / 64), (unsigned)(N < 65535 ? N : 65535));
+            adapt::ste_channels_last16_kernel<<<grid, 256, 0, s>>>(src, dst, N, C, pixels, ld, scale, Q, factor, plane);
+        };
+        copy16(dy_dev, pieces, Cout, P, lda, 0.0f, 1.0f);
+        HIP_TRY(hipGetLastError());
+        copy16(x_dev, codes, Cin, HW, Cp, s_x, pow2);
+        HIP_TRY(hipGetLastError());
+        adapt::SteDwParams p{};
+        p.a = pieces; p.b = codes; p.plane = plane; p.I = Cout; p.R = M; p.lda = lda; p.g = g;
+        for (int ky = 0; ky < kh; ky += pl.dw_rows) {
+            p.g.kh = kh - ky < pl.dw_rows ? kh - ky : pl.dw_rows;
+            p.g.ph = g.ph - ky * g.dh;
+            p.J = p.g.kh * kw * Cp;
+            launch_ste_dw16(p, w_dev, s_w, Q, rest, dw_dev, s, partials, ky * kw, kh * kw);
+            HIP_TRY(hipGetLastError());
+        }
+    }
+    if ((dw_dev && !dw16) || (dx_dev && !pl.direct)) {
         channels_last(dy_dev, rows, Cout, P, Cout, 0.0f);
         HIP_TRY(hipGetLastError());
     }
-    if (dw_dev) {           // dw [Cout][K] = inside(w) * rows^T [Cout][M] . fq(col(x)) [M][K], col(x) read from the copy xq
+    if (dw_dev && !dw16) {  // dw [Cout][K] = inside(w) * rows^T [Cout][M] . fq(col(x)) [M][K], col(x) read from the copy xq
         channels_last(x_dev, xq, Cin, HW, Cp, s_x);
         HIP_TRY(hipGetLastError());
         adapt::SteParams p{};
@@ -241,7 +308,19 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
             HIP_TRY(hipGetLastError());
         }
     }
-    if (dx_dev && pl.direct) {
+    if (dx_dev && pl.direct && dx16 && pl.padded_weights) {
+        float pow2, rest;
+        split_scale(s_w, &pow2, &rest);
+        const int Op = (Cout + 31) / 32 * 32, Cq = (Cin + 63) / 64 * 64;
+        uint4 *const wq = reinterpret_cast<uint4 *>(wp);
+        adapt::ste_weights16_kernel<<<ew_grid((size_t)kh * kw * (Op / 8) * Cq), 256, 0, s>>>(w_dev, wq, Cout, Cin, Op, Cq, kh * kw, s_w, Q, pow2);
+        HIP_TRY(hipGetLastError());
+        adapt::SteDx16Params p{};
+        p.dy = dy_dev; p.x = x_dev; p.wq = wq; p.dx = dx_dev;
+        p.pixels = N * HW; p.og = Op / 8; p.Cq = Cq; p.so = s_x; p.Q = Q; p.scale = rest; p.g = g;
+        adapt::ste_dx16_kernel<<<dim3((unsigned)((p.pixels + 63) / 64), (unsigned)((Cin + 63) / 64)), adapt::STE_THREADS, 0, s>>>(p);
+        HIP_TRY(hipGetLastError());
+    } else if (dx_dev && pl.direct) {
         const size_t wq_n = (size_t)kh * kw * Cout * Cp;
         adapt::ste_weights_by_tap_kernel<<<ew_grid(wq_n), 256, 0, s>>>(w_dev, wp, Cout, Cin, Cp, kh * kw, s_w, Q);
         HIP_TRY(hipGetLastError());
@@ -268,7 +347,7 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
         const int Z = N < 16 ? N : 16;
         if ((size_t)Z * Cout <= STE_PARTIAL_FLOATS && Z > 1) {
             adapt::ste_bias_grad_nchw_kernel<<<dim3((unsigned)Cout, (unsigned)Z), 256, 0, s>>>(dy_dev, partials, N, Cout, P);
-            adapt::ste_reduce_masked_kernel<<<(unsigned)((Cout + 255) / 256), 256, 0, s>>>(partials, Z, (size_t)Cout, nullptr, 1.0f, Q, db_dev, 0, 0, 0, 0, 0);
+            adapt::ste_reduce_masked_kernel<<<(unsigned)((Cout + 255) / 256), 256, 0, s>>>(partials, Z, (size_t)Cout, nullptr, 1.0f, Q, db_dev, 0, 0, 0, 0, 0, 1.0f);
         } else {
             adapt::ste_bias_grad_nchw_kernel<<<dim3((unsigned)Cout, 1), 256, 0, s>>>(dy_dev, db_dev, N, Cout, P);
         }

@@ -59,6 +59,15 @@ __device__ __forceinline__ float ste_fake_quant(float x, float s, float Q) {
     return r * s;
 }
 
+// the same code times a factor of its own
+__device__ __forceinline__ float ste_fake_quant(float x, float s, float Q, float factor) {
+    float r = rintf(x / s);
+    if (r != r) r = 0.0f;
+    if (r > Q) r = Q;
+    if (r < -Q) r = -Q;
+    return r * factor;
+}
+
 __device__ __forceinline__ bool ste_inside(float x, float s, float Q) { return fabsf(rintf(x / s)) <= Q; }     // NaN: false
 
 // Four consecutive elements of a row-major matrix (col a multiple of 4).  FULL: the whole tile lies inside the matrix
@@ -256,9 +265,9 @@ __global__ __launch_bounds__(STE_THREADS * KS) void ste_gemm_kernel(SteParams p)
 // contraction was split over grid z.  Eight parts are requested together (one at a time, 57 parts of 36864 took 15.5 us, the
 // latency of memory 57 times over; now 5.4 us).
 // taps > 0: the parts are rows of (tap, channel), taps x Cp columns, and c, o the weight tensor [row][C][all_taps], of which these
-// are taps tap0 .. tap0 + taps - 1.
+// are taps tap0 .. tap0 + taps - 1.  scale: of the sums.
 __global__ __launch_bounds__(256) void ste_reduce_masked_kernel(const float *__restrict__ part, int S, size_t n, const float *__restrict__ o,
-                                                                float so, float Q, float *__restrict__ c, int taps, int C, int Cp, int tap0, int all_taps) {
+                                                                float so, float Q, float *__restrict__ c, int taps, int C, int Cp, int tap0, int all_taps, float scale) {
     const size_t stride = (size_t)gridDim.x * 256;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
         float s = part[i];
@@ -278,7 +287,7 @@ __global__ __launch_bounds__(256) void ste_reduce_masked_kernel(const float *__r
             if (ch >= C) continue;
             at = (row * C + ch) * (size_t)all_taps + tap0 + tap;
         }
-        c[at] = (!o || ste_inside(o[at], so, Q)) ? s : 0.0f;
+        c[at] = (!o || ste_inside(o[at], so, Q)) ? s * scale : 0.0f;
     }
 }
 
@@ -515,6 +524,311 @@ __global__ __launch_bounds__(STE_THREADS, 2) void ste_dx_kernel(const SteDxParam
     for (int v = 0; v < 16; ++v) {
         const int c = i0 + wi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
         if (c < g.C) p.dx[((size_t)n * g.C + c) * (size_t)HW + (size_t)pin] = ste_inside(xv[v], p.so, p.Q) ? tot[v] : 0.0f;
+    }
+}
+
+// ---- the same two products on 16-bit matrix instructions ----------------------------------------------------------
+// Operands of up to 9 bits: a code is a bf16 number, so one operand of either product needs no more than that, and the gradient is
+// the sum of three bf16 numbers (24 bits).  Every product of a piece and a code is exact in fp32, sums are fp32: nothing is
+// rounded that the fp32 form does not round (there a fake-quantised value is rounded; here the sum is scaled once).  The first
+// pieces, which carry the sum, have an accumulator of their own: it is rounded once for 16 products.  Three bf16
+// instructions replace eight fp32 ones of twice their length.  A code carries the power of two of its scale, so that products have
+// the range they have in fp32; what is left of the scale, in [1, 2), multiplies the sum.
+// Error against 64 bits (2-norm of the difference over that of the result), fp32 form -> this one: weight gradient 1.8e-7 -> 1.4e-7, input
+// gradient 1.2e-7 -> 7.3e-8 (64 -> 64 channels, 3 x 3, 8 images of 32 x 32); 13 other layers likewise or better.
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+// v = the sum of the three numbers whose upper halves are p[0..2] (infinities and NaN: all of it in the first)
+__device__ __forceinline__ void ste_split(float v, uint32_t (&p)[3]) {
+    const uint32_t u = __float_as_uint(v);
+    const bool finite = fabsf(v) < __builtin_inff();
+    p[0] = v != v ? 0x7fc00000u : u & 0xffff0000u;
+    const float r = finite ? v - __uint_as_float(u & 0xffff0000u) : 0.0f;
+    p[1] = __float_as_uint(r) & 0xffff0000u;
+    p[2] = __float_as_uint(r - __uint_as_float(p[1]));
+}
+
+// upper halves of a and b as one word, a's in the lower half
+__device__ __forceinline__ uint32_t ste_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+// the code of x with scale s, times pow2, as upper half of a word (exact)
+__device__ __forceinline__ uint32_t ste_code16(float x, float s, float Q, float pow2) { return __float_as_uint(ste_fake_quant(x, s, Q, pow2)); }
+
+// src [N][C][P] -> dst [N][P][ld] bf16 (zeros in channels C .. ld - 1): codes with (s, Q) times pow2 if s > 0, else three planes of pieces,
+// `plane` elements apart.  The walk of ste_channels_last_kernel; a thread writes two channels at once (ld is a multiple of 4).
+__global__ __launch_bounds__(256) void ste_channels_last16_kernel(const float *__restrict__ src, uint16_t *__restrict__ dst, int N, int C, int P, int ld, float s, float Q,
+                                                                  float pow2, size_t plane) {
+    __shared__ float tile[64][33];
+    const int c0 = blockIdx.y * 64, tid = threadIdx.x, blocks = (int)((P + 31LL) / 32);
+    for (int n = blockIdx.z, b = blockIdx.x; n < N; b += gridDim.x) {
+        if (b >= blocks) {
+            b = (int)blockIdx.x - (int)gridDim.x;
+            n += gridDim.z;
+            continue;
+        }
+        const int p0 = b * 32;
+        const int pl = tid & 31, cl = tid >> 5;
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int c = c0 + cl + 8 * q;
+            const bool ok = c < C && p0 + pl < P;
+            const float t = src[ok ? ((size_t)n * C + c) * (size_t)P + (size_t)(p0 + pl) : 0];
+            v[q] = ok ? t : 0.0f;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) tile[cl + 8 * q][pl] = v[q];
+        __syncthreads();
+        const int wc = (tid & 31) * 2, wp = tid >> 5;
+        if (c0 + wc < ld) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int pp = wp + 8 * q;
+                if (p0 + pp < P) {
+                    const float x0 = tile[wc][pp], x1 = tile[wc + 1][pp];
+                    uint32_t *const to = reinterpret_cast<uint32_t *>(dst + ((size_t)n * P + (size_t)(p0 + pp)) * (size_t)ld + (size_t)(c0 + wc));
+                    if (s > 0.0f) {
+                        *to = ste_halves(ste_code16(x0, s, Q, pow2), ste_code16(x1, s, Q, pow2));
+                    } else {
+                        uint32_t a[3], d[3];
+                        ste_split(x0, a);
+                        ste_split(x1, d);
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) to[i * (plane / 2)] = ste_halves(a[i], d[i]);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+struct SteDwParams {
+    const uint16_t *a;          // [piece][R][lda] bf16, pieces `plane` elements apart
+    const uint16_t *b;          // channel-last copy of the image tensor, codes as bf16 [N][H][W][Cp]
+    float *c;                   // [z][I][J] partial sums
+    size_t plane;
+    int I, J, R, lda, cps;
+    SteConvGeo g;
+};
+
+// Partial sums of dy^T . col(x) (see ste_gemm_kernel with an unfolded operand): 64 x 64 outputs per workgroup, a 32 x 32 block per wave,
+// chunks of 32 contraction indices through two LDS buffers, transposed on the way in (a thread packs two rows of four columns: rows of
+// 18 words keep writes two-way and reads free of bank conflicts).
+__global__ __launch_bounds__(STE_THREADS) void ste_dw16_kernel(const SteDwParams p) {
+    constexpr int LD = 18;                                  // words of a row of 32 bf16
+    __shared__ __align__(16) uint32_t As[2][3][64][LD];     // [piece][i][r]
+    __shared__ __align__(16) uint32_t Bs[2][64][LD];        // [j][r]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+    const int wi = (wave & 1) * 32, wj = (wave >> 1) * 32;
+    const int pair = tid >> 4, c4 = (tid & 15) * 4;
+    const SteConvGeo &g = p.g;
+    // this thread's columns: of dy (clamped: what lies beyond is never stored), and the tap and channels of x
+    const int ac = min(i0 + c4, p.lda - 4);
+    const uint32_t k = (uint32_t)min(j0 + c4, p.J - 4), tap = g.dCp.div(k), ch = k - tap * g.dCp.d;
+    const int ky = (int)g.dkw.div(tap), kx = (int)tap - ky * g.kw;
+    const int offy = ky * g.dh - g.ph, offx = kx * g.dw - g.pw;
+    uint2 ra[3][2], rb[2];
+    uint32_t live[2], in[2];
+    auto fetch = [&](int r0) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int row = r0 + 2 * pair + h;
+            const uint32_t m = (uint32_t)min(row, p.R - 1);
+            live[h] = row < p.R ? ~0u : 0u;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) ra[q][h] = *reinterpret_cast<const uint2 *>(p.a + q * p.plane + (size_t)m * (size_t)p.lda + (size_t)ac);
+            const uint32_t n = g.dHoWo.div(m), pix = m - n * (uint32_t)(g.Ho * g.Wo);
+            const int oy = (int)g.dWo.div(pix), ox = (int)pix - oy * g.Wo, iy = oy * g.sh + offy, ix = ox * g.sw + offx;
+            const bool ok = iy >= 0 && iy < g.H && ix >= 0 && ix < g.W;
+            in[h] = ok ? ~0u : 0u;
+            rb[h] = *reinterpret_cast<const uint2 *>(p.b + (ok ? (((size_t)n * g.H + iy) * g.W + ix) * g.dCp.d + ch : 0));
+        }
+    };
+    // rows r and r + 1 of four columns -> the word of both of each column
+    auto put = [&](uint32_t (*to)[LD], const uint2 &e, const uint2 &o, uint32_t me, uint32_t mo) {
+        const uint32_t e0 = e.x & me, e1 = e.y & me, o0 = o.x & mo, o1 = o.y & mo;
+        to[c4 + 0][pair] = __builtin_amdgcn_perm(o0, e0, 0x05040100u);
+        to[c4 + 1][pair] = __builtin_amdgcn_perm(o0, e0, 0x07060302u);
+        to[c4 + 2][pair] = __builtin_amdgcn_perm(o1, e1, 0x05040100u);
+        to[c4 + 3][pair] = __builtin_amdgcn_perm(o1, e1, 0x07060302u);
+    };
+    auto stash = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) put(As[buf][q], ra[q][0], ra[q][1], live[0], live[1]);
+        put(Bs[buf], rb[0], rb[1], in[0], in[1]);
+    };
+    auto operand = [&](const uint32_t *row) {               // 8 bf16 of a row (8-byte aligned)
+        const uint2 lo = *reinterpret_cast<const uint2 *>(row), hi = *reinterpret_cast<const uint2 *>(row + 2);
+        return __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+    };
+    f32x16_t acc, low;              // sums of the first pieces, of the others
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = low[v] = 0.0f;
+    const int ch0 = blockIdx.z * p.cps, chunks = max(0, min((p.R + STE_TR - 1) / STE_TR, ch0 + p.cps) - ch0);
+    if (chunks > 0) {
+        fetch(ch0 * STE_TR);
+        stash(0);
+    }
+    __syncthreads();
+    for (int c = 0; c < chunks; ++c) {
+        const int cur = c & 1;
+        const bool more = c + 1 < chunks;
+        if (more) fetch((ch0 + c + 1) * STE_TR);
+        bf16x8_t a[2][3], b[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const int at = 8 * ks + 4 * (lane >> 5);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) a[ks][q] = operand(&As[cur][q][wi + (lane & 31)][at]);
+            b[ks] = operand(&Bs[cur][wj + (lane & 31)][at]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int q = 2; q >= 0; --q) (q ? low : acc) = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][q], b[ks], q ? low : acc, 0, 0, 0);
+        if (more) stash(cur ^ 1);
+        __syncthreads();
+    }
+    float *const cout = p.c + (size_t)blockIdx.z * (size_t)p.I * (size_t)p.J;
+    const int j = j0 + wj + (lane & 31);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int i = i0 + wi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        if (i < p.I && j < p.J) cout[(size_t)i * (size_t)p.J + (size_t)j] = acc[v] + low[v];
+    }
+}
+
+// w [O][C][T] -> wq [T][Op / 8][Cq][8] bf16 codes times pow2, zeros beyond O and C (Op: O rounded up to 32, Cq: C to 64)
+__global__ __launch_bounds__(256) void ste_weights16_kernel(const float *__restrict__ w, uint4 *__restrict__ wq, int O, int C, int Op, int Cq, int T, float s, float Q, float pow2) {
+    const size_t total = (size_t)T * (Op / 8) * Cq, stride = (size_t)gridDim.x * 256;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
+        const size_t t = i / ((size_t)(Op / 8) * Cq), rem = i - t * (size_t)(Op / 8) * Cq, og = rem / Cq, c = rem - og * Cq;
+        uint32_t v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const size_t o = og * 8 + q;
+            v[q] = o < (size_t)O && c < (size_t)C ? ste_code16(w[(o * C + c) * T + t], s, Q, pow2) : 0u;
+        }
+        wq[i] = make_uint4(ste_halves(v[0], v[1]), ste_halves(v[2], v[3]), ste_halves(v[4], v[5]), ste_halves(v[6], v[7]));
+    }
+}
+
+struct SteDx16Params {
+    const float *dy, *x;
+    const uint4 *wq;
+    float *dx;
+    int pixels, og, Cq;         // N H W; groups of 8 output channels per tap, channels, as wq has them
+    float so, Q, scale;
+    SteConvGeo g;
+};
+
+// ste_dx_kernel on bf16 instructions: the gradient of a chunk is split while it is staged ([piece][pixel][o], so that a lane's eight
+// output channels are one 16-byte read), the weights go from memory to registers as the instruction wants them.
+__global__ __launch_bounds__(STE_THREADS, 2) void ste_dx16_kernel(const SteDx16Params p) {
+    constexpr int LD = 20;                                  // words of a row of 32 bf16: 16-byte rows, 4 banks apart
+    __shared__ __align__(16) uint32_t Bs[2][3][64][LD];     // [piece][pixel][o]
+    const SteConvGeo &g = p.g;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+    const int wi = (wave & 1) * 32, wj = (wave >> 1) * 32;
+    const int P = g.Ho * g.Wo, HW = g.H * g.W;
+    auto decode = [&](int j, int &n, int &pin) {
+        n = (int)g.dHW.div((uint32_t)j);
+        pin = j - n * HW;
+    };
+    int sn, spin;
+    decode(min(j0 + lane, p.pixels - 1), sn, spin);
+    const int sy = (int)g.dW.div((uint32_t)spin), sx = spin - sy * g.W;
+    const float *const dyn = p.dy + (size_t)sn * g.O * (size_t)P;
+    const int cpt = p.og / 4, chunks = g.kh * g.kw * cpt;
+    int ky = 0, kx = 0, part = 0, group = 0;                // of the chunk that is fetched next
+    float rb[2][8];
+    uint4 ra[2][2];
+    uint32_t inside[2];
+    int from_o[2];
+    auto fetch = [&](float (&b)[8], uint4 (&a)[2], uint32_t &in, int &first_o) {
+        const int oy = sy + g.ph - ky * g.dh, ox = sx + g.pw - kx * g.dw, o0 = part * STE_TR + 8 * wave;
+        const bool ok = oy >= 0 && oy < g.Ho && ox >= 0 && ox < g.Wo;
+        const float *const from = dyn + (ok ? oy * g.Wo + ox : 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b[i] = from[(size_t)min(o0 + i, g.O - 1) * (size_t)P];
+        in = ok ? ~0u : 0u;
+        first_o = o0;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) a[ks] = p.wq[((size_t)group + 2 * ks + (lane >> 5)) * (size_t)p.Cq + (size_t)(i0 + wi + (lane & 31))];
+        group += 4;
+        if (++part == cpt) {
+            part = 0;
+            if (++kx == g.kw) {
+                kx = 0;
+                ++ky;
+            }
+        }
+    };
+    auto stash = [&](int buf, const float (&b)[8], uint32_t in, int first_o) {
+        uint32_t s[8][3];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ste_split(__uint_as_float(__float_as_uint(b[i]) & (first_o + i < g.O ? in : 0u)), s[i]);
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            *reinterpret_cast<uint4 *>(&Bs[buf][q][lane][4 * wave]) =
+                make_uint4(ste_halves(s[0][q], s[1][q]), ste_halves(s[2][q], s[3][q]), ste_halves(s[4][q], s[5][q]), ste_halves(s[6][q], s[7][q]));
+    };
+    f32x16_t acc, low, tot;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = low[v] = tot[v] = 0.0f;
+    int left = cpt;                 // chunks of this tap that are still to be multiplied
+    auto chunk = [&](int ch, auto set_c) {                  // see ste_dx_kernel
+        constexpr int S = decltype(set_c)::value;
+        const uint4 a0 = ra[S][0], a1 = ra[S][1];
+        if (ch + 2 < chunks) fetch(rb[S], ra[S], inside[S], from_o[S]);
+        bf16x8_t b[2][3];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) b[ks][q] = *reinterpret_cast<const bf16x8_t *>(&Bs[S][q][wj + (lane & 31)][8 * ks + 4 * (lane >> 5)]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int q = 2; q >= 0; --q)
+                (q ? low : acc) = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ks ? a1 : a0), b[ks][q], q ? low : acc, 0, 0, 0);
+        if (ch + 1 < chunks) stash(1 - S, rb[1 - S], inside[1 - S], from_o[1 - S]);
+        if (--left == 0) {
+            left = cpt;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                tot[v] += acc[v] + low[v];
+                acc[v] = low[v] = 0.0f;
+            }
+        }
+        __syncthreads();
+    };
+    fetch(rb[0], ra[0], inside[0], from_o[0]);
+    if (chunks > 1) fetch(rb[1], ra[1], inside[1], from_o[1]);
+    stash(0, rb[0], inside[0], from_o[0]);
+    __syncthreads();
+    for (int ch = 0; ch < chunks; ch += 2) {
+        chunk(ch, std::integral_constant<int, 0>{});
+        if (ch + 1 < chunks) chunk(ch + 1, std::integral_constant<int, 1>{});
+    }
+    const int j = j0 + wj + (lane & 31);
+    if (j >= p.pixels) return;
+    int n, pin;
+    decode(j, n, pin);
+    float xv[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int c = i0 + wi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        xv[v] = c < g.C ? p.x[((size_t)n * g.C + c) * (size_t)HW + (size_t)pin] : 0.0f;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int c = i0 + wi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        if (c < g.C) p.dx[((size_t)n * g.C + c) * (size_t)HW + (size_t)pin] = ste_inside(xv[v], p.so, p.Q) ? tot[v] * p.scale : 0.0f;
     }
 }
 

@@ -348,6 +348,38 @@ def test_ste_conv2d_backward_stride1_tiles(B, case):
     test_ste_conv2d_backward_matches_oracle(B, case)
 
 
+CODE_CASES = [
+    # edges of the tiles and chunks of the products on 16-bit codes, and what stays on fp32 instructions
+    (1, 64, 8, 8, 64, 3, 3, (1, 1), (1, 1), (1, 1), 9),            # whole tiles, the widest codes
+    (1, 64, 8, 8, 64, 3, 3, (1, 1), (1, 1), (1, 1), 10),           # one bit too many
+    (3, 4, 7, 5, 31, 3, 3, (1, 1), (1, 1), (1, 1), 8),             # chunks of output channels and of pixels less one
+    (2, 66, 9, 7, 65, 1, 1, (1, 1), (0, 0), (1, 1), 8),            # one past the tiles
+    (5, 3, 11, 6, 1, 2, 5, (2, 1), (0, 3), (1, 1), 5),             # one output channel; vertical stride: dw alone on codes
+    (40, 9, 20, 20, 6, 3, 3, (1, 1), (1, 1), (1, 1), 8),           # a long contraction in parts
+]
+
+
+@pytest.mark.parametrize("case", CODE_CASES)
+def test_ste_conv2d_backward_on_codes(B, case):
+    test_ste_conv2d_backward_matches_oracle(B, case)
+
+
+@pytest.mark.parametrize("scale,size", [(1e-31, 1e30), (3e-5, 1e-20), (3e-5, 1e30), (0.5, 1e-25), (1e29, 1.0), (1e31, 1e-20), (1e31, 1.0)])
+def test_ste_conv2d_backward_over_the_range_of_scales(B, scale, size):
+    """Scales whose power of two the codes can carry and those beyond, small and large gradients: as in the fp32 form nothing
+    overflows or vanishes that the result does not."""
+    rng = np.random.default_rng(7)
+    s = np.float32(scale)
+    x, w = (rng.integers(-140, 141, (2, 6, 5, 6)) * s).astype(np.float32), (rng.integers(-140, 141, (7, 6, 3, 3)) * s).astype(np.float32)
+    dy = (rng.standard_normal((2, 7, 5, 6)) * size).astype(np.float32)
+    args = ((1, 1), (1, 1), (1, 1), s, s, 8)
+    ox, ow, _ = ste.ste_conv2d_backward(dy, x, w, *args)
+    bx, bw, _ = ste.ste_conv2d_backward(dy, x, w, *args, absolute=True)
+    dx, dw, _ = B.adapt_ste_conv2d_backward_f32(dev(dy), dev(x), dev(w), *args)
+    check(dx, ox, bx, 7 + 9)
+    check(dw, ow, bw, 2 * 5 * 6)
+
+
 def test_ste_conv2d_backward_keeps_infinities_to_their_pixels(B):
     """An infinite or NaN gradient reaches the pixels under its taps and nothing else: padding and tile remainders add nothing."""
     rng = np.random.default_rng(3)
