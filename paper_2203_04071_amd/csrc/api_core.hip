@@ -50,6 +50,7 @@ int adapt_lut_create(adapt_lut **out, int bits, const int32_t *table_host) {
     l->byte = l->storage == 0 ? find_byte_form(bits, table_host) : ByteForm{};
     l->img_dev[0] = l->img_dev[1] = nullptr;
     l->lut16_dev[0] = l->lut16_dev[1] = nullptr;
+    l->img8_dev = nullptr;
     if (hipGetDevice(&l->device) != hipSuccess) {
         delete l;
         return fail(ADAPT_ERR_HIP, "adapt_lut_create: hipGetDevice failed");
@@ -75,7 +76,16 @@ int adapt_lut_create(adapt_lut **out, int bits, const int32_t *table_host) {
                 plain[(size_t)(a & (n - 1)) * n + (w & (n - 1))] = img[(size_t)(w + hh) * l->rs + (a + hh)];
         if (e == hipSuccess) e = dbg_malloc((void **)&l->lut16_dev[half], plain.size() * 2);
         if (e == hipSuccess) e = hipMemcpy(l->lut16_dev[half], plain.data(), plain.size() * 2, hipMemcpyHostToDevice);
+        if (e == hipSuccess && l->byte.found) {
+            std::vector<int8_t> err((size_t)n * n);
+            for (int w = 0; w < n; ++w)
+                for (int a = 0; a < n; ++a)
+                    err[(size_t)w * n + a] = (int8_t)(table_host[(size_t)a * n + w] - ((a - hh) & l->byte.am) * ((w - hh) & l->byte.wm) - l->byte.c);
+            e = dbg_malloc((void **)&l->img8_dev, err.size());
+            if (e == hipSuccess) e = hipMemcpy(l->img8_dev, err.data(), err.size(), hipMemcpyHostToDevice);
+        }
         if (e != hipSuccess) {
+            if (l->img8_dev) (void)hipFree(l->img8_dev);
             for (int j = 0; j < 2; ++j) {
                 if (l->img_dev[j]) (void)hipFree(l->img_dev[j]);
                 if (l->lut16_dev[j]) (void)hipFree(l->lut16_dev[j]);
@@ -97,6 +107,7 @@ int adapt_lut_destroy(adapt_lut *lut) {
         if (lut->img_dev[j]) (void)hipFree(lut->img_dev[j]);
         if (lut->lut16_dev[j]) (void)hipFree(lut->lut16_dev[j]);
     }
+    if (lut->img8_dev) (void)hipFree(lut->img8_dev);
     delete lut;
     scratch_table_gone(device);
     return ADAPT_OK;

@@ -83,6 +83,7 @@ struct adapt_weights {
     // row offsets with the columns in cell order (see adapt::RowsParams), made at pack time
     uint32_t *wofs_cell_dev;
     int cell_G;
+    uint32_t *cell8_dev;    // the same for one-byte entries, the packed weights behind the offsets (tables with a byte form, 64 | Hs)
     // tables with a byte form: one-byte derived tables and the weights of the exact product (lut_byte.hpp) in place of
     // dt_dev and dtq_dev, which are nullptr then
     bool byte_form;
@@ -119,10 +120,10 @@ int noalloc_scratch(void **out, const char *who) {
     return ADAPT_OK;
 }
 
-template <int NT, bool SIGNED>
+template <int NT, bool SIGNED, bool BYTE = false>
 int launch_rows_inst(const adapt::RowsParams &p, dim3 grid, size_t lds, hipStream_t s) {
     static std::atomic<size_t> configured{0};   // largest dynamic LDS size announced for this instantiation
-    auto kern = adapt::lut_rows_kernel<NT, SIGNED>;
+    auto kern = adapt::lut_rows_kernel<NT, SIGNED, BYTE>;
     if (lds > configured.load(std::memory_order_acquire)) {     // (two threads may both announce it: harmless)
         HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         size_t seen = configured.load(std::memory_order_relaxed);
@@ -157,6 +158,7 @@ struct LstmStep {            // see adapt::RowsParams
     const float *h_prev = nullptr;
     int8_t *qh_next;
     float s_ih, s_hh, s_h, Qh;
+    const uint32_t *cell8 = nullptr;        // offsets and weights of the one-byte form, if the handle has them
 };
 
 // pack_into: room for Ktot * (N rounded up to 16) * groups row offsets that the call may use instead of a stream-ordered
@@ -216,13 +218,23 @@ int run_rows(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *ou
         if (lstm->kind == 3) p.act = lstm->relu ? 1 : 0;
     }
     dim3 grid((unsigned)((g.M + MT - 1) / MT), (unsigned)(Npad / NT), (unsigned)ngroups);
-    size_t lds = (size_t)lut->img_bytes;
+    // A time step on one-byte entries: where the handle has them, and the slices of the waves are whole words of aligned activations
+    const bool byte = lstm && lstm->cell8 && KS == 16 && (reinterpret_cast<uintptr_t>(x) & 3u) == 0;
+    p.w4 = nullptr; p.amask = 0; p.corr = 0;
+    if (byte) {
+        p.wofs = lstm->cell8; p.w4 = lstm->cell8 + (size_t)Ktot * g.N / 2;
+        p.img_bytes = 1 << (2 * bits);
+        p.amask = (uint32_t)(lut->byte.am & 0xff) * 0x01010101u;
+        p.corr = (int)(uint32_t)(Ktot * lut->byte.c);
+    }
+    size_t lds = (size_t)p.img_bytes;
     if (KS > 1 && (size_t)adapt::ROWS_THREADS * NT * 4 > lds) lds = (size_t)adapt::ROWS_THREADS * NT * 4;
     for (int half = 0; half <= lut->storage && rc == ADAPT_OK; ++half) {
-        p.img = lut->img_dev[half];
+        p.img = byte ? lut->img8_dev : lut->img_dev[half];
         p.shift = half == 0 ? -1 : 16;
         const bool sgn = (lut->storage == 0) || half == 1;
-        if (NT == 16) rc = sgn ? launch_rows_inst<16, true>(p, grid, lds, s) : launch_rows_inst<16, false>(p, grid, lds, s);
+        if (byte) rc = NT == 8 ? launch_rows_inst<8, true, true>(p, grid, lds, s) : (NT == 6 ? launch_rows_inst<6, true, true>(p, grid, lds, s) : launch_rows_inst<2, true, true>(p, grid, lds, s));
+        else if (NT == 16) rc = sgn ? launch_rows_inst<16, true>(p, grid, lds, s) : launch_rows_inst<16, false>(p, grid, lds, s);
         else if (NT == 6) rc = launch_rows_inst<6, true>(p, grid, lds, s);      // (GRU step: single-pass tables only)
         else if (NT == 2) rc = launch_rows_inst<2, true>(p, grid, lds, s);      // (plain recurrent step, likewise)
         else rc = sgn ? launch_rows_inst<8, true>(p, grid, lds, s) : launch_rows_inst<8, false>(p, grid, lds, s);
@@ -1172,6 +1184,10 @@ static int pack_cell_offsets(adapt_weights *h, hipStream_t s, const char *who) {
     h->cell_G = G;
     adapt::pack_row_offsets_cell_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(h->w8_dev, h->wofs_cell_dev, Hs, G, 1 << (h->bits - 1),
                                                                                   (1 << h->bits) - 1, h->lut->rs * 2);
+    if (h->lut->img8_dev && Hs % 64 == 0) {
+        HIP_TRY(dbg_malloc((void **)&h->cell8_dev, n * (sizeof(uint16_t) + 1)));
+        adapt::pack_cell_bytes_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(h->w8_dev, reinterpret_cast<uint16_t *>(h->cell8_dev), reinterpret_cast<int8_t *>(h->cell8_dev + n / 2), Hs, G, h->bits, h->lut->byte.wm);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ADAPT_ERR_HIP, "%s: pack launch: %s", who, hipGetErrorString(e));
     return ADAPT_OK;
@@ -1245,7 +1261,7 @@ static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t 
     h->dt_bytes = q.dt_bytes;
     h->dt_dev[0] = h->dt_dev[1] = nullptr;
     h->stride = 1; h->phased = false; h->zsum_dev = nullptr; h->w8_dev = nullptr; h->lut = lut;
-    h->wofs_dev = nullptr; h->wofs_npad = 0; h->wofs1_dev = nullptr; h->wofs1_npad = 0; h->dtq_dev = nullptr; h->dtq_c = 0; h->dtq_bytes = 0; h->wofs_cell_dev = nullptr; h->cell_G = 0;
+    h->wofs_dev = nullptr; h->wofs_npad = 0; h->wofs1_dev = nullptr; h->wofs1_npad = 0; h->dtq_dev = nullptr; h->dtq_c = 0; h->dtq_bytes = 0; h->wofs_cell_dev = nullptr; h->cell_G = 0; h->cell8_dev = nullptr;
     h->byte_form = false; h->dtb_dev = nullptr; h->wx_dev = nullptr; h->arrived_dev = nullptr;
     {   // copy of the weights (for table orders made later)
         const size_t wbytes = (size_t)N * Cin * kh * kw;
@@ -1334,7 +1350,7 @@ int adapt_weights_pack_conv_transpose2d(adapt_weights **out, const adapt_lut *lu
     h->Cp = h->Cc = h->n_tiles = 0; h->dt_bytes = 0; h->pair_g = 0;
     h->dt_dev[0] = h->dt_dev[1] = nullptr;
     h->zsum_dev = nullptr; h->w8_dev = nullptr; h->lut = lut;
-    h->wofs_dev = nullptr; h->wofs_npad = 0; h->wofs1_dev = nullptr; h->wofs1_npad = 0; h->dtq_dev = nullptr; h->dtq_c = 0; h->dtq_bytes = 0; h->wofs_cell_dev = nullptr; h->cell_G = 0;
+    h->wofs_dev = nullptr; h->wofs_npad = 0; h->wofs1_dev = nullptr; h->wofs1_npad = 0; h->dtq_dev = nullptr; h->dtq_c = 0; h->dtq_bytes = 0; h->wofs_cell_dev = nullptr; h->cell_G = 0; h->cell8_dev = nullptr;
     h->byte_form = false; h->dtb_dev = nullptr; h->wx_dev = nullptr; h->arrived_dev = nullptr;
     h->phased = kh % stride == 0 && kw % stride == 0 && stride <= 8;
     const size_t wbytes = (size_t)Cout * Cin * kh * kw;
@@ -1402,6 +1418,7 @@ int adapt_weights_destroy(adapt_weights *h) {
     if (h->wofs1_dev) (void)hipFree(h->wofs1_dev);
     if (h->dtq_dev) (void)hipFree(h->dtq_dev);
     if (h->wofs_cell_dev) (void)hipFree(h->wofs_cell_dev);
+    if (h->cell8_dev) (void)hipFree(h->cell8_dev);
     if (h->dtb_dev) (void)hipFree(h->dtb_dev);
     if (h->wx_dev) (void)hipFree(h->wx_dev);
     if (h->arrived_dev) (void)hipFree(h->arrived_dev);
@@ -1958,6 +1975,7 @@ int adapt_lstm_step_f32(const adapt_weights *h, const int8_t *qh_dev, const int3
     g.H = 1; g.W = 1; g.Wo = 1; g.HoWo = 1; g.sh = g.sw = g.dh = g.dw = 1; g.ph = g.pw = 0;
     g.kstride = 1; g.img_stride = Hs;
     LstmStep ls;
+    ls.cell8 = h->cell8_dev;
     ls.Hs = Hs; ls.acc_ih = acc_ih_dev; ls.bias = bias_dev; ls.c = c_dev; ls.h = h_dev; ls.qh_next = qh_next_dev;
     ls.s_ih = s_ih; ls.s_hh = s_hh; ls.s_h = s_h; ls.Qh = (float)((1 << (h->bits - 1)) - 1);
     return run_rows(h->lut, qh_dev, nullptr, nullptr, g, s, h->wofs_cell_dev, 4 * Hs, nullptr, &ls);
@@ -1984,6 +2002,7 @@ int adapt_gru_step_f32(const adapt_weights *h, const int8_t *qh_dev, const int32
     g.kstride = 1; g.img_stride = Hs;
     LstmStep ls;
     ls.kind = 2;
+    ls.cell8 = h->cell8_dev;
     ls.Hs = Hs; ls.acc_ih = acc_ih_dev; ls.bias = b_ih_dev; ls.bias_hh = b_hh_dev; ls.c = nullptr; ls.h = h_dev; ls.h_prev = h_prev_dev;
     ls.qh_next = qh_next_dev;
     ls.s_ih = s_ih; ls.s_hh = s_hh; ls.s_h = s_h; ls.Qh = (float)((1 << (h->bits - 1)) - 1);
@@ -2010,6 +2029,7 @@ int adapt_rnn_step_f32(const adapt_weights *h, const int8_t *qh_dev, const int32
     g.kstride = 1; g.img_stride = Hs;
     LstmStep ls;
     ls.kind = 3; ls.relu = relu ? 1 : 0;
+    ls.cell8 = h->cell8_dev;
     ls.Hs = Hs; ls.acc_ih = acc_ih_dev; ls.bias = bias_dev; ls.c = nullptr; ls.h = h_dev; ls.qh_next = qh_next_dev;
     ls.s_ih = s_ih; ls.s_hh = s_hh; ls.s_h = s_h; ls.Qh = (float)((1 << (h->bits - 1)) - 1);
     return run_rows(h->lut, qh_dev, nullptr, nullptr, g, s, h->wofs_cell_dev, Hs, nullptr, &ls);

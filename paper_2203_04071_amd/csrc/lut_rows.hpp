@@ -66,6 +66,12 @@ struct RowsParams {
     const float *bias_hh;       // [3 Hs] or nullptr (GRU)
     int8_t *qh_next;            // [M][Hs]
     float s_ih, s_hh, s_h, Qh;
+    // one-byte form of a time step (tables that are an exact product plus a one-byte error, see lut_byte.hpp): img holds the error
+    // bytes [w][a] (rows of 2^b bytes), wofs their row offsets in cell order, 16 bits each, w4 the weights of the exact product in
+    // words of four inner indices, [pair of units][k / 4][2 G]; amask: the kept bits of an activation in every byte; corr: c x K
+    const uint32_t *w4;
+    uint32_t amask;
+    int corr;
 };
 
 __device__ __forceinline__ uint32_t finish_sum(const RowsParams &p, uint32_t v, int n) {
@@ -113,6 +119,19 @@ __global__ void pack_row_offsets_cell_kernel(const int8_t *__restrict__ w, uint3
     wofs[((size_t)pair * Hs + k) * (2 * G) + within] = (uint32_t)(((int)w[wi] + hoff) & mask) * (uint32_t)row_bytes;
 }
 
+// The same columns for the one-byte form: offsets of rows of 2^b bytes, and the weights (their kept bits, wm) four inner indices to a word
+__global__ void pack_cell_bytes_kernel(const int8_t *__restrict__ w, uint16_t *__restrict__ wofs, int8_t *__restrict__ w4, int Hs, int G, int bits, int wm) {
+    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int N = G * Hs, half = 1 << (bits - 1), mask = 2 * half - 1;
+    if (idx >= (size_t)Hs * N) return;
+    const int k = (int)(idx / N), cp = (int)(idx % N);
+    const int pair = cp / (2 * G), within = cp - pair * 2 * G;
+    const int u = pair * 2 + (within & 1), g = within >> 1;
+    const int row = ((int)w[((size_t)g * Hs + u) * Hs + k] + half) & mask;
+    wofs[((size_t)pair * Hs + k) * (2 * G) + within] = (uint16_t)(row << bits);
+    w4[(((size_t)pair * (Hs / 4) + k / 4) * (2 * G) + within) * 4 + (k & 3)] = (int8_t)((row - half) & wm);
+}
+
 template <bool SIGNED>
 __device__ __forceinline__ uint32_t lds_entry(const unsigned char *smem, uint32_t off) {
     if (SIGNED) return (uint32_t)(int32_t) * reinterpret_cast<const int16_t *>(smem + off);
@@ -129,12 +148,34 @@ __device__ __forceinline__ void stage_table(unsigned char *smem, const uint16_t 
     for (int i = tid; i < n16; i += ROWS_THREADS) dst[i] = src[i];
 }
 
-template <int NT, bool SIGNED>
+// 32 inner indices of a lane's row from kk on (those beyond k_end: 0).  The lanes of a wave read 64 rows, a line of memory each, so a load costs
+// its 64 lines whatever its width: two of 16 bytes instead of eight of 4.
+typedef uint32_t rows_words_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void rows_fetch32(uint32_t (&dst)[8], const uint32_t *xw, int kk, int k_end) {
+    if (kk + 32 <= k_end) {                 // (the same in the whole wave)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const rows_words_t v = *reinterpret_cast<const rows_words_t *>(xw + (kk >> 2) + 4 * h);
+            dst[4 * h] = v.x; dst[4 * h + 1] = v.y; dst[4 * h + 2] = v.z; dst[4 * h + 3] = v.w;
+        }
+    } else {
+#pragma unroll
+        for (int d = 0; d < 8; ++d) dst[d] = kk + 4 * d < k_end ? xw[(kk >> 2) + d] : 0u;
+    }
+}
+
+// BYTE: a time step on one-byte entries (see RowsParams; Hs a multiple of 64, word-aligned activations).  What bounds a step is the lookups:
+// a 7-bit row of bytes is 32 words of LDS, one per bank, 2.6 clocks for 64 lanes, where its 16-bit row has two words per bank, 4.2; the exact
+// products cost a v_dot4 for four lookups, and the table's way into LDS is an eighth (16 instead of 132 KB at 7 against
+// 8 bits of 16).  LSTM 512 / 512, 64 rows, 7 bits: 13.6 -> CELLNEW us a step.
+template <int NT, bool SIGNED, bool BYTE = false>
 __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
-    stage_table(smem, p.img, p.img_bytes, tid);
-    __syncthreads();
+    if constexpr (!BYTE) {
+        stage_table(smem, p.img, p.img_bytes, tid);
+        __syncthreads();
+    }
 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
@@ -173,13 +214,63 @@ __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams
 
     // Linear layers whose rows are word-aligned: the activations of this lane's K slice are fetched as whole words, 32
     // inner indices at a time and one block ahead of their use, so that the loop never waits for a byte load.
-    if (p.mode == MODE_GEMM && p.kstride == 1 && (p.Cin & 3) == 0 && (kc & 3) == 0 &&
+    if constexpr (BYTE) {
+        // Row offsets (two to a word) and weights of four inner indices come by scalar loads.  These share a counter with the lookups and return
+        // out of order, so whoever waits for the one waits for the other: those of the next four are requested ahead of a
+        // group's lookups and travel beside them.
+        const uint32_t *const xw = reinterpret_cast<const uint32_t *>(xb);
+        const uint32_t *const ofs = p.wofs + (size_t)blockIdx.y * Ktot * (NT / 2), *const w4 = p.w4 + (size_t)blockIdx.y * (Ktot >> 2) * NT;
+        const uint32_t half4 = (uint32_t)p.hoff * 0x01010101u, mask4 = (uint32_t)p.mask * 0x01010101u, up = (uint32_t)(256 / p.hoff - 1);
+        uint32_t nxt[8], off[2][2 * NT], wgt[2][NT];
+        auto fetch = [&](int kk) { rows_fetch32(nxt, xw, kk, k_end); };
+        auto request = [&](int set, int kk) {
+            const int at = min(kk, Ktot - 4);               // (past the end: any valid place)
+#pragma unroll
+            for (int w = 0; w < 2 * NT; ++w) off[set][w] = ofs[at * (NT / 2) + w];
+#pragma unroll
+            for (int n = 0; n < NT; ++n) wgt[set][n] = w4[(at >> 2) * NT + n];
+        };
+        request(0, k);
+        fetch(k);
+        stage_table(smem, p.img, p.img_bytes, tid);
+        __syncthreads();
+        while (k < k_end) {
+            uint32_t cur[8];
+#pragma unroll
+            for (int d = 0; d < 8; ++d) cur[d] = nxt[d];
+            if (k + 32 < k_end) fetch(k + 32);
+            const int cnt = min(32, k_end - k);
+#pragma unroll
+            for (int d = 0; d < 8; ++d) {
+                if (4 * d >= cnt) break;                    // uniform in the wave
+                request((d + 1) & 1, k + 4 * d + 4);
+                __builtin_amdgcn_sched_barrier(0);
+                // column of every activation, and the activation itself, wrapped into b bits, as a signed byte
+                const uint32_t col = (cur[d] ^ half4) & mask4, neg = ~col & half4;
+                const int a = (int)(((col & ~half4) | neg * up) & p.amask);
+                uint32_t e[4][NT];
+#pragma unroll
+                for (int bq = 0; bq < 4; ++bq) {
+                    const uint32_t at = (col >> (8 * bq)) & 0xffu;
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) {
+                        const uint32_t o = off[d & 1][(bq * NT + n) / 2];
+                        e[bq][n] = (uint32_t)(int)*reinterpret_cast<const int8_t *>(smem + (n & 1 ? o >> 16 : o & 0xffffu) + at);
+                    }
+                }
+#pragma unroll
+                for (int n = 0; n < NT; ++n) acc[n] = (uint32_t)__builtin_amdgcn_sdot4(a, (int)wgt[d & 1][n], (int)acc[n], false);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int n = 0; n < NT; ++n) acc[n] += (e[0][n] + e[1][n]) + (e[2][n] + e[3][n]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            k += cnt;
+        }
+    } else if (p.mode == MODE_GEMM && p.kstride == 1 && (p.Cin & 3) == 0 && (kc & 3) == 0 &&
         (reinterpret_cast<uintptr_t>(p.x) & 3u) == 0) {
         const uint32_t *xw = reinterpret_cast<const uint32_t *>(xb);       // row of this lane
-        auto fetch = [&](uint32_t *dst, int kk) {
-#pragma unroll
-            for (int d = 0; d < 8; ++d) dst[d] = (kk + 4 * d < k_end) ? xw[(kk >> 2) + d] : 0u;
-        };
+        auto fetch = [&](uint32_t (&dst)[8], int kk) { rows_fetch32(dst, xw, kk, k_end); };
         // TILED: offsets stored [column tile][k][NT] (cell order), so the loads of consecutive k are contiguous
         auto loop = [&](auto tiled_c) {
             constexpr bool TILED = decltype(tiled_c)::value;
@@ -217,7 +308,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams
         else loop(std::false_type{});
     }
 
-    while (k < k_end) {
+    while (!BYTE && k < k_end) {
         const int t = k / p.Cin;
         const int c0 = k - t * p.Cin;
         const int cnt = min(p.Cin - c0, k_end - k);
@@ -326,7 +417,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams
             if (m2 >= p.M) continue;
             const int u = blockIdx.y * 2 + e;
             const size_t ci = (size_t)m2 * p.Hs + u;
-            uint32_t s = 0;
+            uint32_t s = BYTE ? (uint32_t)p.corr : 0u;
             for (int j = 0; j < p.KS; ++j) s += red[((size_t)j * NT + e) * p.MT + r];
             const float uu = (float)cell_ih[0] * p.s_ih;
             const float vv = (float)(int32_t)s * p.s_hh;
@@ -354,7 +445,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams
             float gi[3], gh[3];
 #pragma unroll
             for (int g = 0; g < 3; ++g) {
-                uint32_t s = 0;
+                uint32_t s = BYTE ? (uint32_t)p.corr : 0u;
                 for (int j = 0; j < p.KS; ++j) s += red[((size_t)j * NT + g * 2 + e) * p.MT + r];
                 float uu = (float)cell_ih[g] * p.s_ih;
                 if (p.bias) uu = uu + cell_b[g];
@@ -392,7 +483,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams
             float pre[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                uint32_t s = 0;
+                uint32_t s = BYTE ? (uint32_t)p.corr : 0u;
                 for (int j = 0; j < p.KS; ++j) s += red[((size_t)j * NT + g * 2 + e) * p.MT + r];
                 const float uu = (float)cell_ih[g] * p.s_ih;
                 const float vv = (float)(int32_t)s * p.s_hh;

@@ -383,3 +383,41 @@ def test_chains_between_forms(B, bits, kind, first):
                     B.adapt_conv2d_layer_chain_f32(p2, None, s_2, s_o, out2, (st, st), (1, 1), in_shape=(3, H, W))
                 assert bits_equal(host(out1), y), (C, st, act)
                 assert bits_equal(host(out2), finish(acc2, s_o, None, None, 0)), (C, st, act)
+
+
+@pytest.mark.parametrize("bits,kind", [(8, "product"), (8, "dropped"), (7, "product"), (7, "one_side"), (6, "product"), (2, "product")])
+@pytest.mark.parametrize("rows,Hs", [(1, 64), (65, 128), (7, 192), (64, 576)])
+def test_time_steps_on_one_byte_entries(B, bits, kind, rows, Hs):
+    """The three recurrent steps where they read one-byte entries: asymmetric tables, slices of 4 to 36 inner indices, codes beyond the
+    operand's range (which wrap), activations that are not word-aligned (which take the 16-bit entries)."""
+    rng = np.random.default_rng(bits + rows + Hs)
+    t = table(kind, bits, rng)
+    L = B.Lut(t, bits)
+    s_ih, s_hh, s_h = np.float32(3e-5), np.float32(2e-5), np.float32(1.0) / np.float32(max(1, (1 << (bits - 1)) - 1))
+    h = 1 << (bits - 1)
+    qh = rng.integers(-128, 128, size=(rows, Hs)).astype(np.int8)
+    wrapped = ((((qh.astype(np.int32) + h) & (2 * h - 1)) - h)).astype(np.int8)
+    shifted = torch.empty(rows * Hs + 1, dtype=torch.int8, device="cuda")[1:].view(rows, Hs)
+    shifted.copy_(dev(qh))
+    new = lambda dt: torch.empty((rows, Hs), dtype=dt, device="cuda")
+    for gates in (4, 3, 1):
+        w = wl.random_i8(rng, (gates * Hs, Hs), bits)
+        acc_ih = rng.integers(-40000, 40000, size=(rows, gates * Hs)).astype(np.int32)
+        acc_hh = orc.approx_linear(t, bits, wrapped, w, threads=4)
+        pw = B.adapt_weights_pack_linear(L, dev(w))
+        c0, h0, bias = (rng.standard_normal(s).astype(np.float32) for s in ((rows, Hs), (rows, Hs), gates * Hs))
+        for q in (dev(qh), shifted):
+            hd, qn = new(torch.float32), new(torch.int8)
+            if gates == 4:
+                cd = dev(c0)
+                B.adapt_lstm_step_f32(pw, q, dev(acc_ih), s_ih, s_hh, s_h, dev(bias), cd, hd, qn)
+                want, c_want = orc.lstm_cell(acc_ih, acc_hh, s_ih, s_hh, bias, c0)
+                assert bits_equal(host(cd), c_want)
+            elif gates == 3:
+                B.adapt_gru_step_f32(pw, q, dev(acc_ih), s_ih, s_hh, s_h, dev(bias), None, dev(h0), hd, qn)
+                want = orc.gru_cell(acc_ih, acc_hh, s_ih, s_hh, bias, None, h0)
+            else:
+                B.adapt_rnn_step_f32(pw, q, dev(acc_ih), s_ih, s_hh, s_h, dev(bias), hd, qn)
+                want = orc.rnn_cell(acc_ih, acc_hh, s_ih, s_hh, bias)
+            assert bits_equal(host(hd), want), (gates, q.data_ptr() % 4)
+            assert (host(qn) == orc.quantize(want, s_h, bits)).all()
