@@ -72,6 +72,7 @@ struct RowsParams {
     const uint32_t *w4;
     uint32_t amask;
     int corr;
+    int x_row;              // > 0: the rows of a workgroup are staged in LDS behind the table, this many bytes apart
 };
 
 __device__ __forceinline__ uint32_t finish_sum(const RowsParams &p, uint32_t v, int n) {
@@ -167,7 +168,7 @@ __device__ __forceinline__ void rows_fetch32(uint32_t (&dst)[8], const uint32_t 
 // BYTE: a time step on one-byte entries (see RowsParams; Hs a multiple of 64, word-aligned activations).  What bounds a step is the lookups:
 // a 7-bit row of bytes is 32 words of LDS, one per bank, 2.6 clocks for 64 lanes, where its 16-bit row has two words per bank, 4.2; the exact
 // products cost a v_dot4 for four lookups, and the table's way into LDS is an eighth (16 instead of 132 KB at 7 against
-// 8 bits of 16).  LSTM 512 / 512, 64 rows, 7 bits: 13.6 -> CELLNEW us a step.
+// 8 bits of 16).  LSTM 512 / 512, 64 rows, 7 bits: 13.6 -> 11.6 us a step.
 template <int NT, bool SIGNED, bool BYTE = false>
 __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -231,14 +232,35 @@ __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams
             for (int n = 0; n < NT; ++n) wgt[set][n] = w4[(at >> 2) * NT + n];
         };
         request(0, k);
-        fetch(k);
-        stage_table(smem, p.img, p.img_bytes, tid);
-        __syncthreads();
+        const unsigned char *const mine = smem + p.img_bytes + r_in_tile * p.x_row;
+        auto fetch_staged = [&](int kk) {
+            rows_fetch32(nxt, reinterpret_cast<const uint32_t *>(mine), kk, k_end);
+        };
+        if (p.x_row > 0) {
+            // The 64 rows as whole lines, beside the table (a lane reading its own row: 64 lines a load, 2000 clocks of a step)
+            const int c16 = Ktot >> 4, c = tid & 31, r0 = tid >> 5, m0 = blockIdx.x * 64;
+            const uint4 *const x16 = reinterpret_cast<const uint4 *>(p.x);
+            const uint4 *const a_row = x16 + (size_t)min(m0 + r0, p.M - 1) * c16, *const b_row = x16 + (size_t)min(m0 + r0 + 32, p.M - 1) * c16;
+            uint4 *const a_to = reinterpret_cast<uint4 *>(smem + p.img_bytes + r0 * p.x_row), *const b_to = reinterpret_cast<uint4 *>(smem + p.img_bytes + (r0 + 32) * p.x_row);
+            const uint4 a = a_row[min(c, c16 - 1)], b = b_row[min(c, c16 - 1)];
+            stage_table(smem, p.img, p.img_bytes, tid);
+            if (c < c16) { a_to[c] = a; b_to[c] = b; }
+            for (int i = c + 32; i < c16; i += 32) { a_to[i] = a_row[i]; b_to[i] = b_row[i]; }
+            __syncthreads();
+            fetch_staged(k);
+        } else {
+            fetch(k);
+            stage_table(smem, p.img, p.img_bytes, tid);
+            __syncthreads();
+        }
         while (k < k_end) {
             uint32_t cur[8];
 #pragma unroll
             for (int d = 0; d < 8; ++d) cur[d] = nxt[d];
-            if (k + 32 < k_end) fetch(k + 32);
+            if (k + 32 < k_end) {
+                if (p.x_row > 0) fetch_staged(k + 32);
+                else fetch(k + 32);
+            }
             const int cnt = min(32, k_end - k);
 #pragma unroll
             for (int d = 0; d < 8; ++d) {
