@@ -1008,7 +1008,7 @@ int convt_any(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *a
     const int Ho = (H - 1) * stride - 2 * pad + kh, Wo = (W - 1) * stride - 2 * pad + kw;
     const long long M = (long long)N * Ho * Wo;
     if (convt_phases_ok(H, W, kh, kw, stride, pad) && M >= LINES_MIN_ROWS && stride <= 8 && lut->byte.found) {
-        const ByteShape q = byte_shape(lut->bits, Cout, Cin, kh, kw, stride);
+        const ByteShape q = byte_shape(lut->bits, lut->byte.shift, Cout, Cin, kh, kw, stride);
         if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * (q.kh - 1), W + 2 * (q.kw - 1), 1) &&
             byte_rows_ok((long long)N * (Ho / stride), Wo / stride))
             return with_temp_byte_tables(lut, w, q, true, s, [&](const ByteTables &t) {
@@ -1061,10 +1061,10 @@ int adapt_approx_linear(const adapt_lut *lut, const int8_t *a_dev, const int8_t 
     g.H = 1; g.W = 1; g.Wo = 1; g.HoWo = 1; g.sh = g.sw = g.dh = g.dw = 1; g.ph = g.pw = 0;
     g.kstride = 1; g.img_stride = K;
     if (lut->byte.found && K >= 8) {
-        const ByteShape q = byte_shape(lut->bits, N, K, 1, 1);
+        const ByteShape q = byte_shape(lut->bits, lut->byte.shift, N, K, 1, 1);
         BytePlan pl;
         if (byte_packable(q, (size_t)4 << 30) && (long long)q.cg * 4 * (M + 4) < 0x7fffff00LL && (M >= LINES_MIN_ROWS || byte_call_pays(lut, q, M, true, &pl))) {
-            if (M >= LINES_MIN_ROWS) pl = byte_plan_of(q, lut->bits, 1, 1, M, false);
+            if (M >= LINES_MIN_ROWS) pl = byte_plan_of(q, 1, 1, M, false);
             rc = with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
                 return byte_linear(lut, t, q, a_dev, acc_dev, M, (hipStream_t)stream, nullptr, nullptr, pl);
             });
@@ -1132,7 +1132,7 @@ int adapt_approx_conv2d(const adapt_lut *lut, const int8_t *x_dev, const int8_t 
     g.sh = stride_h; g.sw = stride_w; g.ph = pad_h; g.pw = pad_w; g.dh = dil_h; g.dw = dil_w;
     g.kstride = H * W; g.img_stride = Cin * H * W; g.groups = groups;
     if (groups == 1 && g.M >= LINES_MIN_ROWS && lut->byte.found) {
-        const ByteShape q = byte_shape(lut->bits, Cout, Cin, kh, kw);
+        const ByteShape q = byte_shape(lut->bits, lut->byte.shift, Cout, Cin, kh, kw);
         if (byte_packable(q, (size_t)4 << 30) && byte_copy_bytes(N, Cin, H + 2 * pad_h, W + 2 * pad_w, byte_col_classes(stride_w, Wo)) &&
             byte_rows_ok((long long)N * Ho, Wo))
             return with_temp_byte_tables(lut, w_dev, q, false, (hipStream_t)stream, [&](const ByteTables &t) {
@@ -1207,7 +1207,7 @@ static int pack_byte_handle(adapt_weights *h, const int8_t *w_dev, const ByteSha
 
 static ByteTables byte_tables_of(const adapt_weights *h) { return ByteTables{h->dtb_dev, h->wx_dev, h->arrived_dev}; }
 static ByteShape byte_shape_of(const adapt_weights *h) {
-    return byte_shape(h->bits, h->N, h->Cin, h->kh, h->kw, h->kind == 2 ? h->stride : 1);
+    return byte_shape(h->bits, h->lut->byte.shift, h->N, h->Cin, h->kh, h->kw, h->kind == 2 ? h->stride : 1);
 }
 
 // Place and layout of the input copy that the layer before a prepared handle writes (its own output quantised with s_next)
@@ -1220,7 +1220,7 @@ static adapt::ChainOut chain_out_of(const adapt_weights *next, float s_next) {
     o.scale = s_next; o.Q = (float)((1 << (next->bits - 1)) - 1); o.mask = (1u << next->bits) - 1u;
     if (next->byte_form) {
         const int sw = next->kind == 1 ? byte_col_classes(ci.sw, (o.Wp - (long long)ci.dw * (next->kw - 1) - 1) / ci.sw + 1) : 1, wsub = (o.Wp + sw - 1) / sw;
-        o.xmajor = 1; o.Cp = (next->Cin + 3) / 4 * 4; o.Wp = sw * wsub; o.wsub = (uint32_t)wsub; o.dsw = fast_div((uint32_t)sw); o.mask = 0xffu;
+        o.xmajor = 1; o.Cp = (next->Cin + 3) / 4 * 4; o.Wp = sw * wsub; o.wsub = (uint32_t)wsub; o.dsw = fast_div((uint32_t)sw); o.mask = 0xffu; o.shift = next->lut->byte.shift;
     }
     return o;
 }
@@ -1229,7 +1229,7 @@ static adapt::ChainOut chain_out_of(const adapt_weights *next, float s_next) {
 static int byte_chain_prepare(const adapt_weights *h, size_t copy_bytes, int N, int Ho, int Wo, hipStream_t s) {
     if (!copy_bytes) return fail(ADAPT_ERR_UNSUPPORTED, "chain prepare: input copy of 4 GiB or more");
     const ByteShape q = byte_shape_of(h);
-    const BytePartials sums(q, h->bits, BytePlan{}, N, Ho, Wo);
+    const BytePartials sums(q, BytePlan{}, N, Ho, Wo);
     void *xt = nullptr;
     int32_t *partial = nullptr;
     int rc = ws_get(&h->ws, copy_bytes, 0, sums.rows, [&] { return sums.reserve(); }, s, &xt, &partial);
@@ -1251,7 +1251,7 @@ static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t 
     if (!w_dev) return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: w_dev is NULL", who);
     if ((long long)N * Cin * kh * kw > 0x7fffffffLL) return fail(ADAPT_ERR_UNSUPPORTED, "%s: more than 2^31-1 weights", who);
     const LinesShape q = lines_shape(kind, lut->bits, N, Cin, kh, kw, lut->storage == 0);
-    const ByteShape bq = byte_shape(lut->bits, N, Cin, kh, kw);
+    const ByteShape bq = byte_shape(lut->bits, lut->byte.shift, N, Cin, kh, kw);
     const bool byte_form = lut->byte.found && byte_packable(bq, PACK_LIMIT);
     if (!byte_form && q.dt_bytes * (size_t)(lut->storage + 1) > PACK_LIMIT)
         return fail(ADAPT_ERR_OUT_OF_MEMORY, "%s: packed tables would need %zu bytes", who, q.dt_bytes * (size_t)(lut->storage + 1));
@@ -1374,7 +1374,7 @@ int adapt_weights_pack_conv_transpose2d(adapt_weights **out, const adapt_lut *lu
     if (e == hipSuccess && h->phased) {
         const LinesShape q = convt_phase_shape(lut->bits, Cout, Cin, kh, kw, stride);
         const size_t all = q.dt_bytes * stride * stride;
-        const ByteShape bq = byte_shape(lut->bits, Cout, Cin, kh, kw, stride);
+        const ByteShape bq = byte_shape(lut->bits, lut->byte.shift, Cout, Cin, kh, kw, stride);
         if (lut->byte.found && byte_packable(bq, PACK_LIMIT)) {
             h->Cp = q.Cp; h->Cc = q.Cc; h->n_tiles = q.n_tiles;
             e = dbg_malloc((void **)&h->zsum_dev, (size_t)Cout * kh * kw * sizeof(int32_t));
@@ -1462,7 +1462,7 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
         return fail(ADAPT_ERR_INVALID_ARGUMENT, "%s: bad argument", who);
     int k = 0, rpw = 0, ks = 1, st = 0, wg = 0;
     const bool phased = kind == 2 && kh % stride == 0 && kw % stride == 0 && stride <= 8;
-    const ByteShape bq = byte_shape(bits, Cout, Cin, kh, kw, phased ? stride : 1);
+    const ByteShape bq = byte_shape(bits, 0, Cout, Cin, kh, kw, phased ? stride : 1);
     BytePlan found;
     if (storage == 2 && !byte_packable(bq, PACK_LIMIT)) storage = 0;        // (such a handle keeps the other tables)
     if (kind == 0 && rows < LINES_MIN_ROWS && (storage != 2 || !byte_pays(bq, bits, 0, rows, false, cu, &found))) {
@@ -1472,7 +1472,7 @@ int adapt_plan_packed(int kind, int bits, int storage, int Cout, int Cin, int kh
     } else if (storage == 2) {                  // lut_byte_kernel
         const ByteShape &q = bq;
         const int lines = rows / Wo;            // image rows of the output
-        const BytePlan pl = byte_plan_of(q, bits, 1, lines > 0 ? lines : 1, Wo, false, cu);
+        const BytePlan pl = byte_plan_of(q, 1, lines > 0 ? lines : 1, Wo, false, cu);
         const int V = pl.R < 4 ? pl.R : 4;
         k = 4; rpw = 256 * pl.R; ks = pl.ksplit; st = q.steps;
         wg = (int)(((long long)(lines > 0 ? lines : 1) * ((Wo + V - 1) / V * V) + rpw - 1) / rpw) * q.n_tiles * q.phases * ks;
@@ -1499,7 +1499,7 @@ static int byte_linear_reserve(const adapt_weights *h, int M, hipStream_t s, boo
     const ByteShape q = byte_shape_of(h);
     const int rows = M > h->rows_without_room ? M : h->rows_without_room;
     const size_t copy_bytes = byte_linear_copy_bytes(q, rows);
-    const BytePartials sums(q, h->bits, BytePlan{}, 1, 1, rows);
+    const BytePartials sums(q, BytePlan{}, 1, 1, rows);
     if (h->ws.holds(copy_bytes, sums.rows)) return ADAPT_OK;
     if (if_any_runs && byte_never_pays(q, h->bits, h->storage, rows)) {
         h->rows_without_byte = rows;
@@ -1518,7 +1518,7 @@ static int byte_linear_reserve(const adapt_weights *h, int M, hipStream_t s, boo
 // byte kernel's, where it runs.
 static bool linear_on_rows(const adapt_weights *h, int M, hipStream_t s, BytePlan *plan) {
     if (M >= LINES_MIN_ROWS) {
-        if (h->byte_form) *plan = byte_plan_of(byte_shape_of(h), h->bits, 1, 1, M, false);
+        if (h->byte_form) *plan = byte_plan_of(byte_shape_of(h), 1, 1, M, false);
         return false;
     }
     if (!h->byte_form) return true;

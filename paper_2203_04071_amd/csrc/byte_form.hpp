@@ -9,6 +9,7 @@ namespace adapt_api {
 struct ByteForm {
     bool found = false;
     int c = 0, am = -1, wm = -1;
+    int shift = 0;              // low bits of an activation that change no entry at all (no more than am clears): 2^shift rows are the same
 };
 
 // table: [a + H][w + H], entries of 16 bits.  The exact product of the operands, or of the operands without their low ta / tw
@@ -31,6 +32,12 @@ inline ByteForm find_byte_form(int bits, const int32_t *table) {
             ByteForm f;
             f.found = true;
             f.c = lo + 128; f.am = am; f.wm = wm;
+            for (int t = ta < bits - 2 ? ta : bits - 2; t > 0 && f.shift == 0; --t) {       // (four different rows at least)
+                bool same = true;
+                for (int a = 0; a < n && same; ++a)
+                    for (int w = 0; w < n && same; ++w) same = table[(size_t)a * n + w] == table[(size_t)(a & -(1 << t)) * n + w];
+                if (same) f.shift = t;
+            }
             return f;
         }
     return ByteForm{};

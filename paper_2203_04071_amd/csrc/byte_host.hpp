@@ -15,17 +15,19 @@ struct ByteShape {
     int N, Cin, kh, kw;             // filter of one phase
     int phases, st;                 // transposed convolution: st * st phases
     int cg, steps, n_tiles;
+    int lbits;                      // 2^lbits lines of a table (operand bits less those that change no entry)
     size_t dt_bytes, wx_bytes;      // all phases together
 };
 
-ByteShape byte_shape(int bits, int N, int Cin, int kh, int kw, int st = 1) {
+ByteShape byte_shape(int bits, int shift, int N, int Cin, int kh, int kw, int st = 1) {
     ByteShape q;
+    q.lbits = bits - shift;
     q.N = N; q.Cin = Cin; q.kh = kh / st; q.kw = kw / st; q.st = st; q.phases = st * st;
     q.cg = (Cin + 3) / 4;
     q.steps = (int)(((long long)q.kh * q.kw * q.cg + 3) / 4);
     q.n_tiles = (N + adapt::BYTE_TILE - 1) / adapt::BYTE_TILE;
     const size_t tables = (size_t)q.phases * q.n_tiles * q.steps;
-    q.dt_bytes = tables * ((size_t)adapt::BYTE_LINE << bits);
+    q.dt_bytes = tables * ((size_t)adapt::BYTE_LINE << q.lbits);
     q.wx_bytes = tables * adapt::BYTE_TILE * adapt::BYTE_STEP + 1024;       // (a group of four steps may read past the last one)
     return q;
 }
@@ -33,11 +35,11 @@ ByteShape byte_shape(int bits, int N, int Cin, int kh, int kw, int st = 1) {
 int pack_byte(const adapt_lut *lut, const int8_t *w, const ByteShape &q, const ByteTables &t, bool convt, hipStream_t s) {
     adapt::BytePack p;
     p.lut16 = lut->lut16_dev[0]; p.w = w; p.dt = t.dt; p.wx = t.wx; p.arrived = t.arrived;
-    p.bits = lut->bits; p.N = q.N; p.Cin = q.Cin; p.taps = q.kh * q.kw; p.cg = q.cg; p.n_tiles = q.n_tiles; p.steps = q.steps;
+    p.bits = lut->bits; p.shift = lut->byte.shift; p.N = q.N; p.Cin = q.Cin; p.taps = q.kh * q.kw; p.cg = q.cg; p.n_tiles = q.n_tiles; p.steps = q.steps;
     p.wmode = convt ? 1 : 0; p.kh = q.kh * q.st; p.kw = q.kw * q.st; p.st = q.st;
     p.c = lut->byte.c; p.am = lut->byte.am; p.wm = lut->byte.wm;
     // about eight workgroups per compute unit: enough to hide the latencies, and each stages its band for several tables
-    const int bands = ((1 << lut->bits) + adapt::BYTE_PACK_LINES - 1) / adapt::BYTE_PACK_LINES;
+    const int bands = ((1 << q.lbits) + adapt::BYTE_PACK_LINES - 1) / adapt::BYTE_PACK_LINES;
     p.tables = q.phases * q.n_tiles * q.steps;
     p.per_wg = (int)((long long)p.tables * bands / (8 * device_cus()));
     p.per_wg = p.per_wg < 1 ? 1 : (p.per_wg > 64 ? 64 : p.per_wg);
@@ -78,15 +80,15 @@ struct ByteCall {
     int cv_Ho = 0, cv_Wo = 0, cv_H = 0, cv_W = 0, cv_kh = 0, cv_kw = 0, cv_s = 1, cv_pad = 0, cv_Ly = 0, cv_Lx = 0;
 };
 
-BytePlanIn byte_plan_in(const ByteShape &q, int bits, int images, int Ho, int Wo, bool nonneg, int cu = 0) {
+BytePlanIn byte_plan_in(const ByteShape &q, int images, int Ho, int Wo, bool nonneg, int cu = 0) {
     BytePlanIn in;
     in.rows4 = (long long)images * Ho * ((Wo + 3) / 4 * 4); in.rows2 = (long long)images * Ho * ((Wo + 1) / 2 * 2);
-    in.tiles = q.n_tiles * q.phases; in.steps = q.steps; in.copy_lines = (1 << bits) >> (nonneg ? 1 : 0); in.cu = cu > 0 ? cu : device_cus();
+    in.tiles = q.n_tiles * q.phases; in.steps = q.steps; in.copy_lines = (1 << q.lbits) >> (nonneg ? 1 : 0); in.cu = cu > 0 ? cu : device_cus();
     return in;
 }
 
-BytePlan byte_plan_of(const ByteShape &q, int bits, int images, int Ho, int Wo, bool nonneg, int cu = 0) {
-    BytePlan pl = plan_byte(byte_plan_in(q, bits, images, Ho, Wo, nonneg, cu));
+BytePlan byte_plan_of(const ByteShape &q, int images, int Ho, int Wo, bool nonneg, int cu = 0) {
+    BytePlan pl = plan_byte(byte_plan_in(q, images, Ho, Wo, nonneg, cu));
 #ifdef ADAPT_TUNING_KNOBS
     if (const char *e = getenv("ADAPT_BYTE_PLAN")) {        // "R,ksplit": tuning experiments only (not compiled into the product)
         int R = 0, ks = 0;
@@ -103,19 +105,19 @@ BytePlan byte_plan_of(const ByteShape &q, int bits, int images, int Ho, int Wo, 
 bool byte_pays(const ByteShape &q, int bits, int storage, int M, bool pack, int cu, BytePlan *plan) {
 #ifdef ADAPT_TUNING_KNOBS
     if (const char *e = getenv("ADAPT_BYTE_PAYS")) {
-        *plan = byte_plan_of(q, bits, 1, 1, M, false, cu);
+        *plan = byte_plan_of(q, 1, 1, M, false, cu);
         return atoi(e) != 0;
     }
 #endif
     const long long rows = rows_clocks(bits, M, q.N, q.Cin, cu > 0 ? cu : device_cus()) * (storage + 1);
-    if (!byte_beats_rows(byte_call_clocks_floor(q.steps, 1 << bits, q.dt_bytes, pack), rows)) return false;
-    *plan = byte_plan_of(q, bits, 1, 1, M, false, cu);
+    if (!byte_beats_rows(byte_call_clocks_floor(q.steps, 1 << q.lbits, q.dt_bytes, pack), rows)) return false;
+    *plan = byte_plan_of(q, 1, 1, M, false, cu);
     return byte_beats_rows(byte_call_clocks(*plan, q.dt_bytes, pack), rows);
 }
 // No linear layer of up to M rows on these (packed) tables runs on the byte kernel: what is cheapest for one row (more rows make every
 // plan dearer and rule some out) against the most that any of them takes on the other kernel
 bool byte_never_pays(const ByteShape &q, int bits, int storage, int M) {
-    const long long one_row = byte_call_clocks(byte_plan_of(q, bits, 1, 1, 1, false), q.dt_bytes, false);
+    const long long one_row = byte_call_clocks(byte_plan_of(q, 1, 1, 1, false), q.dt_bytes, false);
     return !byte_beats_rows(one_row, rows_clocks_up_to(bits, M, q.N, q.Cin, device_cus()) * (storage + 1));
 }
 bool byte_call_pays(const adapt_lut *lut, const ByteShape &q, int M, bool pack, BytePlan *plan) {
@@ -125,18 +127,17 @@ bool byte_call_pays(const adapt_lut *lut, const ByteShape &q, int M, bool pack, 
 // room for the sums that the slices of a split product leave behind: `bytes` for this one, reserve() for all that are no larger
 struct BytePartials {
     const ByteShape &q;
-    int bits;
     long long rows;
     size_t bytes;
-    BytePartials(const ByteShape &shape, int operand_bits, const BytePlan &pl, int images, int Ho, int Wo) : q(shape), bits(operand_bits) {
-        const BytePlanIn in = byte_plan_in(q, bits, images, Ho, Wo, false);
+    BytePartials(const ByteShape &shape, const BytePlan &pl, int images, int Ho, int Wo) : q(shape) {
+        const BytePlanIn in = byte_plan_in(q, images, Ho, Wo, false);
         rows = in.rows4;
         bytes = byte_partial_bytes(pl.R, pl.ksplit, pl.R >= 4 ? in.rows4 : in.rows2, launch_tiles());
     }
     long long launch_tiles() const { return (long long)q.n_tiles * (q.phases < 4 ? q.phases : 4); }
     // (whether all activations are known to be >= 0 changes the plan, and is only known call by call)
     size_t reserve() const {
-        const BytePlanIn all = byte_plan_in(q, bits, 1, 1, 1, false), half = byte_plan_in(q, bits, 1, 1, 1, true);
+        const BytePlanIn all = byte_plan_in(q, 1, 1, 1, false), half = byte_plan_in(q, 1, 1, 1, true);
         const size_t a = byte_partial_reserve(all, rows, launch_tiles()), h = byte_partial_reserve(half, rows, launch_tiles());
         return a > h ? a : h;
     }
@@ -147,7 +148,7 @@ bool byte_rows_ok(long long image_rows, long long Wo) { return image_rows * ((Wo
 
 int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, const BytePlan &pl, const ByteCall &c, const int8_t *xt, int32_t *partial,
              int32_t *out, hipStream_t s, const LayerIO *io) {
-    const int bits = lut->bits, R = pl.R, V = R < 4 ? R : 4;
+    const int lbits = q.lbits, R = pl.R, V = R < 4 ? R : 4;
     adapt::ByteParams p;
     p.xt = xt; p.out = out; p.partial = partial; p.arrived = t.arrived;
     p.Wo = c.Wo; p.Wv = (c.Wo + V - 1) / V * V;
@@ -156,7 +157,7 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
     p.Mv = (int)Mv;
     p.N = q.N; p.n_tiles = q.n_tiles; p.m_tiles = (int)((Mv + 256 * R - 1) / (256 * R));
     p.cg = q.cg; p.taps = q.kh * q.kw; p.kw = q.kw; p.steps = q.steps; p.ksplit = pl.ksplit; p.even = pl.even;
-    p.bits = bits; p.copy_lines = (1 << bits) >> (c.nonneg ? 1 : 0);
+    p.bits = lbits; p.shift = lut->byte.shift; p.copy_lines = (1 << lbits) >> (c.nonneg ? 1 : 0);
     p.img_stride = c.img_stride; p.oy_stride = c.oy_stride; p.ch_stride = c.ch_stride; p.ky_stride = c.ky_stride; p.dw = c.dw; p.wsub = c.wsub;
     p.amask = (uint32_t)(lut->byte.am & 0xff) * 0x01010101u;
     p.corr = (int)(uint32_t)((long long)q.kh * q.kw * q.Cin * lut->byte.c);
@@ -186,7 +187,7 @@ int run_byte(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, cons
     for (int first = 0; first < n_phases; first += 4) {         // up to four phases per launch
         p.phases = n_phases - first < 4 ? n_phases - first : 4;
         p.d_phases = fast_div((uint32_t)p.phases);
-        p.dt = t.dt + first * tables * (((size_t)adapt::BYTE_LINE << bits) / 16);
+        p.dt = t.dt + first * tables * (((size_t)adapt::BYTE_LINE << lbits) / 16);
         p.wx = t.wx + first * tables * (adapt::BYTE_TILE * adapt::BYTE_STEP);
         for (int i = 0; i < 4; ++i) {
             const int f = first + (i < p.phases ? i : 0);
@@ -209,7 +210,7 @@ constexpr long long BYTE_MAX_COPY = 0xfffffe00LL;
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
 // int8 or fp32 activations -> the copy of byte_copy_kernel
-int launch_byte_copy(const LayerIO *io, const int8_t *x, int bits, int8_t *xt, int N, int C, int H, int W, int ph, int pw, int sw, int wsub,
+int launch_byte_copy(const LayerIO *io, const int8_t *x, int bits, int shift, int8_t *xt, int N, int C, int H, int W, int ph, int pw, int sw, int wsub,
                      hipStream_t s) {
     const int cg = (C + 3) / 4;
     const size_t total = (size_t)N * (H + 2 * ph) * cg * sw * wsub;
@@ -218,9 +219,9 @@ int launch_byte_copy(const LayerIO *io, const int8_t *x, int bits, int8_t *xt, i
     const adapt::FastDiv dws = fast_div((uint32_t)wsub), dsw = fast_div((uint32_t)sw), dcg = fast_div((uint32_t)cg), dhp = fast_div((uint32_t)(H + 2 * ph));
     const uint32_t mask = (1u << bits) - 1u;
     if (io && io->xf)
-        adapt::byte_copy_kernel<adapt::SrcF32, U><<<blocks, 256, 0, s>>>(adapt::SrcF32{io->xf, io->s_x, io->Q, mask}, xt, C, H, W, ph, pw, dws, dsw, dcg, dhp, (uint32_t)total);
+        adapt::byte_copy_kernel<adapt::SrcF32, U><<<blocks, 256, 0, s>>>(adapt::SrcF32{io->xf, io->s_x, io->Q, mask, shift}, xt, C, H, W, ph, pw, dws, dsw, dcg, dhp, (uint32_t)total);
     else
-        adapt::byte_copy_kernel<adapt::SrcI8, U><<<blocks, 256, 0, s>>>(adapt::SrcI8{x, mask}, xt, C, H, W, ph, pw, dws, dsw, dcg, dhp, (uint32_t)total);
+        adapt::byte_copy_kernel<adapt::SrcI8, U><<<blocks, 256, 0, s>>>(adapt::SrcI8{x, mask, shift}, xt, C, H, W, ph, pw, dws, dsw, dcg, dhp, (uint32_t)total);
     HIP_TRY(hipGetLastError());
     return ADAPT_OK;
 }
@@ -244,7 +245,7 @@ int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
     const int Mp = (M + 3) / 4 * 4;
     const size_t copy_bytes = byte_linear_copy_bytes(q, M);
     if ((long long)q.cg * Mp * 4 > BYTE_MAX_COPY) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: tensor with more than 2^31-1 elements");
-    const BytePartials sums(q, lut->bits, pl, 1, 1, M);
+    const BytePartials sums(q, pl, 1, 1, M);
     unsigned char *mem = nullptr;
     int32_t *partial = nullptr;
     int rc = ws_get(ws, copy_bytes, sums.bytes, sums.rows, [&] { return sums.reserve(); }, s, (void **)&mem, &partial);
@@ -252,8 +253,8 @@ int byte_linear(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
     int8_t *xt = reinterpret_cast<int8_t *>(mem);
     const dim3 grid((unsigned)((M + 63) / 64), (unsigned)((q.cg + 15) / 16));
     const uint32_t mask = (1u << lut->bits) - 1u;
-    if (io && io->xf) adapt::byte_rows_kernel<<<grid, 256, 0, s>>>(adapt::SrcF32{io->xf, io->s_x, io->Q, mask}, xt, M, q.Cin, q.cg, Mp);
-    else adapt::byte_rows_kernel<<<grid, 256, 0, s>>>(adapt::SrcI8{a, mask}, xt, M, q.Cin, q.cg, Mp);
+    if (io && io->xf) adapt::byte_rows_kernel<<<grid, 256, 0, s>>>(adapt::SrcF32{io->xf, io->s_x, io->Q, mask, lut->byte.shift}, xt, M, q.Cin, q.cg, Mp);
+    else adapt::byte_rows_kernel<<<grid, 256, 0, s>>>(adapt::SrcI8{a, mask, lut->byte.shift}, xt, M, q.Cin, q.cg, Mp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return ws_put(ws, mem, s, fail(ADAPT_ERR_HIP, "activation copy: %s", hipGetErrorString(e)));
     ByteCall c;
@@ -287,18 +288,18 @@ int byte_conv2d(const adapt_lut *lut, const ByteTables &t, const ByteShape &q, c
     if (!copy_bytes) return fail(ADAPT_ERR_UNSUPPORTED, "byte path: tensor with more than 2^31-1 elements");
     ByteCall c;
     c.nonneg = input_ready && wh && wh->chain_in.nonneg;
-    const BytePlan pl = byte_plan_of(q, lut->bits, N, Ho, Wo, c.nonneg);
+    const BytePlan pl = byte_plan_of(q, N, Ho, Wo, c.nonneg);
     if (!input_ready && wh && wh->chain_in.valid) {     // an ordinary call with another geometry ends the prepared state
         const auto &ci = wh->chain_in;
         if (ci.N != N || ci.H != H || ci.W != W || ci.sh != sh || ci.sw != sw || ci.ph != ph || ci.pw != pw || ci.dh != dh || ci.dw != dw)
             wh->chain_in.valid = false;
         wh->chain_in.nonneg = false;        // (and any other leaves its own copy there)
     }
-    const BytePartials sums(q, lut->bits, pl, N, Ho, Wo);
+    const BytePartials sums(q, pl, N, Ho, Wo);
     unsigned char *mem = nullptr;
     int32_t *partial = nullptr;
     int rc = byte_input(copy_bytes, sums, ws, input_ready, s, &mem, &partial, [&](int8_t *xt) {
-        return launch_byte_copy(io, x, lut->bits, xt, N, q.Cin, H, W, ph, pw, csw, wsub, s);
+        return launch_byte_copy(io, x, lut->bits, lut->byte.shift, xt, N, q.Cin, H, W, ph, pw, csw, wsub, s);
     });
     if (rc) return rc;
     const uint32_t row = 4u * (uint32_t)csw * (uint32_t)wsub;      // bytes of one channel group of one padded row
@@ -323,13 +324,13 @@ int byte_conv_transpose2d(const adapt_lut *lut, const ByteTables &t, const ByteS
     ByteCall c;
     c.images = N; c.Ho = Ho / st; c.Wo = Wo / st;
     c.nonneg = input_ready && wh && wh->chain_in.nonneg;
-    const BytePlan pl = byte_plan_of(q, lut->bits, N, c.Ho, c.Wo, c.nonneg);
+    const BytePlan pl = byte_plan_of(q, N, c.Ho, c.Wo, c.nonneg);
     if (!input_ready && wh) wh->chain_in.valid = false;     // (an ordinary call overwrites a prepared copy)
-    const BytePartials sums(q, lut->bits, pl, N, c.Ho, c.Wo);
+    const BytePartials sums(q, pl, N, c.Ho, c.Wo);
     unsigned char *mem = nullptr;
     int32_t *partial = nullptr;
     int rc = byte_input(copy_bytes, sums, ws, input_ready, s, &mem, &partial, [&](int8_t *xt) {
-        return launch_byte_copy(io, x, lut->bits, xt, N, q.Cin, H, W, Ty - 1, Tx - 1, 1, Wp, s);
+        return launch_byte_copy(io, x, lut->bits, lut->byte.shift, xt, N, q.Cin, H, W, Ty - 1, Tx - 1, 1, Wp, s);
     });
     if (rc) return rc;
     const uint32_t row = 4u * (uint32_t)Wp, line = (uint32_t)q.cg * row;

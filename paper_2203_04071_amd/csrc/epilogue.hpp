@@ -19,6 +19,7 @@ struct ChainOut {
     int xmajor, Hp, Wp, Cp, ph, pw;
     float scale, Q;
     uint32_t mask;
+    int shift;              // low bits of the codes that the reader's tables do not tell apart (they are left out)
     uint32_t wsub;          // columns per residue class (read only if dsw.d > 1)
     FastDiv dsw;            // division by the horizontal stride of the layer that reads the copy; d <= 1: columns in order
     __device__ __forceinline__ uint32_t col_pos(uint32_t col) const {
@@ -28,7 +29,7 @@ struct ChainOut {
     }
     // element (image, channel c, row oy, column ox) of the producing layer's fp32 output y
     __device__ __forceinline__ void put(int img, int c, int oy, int ox, float y) const {
-        const uint32_t q = (uint32_t)quant1(y, scale, Q) & mask;
+        const uint32_t q = (uint32_t)((int)(int8_t)code(y) >> shift);
         // (a copy is smaller than 2^32 bytes: 32-bit offsets)
         const uint32_t row = (uint32_t)img * (uint32_t)Hp + (uint32_t)(oy + ph), col = col_pos((uint32_t)(ox + pw));
         const uint32_t a = xmajor ? ((row * (uint32_t)(Cp >> 2) + (uint32_t)(c >> 2)) * (uint32_t)Wp + col) * 4u + (uint32_t)(c & 3)
@@ -39,6 +40,8 @@ struct ChainOut {
     // of either copy
     __device__ __forceinline__ uint32_t code(float y) const { return (uint32_t)quant1(y, scale, Q) & mask; }
     __device__ __forceinline__ void put4(int img, int c, int oy, int ox, uint32_t codes) const {
+        if (shift)          // (four signed bytes at once; the same in the whole launch)
+            codes = ((codes >> shift) & ((0xffu >> shift) * 0x01010101u)) | ((codes >> 7) & 0x01010101u) * ((0xff00u >> shift) & 0xffu);
         const uint32_t row = (uint32_t)img * (uint32_t)Hp + (uint32_t)(oy + ph), col = col_pos((uint32_t)(ox + pw));
         const uint32_t a = xmajor ? ((row * (uint32_t)(Cp >> 2) + (uint32_t)(c >> 2)) * (uint32_t)Wp + col) * 4u
                                   : (row * (uint32_t)Wp + col) * (uint32_t)Cp + (uint32_t)c;
@@ -95,17 +98,18 @@ __device__ __forceinline__ T pick4(const T *v, int i) {
 // indices (the kernels that extract a bit field do not care, the quad kernel relies on it).
 // byte(): the operand as a table line index, i.e. its two's-complement bits below 2^b (mask = 2^b - 1)
 // load() / code(): the two halves of byte(), for kernels that request several operands before they convert the first
-// code8(): the operand itself as a signed byte (wrapped into b bits), what the copies of the byte kernel hold
+// code8(): the operand itself as a signed byte (wrapped into b bits), without its low `shift` bits: what the copies of the byte kernel hold
 struct SrcI8 {
     typedef int8_t raw_t;
     const int8_t *x;
     uint32_t mask;
+    int shift = 0;
     __device__ __forceinline__ uint32_t byte(size_t i) const { return (uint32_t)(uint8_t)x[i] & mask; }
     __device__ __forceinline__ raw_t load(uint32_t i) const { return x[i]; }
     __device__ __forceinline__ uint32_t code(raw_t v) const { return (uint32_t)(uint8_t)v & mask; }
     __device__ __forceinline__ uint32_t code8(raw_t v) const {
         const uint32_t h = (mask + 1u) >> 1;
-        return ((((uint32_t)(uint8_t)v & mask) ^ h) - h) & 0xffu;
+        return (uint32_t)((int)((((uint32_t)(uint8_t)v & mask) ^ h) - h) >> shift) & 0xffu;
     }
 };
 struct SrcF32 {
@@ -113,10 +117,11 @@ struct SrcF32 {
     const float *x;
     float scale, Q;
     uint32_t mask;
+    int shift = 0;
     __device__ __forceinline__ uint32_t byte(size_t i) const { return (uint32_t)quant1(x[i], scale, Q) & mask; }
     __device__ __forceinline__ raw_t load(uint32_t i) const { return x[i]; }
     __device__ __forceinline__ uint32_t code(raw_t v) const { return (uint32_t)quant1(v, scale, Q) & mask; }
-    __device__ __forceinline__ uint32_t code8(raw_t v) const { return (uint32_t)quant1(v, scale, Q) & 0xffu; }
+    __device__ __forceinline__ uint32_t code8(raw_t v) const { return (uint32_t)(quant1(v, scale, Q) >> shift) & 0xffu; }
 };
 
 }  // namespace adapt

@@ -43,6 +43,9 @@
 // Waves take turns by priority: a wave drops one level after every quarter of a step's reads, so that all 16 reach the barrier at about
 // the same time; oldest first, as the hardware does it, four waves were left alone with the last third of a step (3250 -> 2850 clocks).
 //
+// Tables whose entries do not change with the low bits of an activation (multipliers that drop them) have a line for every code that is left;
+// the copies hold the codes without those bits (8 bits, two of them dropped: 16 instead of 64 KB a step).
+//
 // Inner dimension.  Channels come in groups of four per filter tap; byte_slot() numbers the groups of all taps without
 // gaps (only the last step is padded), and a table in LDS holds the byte offset of every group inside a window: strides,
 // dilations, channel counts and taps need no further case.  Activation copy: [image][row][channel group][residue of the
@@ -98,7 +101,8 @@ struct ByteParams {
     int cg, taps, kw, steps;    // channel groups per tap, taps, filter width, steps of the whole inner dimension
     int units;                  // > 0: workgroups by units, see the kernel
     int ksplit, even;           // slices of the inner dimension: slice i ends at step (i + 1) even / ksplit, the last one at the end
-    int bits, copy_lines;       // copy_lines: 2^bits, or half of it where all activations are >= 0
+    int bits, copy_lines;       // 2^bits lines of a table; copy_lines: all of them, or half where all activations are >= 0
+    int shift;                  // low bits that the copied codes do without
     int Wo, Wv;                 // output width (per phase), the same rounded up to runs
     uint32_t img_stride, oy_stride;     // bytes of xt per image / output row
     uint32_t ch_stride, ky_stride;      // bytes of xt per channel group / filter row
@@ -555,8 +559,8 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
         b.x = (int)(bit3 ? s[1] : s[0]);
         b.y = (int)(bit3 ? s[0] : s[1]);
         if constexpr (LEVEL == 4) {
-            b.x &= (int)p.amask;
-            b.y &= (int)p.amask;
+            b.x = (int)((uint32_t)b.x << p.shift) & (int)p.amask;       // (what crosses into the next byte falls to bits that am clears)
+            b.y = (int)((uint32_t)b.y << p.shift) & (int)p.amask;
         }
         byte_exact(acc[j], weights, b);
     };
@@ -785,7 +789,7 @@ struct BytePack {
     const int8_t *w;
     uint4 *dt;
     int8_t *wx;
-    int bits, N, Cin, taps, cg, n_tiles, steps;
+    int bits, shift, N, Cin, taps, cg, n_tiles, steps;      // operand bits; tables have 2^(bits - shift) lines
     int tables, per_wg;         // phases * n_tiles * steps; tables per workgroup
     int wmode;                  // 0: [N][Cin][taps]; 1: [Cin][N][kh][kw], transposed convolution with stride st (phases as in pack_line_tables_convt_kernel)
     int kh, kw, st;
@@ -803,17 +807,17 @@ static __global__ __launch_bounds__(256) void pack_byte_tables_kernel(const Byte
     __shared__ uint8_t band[BYTE_PACK_LINES * (256 + 4)];       // rows of lines + 4 bytes (consecutive rows start in different banks)
     __shared__ __align__(16) uint16_t index[2][16 * 16];        // [slot][channel]: column of the band
     const int tid = threadIdx.x;
-    const int lines = 1 << p.bits, mask = lines - 1, half = lines >> 1, row = lines + 4;
+    const int cols = 1 << p.bits, mask = cols - 1, half = cols >> 1, row = cols + 4, lines = cols >> p.shift;
     const int first = blockIdx.y * BYTE_PACK_LINES, here = min(BYTE_PACK_LINES, lines - first);
     const int t0 = (int)blockIdx.x * p.per_wg, t1 = min(t0 + p.per_wg, p.tables);
     if (p.arrived && blockIdx.x == 0 && blockIdx.y == 0)
         for (int i = tid; i < BYTE_MAX_TILES; i += 256) p.arrived[i] = 0u;
-    for (int i = tid; i < here * lines; i += 256) {
-        const int r = i >> p.bits, u = i & mask, l = first + r;
-        const int a = (l < half ? l : l - lines) & p.am, w = (u < half ? u : u - lines) & p.wm;
-        band[r * row + u] = (uint8_t)((int)(int16_t)p.lut16[(size_t)l * lines + u] - a * w - p.c);
+    for (int i = tid; i < here * cols; i += 256) {
+        const int r = i >> p.bits, u = i & mask, l = (first + r) << p.shift;
+        const int a = (l < half ? l : l - cols) & p.am, w = (u < half ? u : u - cols) & p.wm;
+        band[r * row + u] = (uint8_t)((int)(int16_t)p.lut16[(size_t)l * cols + u] - a * w - p.c);
     }
-    if (tid < here) band[tid * row + lines] = 0;                // column of weights that do not exist
+    if (tid < here) band[tid * row + cols] = 0;                // column of weights that do not exist
     for (int tb = t0; tb < t1; ++tb) {
         const int tn = tb / p.steps, step = tb - tn * p.steps, nt = tn % p.n_tiles, phase = tn / p.n_tiles;
         uint16_t *const idx = index[(tb - t0) & 1];
@@ -823,7 +827,7 @@ static __global__ __launch_bounds__(256) void pack_byte_tables_kernel(const Byte
             const int rest = p.cg & 3;
             byte_slot(step * 4 + (slot >> 2), p.taps, p.cg, [&](int v) { return v / p.taps; }, [&](int v) { return v / rest; }, &tap, &c);
             const int n = nt * BYTE_TILE + ch, ci = c * 4 + (slot & 3);
-            int u = lines;
+            int u = cols;
             if (n < p.N && ci < p.Cin && tap < p.taps) {
                 size_t wi;
                 if (p.wmode == 0) {
@@ -837,7 +841,7 @@ static __global__ __launch_bounds__(256) void pack_byte_tables_kernel(const Byte
                 u = (int)p.w[wi] & mask;
             }
             idx[slot * 16 + ch] = (uint16_t)u;
-            if (blockIdx.y == 0) p.wx[(size_t)tb * (BYTE_TILE * BYTE_STEP) + ch * BYTE_STEP + byte_wx_pos(slot)] = (int8_t)(u == lines ? 0 : (u < half ? u : u - lines) & p.wm);
+            if (blockIdx.y == 0) p.wx[(size_t)tb * (BYTE_TILE * BYTE_STEP) + ch * BYTE_STEP + byte_wx_pos(slot)] = (int8_t)(u == cols ? 0 : (u < half ? u : u - cols) & p.wm);
         }
         __syncthreads();            // (two buffers: a wave is at most one table ahead of the slowest)
         const int slot = tid & 15;

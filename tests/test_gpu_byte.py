@@ -39,6 +39,9 @@ def table(kind, bits, rng):
         t = ((v >> d) << d)[:, None] * ((v >> d) << d)[None, :] + rng.integers(-9, 10, size=(n, n))
     elif kind == "one_side":        # only the activation loses bits
         t = ((v >> 1) << 1)[:, None] * v[None, :] + rng.integers(-100, 101, size=(n, n))
+    elif kind in ("bare", "bare_activation"):       # dropped bits change no entry: activations that differ in them share a table line
+        d = 2 if bits > 3 else 1
+        t = ((v >> d) << d)[:, None] * (((v >> d) << d) if kind == "bare" else v)[None, :] + rng.integers(-100, 101, size=(n, n))[(np.arange(n) >> d) << d]
     else:                           # spans 256: no byte form
         t = v[:, None] * v[None, :] + rng.integers(-128, 128, size=(n, n))
         t[0, 0], t[-1, -1] = h * h - 128, (h - 1) ** 2 + 128
@@ -421,3 +424,43 @@ def test_time_steps_on_one_byte_entries(B, bits, kind, rows, Hs):
                 want = orc.rnn_cell(acc_ih, acc_hh, s_ih, s_hh, bias)
             assert bits_equal(host(hd), want), (gates, q.data_ptr() % 4)
             assert (host(qn) == orc.quantize(want, s_h, bits)).all()
+
+
+BARE = [(8, "bare"), (8, "bare_activation"), (7, "bare"), (4, "bare_activation"), (3, "bare"), (2, "bare")]
+
+
+@pytest.mark.parametrize("bits,kind", BARE)
+@pytest.mark.parametrize("case", CONVS)
+def test_convolution_where_activations_share_lines(B, bits, kind, case):
+    test_convolution(B, bits, kind, case)
+
+
+@pytest.mark.parametrize("bits,kind", BARE[:4])
+@pytest.mark.parametrize("act", [0, 1, 2])
+def test_fused_layers_where_activations_share_lines(B, bits, kind, act):
+    test_fused_layers_on_every_form(B, bits, kind, act)
+
+
+@pytest.mark.parametrize("bits,kind", BARE[:4])
+@pytest.mark.parametrize("first", ["conv", "transposed", "depthwise", "grouped"])
+def test_chains_where_activations_share_lines(B, bits, kind, first):
+    test_chains_between_forms(B, bits, kind, first)
+
+
+@pytest.mark.parametrize("bits,kind", BARE[:3])
+@pytest.mark.parametrize("rows,Hs", [(65, 128)])
+def test_time_steps_where_activations_share_lines(B, bits, kind, rows, Hs):
+    test_time_steps_on_one_byte_entries(B, bits, kind, rows, Hs)
+
+
+@pytest.mark.parametrize("bits,kind", BARE[:3])
+@pytest.mark.parametrize("M,K,N", [(512, 77, 37), (4097, 130, 33)])
+def test_linear_where_activations_share_lines(B, bits, kind, M, K, N):
+    """Packed and plain, the codes' whole int8 range (which wraps)."""
+    rng = np.random.default_rng(bits + M)
+    t, h = table(kind, bits, rng), 1 << (bits - 1)
+    L = B.Lut(t, bits)
+    a, w = rng.integers(-128, 128, size=(M, K)).astype(np.int8), wl.random_i8(rng, (N, K), bits)
+    want = orc.approx_linear(t, bits, (((a.astype(np.int32) + h) & (2 * h - 1)) - h).astype(np.int8), w, threads=4)
+    assert (host(B.adapt_approx_linear_packed(B.adapt_weights_pack_linear(L, dev(w)), dev(a))) == want).all()
+    assert (host(B.adapt_approx_linear(L, dev(a), dev(w))) == want).all()
