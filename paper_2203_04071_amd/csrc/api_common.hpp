@@ -135,5 +135,5 @@ struct adapt_lut {
     uint16_t *img_dev[2];   // [0] = only / low half, [1] = high half
     uint16_t *lut16_dev[2]; // same halves, plain [a & mask][w & mask] order (source of the derived line tables)
     adapt_api::ByteForm byte;   // for the byte kernel, if the table has such a form:
-    uint16_t *img8_dev;         // its error bytes [w + H][a + H], else nullptr
+    uint16_t *img8_dev;         // its error bytes [w + H][a + H], in the allocation of lut16_dev[0], else nullptr
 };

@@ -57,10 +57,12 @@ int adapt_lut_create(adapt_lut **out, int bits, const int32_t *table_host) {
     }
     // private image order: row = weight operand, column = activation operand, then a zero column
     std::vector<uint16_t> img((size_t)l->img_bytes / 2, 0);
+    std::vector<int8_t> err(l->byte.found ? (size_t)n * n : 0);     // error bytes of the byte form [w + H][a + H]
     for (int half = 0; half <= l->storage; ++half) {
         for (int w = 0; w < n; ++w)
             for (int a = 0; a < n; ++a) {
                 const uint32_t v = (uint32_t)table_host[(size_t)a * n + w];
+                if (l->byte.found) err[(size_t)w * n + a] = (int8_t)((int)v - ((a - n / 2) & l->byte.am) * ((w - n / 2) & l->byte.wm) - l->byte.c);
                 uint16_t e;
                 if (l->storage == 0) e = (uint16_t)v;
                 else e = half == 0 ? (uint16_t)(v & 0xffffu) : (uint16_t)(v >> 16);
@@ -74,18 +76,14 @@ int adapt_lut_create(adapt_lut **out, int bits, const int32_t *table_host) {
         for (int a = -hh; a < hh; ++a)
             for (int w = -hh; w < hh; ++w)
                 plain[(size_t)(a & (n - 1)) * n + (w & (n - 1))] = img[(size_t)(w + hh) * l->rs + (a + hh)];
+        // (the error bytes lie behind it: one allocation and one copy)
+        const size_t entries = plain.size();
+        plain.resize(entries + err.size() / 2);
+        if (!err.empty()) std::memcpy(plain.data() + entries, err.data(), err.size());
         if (e == hipSuccess) e = dbg_malloc((void **)&l->lut16_dev[half], plain.size() * 2);
         if (e == hipSuccess) e = hipMemcpy(l->lut16_dev[half], plain.data(), plain.size() * 2, hipMemcpyHostToDevice);
-        if (e == hipSuccess && l->byte.found) {
-            std::vector<int8_t> err((size_t)n * n);
-            for (int w = 0; w < n; ++w)
-                for (int a = 0; a < n; ++a)
-                    err[(size_t)w * n + a] = (int8_t)(table_host[(size_t)a * n + w] - ((a - hh) & l->byte.am) * ((w - hh) & l->byte.wm) - l->byte.c);
-            e = dbg_malloc((void **)&l->img8_dev, err.size());
-            if (e == hipSuccess) e = hipMemcpy(l->img8_dev, err.data(), err.size(), hipMemcpyHostToDevice);
-        }
+        if (e == hipSuccess && l->byte.found) l->img8_dev = l->lut16_dev[half] + entries;
         if (e != hipSuccess) {
-            if (l->img8_dev) (void)hipFree(l->img8_dev);
             for (int j = 0; j < 2; ++j) {
                 if (l->img_dev[j]) (void)hipFree(l->img_dev[j]);
                 if (l->lut16_dev[j]) (void)hipFree(l->lut16_dev[j]);
@@ -107,7 +105,6 @@ int adapt_lut_destroy(adapt_lut *lut) {
         if (lut->img_dev[j]) (void)hipFree(lut->img_dev[j]);
         if (lut->lut16_dev[j]) (void)hipFree(lut->lut16_dev[j]);
     }
-    if (lut->img8_dev) (void)hipFree(lut->img8_dev);
     delete lut;
     scratch_table_gone(device);
     return ADAPT_OK;
