@@ -475,7 +475,7 @@ def network_roofline(cfg_id, bits, macs, ms_per_step, ceilings, model_peak, gnet
     t = gathered / g16 + (macs - gathered) / lds
     dom = {3: "lut_byte_kernel (19 layers of 11 - 20 us; the 32- and 64-channel ones in slices joined in the kernel)",
            4: "lut_rows_kernel (recurrent step: product + cell, 100 launches)",
-           5: "lut_byte_kernel<%d, 8, 1>" % (2 if bits == 8 else 1),
+           5: "lut_byte_kernel<%d, 8, 2>" % (2 if bits == 8 else 1),
            6: "lut_grouped_tiled_kernel + lut_byte_kernel",
            7: "lut_rows_kernel (recurrent step: product + cell, 100 launches)"}[cfg_id]
     bound = {4: "lds_gather16 (recurrence) + lds_read (input products)", 6: "lds_gather16 (depthwise) + lds_read (pointwise)",
@@ -608,7 +608,7 @@ def main():
             table_bytes = 256 << 8
             lds_bytes = 1.0 * macs                                          # one 16-byte read per 16 lookups
             fill_bytes = float(wgs) * (steps_k / ksplit) * (table_bytes + rpw * 16)  # tables into LDS + activations into registers, per step
-            mfma_insts = macs / 1024.0 * (1 + 1 / 16)                       # one matrix instruction per 64 reads; the exact product
+            mfma_insts = macs / 1024.0 * (1 / 2 + 1 / 8)                    # a sparse instruction adds two reads of a wave; the exact product, one for eight reads
             hbm_bytes = 32 * 34 * 34 * 64 + 4 * steps_k * table_bytes + 4.0 * 32 * 64 * 32 * 32      # padded copy + tables + fp32 output
             hbm_bytes += 2.0 * 64 * rpw * (wgs - wgs // ksplit)             # sums that slices leave behind (64 B per row), written and read
             res_us = dict(lds_read=lds_bytes / (ceilings["lds_read_b128_TB_s"] * 1e12) * 1e6,

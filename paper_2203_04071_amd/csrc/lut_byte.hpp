@@ -59,8 +59,8 @@
 // (32 KB); measured 2850 to 3300 (odd and even steps; 4700 before reads, exact product and copies were interleaved and paired).  With
 // 64 KB tables and R <= 4 the path that fills LDS (46 B per clock and compute unit) is as long.  Measured against the two-digit form
 // (lut_quad.hpp): 3 x 3, 64 -> 64 channels, 32 images of 32 x 32, 8 bits: 41 -> 30 us; against the
-// 128-byte-line kernel on odd sizes (100 -> 200 channels, stride 2, 27 -> 14 pixels wide, 50 images): 271 -> 74 us.  A launch costs
-// 4500 clocks before its first step (first table).
+// 128-byte-line kernel on odd sizes (100 -> 200 channels, stride 2, 27 -> 14 pixels wide, 50 images): 271 -> 64 us, 52 with a table that
+// drops two bits of the activation.  A launch costs 4500 clocks before its first step (first table).
 //
 // Split inner dimension: ksplit workgroups share a tile.  All but the last to arrive (a counter per tile) leave their sums
 // in memory, the last one adds them to its own and finishes; its slice is a little longer, so that the others have stored
