@@ -530,23 +530,28 @@ __global__ __launch_bounds__(STE_THREADS, 2) void ste_dx_kernel(const SteDxParam
 // ---- the same two products on 16-bit matrix instructions ----------------------------------------------------------
 // Operands of up to 9 bits: a code is a bf16 number, so one operand of either product needs no more than that, and the gradient is
 // the sum of three bf16 numbers (24 bits).  Every product of a piece and a code is exact in fp32, sums are fp32: nothing is
-// rounded that the fp32 form does not round (there a fake-quantised value is rounded; here the sum is scaled once).  The first
-// pieces, which carry the sum, have an accumulator of their own: it is rounded once for 16 products.  Three bf16
+// rounded that the fp32 form does not round (there a fake-quantised value is rounded; here the sum is scaled once).  Each
+// piece has an accumulator of its own: that of the first, which carries the sum, is rounded once for 16 products, and the others
+// hold their piece times 2^8 and 2^16, about the size of the first.  (Unscaled, the third piece of a gradient below 2^-110 is
+// subnormal and has fewer than eight bits: 2-norm of the error 5e-6 at 1e-35.)  Three bf16
 // instructions replace eight fp32 ones of twice their length.  A code carries the power of two of its scale, so that products have
 // the range they have in fp32; what is left of the scale, in [1, 2), multiplies the sum.
 // Error against 64 bits (2-norm of the difference over that of the result), fp32 form -> this one: weight gradient 1.8e-7 -> 1.4e-7, input
 // gradient 1.2e-7 -> 7.3e-8 (64 -> 64 channels, 3 x 3, 8 images of 32 x 32); 13 other layers likewise or better.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
-// v = the sum of the three numbers whose upper halves are p[0..2] (infinities and NaN: all of it in the first)
+// v = p[0] + 2^-8 p[1] + 2^-16 p[2], of whose words the upper halves count.  Exact for every v, subnormal ones included, and none of the
+// three is larger than 2^(exponent of v + 1) (2^-123 where v is subnormal).  An infinity is the first piece alone; a NaN is one in the second piece, whatever is left of it in
+// the first.
 __device__ __forceinline__ void ste_split(float v, uint32_t (&p)[3]) {
-    const uint32_t u = __float_as_uint(v);
-    const bool finite = fabsf(v) < __builtin_inff();
-    p[0] = v != v ? 0x7fc00000u : u & 0xffff0000u;
-    const float r = finite ? v - __uint_as_float(u & 0xffff0000u) : 0.0f;
+    p[0] = __float_as_uint(v) & 0xffff0000u;
+    const float r = fabsf(v) == __builtin_inff() ? 0.0f : (v - __uint_as_float(p[0])) * 0x1p8f;
     p[1] = __float_as_uint(r) & 0xffff0000u;
-    p[2] = __float_as_uint(r - __uint_as_float(p[1]));
+    p[2] = __float_as_uint((r - __uint_as_float(p[1])) * 0x1p8f);
 }
+
+// the value of three sums of such pieces
+__device__ __forceinline__ float ste_join(float first, float second, float third) { return first + (second * 0x1p-8f + third * 0x1p-16f); }
 
 // upper halves of a and b as one word, a's in the lower half
 __device__ __forceinline__ uint32_t ste_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
@@ -663,9 +668,9 @@ __global__ __launch_bounds__(STE_THREADS) void ste_dw16_kernel(const SteDwParams
         const uint2 lo = *reinterpret_cast<const uint2 *>(row), hi = *reinterpret_cast<const uint2 *>(row + 2);
         return __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
     };
-    f32x16_t acc, low;              // sums of the first pieces, of the others
+    f32x16_t acc[3];                // one for each piece
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = low[v] = 0.0f;
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = acc[2][v] = 0.0f;
     const int ch0 = blockIdx.z * p.cps, chunks = max(0, min((p.R + STE_TR - 1) / STE_TR, ch0 + p.cps) - ch0);
     if (chunks > 0) {
         fetch(ch0 * STE_TR);
@@ -688,7 +693,7 @@ __global__ __launch_bounds__(STE_THREADS) void ste_dw16_kernel(const SteDwParams
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-            for (int q = 2; q >= 0; --q) (q ? low : acc) = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][q], b[ks], q ? low : acc, 0, 0, 0);
+            for (int q = 0; q < 3; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][q], b[ks], acc[q], 0, 0, 0);
         if (more) stash(cur ^ 1);
         __syncthreads();
     }
@@ -697,7 +702,7 @@ __global__ __launch_bounds__(STE_THREADS) void ste_dw16_kernel(const SteDwParams
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int i = i0 + wi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (i < p.I && j < p.J) cout[(size_t)i * (size_t)p.J + (size_t)j] = acc[v] + low[v];
+        if (i < p.I && j < p.J) cout[(size_t)i * (size_t)p.J + (size_t)j] = ste_join(acc[0][v], acc[1][v], acc[2][v]);
     }
 }
 
@@ -777,9 +782,9 @@ __global__ __launch_bounds__(STE_THREADS, 2) void ste_dx16_kernel(const SteDx16P
             *reinterpret_cast<uint4 *>(&Bs[buf][q][lane][4 * wave]) =
                 make_uint4(ste_halves(s[0][q], s[1][q]), ste_halves(s[2][q], s[3][q]), ste_halves(s[4][q], s[5][q]), ste_halves(s[6][q], s[7][q]));
     };
-    f32x16_t acc, low, tot;
+    f32x16_t acc[3], tot;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = low[v] = tot[v] = 0.0f;
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = acc[2][v] = tot[v] = 0.0f;
     int left = cpt;                 // chunks of this tap that are still to be multiplied
     auto chunk = [&](int ch, auto set_c) {                  // see ste_dx_kernel
         constexpr int S = decltype(set_c)::value;
@@ -794,15 +799,15 @@ __global__ __launch_bounds__(STE_THREADS, 2) void ste_dx16_kernel(const SteDx16P
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-            for (int q = 2; q >= 0; --q)
-                (q ? low : acc) = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ks ? a1 : a0), b[ks][q], q ? low : acc, 0, 0, 0);
+            for (int q = 0; q < 3; ++q)
+                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ks ? a1 : a0), b[ks][q], acc[q], 0, 0, 0);
         if (ch + 1 < chunks) stash(1 - S, rb[1 - S], inside[1 - S], from_o[1 - S]);
         if (--left == 0) {
             left = cpt;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                tot[v] += acc[v] + low[v];
-                acc[v] = low[v] = 0.0f;
+                tot[v] += ste_join(acc[0][v], acc[1][v], acc[2][v]);
+                acc[0][v] = acc[1][v] = acc[2][v] = 0.0f;
             }
         }
         __syncthreads();

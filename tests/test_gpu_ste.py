@@ -380,6 +380,24 @@ def test_ste_conv2d_backward_over_the_range_of_scales(B, scale, size):
     check(dw, ow, bw, 2 * 5 * 6)
 
 
+@pytest.mark.parametrize("exponent", [100, -100, -111, -116, -120])
+def test_ste_conv2d_backward_does_not_depend_on_the_size_of_the_gradient(B, exponent):
+    """A power of two on dY is the same power on the gradients: every operation of a sum of products commutes with it as long as nothing overflows
+    or is subnormal on the way (scales of 1024 keep the results away from that).  Tolerance: where pieces of dY become subnormal they are other
+    pieces of the same sum, so the ten additions of an element (one per tap, the last scaled) may each round the other way: 10 x 2^-24."""
+    rng = np.random.default_rng(11)
+    s = np.float32(1024.0)
+    x, w = (rng.integers(-140, 141, (4, 36, 9, 8)) * s).astype(np.float32), (rng.integers(-140, 141, (40, 36, 3, 3)) * s).astype(np.float32)
+    factor = np.float32(2.0 ** -exponent)
+    # 24 bits each, from 2^-6 to 2^3: none is subnormal at 2^-120
+    dy = (np.ldexp(1.0 + rng.random((4, 40, 9, 8)), rng.integers(-6, 3, (4, 40, 9, 8))) * rng.choice([-1.0, 1.0], (4, 40, 9, 8))).astype(np.float32)
+    args = ((1, 1), (1, 1), (1, 1), s, s, 8)
+    want = B.adapt_ste_conv2d_backward_f32(dev(dy), dev(x), dev(w), *args)
+    got = B.adapt_ste_conv2d_backward_f32(dev(dy / factor), dev(x), dev(w), *args)
+    for a, b in zip(got, want):
+        assert (a * float(factor) - b).abs().max() <= 10 * U * b.abs().max(), float((a * float(factor) - b).abs().max() / b.abs().max())
+
+
 def test_ste_conv2d_backward_keeps_infinities_to_their_pixels(B):
     """An infinite or NaN gradient reaches the pixels under its taps and nothing else: padding and tile remainders add nothing."""
     rng = np.random.default_rng(3)
