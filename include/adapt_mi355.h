@@ -482,10 +482,13 @@ int adapt_ste_linear_backward_f32(const float *dy_dev, const float *x_dev, const
  *     db[o]            = sum_{n,oy,ox} dy[n][o][oy][ox]
  * dy_dev [N][Cout][Ho][Wo], x_dev [N][Cin][H][W], w_dev [Cout][Cin][kh][kw]: fp32 device pointers, dense; geometry as in
  * adapt_approx_conv2d.  dx_dev, dw_dev, db_dev: shapes of x, w and [Cout]; fully overwritten; NULL = not computed; none
- * may alias an input.  workspace_dev: device memory of at least the number of bytes that
+ * may alias an input.  workspace_dev: device memory of the number of bytes that
  * adapt_ste_conv2d_backward_workspace reports for the same arguments (want_dx / want_dw: whether dx_dev / dw_dev are
  * given), aligned to 256 bytes, owned by the caller, contents undefined afterwards; it holds dy as rows, the gradient of
- * the unfolded input and partial sums (the unfolded input itself is read from x_dev, never written).  fp32 sums (matrix instructions for the products, a fixed tap order for dx).  Asynchronous on `stream`, no
+ * the unfolded input and partial sums (the unfolded input itself is read from x_dev, never written).  A call also takes less, without
+ * the fastest form of dw, down to 4 bytes for every element of dy, of x with channels rounded up to 4 (dw), of w likewise (dx),
+ * of the unfolded input (dx, strides above 1), each rounded up to 256 bytes, and for 768 * 64 * 64 partial sums (or the elements
+ * of w, channels rounded up to 4, if these are more).  fp32 sums (matrix instructions for the products, a fixed tap order for dx).  Asynchronous on `stream`, no
  * allocation.  Errors: ADAPT_ERR_INVALID_ARGUMENT (pointers, geometry, bits, scales, workspace too small or misaligned),
  * ADAPT_ERR_UNSUPPORTED (N Ho Wo above 65535 * 64), ADAPT_ERR_HIP. */
 int adapt_ste_conv2d_backward_workspace(int N, int Cin, int H, int W, int Cout, int kh, int kw, int stride_h, int stride_w, int pad_h,

@@ -66,21 +66,26 @@ void launch_ste_gemm(const adapt::SteParams &p_in, bool a_t, bool aligned, hipSt
 }
 
 // Weight gradient of a convolution on bf16 instructions (ste_dw16_kernel): partial sums as launch_ste_gemm makes them, 64 x 64 outputs
-// per workgroup and two workgroups per compute unit where the contraction is long enough.  o, so: mask; scale: of the sums.
-void launch_ste_dw16(const adapt::SteDwParams &p_in, const float *o, float so, float Q, float scale, float *dw, hipStream_t s, float *partials, int tap0, int all_taps) {
-    adapt::SteDwParams p = p_in;
-    const int cus = device_cus(), chunks = (p.R + adapt::STE_TR - 1) / adapt::STE_TR;
-    dim3 grid((unsigned)((p.J + 63) / 64), (unsigned)((p.I + 63) / 64), 1);
+// per workgroup and two workgroups per compute unit where the contraction of R rows is long enough.
+dim3 ste_dw16_grid(int I, int J, int R, int *chunks_per_slice) {
+    const int cus = device_cus(), chunks = (R + adapt::STE_TR - 1) / adapt::STE_TR;
+    dim3 grid((unsigned)((J + 63) / 64), (unsigned)((I + 63) / 64), 1);
     const long long tiles = (long long)grid.x * grid.y;
-    p.cps = chunks;
+    *chunks_per_slice = chunks;
     if (tiles < cus && chunks >= 8) {
         int want = (int)((2 * cus + tiles - 1) / tiles);
         if (want > chunks / 4) want = chunks / 4;
         if (want >= 2) {
-            p.cps = (chunks + want - 1) / want;
-            grid.z = (unsigned)((chunks + p.cps - 1) / p.cps);
+            *chunks_per_slice = (chunks + want - 1) / want;
+            grid.z = (unsigned)((chunks + *chunks_per_slice - 1) / *chunks_per_slice);
         }
     }
+    return grid;
+}
+// o, so: mask; scale: of the sums
+void launch_ste_dw16(const adapt::SteDwParams &p_in, const float *o, float so, float Q, float scale, float *dw, hipStream_t s, float *partials, int tap0, int all_taps) {
+    adapt::SteDwParams p = p_in;
+    const dim3 grid = ste_dw16_grid(p.I, p.J, p.R, &p.cps);
     p.c = partials;
     adapt::ste_dw16_kernel<<<grid, adapt::STE_THREADS, 0, s>>>(p);
     const size_t n = (size_t)p.I * (size_t)p.J, blocks = (n + 255) / 256;
@@ -149,9 +154,12 @@ struct SteConvPlan {
     adapt::SteConvGeo g;
     long long M, K;
     bool direct;                // stride 1: the input gradient is one product (ste_dx_kernel, ste_dx16_kernel)
-    bool padded_weights;        // there is room for the weights as ste_dx16_kernel reads them
     int dw_rows;                // filter rows per product of the weight gradient: all, unless there are more than MAX_COLS columns (tap, channel rounded up to 4)
-    size_t rows_bytes, col_bytes, wp_bytes, xq_bytes, part_bytes, total;
+    size_t rows_bytes, col_bytes, wp_bytes, xq_bytes, part_bytes, total;    // of the forms on fp32 instructions: what a call needs in any case
+    // Weight gradient on bf16 instructions: its copies and sums, which nothing needs once it is finished, lie over everything else.
+    // all: with room for them; only layers with more output than input channels need more.
+    int lda;
+    size_t pieces_bytes, codes_bytes, sums_bytes, all;
 };
 int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int kh, int kw, int stride_h, int stride_w, int pad_h, int pad_w,
                   int dil_h, int dil_w, bool want_dx, bool want_dw, const char *who) {
@@ -177,9 +185,7 @@ int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int k
     g.dHoWo = fast_div((uint32_t)(Ho * Wo)); g.dC = fast_div((uint32_t)Cin); g.dW = fast_div((uint32_t)W); g.dHW = fast_div((uint32_t)(H * W));
     g.dsh = fast_div((uint32_t)stride_h); g.dsw = fast_div((uint32_t)stride_w);
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-    // rows of the gradient: fp32, or three bf16 pieces of whole groups of four channels
-    const size_t row16 = (size_t)(((long long)Cout + 3) / 4 * 4) * 6, row32 = (size_t)Cout * sizeof(float);
-    pl->rows_bytes = up((size_t)pl->M * (want_dw && row16 > row32 ? row16 : row32));
+    pl->rows_bytes = up((size_t)pl->M * Cout * sizeof(float));
     const long long row_cols = (long long)kw * Cp;
     if (want_dw && row_cols > 0x7fffff00LL)
         return fail(ADAPT_ERR_UNSUPPORTED, "%s: a filter row is limited to 2^31 - 256 weights (channels rounded up to 4)", who);
@@ -190,12 +196,17 @@ int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int k
     pl->xq_bytes = want_dw ? up((size_t)N * H * W * (size_t)Cp * sizeof(float)) : 0;
     const size_t dw_cols = (size_t)pl->dw_rows * (size_t)row_cols;
     pl->part_bytes = up((want_dw && Cout * dw_cols > STE_PARTIAL_FLOATS ? Cout * dw_cols : STE_PARTIAL_FLOATS) * sizeof(float));
-    // weights for the input gradient: fp32 [taps][Cout][Cp], or bf16 with Cout rounded up to 32 and the channels to 64
-    const size_t wp16 = pl->direct ? (size_t)kh * kw * (((size_t)Cout + 31) / 32 * 32) * (((size_t)Cin + 63) / 64 * 64) * 2 : 0, wp32 = (size_t)Cout * cols * sizeof(float);
-    // (the padding of narrow layers is not worth gigabytes for filters of millions of taps)
-    pl->padded_weights = pl->direct && (wp16 <= wp32 * 4 || wp16 <= ((size_t)64 << 20));
-    pl->wp_bytes = want_dx ? up(pl->padded_weights && wp16 > wp32 ? wp16 : wp32) : 0;
-    pl->total = pl->rows_bytes + pl->col_bytes + pl->wp_bytes + pl->xq_bytes + pl->part_bytes;
+    pl->wp_bytes = want_dx ? up((size_t)Cout * cols * sizeof(float)) : 0;
+    pl->total = pl->all = pl->rows_bytes + pl->col_bytes + pl->wp_bytes + pl->xq_bytes + pl->part_bytes;
+    if (want_dw && pl->M > 0) {
+        int cps;
+        pl->lda = (int)(((long long)Cout + 3) / 4 * 4);
+        pl->pieces_bytes = up((size_t)pl->M * pl->lda * 6);
+        pl->codes_bytes = up((size_t)N * H * W * (size_t)Cp * 2);
+        pl->sums_bytes = up((size_t)ste_dw16_grid(Cout, (int)dw_cols, (int)pl->M, &cps).z * Cout * dw_cols * sizeof(float));
+        const size_t need = pl->pieces_bytes + pl->codes_bytes + pl->sums_bytes;
+        pl->all = need > pl->all ? need : pl->all;
+    }
     return ADAPT_OK;
 }
 }  // namespace
@@ -209,7 +220,7 @@ int adapt_ste_conv2d_backward_workspace(int N, int Cin, int H, int W, int Cout, 
     SteConvPlan pl;
     int rc = ste_conv_plan(&pl, N, Cin, H, W, Cout, kh, kw, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, want_dx != 0, want_dw != 0, who);
     if (rc) return rc;
-    *bytes = pl.total;
+    *bytes = pl.all;
     return ADAPT_OK;
 }
 
@@ -250,7 +261,7 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
     float *dcol = reinterpret_cast<float *>(ws + pl.rows_bytes);
     float *wp = reinterpret_cast<float *>(ws + pl.rows_bytes + pl.col_bytes);           // the weights in the order that the input gradient reads
     float *xq = reinterpret_cast<float *>(ws + pl.rows_bytes + pl.col_bytes + pl.wp_bytes);
-    float *partials = reinterpret_cast<float *>(ws + pl.total - pl.part_bytes);      // used by one kernel pair at a time (stream order)
+    float *partials = reinterpret_cast<float *>(ws + pl.total - pl.part_bytes);         // used by one kernel pair at a time (stream order)
     const int M = (int)pl.M, K = (int)pl.K, P = g.Ho * g.Wo, HW = H * W, Cp = (int)g.dCp.d;
     const size_t col_n = (size_t)M * K;     // elements of dcol
     auto channels_last = [&](const float *src, float *dst, int C, int pixels, int ld, float scale) {
@@ -262,11 +273,14 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
     // leaves none to the codes, takes the fp32 form).  64 -> 64 channels, 3 x 3, 32 images of 32 x 32: weight gradient 43 -> 28 us,
     // input gradient 42 -> 28 us, with errors against 64 bits of 0.4 to 0.9 of the fp32 form (2-norms of 4e-8 to 2e-7 over 14 layers).
     const bool codes16 = bits <= 9;
-    const bool dw16 = codes16 && s_x > 1e-30f && s_x < 1e30f, dx16 = codes16 && s_w > 1e-30f && s_w < 1e30f;
-    if (dw_dev && dw16) {
-        const int lda = (Cout + 3) / 4 * 4;
+    const bool dw16 = dw_dev && codes16 && s_x > 1e-30f && s_x < 1e30f && workspace_bytes >= pl.pieces_bytes + pl.codes_bytes + pl.sums_bytes;
+    const bool dx16 = codes16 && s_w > 1e-30f && s_w < 1e30f;
+    if (dw16) {
+        const int lda = pl.lda;
         const size_t plane = (size_t)M * lda;
-        uint16_t *const pieces = reinterpret_cast<uint16_t *>(rows), *const codes = reinterpret_cast<uint16_t *>(xq);
+        char *const copies = ws;
+        uint16_t *const pieces = reinterpret_cast<uint16_t *>(copies), *const codes = reinterpret_cast<uint16_t *>(copies + pl.pieces_bytes);
+        float *const sums = reinterpret_cast<float *>(copies + pl.pieces_bytes + pl.codes_bytes);
         float pow2, rest;
         split_scale(s_x, &pow2, &rest);
         auto copy16 = [&](const float *src, uint16_t *dst, int C, int pixels, int ld, float scale, float factor) {
@@ -284,7 +298,7 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
             p.g.kh = kh - ky < pl.dw_rows ? kh - ky : pl.dw_rows;
             p.g.ph = g.ph - ky * g.dh;
             p.J = p.g.kh * kw * Cp;
-            launch_ste_dw16(p, w_dev, s_w, Q, rest, dw_dev, s, partials, ky * kw, kh * kw);
+            launch_ste_dw16(p, w_dev, s_w, Q, rest, dw_dev, s, sums, ky * kw, kh * kw);
             HIP_TRY(hipGetLastError());
         }
     }
@@ -308,16 +322,18 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
             HIP_TRY(hipGetLastError());
         }
     }
-    if (dx_dev && pl.direct && dx16 && pl.padded_weights) {
+    // weights for the input gradient: fp32 [taps][Cout][Cp], or bf16 with Cout rounded up to 32 and the channels to 64, where the
+    // workspace holds that (and the padding of narrow layers is not gigabytes, for filters of millions of taps)
+    const size_t Op = ((size_t)Cout + 31) / 32 * 32, Cq = ((size_t)Cin + 63) / 64 * 64, wq_bytes = (size_t)kh * kw * Op * Cq * 2;
+    if (dx_dev && pl.direct && dx16 && wq_bytes <= pl.total && (wq_bytes <= pl.wp_bytes * 4 || wq_bytes <= ((size_t)64 << 20))) {
         float pow2, rest;
         split_scale(s_w, &pow2, &rest);
-        const int Op = (Cout + 31) / 32 * 32, Cq = (Cin + 63) / 64 * 64;
-        uint4 *const wq = reinterpret_cast<uint4 *>(wp);
-        adapt::ste_weights16_kernel<<<ew_grid((size_t)kh * kw * (Op / 8) * Cq), 256, 0, s>>>(w_dev, wq, Cout, Cin, Op, Cq, kh * kw, s_w, Q, pow2);
+        uint4 *const wq = reinterpret_cast<uint4 *>(ws);        // (the weight gradient is done with what it had there)
+        adapt::ste_weights16_kernel<<<ew_grid((size_t)kh * kw * (Op / 8) * Cq), 256, 0, s>>>(w_dev, wq, Cout, Cin, (int)Op, (int)Cq, kh * kw, s_w, Q, pow2);
         HIP_TRY(hipGetLastError());
         adapt::SteDx16Params p{};
         p.dy = dy_dev; p.x = x_dev; p.wq = wq; p.dx = dx_dev;
-        p.pixels = N * HW; p.og = Op / 8; p.Cq = Cq; p.so = s_x; p.Q = Q; p.scale = rest; p.g = g;
+        p.pixels = N * HW; p.og = (int)(Op / 8); p.Cq = (int)Cq; p.so = s_x; p.Q = Q; p.scale = rest; p.g = g;
         adapt::ste_dx16_kernel<<<dim3((unsigned)((p.pixels + 63) / 64), (unsigned)((Cin + 63) / 64)), adapt::STE_THREADS, 0, s>>>(p);
         HIP_TRY(hipGetLastError());
     } else if (dx_dev && pl.direct) {

@@ -380,6 +380,53 @@ def test_ste_conv2d_backward_over_the_range_of_scales(B, scale, size):
     check(dw, ow, bw, 2 * 5 * 6)
 
 
+WORKSPACE_CASES = [
+    # N, C, H, W, O, kh, kw, stride, pad, whether the copies on 16-bit codes need more than the fp32 form
+    (4, 64, 16, 16, 64, 3, 3, (1, 1), (1, 1), False),
+    (5, 6, 15, 16, 10, 3, 3, (2, 2), (1, 1), False),            # behind the rows that the strided input gradient reads
+    (3, 1, 128, 160, 160, 3, 3, (1, 1), (1, 1), True),
+    (6, 5, 140, 150, 250, 1, 1, (2, 2), (0, 0), True),          # strided
+    (2, 70, 6, 5, 3, 1, 1, (1, 1), (0, 0), False),              # padded weights larger than the fp32 form's
+]
+
+
+@pytest.mark.parametrize("want", [("dx", "dw", "db"), ("dw",), ("dx",)])
+@pytest.mark.parametrize("case", WORKSPACE_CASES)
+def test_ste_conv2d_backward_stays_inside_its_workspace(B, case, want):
+    """A call takes a workspace of the fp32 form: 4 bytes for every element of dy, of the unfolded gradient (strides), of the weights and of x with
+    channels rounded up to four, and 12 MB of partial sums; more is asked for only where there are more output than input channels.  Nothing is
+    written beyond either."""
+    import ctypes
+    N, C, H, W, O, kh, kw, stride, pad, more = case
+    rng = np.random.default_rng(sum(case[:7]))
+    Ho, Wo = (H + 2 * pad[0] - kh) // stride[0] + 1, (W + 2 * pad[1] - kw) // stride[1] + 1
+    x, dy = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((N, O, Ho, Wo)).astype(np.float32)
+    w = (rng.standard_normal((O, C, kh, kw)) * 0.1).astype(np.float32)
+    s_x, s_w, bits = np.float32(0.02), np.float32(0.002), 8
+    up = lambda b: (b + 255) // 256 * 256
+    Cp, dx_too, dw_too = (C + 3) // 4 * 4, "dx" in want, "dw" in want
+    least = up(4 * N * Ho * Wo * O) + 4 * 768 * 64 * 64 + (up(4 * N * H * W * Cp) if dw_too else 0) + (up(4 * O * kh * kw * Cp) if dx_too else 0)
+    least += up(4 * N * Ho * Wo * C * kh * kw) if dx_too and stride != (1, 1) else 0
+    geo, asked = (N, C, H, W, O, kh, kw, *stride, *pad, 1, 1), ctypes.c_size_t(0)
+    assert B.load().adapt_ste_conv2d_backward_workspace(*geo, dx_too, dw_too, ctypes.byref(asked)) == 0
+    assert asked.value > least if more and dw_too else asked.value == least
+    wants = ste.ste_conv2d_backward(dy, x, w, stride, pad, (1, 1), s_x, s_w, bits)
+    bounds = ste.ste_conv2d_backward(dy, x, w, stride, pad, (1, 1), s_x, s_w, bits, absolute=True)
+    dyd, xd, wd = dev(dy), dev(x), dev(w)
+    for size in {least, asked.value}:
+        memory = torch.full((size + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+        grads = [torch.empty_like(xd), torch.empty_like(wd), torch.empty(O, device="cuda")]
+        to = [g.data_ptr() if name in want else None for name, g in zip(("dx", "dw", "db"), grads)]
+        call = lambda bytes: B.load().adapt_ste_conv2d_backward_f32(dyd.data_ptr(), xd.data_ptr(), wd.data_ptr(), *geo, ctypes.c_float(s_x), ctypes.c_float(s_w), bits,
+                                                                    *to, memory.data_ptr(), bytes, torch.cuda.current_stream().cuda_stream)
+        assert call(least - 1) == -1 and call(size) == 0
+        torch.cuda.synchronize()
+        assert (memory[size:] == 0x5a).all()
+        for name, g, e, b, R in zip(("dx", "dw", "db"), grads, wants, bounds, (O + kh * kw, N * Ho * Wo, N * Ho * Wo)):
+            if name in want:
+                check(g, e, b, R)
+
+
 @pytest.mark.parametrize("exponent", [100, -100, -111, -116, -120])
 def test_ste_conv2d_backward_does_not_depend_on_the_size_of_the_gradient(B, exponent):
     """A power of two on dY is the same power on the gradients: every operation of a sum of products commutes with it as long as nothing overflows
