@@ -156,10 +156,10 @@ struct SteConvPlan {
     bool direct;                // stride 1: the input gradient is one product (ste_dx_kernel, ste_dx16_kernel)
     int dw_rows;                // filter rows per product of the weight gradient: all, unless there are more than MAX_COLS columns (tap, channel rounded up to 4)
     size_t rows_bytes, col_bytes, wp_bytes, xq_bytes, part_bytes, total;    // of the forms on fp32 instructions: what a call needs in any case
-    // Weight gradient on bf16 instructions: its copies and sums, which nothing needs once it is finished, lie over everything else.
-    // all: with room for them; only layers with more output than input channels need more.
+    // Weight gradient on bf16 instructions: its copies and sums, which nothing needs once it is finished, lie over everything but the rows
+    // that a strided layer's input gradient reads (kept_bytes).  all: with room for them; only layers with more output than input channels need more.
     int lda;
-    size_t pieces_bytes, codes_bytes, sums_bytes, all;
+    size_t kept_bytes, pieces_bytes, codes_bytes, sums_bytes, all;
 };
 int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int kh, int kw, int stride_h, int stride_w, int pad_h, int pad_w,
                   int dil_h, int dil_w, bool want_dx, bool want_dw, const char *who) {
@@ -201,10 +201,11 @@ int ste_conv_plan(SteConvPlan *pl, int N, int Cin, int H, int W, int Cout, int k
     if (want_dw && pl->M > 0) {
         int cps;
         pl->lda = (int)(((long long)Cout + 3) / 4 * 4);
+        pl->kept_bytes = want_dx && !pl->direct ? pl->rows_bytes : 0;
         pl->pieces_bytes = up((size_t)pl->M * pl->lda * 6);
         pl->codes_bytes = up((size_t)N * H * W * (size_t)Cp * 2);
         pl->sums_bytes = up((size_t)ste_dw16_grid(Cout, (int)dw_cols, (int)pl->M, &cps).z * Cout * dw_cols * sizeof(float));
-        const size_t need = pl->pieces_bytes + pl->codes_bytes + pl->sums_bytes;
+        const size_t need = pl->kept_bytes + pl->pieces_bytes + pl->codes_bytes + pl->sums_bytes;
         pl->all = need > pl->all ? need : pl->all;
     }
     return ADAPT_OK;
@@ -273,24 +274,24 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
     // leaves none to the codes, takes the fp32 form).  64 -> 64 channels, 3 x 3, 32 images of 32 x 32: weight gradient 43 -> 28 us,
     // input gradient 42 -> 28 us, with errors against 64 bits of 0.4 to 0.9 of the fp32 form (2-norms of 4e-8 to 2e-7 over 14 layers).
     const bool codes16 = bits <= 9;
-    const bool dw16 = dw_dev && codes16 && s_x > 1e-30f && s_x < 1e30f && workspace_bytes >= pl.pieces_bytes + pl.codes_bytes + pl.sums_bytes;
+    const bool dw16 = dw_dev && codes16 && s_x > 1e-30f && s_x < 1e30f && workspace_bytes >= pl.kept_bytes + pl.pieces_bytes + pl.codes_bytes + pl.sums_bytes;
     const bool dx16 = codes16 && s_w > 1e-30f && s_w < 1e30f;
     if (dw16) {
         const int lda = pl.lda;
         const size_t plane = (size_t)M * lda;
-        char *const copies = ws;
+        char *const copies = ws + pl.kept_bytes;
         uint16_t *const pieces = reinterpret_cast<uint16_t *>(copies), *const codes = reinterpret_cast<uint16_t *>(copies + pl.pieces_bytes);
         float *const sums = reinterpret_cast<float *>(copies + pl.pieces_bytes + pl.codes_bytes);
         float pow2, rest;
         split_scale(s_x, &pow2, &rest);
-        auto copy16 = [&](const float *src, uint16_t *dst, int C, int pixels, int ld, float scale, float factor) {
+        auto copy16 = [&](const float *src, uint16_t *dst, int C, int pixels, int ld, float scale, float factor, float *as_rows) {
             const long long blocks = (pixels + 31LL) / 32;
             const dim3 grid((unsigned)(blocks < (1 << 22) ? blocks : (1 << 22)), (unsigned)((ld + 63) / 64), (unsigned)(N < 65535 ? N : 65535));
-            adapt::ste_channels_last16_kernel<<<grid, 256, 0, s>>>(src, dst, N, C, pixels, ld, scale, Q, factor, plane);
+            adapt::ste_channels_last16_kernel<<<grid, 256, 0, s>>>(src, dst, N, C, pixels, ld, scale, Q, factor, plane, as_rows);
         };
-        copy16(dy_dev, pieces, Cout, P, lda, 0.0f, 1.0f);
+        copy16(dy_dev, pieces, Cout, P, lda, 0.0f, 1.0f, pl.kept_bytes ? rows : nullptr);
         HIP_TRY(hipGetLastError());
-        copy16(x_dev, codes, Cin, HW, Cp, s_x, pow2);
+        copy16(x_dev, codes, Cin, HW, Cp, s_x, pow2, nullptr);
         HIP_TRY(hipGetLastError());
         adapt::SteDwParams p{};
         p.a = pieces; p.b = codes; p.plane = plane; p.I = Cout; p.R = M; p.lda = lda; p.g = g;
@@ -301,8 +302,7 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
             launch_ste_dw16(p, w_dev, s_w, Q, rest, dw_dev, s, sums, ky * kw, kh * kw);
             HIP_TRY(hipGetLastError());
         }
-    }
-    if ((dw_dev && !dw16) || (dx_dev && !pl.direct)) {
+    } else if (dw_dev || (dx_dev && !pl.direct)) {
         channels_last(dy_dev, rows, Cout, P, Cout, 0.0f);
         HIP_TRY(hipGetLastError());
     }

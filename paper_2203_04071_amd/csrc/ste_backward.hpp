@@ -561,8 +561,9 @@ __device__ __forceinline__ uint32_t ste_code16(float x, float s, float Q, float 
 
 // src [N][C][P] -> dst [N][P][ld] bf16 (zeros in channels C .. ld - 1): codes with (s, Q) times pow2 if s > 0, else three planes of pieces,
 // `plane` elements apart.  The walk of ste_channels_last_kernel; a thread writes two channels at once (ld is a multiple of 4).
+// rows: the values as they are too, [N][P][C], or nullptr (a launch of its own for them cost a layer with strides 2 us).
 __global__ __launch_bounds__(256) void ste_channels_last16_kernel(const float *__restrict__ src, uint16_t *__restrict__ dst, int N, int C, int P, int ld, float s, float Q,
-                                                                  float pow2, size_t plane) {
+                                                                  float pow2, size_t plane, float *__restrict__ rows) {
     __shared__ float tile[64][33];
     const int c0 = blockIdx.y * 64, tid = threadIdx.x, blocks = (int)((P + 31LL) / 32);
     for (int n = blockIdx.z, b = blockIdx.x; n < N; b += gridDim.x) {
@@ -602,6 +603,13 @@ __global__ __launch_bounds__(256) void ste_channels_last16_kernel(const float *_
                         for (int i = 0; i < 3; ++i) to[i * (plane / 2)] = ste_halves(a[i], d[i]);
                     }
                 }
+            }
+        }
+        if (rows && c0 + (tid & 63) < C) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int pp = (tid >> 6) + 4 * q;
+                if (p0 + pp < P) rows[((size_t)n * P + (size_t)(p0 + pp)) * (size_t)C + (size_t)(c0 + (tid & 63))] = tile[tid & 63][pp];
             }
         }
         __syncthreads();
