@@ -551,7 +551,7 @@ __device__ __forceinline__ void ste_split(float v, uint32_t (&p)[3]) {
 }
 
 // the value of three sums of such pieces
-__device__ __forceinline__ float ste_join(float first, float second, float third) { return first + (second * 0x1p-8f + third * 0x1p-16f); }
+__device__ __forceinline__ float ste_join(float first, float second, float third) { return __builtin_fmaf(__builtin_fmaf(third, 0x1p-8f, second), 0x1p-8f, first); }
 
 // upper halves of a and b as one word, a's in the lower half
 __device__ __forceinline__ uint32_t ste_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
@@ -814,8 +814,8 @@ __global__ __launch_bounds__(STE_THREADS, 2) void ste_dx16_kernel(const SteDx16P
             left = cpt;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                tot[v] += ste_join(acc[0][v], acc[1][v], acc[2][v]);
-                acc[0][v] = acc[1][v] = acc[2][v] = 0.0f;
+                tot[v] += acc[0][v];            // (the others are small: rounded less than the first at any length)
+                acc[0][v] = 0.0f;
             }
         }
         __syncthreads();
@@ -841,7 +841,7 @@ __global__ __launch_bounds__(STE_THREADS, 2) void ste_dx16_kernel(const SteDx16P
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int c = i0 + wi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (c < g.C) p.dx[((size_t)n * g.C + c) * (size_t)HW + (size_t)pin] = ste_inside(xv[v], p.so, p.Q) ? tot[v] * p.scale : 0.0f;
+        if (c < g.C) p.dx[((size_t)n * g.C + c) * (size_t)HW + (size_t)pin] = ste_inside(xv[v], p.so, p.Q) ? ste_join(tot[v], acc[1][v], acc[2][v]) * p.scale : 0.0f;
     }
 }
 
