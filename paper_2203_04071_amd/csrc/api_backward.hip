@@ -274,8 +274,17 @@ int adapt_ste_conv2d_backward_f32(const float *dy_dev, const float *x_dev, const
     // leaves none to the codes, takes the fp32 form).  64 -> 64 channels, 3 x 3, 32 images of 32 x 32: weight gradient 43 -> 28 us,
     // input gradient 42 -> 28 us, with errors against 64 bits of 0.4 to 0.9 of the fp32 form (2-norms of 4e-8 to 2e-7 over 14 layers).
     const bool codes16 = bits <= 9;
-    const bool dw16 = dw_dev && codes16 && s_x > 1e-30f && s_x < 1e30f && workspace_bytes >= pl.kept_bytes + pl.pieces_bytes + pl.codes_bytes + pl.sums_bytes;
-    const bool dx16 = codes16 && s_w > 1e-30f && s_w < 1e30f;
+    // Weight gradient of at most 64 columns (taps x channels): one pass over the copies, which are 6 bytes an element of dY instead of 4.  What is read
+    // and written of dY (10 bytes, 14 with the rows of a strided layer) beyond the last-level cache costs more than the instructions gain: 1 -> 250
+    // channels, 1 x 1, fp32 form / this one: 210 MB 116 / 121 us, 280 MB 211 / 242, 1.6 GB 720 / 863; 8 -> 112: 183 MB 129 / 119, 257 MB 237 / 252.
+    const bool beyond_cache = (long long)pl.dw_rows * kw * Cp <= 64 && (size_t)M * Cout * (dx_dev && !pl.direct ? 14 : 10) > ((size_t)192 << 20);
+    const bool dw16 = dw_dev && !beyond_cache && codes16 && s_x > 1e-30f && s_x < 1e30f && workspace_bytes >= pl.kept_bytes + pl.pieces_bytes + pl.codes_bytes + pl.sums_bytes;
+    // Input gradient: the 16-bit form pays for its start (its weights come padded, its gradient is split while it is staged) and gains with
+    // every chunk of 32 output channels of a tap.  Speed against the fp32 form, up to one workgroup per compute unit: 1 chunk 0.85 - 0.92,
+    // 4 chunks 0.92 - 0.98, 6 chunks 0.99 - 1.02, 18 chunks 1.10 - 1.14; up to two: 2 chunks 0.95 - 1.00, 3 chunks 0.96 - 1.05, 9 chunks
+    // 1.19 - 1.34; more: 1 chunk 0.93 - 1.07, 2 chunks 0.97 - 1.15, 9 chunks 1.21 - 1.44.
+    const long long dx_chunks = (long long)kh * kw * ((Cout + 31) / 32), dx_wgs = ((long long)N * HW + 63) / 64 * ((Cin + 63) / 64);
+    const bool dx16 = codes16 && s_w > 1e-30f && s_w < 1e30f && dx_chunks >= (dx_wgs > 2 * device_cus() ? 2 : (dx_wgs > device_cus() ? 3 : 6));
     if (dw16) {
         const int lda = pl.lda;
         const size_t plane = (size_t)M * lda;

@@ -356,6 +356,13 @@ CODE_CASES = [
     (2, 66, 9, 7, 65, 1, 1, (1, 1), (0, 0), (1, 1), 8),            # one past the tiles
     (5, 3, 11, 6, 1, 2, 5, (2, 1), (0, 3), (1, 1), 5),             # one output channel; vertical stride: dw alone on codes
     (40, 9, 20, 20, 6, 3, 3, (1, 1), (1, 1), (1, 1), 8),           # a long contraction in parts
+    # the input gradient takes them from 6 chunks of 32 output channels on, from 3 or 2 where there are more workgroups than compute units
+    (1, 5, 6, 7, 161, 1, 1, (1, 1), (0, 0), (1, 1), 8),            # 6, the last with one channel
+    (1, 5, 6, 7, 160, 1, 1, (1, 1), (0, 0), (1, 1), 8),            # 5
+    (2, 66, 9, 7, 65, 2, 2, (1, 1), (1, 1), (1, 1), 8),            # 12, one past the tiles
+    (4, 6, 64, 65, 65, 1, 1, (1, 1), (0, 0), (1, 1), 7),           # 3 in 260 workgroups
+    (4, 6, 64, 65, 64, 1, 1, (1, 1), (0, 0), (1, 1), 7),           # 2
+    (8, 6, 64, 65, 33, 1, 1, (1, 1), (0, 0), (1, 1), 7),           # 2 in 520
 ]
 
 
