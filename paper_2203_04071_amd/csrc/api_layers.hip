@@ -218,17 +218,16 @@ int run_rows(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *ou
         if (lstm->kind == 3) p.act = lstm->relu ? 1 : 0;
     }
     dim3 grid((unsigned)((g.M + MT - 1) / MT), (unsigned)(Npad / NT), (unsigned)ngroups);
-    // A time step on one-byte entries: where the handle has them, and the slices of the waves are whole words of aligned activations
+    // A time step on one-byte entries: where the handle has them, the slices of the waves are whole words of aligned activations
     const bool byte = lstm && lstm->cell8 && KS == 16 && (reinterpret_cast<uintptr_t>(x) & 3u) == 0;
-    p.w4 = nullptr; p.amask = 0; p.corr = 0; p.x_row = 0;
+    p.w4 = nullptr; p.amask = 0; p.corr = 0;
     if (byte) {
         p.wofs = lstm->cell8; p.w4 = lstm->cell8 + (size_t)Ktot * g.N / 2;
         p.img_bytes = 1 << (2 * bits);
         p.amask = (uint32_t)(lut->byte.am & 0xff) * 0x01010101u;
         p.corr = (int)(uint32_t)(Ktot * lut->byte.c);
     }
-    if (byte && Ktot <= 1024 && aligned16(x)) p.x_row = (int)Ktot + 16;     // (16 bytes more: rows a quarter of the banks apart)
-    size_t lds = (size_t)p.img_bytes + (size_t)(64 * p.x_row);
+    size_t lds = (size_t)p.img_bytes;
     if (KS > 1 && (size_t)adapt::ROWS_THREADS * NT * 4 > lds) lds = (size_t)adapt::ROWS_THREADS * NT * 4;
     for (int half = 0; half <= lut->storage && rc == ADAPT_OK; ++half) {
         p.img = byte ? lut->img8_dev : lut->img_dev[half];

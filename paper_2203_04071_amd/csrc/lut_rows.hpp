@@ -72,7 +72,6 @@ struct RowsParams {
     const uint32_t *w4;
     uint32_t amask;
     int corr;
-    int x_row;              // > 0: the rows of a workgroup are staged in LDS behind the table, this many bytes apart
 };
 
 __device__ __forceinline__ uint32_t finish_sum(const RowsParams &p, uint32_t v, int n) {
@@ -165,10 +164,12 @@ __device__ __forceinline__ void rows_fetch32(uint32_t (&dst)[8], const uint32_t 
     }
 }
 
-// BYTE: a time step on one-byte entries (see RowsParams; Hs a multiple of 64, word-aligned activations).  What bounds a step is the lookups:
-// a 7-bit row of bytes is 32 words of LDS, one per bank, 2.6 clocks for 64 lanes, where its 16-bit row has two words per bank, 4.2; the exact
-// products cost a v_dot4 for four lookups, and the table's way into LDS is an eighth (16 instead of 132 KB at 7 against
-// 8 bits of 16).  LSTM 512 / 512, 64 rows, 7 bits: 13.6 -> 11.6 us a step.
+// BYTE: a time step on one-byte entries (see RowsParams; Hs a multiple of 64, word-aligned activations).
+// What bounds a long step is the lookups: a 7-bit row of bytes is 32 words of LDS, one per bank, 2.6 clocks for 64 lanes, where its 16-bit row has
+// two words per bank, 4.2; the exact products cost a v_dot4 for four lookups, and the table's way into LDS is half (64 instead of 132 KB at 8
+// bits, 16 instead of 33 at 7), so that two workgroups of a plain cell share a compute unit.  16-bit -> one-byte form:
+// LSTM 512 / 512, 64 rows, 7 bits 11.9 -> 11.2 us a step, 8 bits 14.6 -> 12.6 (128 rows 26.8 -> 21.6); plain cell of 448, 128 rows, 7 bits 12.9 -> 8.5.
+// (The rows of a workgroup as whole lines in LDS, instead of a line a lane: 1 to 14 % slower at every size from 64 to 1024 units and 1 to 256 rows.)
 template <int NT, bool SIGNED, bool BYTE = false>
 __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -218,77 +219,66 @@ __global__ __launch_bounds__(ROWS_THREADS) void lut_rows_kernel(const RowsParams
     if constexpr (BYTE) {
         // Row offsets (two to a word) and weights of four inner indices come by scalar loads.  These share a counter with the lookups and return
         // out of order, so whoever waits for the one waits for the other: those of the next four are requested ahead of a
-        // group's lookups and travel beside them.
-        const uint32_t *const xw = reinterpret_cast<const uint32_t *>(xb);
+        // group's lookups and travel beside them.  (No branch lies between a request and its use but the loop's own: behind one the
+        // compiler moves the request to its use, and every second group waited for memory.)
         const uint32_t *const ofs = p.wofs + (size_t)blockIdx.y * Ktot * (NT / 2), *const w4 = p.w4 + (size_t)blockIdx.y * (Ktot >> 2) * NT;
         const uint32_t half4 = (uint32_t)p.hoff * 0x01010101u, mask4 = (uint32_t)p.mask * 0x01010101u, up = (uint32_t)(256 / p.hoff - 1);
-        uint32_t nxt[8], off[2][2 * NT], wgt[2][NT];
-        auto fetch = [&](int kk) { rows_fetch32(nxt, xw, kk, k_end); };
-        auto request = [&](int set, int kk) {
+        uint32_t off[2 * NT], wgt[NT], off_next[2 * NT], wgt_next[NT];
+        auto request = [&](int kk) {
             const int at = min(kk, Ktot - 4);               // (past the end: any valid place)
 #pragma unroll
-            for (int w = 0; w < 2 * NT; ++w) off[set][w] = ofs[at * (NT / 2) + w];
+            for (int w = 0; w < 2 * NT; ++w) off_next[w] = ofs[at * (NT / 2) + w];
 #pragma unroll
-            for (int n = 0; n < NT; ++n) wgt[set][n] = w4[(at >> 2) * NT + n];
+            for (int n = 0; n < NT; ++n) wgt_next[n] = w4[(at >> 2) * NT + n];
         };
-        request(0, k);
-        const unsigned char *const mine = smem + p.img_bytes + r_in_tile * p.x_row;
-        auto fetch_staged = [&](int kk) {
-            rows_fetch32(nxt, reinterpret_cast<const uint32_t *>(mine), kk, k_end);
+        auto advance = [&] {
+#pragma unroll
+            for (int w = 0; w < 2 * NT; ++w) off[w] = off_next[w];
+#pragma unroll
+            for (int n = 0; n < NT; ++n) wgt[n] = wgt_next[n];
         };
-        if (p.x_row > 0) {
-            // The 64 rows as whole lines, beside the table (a lane reading its own row: 64 lines a load, 2000 clocks of a step)
-            const int c16 = Ktot >> 4, c = tid & 31, r0 = tid >> 5, m0 = blockIdx.x * 64;
-            const uint4 *const x16 = reinterpret_cast<const uint4 *>(p.x);
-            const uint4 *const a_row = x16 + (size_t)min(m0 + r0, p.M - 1) * c16, *const b_row = x16 + (size_t)min(m0 + r0 + 32, p.M - 1) * c16;
-            uint4 *const a_to = reinterpret_cast<uint4 *>(smem + p.img_bytes + r0 * p.x_row), *const b_to = reinterpret_cast<uint4 *>(smem + p.img_bytes + (r0 + 32) * p.x_row);
-            const uint4 a = a_row[min(c, c16 - 1)], b = b_row[min(c, c16 - 1)];
-            stage_table(smem, p.img, p.img_bytes, tid);
-            if (c < c16) { a_to[c] = a; b_to[c] = b; }
-            for (int i = c + 32; i < c16; i += 32) { a_to[i] = a_row[i]; b_to[i] = b_row[i]; }
-            __syncthreads();
-            fetch_staged(k);
-        } else {
-            fetch(k);
-            stage_table(smem, p.img, p.img_bytes, tid);
-            __syncthreads();
-        }
-        while (k < k_end) {
-            uint32_t cur[8];
+        // lookups and products of the four activations of a word, inner indices kk .. kk + 3
+        auto group = [&](uint32_t word, int kk) {
+            advance();
+            request(kk + 4);
+            __builtin_amdgcn_sched_barrier(0);
+            // column of every activation, and the activation itself, wrapped into b bits, as a signed byte
+            const uint32_t col = (word ^ half4) & mask4, neg = ~col & half4;
+            const int a = (int)(((col & ~half4) | neg * up) & p.amask);
+            uint32_t e[4][NT];
 #pragma unroll
-            for (int d = 0; d < 8; ++d) cur[d] = nxt[d];
-            if (k + 32 < k_end) {
-                if (p.x_row > 0) fetch_staged(k + 32);
-                else fetch(k + 32);
-            }
-            const int cnt = min(32, k_end - k);
+            for (int bq = 0; bq < 4; ++bq) {
+                const uint32_t at = (col >> (8 * bq)) & 0xffu;
 #pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                if (4 * d >= cnt) break;                    // uniform in the wave
-                request((d + 1) & 1, k + 4 * d + 4);
-                __builtin_amdgcn_sched_barrier(0);
-                // column of every activation, and the activation itself, wrapped into b bits, as a signed byte
-                const uint32_t col = (cur[d] ^ half4) & mask4, neg = ~col & half4;
-                const int a = (int)(((col & ~half4) | neg * up) & p.amask);
-                uint32_t e[4][NT];
-#pragma unroll
-                for (int bq = 0; bq < 4; ++bq) {
-                    const uint32_t at = (col >> (8 * bq)) & 0xffu;
-#pragma unroll
-                    for (int n = 0; n < NT; ++n) {
-                        const uint32_t o = off[d & 1][(bq * NT + n) / 2];
-                        e[bq][n] = (uint32_t)(int)*reinterpret_cast<const int8_t *>(smem + (n & 1 ? o >> 16 : o & 0xffffu) + at);
-                    }
+                for (int n = 0; n < NT; ++n) {
+                    const uint32_t o = off[(bq * NT + n) / 2];
+                    e[bq][n] = (uint32_t)(int)*reinterpret_cast<const int8_t *>(smem + (n & 1 ? o >> 16 : o & 0xffffu) + at);
                 }
-#pragma unroll
-                for (int n = 0; n < NT; ++n) acc[n] = (uint32_t)__builtin_amdgcn_sdot4(a, (int)wgt[d & 1][n], (int)acc[n], false);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int n = 0; n < NT; ++n) acc[n] += (e[0][n] + e[1][n]) + (e[2][n] + e[3][n]);
-                __builtin_amdgcn_sched_barrier(0);
             }
-            k += cnt;
+#pragma unroll
+            for (int n = 0; n < NT; ++n) acc[n] = (uint32_t)__builtin_amdgcn_sdot4(a, (int)wgt[n], (int)acc[n], false);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int n = 0; n < NT; ++n) acc[n] += (e[0][n] + e[1][n]) + (e[2][n] + e[3][n]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        request(k);
+        // 16 inner indices of this lane's row, one block ahead of their use (a load costs its 64 lines whatever its width)
+        auto fetch = [&](int kk) { return *reinterpret_cast<const rows_words_t *>(xb + min(kk, Ktot - 16)); };
+        rows_words_t next = fetch(k);
+        stage_table(smem, p.img, p.img_bytes, tid);
+        __syncthreads();
+#pragma unroll 1
+        for (; k + 16 <= k_end; k += 16) {
+            const rows_words_t cur = next;
+            next = fetch(k + 16);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) group(cur[d], k + 4 * d);
         }
+        // up to three groups more, whose words lie further back where the block would have passed the row's end
+        int at = max(0, k + 16 - Ktot) >> 2;                // (the same in the whole wave)
+#pragma unroll 1
+        for (; k < k_end; k += 4, ++at) group(at == 0 ? next.x : (at == 1 ? next.y : (at == 2 ? next.z : next.w)), k);
     } else if (p.mode == MODE_GEMM && p.kstride == 1 && (p.Cin & 3) == 0 && (kc & 3) == 0 &&
         (reinterpret_cast<uintptr_t>(p.x) & 3u) == 0) {
         const uint32_t *xw = reinterpret_cast<const uint32_t *>(xb);       // row of this lane

@@ -389,10 +389,12 @@ def test_chains_between_forms(B, bits, kind, first):
 
 
 @pytest.mark.parametrize("bits,kind", [(8, "product"), (8, "dropped"), (7, "product"), (7, "one_side"), (6, "product"), (2, "product")])
-@pytest.mark.parametrize("rows,Hs", [(1, 64), (65, 128), (7, 192), (64, 576)])
+@pytest.mark.parametrize("rows,Hs", [(1, 64), (65, 128), (7, 192), (64, 576), (50, 320), (33, 448), (70, 832)])
 def test_time_steps_on_one_byte_entries(B, bits, kind, rows, Hs):
-    """The three recurrent steps where they read one-byte entries: asymmetric tables, slices of 4 to 36 inner indices, codes beyond the
-    operand's range (which wrap), activations that are not word-aligned (which take the 16-bit entries)."""
+    """The three recurrent steps on either side of the rule that takes one-byte entries (8 bits: nearly all of these; fewer: from 32 or 48 rows and
+    192 or 256 units on; several rounds of workgroups: all): asymmetric tables, slices of 4 to 52 inner indices, of which up to three groups of four are
+    no block of 16, codes beyond the operand's range (which wrap), activations that are word-aligned only, or not even that
+    (which take the 16-bit entries)."""
     rng = np.random.default_rng(bits + rows + Hs)
     t = table(kind, bits, rng)
     L = B.Lut(t, bits)
@@ -400,8 +402,9 @@ def test_time_steps_on_one_byte_entries(B, bits, kind, rows, Hs):
     h = 1 << (bits - 1)
     qh = rng.integers(-128, 128, size=(rows, Hs)).astype(np.int8)
     wrapped = ((((qh.astype(np.int32) + h) & (2 * h - 1)) - h)).astype(np.int8)
-    shifted = torch.empty(rows * Hs + 1, dtype=torch.int8, device="cuda")[1:].view(rows, Hs)
-    shifted.copy_(dev(qh))
+    shifted = [torch.empty(rows * Hs + by, dtype=torch.int8, device="cuda")[by:].view(rows, Hs) for by in (1, 4)]
+    for q in shifted:
+        q.copy_(dev(qh))
     new = lambda dt: torch.empty((rows, Hs), dtype=dt, device="cuda")
     for gates in (4, 3, 1):
         w = wl.random_i8(rng, (gates * Hs, Hs), bits)
@@ -409,7 +412,7 @@ def test_time_steps_on_one_byte_entries(B, bits, kind, rows, Hs):
         acc_hh = orc.approx_linear(t, bits, wrapped, w, threads=4)
         pw = B.adapt_weights_pack_linear(L, dev(w))
         c0, h0, bias = (rng.standard_normal(s).astype(np.float32) for s in ((rows, Hs), (rows, Hs), gates * Hs))
-        for q in (dev(qh), shifted):
+        for q in (dev(qh), *shifted):
             hd, qn = new(torch.float32), new(torch.int8)
             if gates == 4:
                 cd = dev(c0)
