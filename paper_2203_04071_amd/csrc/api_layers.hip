@@ -161,6 +161,24 @@ struct LstmStep {            // see adapt::RowsParams
     const uint32_t *cell8 = nullptr;        // offsets and weights of the one-byte form, if the handle has them
 };
 
+// Whether a time step of `rows` rows and Hs units (NT columns a workgroup: 8 LSTM, 6 GRU, 2 plain cell) runs on one-byte entries.  Where few
+// lanes have rows of their own the 16-bit lookups have no bank conflicts to lose, narrower tables have fewer of them anyway, and slices of
+// whole blocks of 32 inner indices run without branches there.  Speed of the one-byte form against the other:
+//     7 bits, 1, 32, 48 and 64 rows: LSTM 192: 0.90 0.95 0.99 1.02   320: 0.92 1.02 1.08 1.12   512: 0.90 0.98 1.03 1.06
+//         GRU 192: 0.94 1.02 1.10 1.11   512: 0.95 1.05 1.16 1.18   plain 192: 0.92 0.98 1.04 1.11   320: 0.92 1.03 1.12 1.20
+//         plain 512: 0.89 0.91 0.94 0.94 (65 rows, or 576 units: 1.02 1.04 1.07 1.11: more than one workgroup a compute unit)
+//     6 bits: LSTM 320: 0.91 0.98 1.02 1.06   512: 0.88 0.91 0.92 0.93   GRU 320: 0.96 1.05 1.10 1.16   512: 0.93 0.95 0.96 0.98   plain 320: 0.90 1.02 1.10 1.19
+//     8 bits, 1, 16, 32 and 64 rows: LSTM 64: 1.04 1.04 1.06 1.08   192: 0.95 1.00 1.04 1.12   512: 0.94 1.01 1.07 1.16
+//         GRU 320: 1.03 1.07 1.13 1.19   512: 1.00 1.05 1.10 1.15   plain 320: 0.99 1.03 1.10 1.25   768: 1.20 1.19 1.20 1.35
+// The 16-bit kernels leave room for one workgroup on a compute unit: with several rounds of them the one-byte form of an LSTM or GRU is 1.1 to 1.5 times as
+// fast, whatever the rows and bits (LSTM 768 with 65 rows, GRU and LSTM 1536).
+bool byte_step_pays(int bits, int NT, int rows, int Hs, int cus) {
+    const long long wgs = (long long)((rows + 63) / 64) * (Hs / 2);
+    if (NT >= 6 && (wgs >= 3 * cus || (wgs > 2 * cus && (rows >= 48 || (NT == 6 && bits >= 7))))) return true;
+    if (bits == 8) return rows >= 16 || NT == 6 || Hs <= 128 || (NT == 2 && wgs > cus);
+    return rows >= (NT == 8 || Hs < 256 ? 48 : 32) && Hs >= (NT == 8 ? 256 : 192) && (Hs < 512 || (NT >= 6 ? bits == 7 : wgs > cus));
+}
+
 // pack_into: room for Ktot * (N rounded up to 16) * groups row offsets that the call may use instead of a stream-ordered
 // temporary (then it allocates nothing)
 int run_rows(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *out, const Geometry &g, hipStream_t s,
@@ -218,8 +236,8 @@ int run_rows(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *ou
         if (lstm->kind == 3) p.act = lstm->relu ? 1 : 0;
     }
     dim3 grid((unsigned)((g.M + MT - 1) / MT), (unsigned)(Npad / NT), (unsigned)ngroups);
-    // A time step on one-byte entries: where the handle has them, the slices of the waves are whole words of aligned activations
-    const bool byte = lstm && lstm->cell8 && KS == 16 && (reinterpret_cast<uintptr_t>(x) & 3u) == 0;
+    // A time step on one-byte entries: where the handle has them, the slices of the waves are whole words of aligned activations, and it pays
+    const bool byte = lstm && lstm->cell8 && KS == 16 && (reinterpret_cast<uintptr_t>(x) & 3u) == 0 && byte_step_pays(bits, NT, g.M, lstm->Hs, device_cus());
     p.w4 = nullptr; p.amask = 0; p.corr = 0;
     if (byte) {
         p.wofs = lstm->cell8; p.w4 = lstm->cell8 + (size_t)Ktot * g.N / 2;

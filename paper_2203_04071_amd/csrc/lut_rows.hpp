@@ -164,7 +164,7 @@ __device__ __forceinline__ void rows_fetch32(uint32_t (&dst)[8], const uint32_t 
     }
 }
 
-// BYTE: a time step on one-byte entries (see RowsParams; Hs a multiple of 64, word-aligned activations).
+// BYTE: a time step on one-byte entries (see RowsParams; Hs a multiple of 64, word-aligned activations; which steps take it: byte_step_pays).
 // What bounds a long step is the lookups: a 7-bit row of bytes is 32 words of LDS, one per bank, 2.6 clocks for 64 lanes, where its 16-bit row has
 // two words per bank, 4.2; the exact products cost a v_dot4 for four lookups, and the table's way into LDS is half (64 instead of 132 KB at 8
 // bits, 16 instead of 33 at 7), so that two workgroups of a plain cell share a compute unit.  16-bit -> one-byte form:
