@@ -38,9 +38,16 @@ inline long long byte_step_clocks(int R, int copy_lines) {
 }
 
 // Whether the workgroups of a launch go to the XCDs by units (see lut_byte_kernel): where every XCD then gets as few workgroups as it would
-// get otherwise, and where the row tiles of a channel tile do not share an XCD anyway
+// get otherwise, where the row tiles of a channel tile do not share an XCD anyway, and where the tables that an XCD need not fetch weigh more than the
+// activations of all row tiles that it then does.  Speed by units against channel tile fastest, mean (extremes), 8 bits:
+//     up to 7 row tiles: 3 - 8 channel tiles 1.02 (0.97 - 1.20), 13 - 15 1.14 (0.99 - 1.53), 33 and 50 1.14 (0.98 - 1.58)
+//     8 - 13 row tiles: 9 - 12 channel tiles 1.00 (0.95 - 1.17), 13 - 15 1.06 (0.97 - 1.24), 33 and 50 1.45 (1.36 - 1.57)
+//     14 - 16: 9 - 12 0.96 (0.87 - 1.10), 13 - 15 0.98 (0.94 - 1.04), 33 and 50 1.14 (1.01 - 1.27)
+//     17 - 32: 3 0.89 (0.82 - 0.96), 13 - 15 0.97 (0.89 - 1.05), 20 and 22 0.97 (0.89 - 1.06), 33 and 50 1.12 (1.00 - 1.29)
+// (7 bits likewise, with half of the gains)
 inline bool byte_by_units(int n_tiles, int m_tiles, int phases, int ksplit, int cu) {
     if (phases != 1 || m_tiles == 1 || n_tiles % 8 == 0 || 8 % n_tiles == 0 || cu % 8 != 0) return false;
+    if (n_tiles <= 32 && m_tiles > (n_tiles < 13 ? 7 : 13)) return false;
     const long long units = (long long)n_tiles * ksplit, per_xcd = (units + 7) / 8 * m_tiles, wgs = units * m_tiles;
     return (per_xcd + cu / 8 - 1) / (cu / 8) <= (wgs + cu - 1) / cu && per_xcd * 8 <= 0x7fffffffLL;
 }

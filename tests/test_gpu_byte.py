@@ -178,9 +178,11 @@ def test_linear_layers_below_4096_rows(B, M, K, N, bits):
 
 
 @pytest.mark.parametrize("bits", [8, 7])
-@pytest.mark.parametrize("images,cin,cout,hw,stride", [(50, 20, 200, 27, 2), (24, 36, 140, 20, 1), (40, 33, 72, 14, 1)])
+@pytest.mark.parametrize("images,cin,cout,hw,stride", [(50, 20, 200, 27, 2), (24, 36, 140, 20, 1), (40, 33, 72, 14, 1),
+                                                       (8, 36, 140, 20, 1), (6, 33, 72, 14, 1), (4, 17, 40, 14, 1), (9, 5, 523, 28, 1)])
 def test_channel_tiles_that_no_power_of_two_divides(B, bits, images, cin, cout, hw, stride):
-    """13, 9 and 5 channel tiles with several row tiles: workgroups are dealt to the XCDs by the tables they read, some have none."""
+    """13, 9, 5, 3 and 33 channel tiles with several row tiles: where these are few, or the channel tiles many, workgroups are dealt to the XCDs by
+    the tables they read (some XCDs have none), elsewhere in the usual order."""
     rng = np.random.default_rng(bits + cout)
     t = table("product", bits, rng)
     x, w = wl.random_i8(rng, (images, cin, hw, hw), bits), wl.random_i8(rng, (cout, cin, 3, 3), bits)
