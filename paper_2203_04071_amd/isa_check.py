@@ -8,7 +8,9 @@ allocation).  This script scans the generated gfx950 assembly of every instantia
 and the wait that covers it, no instruction may touch the destination registers.  Every path of a function's
 control-flow graph is walked (the compiler rotates loops, so the order of the text is not the order of execution); two
 queues model the in-order retirement of lgkmcnt / vmcnt.  The same walk checks that no compiler-generated instruction
-touches the accumulators of matrix instructions issued from asm before the kernel has drained the matrix pipe.
+touches the accumulators of matrix instructions (dense and sparse) issued from asm before the kernel has drained the matrix pipe,
+and that no such instruction reads a register that a vector instruction has written less than two wait states before it (the
+compiler knows neither what an asm statement reads nor that it is a matrix instruction, and may copy an operand right in front of it).
 
   python -m paper_2203_04071_amd.isa_check            compiles the translation units that hold hand-scheduled kernels to assembly and checks them
   python -m paper_2203_04071_amd.isa_check file.s     checks an existing assembly file
@@ -18,6 +20,9 @@ import re
 import subprocess
 import sys
 import tempfile
+
+MATRIX = ('v_mfma', 'v_smfmac')
+WRITE_TO_MATRIX = 2         # wait states between a vector instruction's write of a register and a matrix instruction that reads it
 
 def regs(tok):
     out = set()
@@ -70,8 +75,8 @@ def _merge(q1, q2):
 
 def _check_function(fn, body, report):
     """Forward data-flow over the function's basic blocks.  State: the queue of LDS / scalar loads and the queue of vector
-    memory operations in flight (destination registers of those issued from asm), and the accumulators of matrix
-    instructions issued from asm that have not been drained.  Where paths meet, the states are merged entry by entry
+    memory operations in flight (destination registers of those issued from asm), the accumulators of matrix
+    instructions issued from asm that have not been drained, and what vector instructions wrote in the last wait states.  Where paths meet, the states are merged entry by entry
     (what MAY be in flight), so the check errs on the side of reporting."""
     prog, labels, inside = [], {}, False         # (an asm statement may hold branches and labels of its own)
     for ln, s in body:
@@ -89,15 +94,15 @@ def _check_function(fn, body, report):
         op = code.split()[0]
         prog.append((ln, inside, op, code[len(op):]))
     state_in_points = set(labels.values())       # where blocks begin
-    state_in = {0: ((), (), frozenset())}
+    state_in = {0: ((), (), frozenset(), (frozenset(),) * WRITE_TO_MATRIX)}
     work = [0]
     while work:
         pc = work.pop()
-        lq, vq, mf = state_in[pc]
+        lq, vq, mf, wr = state_in[pc]
 
         def flow(to):
             old = state_in.get(to)
-            new = (lq, vq, mf) if old is None else (_merge(old[0], lq), _merge(old[1], vq), old[2] | mf)
+            new = (lq, vq, mf, wr) if old is None else (_merge(old[0], lq), _merge(old[1], vq), old[2] | mf, _merge(old[3], wr))
             if new != old:
                 state_in[to] = new
                 work.append(to)
@@ -113,6 +118,18 @@ def _check_function(fn, body, report):
             code = op + args
             if op == 's_endpgm':
                 break
+            matrix = op.startswith(MATRIX)
+            if matrix and in_asm:
+                late = regs(args) & set().union(*wr)
+                if late:
+                    report(fn, ln, code, f"reads {sorted(late)} less than {WRITE_TO_MATRIX} wait states after a vector instruction wrote them")
+            # (an instruction is one wait state, s_nop n is n + 1)
+            if op.startswith('v_') and not matrix:
+                written = frozenset(regs(args if op.startswith('v_swap') else args.split(',')[0]))
+            else:
+                written = frozenset()
+            states = int(args.strip(), 0) + 1 if op == 's_nop' else 1
+            wr = (wr + (written,) + (frozenset(),) * min(states - 1, WRITE_TO_MATRIX))[-WRITE_TO_MATRIX:]
             if op.startswith('s_cbranch') or op == 's_branch':
                 tgt = args.strip()
                 if tgt in labels:
@@ -138,7 +155,7 @@ def _check_function(fn, body, report):
             # Matrix instructions issued from asm: the compiler does not know that their results need wait states before a
             # vector instruction may read them, so until the kernel drains the pipe (s_nop 15 inside an asm statement) no
             # instruction outside asm may touch an accumulator.
-            if op.startswith('v_mfma') and in_asm:
+            if matrix and in_asm:
                 mf = mf | frozenset(regs(args.split(',')[0]))
             elif op == 's_nop' and in_asm and args.strip() == '15':
                 mf = frozenset()

@@ -37,12 +37,16 @@ def test_checker_flags_a_planted_copy(tmp_path):
     assert isa_check.check(str(p), "kernel") == 1
 
 
-def test_checker_flags_a_touched_matrix_accumulator(tmp_path):
+MATRIX = ["v_mfma_i32_16x16x64_i8 v[4:7], v[8:11], v[12:15], v[4:7]", "v_smfmac_i32_16x16x128_i8 v[4:7], v[8:11], v[12:19], v22"]
+
+
+@pytest.mark.parametrize("instruction", MATRIX)
+def test_checker_flags_a_touched_matrix_accumulator(tmp_path, instruction):
     """A compiler-generated instruction that reads the destination of a matrix instruction issued from asm, before the
     kernel has drained the matrix pipe, must be reported; after the drain it is fine."""
     good = """_Z6kernelv:
 \t;;#ASMSTART
-\tv_mfma_i32_16x16x64_i8 v[4:7], v[8:11], v[12:15], v[4:7]
+\t%s
 \t;;#ASMEND
 \tv_mov_b32_e32 v20, v8
 \t;;#ASMSTART
@@ -51,13 +55,29 @@ def test_checker_flags_a_touched_matrix_accumulator(tmp_path):
 \t;;#ASMEND
 \tv_mov_b32_e32 v21, v5
 \ts_endpgm
-"""
+""" % instruction
     bad = good.replace("v_mov_b32_e32 v20, v8", "v_mov_b32_e32 v20, v6")
     p = tmp_path / "k.s"
     p.write_text(good)
     assert isa_check.check(str(p), "kernel") == 0
     p.write_text(bad)
     assert isa_check.check(str(p), "kernel") == 1
+
+
+@pytest.mark.parametrize("instruction", MATRIX)
+@pytest.mark.parametrize("between", ["", "\ts_nop 0\n", "\ts_branch .LBB0_1\n.LBB0_1:\n"])
+def test_checker_flags_an_operand_written_right_before(tmp_path, instruction, between):
+    """An operand that a vector instruction writes less than two wait states ahead of a matrix instruction issued from asm must be
+    reported, also across a branch; with one instruction more between them, or a write of another register, it is fine."""
+    text = "_Z6kernelv:\n\tv_mov_b32_e32 v13, v2\n" + between + """%s\t;;#ASMSTART
+\t""" + instruction + """
+\t;;#ASMEND
+\ts_endpgm
+"""
+    p = tmp_path / "k.s"
+    for write, nops, want in (("v13", "", 1), ("v13", "\ts_nop 1\n", 0), ("v20", "", 0)):
+        p.write_text((text % nops).replace("v13, v2", write + ", v2"))
+        assert isa_check.check(str(p), "kernel") == want, (write, nops)
 
 
 def test_checker_follows_branches(tmp_path):
