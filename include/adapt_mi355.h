@@ -215,7 +215,8 @@ int adapt_weights_destroy(adapt_weights *w);
 /* Diagnostic, host only (no device call when cu > 0): how a product on a packed handle of this shape is spread over the
  * chip (Sec. IV: the matrix product is where the time goes, so which kernel runs it and in which launch shape is what a
  * profile has to be read against).  kind 0 linear (kh = kw = 1), 1 conv2d, 2 transposed conv2d with `stride`; storage as
- * adapt_lut_info reports it, or 2 for a single-pass table stored as one-byte errors (see above); rows = rows of the
+ * adapt_lut_info reports it, or 2 for a single-pass table stored as one-byte errors (see above) whose activations each have a line of
+ * their own (tables that ignore low bits of an activation have fewer and are planned with those: this query does not cover them); rows = rows of the
  * product (linear: M; convolution: N Ho Wo; transposed convolution: N Ho Wo / stride^2, the rows of one phase), Wo = output width of one image row (linear: M; transposed: Wo / stride), sw =
  * horizontal stride; cu = compute units to plan for (<= 0: those of the current device).
  * *kernel: -1 whole-table kernel (lut_rows_kernel), 0 lut_lines_kernel, 1 lut_lines_fast_kernel, 2 the same on the

@@ -42,6 +42,11 @@ def table(kind, bits, rng):
     elif kind in ("bare", "bare_activation"):       # dropped bits change no entry: activations that differ in them share a table line
         d = 2 if bits > 3 else 1
         t = ((v >> d) << d)[:, None] * (((v >> d) << d) if kind == "bare" else v)[None, :] + rng.integers(-100, 101, size=(n, n))[(np.arange(n) >> d) << d]
+    elif kind.startswith("share"):  # 2^d activations share a line, and no product that keeps more of an activation leaves a byte
+        d = int(kind[-1])
+        t = rng.integers(-77, 179, size=(n, n))[(np.arange(n) >> d) << d]
+        t[:1 << d, 0], t[:1 << d, h] = 178, -77     # (it would add up to h times the lost bits to the first and nothing to the second: beyond 255)
+        t = ((v >> d) << d)[:, None] * v[None, :] + t
     else:                           # spans 256: no byte form
         t = v[:, None] * v[None, :] + rng.integers(-128, 128, size=(n, n))
         t[0, 0], t[-1, -1] = h * h - 128, (h - 1) ** 2 + 128
@@ -431,7 +436,9 @@ def test_time_steps_on_one_byte_entries(B, bits, kind, rows, Hs):
             assert (host(qn) == orc.quantize(want, s_h, bits)).all()
 
 
-BARE = [(8, "bare"), (8, "bare_activation"), (7, "bare"), (4, "bare_activation"), (3, "bare"), (2, "bare")]
+# Tables of which several activations share a line, so that a step copies 4 to 128 of them, half as many behind a ReLU (that each table is
+# taken as one of these is checked on the host, in test_byte_form_host.py)
+BARE = [(8, "bare"), (8, "bare_activation"), (7, "bare"), (8, "share1"), (8, "share3"), (6, "share3"), (5, "share2"), (4, "share1"), (4, "share2"), (3, "share1")]
 
 
 @pytest.mark.parametrize("bits,kind", BARE)
@@ -440,25 +447,25 @@ def test_convolution_where_activations_share_lines(B, bits, kind, case):
     test_convolution(B, bits, kind, case)
 
 
-@pytest.mark.parametrize("bits,kind", BARE[:4])
+@pytest.mark.parametrize("bits,kind", BARE)
 @pytest.mark.parametrize("act", [0, 1, 2])
 def test_fused_layers_where_activations_share_lines(B, bits, kind, act):
     test_fused_layers_on_every_form(B, bits, kind, act)
 
 
-@pytest.mark.parametrize("bits,kind", BARE[:4])
+@pytest.mark.parametrize("bits,kind", BARE)
 @pytest.mark.parametrize("first", ["conv", "transposed", "depthwise", "grouped"])
 def test_chains_where_activations_share_lines(B, bits, kind, first):
     test_chains_between_forms(B, bits, kind, first)
 
 
-@pytest.mark.parametrize("bits,kind", BARE[:3])
-@pytest.mark.parametrize("rows,Hs", [(65, 128)])
+@pytest.mark.parametrize("bits,kind", BARE[:5])
+@pytest.mark.parametrize("rows,Hs", [(65, 128), (65, 320)])
 def test_time_steps_where_activations_share_lines(B, bits, kind, rows, Hs):
     test_time_steps_on_one_byte_entries(B, bits, kind, rows, Hs)
 
 
-@pytest.mark.parametrize("bits,kind", BARE[:3])
+@pytest.mark.parametrize("bits,kind", BARE)
 @pytest.mark.parametrize("M,K,N", [(512, 77, 37), (4097, 130, 33)])
 def test_linear_where_activations_share_lines(B, bits, kind, M, K, N):
     """Packed and plain, the codes' whole int8 range (which wraps)."""
