@@ -457,9 +457,9 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     const int lanes_act = DOPS > 1 ? 64 : min(64, (int)(copy_bytes >> 8));
     const uint64_t dma_mask = ~0ull >> (64 - lanes_act);
     const uint32_t dma_voff = (uint32_t)lane * 16u;
-    // (8-bit tables: workgroup number `rest` of a tile and phase starts two chunks further on than its predecessor, so that
-    // the workgroups that stream one table do not all ask L2 for the same lines at the same moment)
-    const uint32_t dma_rot = DOPS == 4 ? (uint32_t)rest * 2u : 0u;
+    // (8-bit tables: every row tile starts two chunks further on than its predecessor, so that the workgroups that stream one table do not all
+    // ask L2 for the same lines at the same moment)
+    const uint32_t dma_rot = DOPS == 4 ? (uint32_t)mt * 2u : 0u;
     uint32_t pf_sink = 0;                   // (what loads that only keep a count bring back)
 
     // One of the DOPS operations that copy a step's table.  Past the end of the slice there is nothing to copy.  DEEP: a small load
