@@ -145,7 +145,7 @@ struct Geometry {
 };
 
 // Run the rows kernel once per table image of the handle.
-// prepacked: row offsets [K][prepacked_npad] made earlier by pack_row_offsets_kernel (prepacked_npad a multiple of 16),
+// prepacked: row offsets [K][prepacked_npad] made earlier by pack_row_offsets_kernel (prepacked_npad: rows_stride of N rounded up to 16),
 // or nullptr to pack `w` into a stream-ordered temporary.
 struct LstmStep {            // see adapt::RowsParams
     int kind = 1;            // 1: LSTM, 2: GRU, 3: plain cell
@@ -179,8 +179,15 @@ bool byte_step_pays(int bits, int NT, int rows, int Hs, int cus) {
     return rows >= (NT == 8 || Hs < 256 ? 48 : 32) && Hs >= (NT == 8 ? 256 : 192) && (Hs < 512 || (NT >= 6 ? bits == 7 : wgs > cus));
 }
 
-// pack_into: room for Ktot * (N rounded up to 16) * groups row offsets that the call may use instead of a stream-ordered
-// temporary (then it allocates nothing)
+// Row offsets of so many columns: how far those of one inner index lie from those of the next.  A workgroup reads 8 or 16 columns of every index, 32 or
+// 64 bytes of a line each; with lines a multiple of 2 KB apart they meet in few channels and sets, and how much that costs
+// depends on how the waves happen to follow each other.  8 bits, 16 rows, K = N = 1024, distance 4 KB -> 4 KB and 64 bytes: weights packed for the call
+// 47.1 -> 35.8 us (40.6 with 4-byte loads of the rows, which kept the waves apart); 6 bits, handles in turn: 35.8 -> 24.2 us (29.2), K = 512, N = 2048: 26.7
+// -> 13.9 (19.7).  Of 128, 256, 384, 640, 768 and 1280 columns none was slower than its neighbours.
+int rows_stride(int columns) { return columns % 512 == 0 ? columns + 16 : columns; }
+
+// pack_into: NOALLOC_SCRATCH_BYTES for the row offsets, which hold Ktot * (N rounded up to 16) * groups of them, that the call may use instead of
+// a stream-ordered temporary (then it allocates nothing)
 int run_rows(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *out, const Geometry &g, hipStream_t s,
              const uint32_t *prepacked = nullptr, int prepacked_npad = 0, const LayerIO *io = nullptr,
              const LstmStep *lstm = nullptr, uint32_t *pack_into = nullptr) {
@@ -198,7 +205,9 @@ int run_rows(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *ou
     int NT = shape.NT, MT = shape.MT;
     if (lstm) { NT = lstm->kind == 2 ? 6 : (lstm->kind == 3 ? 2 : 8); MT = 64; }    // the cell epilogue sits in the split-K reduction: all gates of two units
     const int KS = adapt::ROWS_THREADS / MT;
-    const int Npad = prepacked ? prepacked_npad : ((g.N + NT - 1) / NT) * NT;
+    const int columns = (g.N + NT - 1) / NT * NT;
+    int Npad = prepacked ? prepacked_npad : rows_stride(columns);
+    if (pack_into && (size_t)Ktot * Npad * ngroups * sizeof(uint32_t) > NOALLOC_SCRATCH_BYTES) Npad = columns;
 
     uint32_t *wofs = nullptr;
     int rc = ADAPT_OK;
@@ -235,7 +244,7 @@ int run_rows(const adapt_lut *lut, const int8_t *x, const int8_t *w, int32_t *ou
         p.h_prev = lstm->h_prev; p.bias_hh = lstm->bias_hh;
         if (lstm->kind == 3) p.act = lstm->relu ? 1 : 0;
     }
-    dim3 grid((unsigned)((g.M + MT - 1) / MT), (unsigned)(Npad / NT), (unsigned)ngroups);
+    dim3 grid((unsigned)((g.M + MT - 1) / MT), (unsigned)(columns / NT), (unsigned)ngroups);
     // A time step on one-byte entries: where the handle has them, the slices of the waves are whole words of aligned activations, and it pays
     const bool byte = lstm && lstm->cell8 && KS == 16 && (reinterpret_cast<uintptr_t>(x) & 3u) == 0 && byte_step_pays(bits, NT, g.M, lstm->Hs, device_cus());
     p.w4 = nullptr; p.amask = 0; p.corr = 0;
@@ -1292,7 +1301,7 @@ static int weights_pack(adapt_weights **out, const adapt_lut *lut, const int8_t 
         }
     }
     if (kind == 0) {
-        h->wofs_npad = ((N + 15) / 16) * 16;
+        h->wofs_npad = rows_stride((N + 15) / 16 * 16);
         const size_t pack_n = (size_t)Cin * h->wofs_npad;
         hipError_t e = dbg_malloc((void **)&h->wofs_dev, pack_n * sizeof(uint32_t));
         if (e != hipSuccess) {
@@ -1376,8 +1385,8 @@ int adapt_weights_pack_conv_transpose2d(adapt_weights **out, const adapt_lut *lu
     if (e == hipSuccess) e = hipMemcpyAsync(h->w8_dev, w_dev, wbytes, hipMemcpyDeviceToDevice, (hipStream_t)stream);
     {   // row offsets for the whole-table kernel, both forms
         const int taps = kh * kw, hoff = 1 << (lut->bits - 1), mask = (1 << lut->bits) - 1;
-        h->wofs_npad = ((Cout + 15) / 16) * 16;
-        h->wofs1_npad = ((Cout * taps + 15) / 16) * 16;
+        h->wofs_npad = rows_stride((Cout + 15) / 16 * 16);
+        h->wofs1_npad = rows_stride((Cout * taps + 15) / 16 * 16);
         const size_t n0 = (size_t)taps * Cin * h->wofs_npad, n1 = (size_t)Cin * h->wofs1_npad;
         if (e == hipSuccess) e = dbg_malloc((void **)&h->wofs_dev, n0 * sizeof(uint32_t));
         if (e == hipSuccess) e = dbg_malloc((void **)&h->wofs1_dev, n1 * sizeof(uint32_t));

@@ -396,10 +396,10 @@ def test_chains_between_forms(B, bits, kind, first):
 
 
 @pytest.mark.parametrize("bits,kind", [(8, "product"), (8, "dropped"), (7, "product"), (7, "one_side"), (6, "product"), (2, "product")])
-@pytest.mark.parametrize("rows,Hs", [(1, 64), (65, 128), (7, 192), (64, 576), (50, 320), (33, 448), (70, 832)])
+@pytest.mark.parametrize("rows,Hs", [(1, 64), (65, 128), (7, 192), (64, 576), (50, 320), (33, 448), (70, 832), (17, 1088)])
 def test_time_steps_on_one_byte_entries(B, bits, kind, rows, Hs):
     """The three recurrent steps on either side of the rule that takes one-byte entries (8 bits: nearly all of these; fewer: from 32 or 48 rows and
-    192 or 256 units on; several rounds of workgroups: all): asymmetric tables, slices of 4 to 52 inner indices, of which up to three groups of four are
+    192 or 256 units on; several rounds of workgroups: all): asymmetric tables, slices of 4 to 68 inner indices, of which up to three groups of four are
     no block of 16, codes beyond the operand's range (which wrap), activations that are word-aligned only, or not even that
     (which take the 16-bit entries)."""
     rng = np.random.default_rng(bits + rows + Hs)
@@ -476,3 +476,24 @@ def test_linear_where_activations_share_lines(B, bits, kind, M, K, N):
     want = orc.approx_linear(t, bits, (((a.astype(np.int32) + h) & (2 * h - 1)) - h).astype(np.int8), w, threads=4)
     assert (host(B.adapt_approx_linear_packed(B.adapt_weights_pack_linear(L, dev(w)), dev(a))) == want).all()
     assert (host(B.adapt_approx_linear(L, dev(a), dev(w))) == want).all()
+
+
+@pytest.mark.parametrize("M,K,N", [(3, 40, 512), (70, 33, 1024), (17, 1008, 1024), (5, 1024, 1024), (2, 9, 1536), (9, 12, 500)])
+def test_row_offsets_a_multiple_of_two_kilobytes_apart(B, M, K, N):
+    """512 columns and their multiples lie 16 further apart, where there is room (1008 x 1040 words are 4 MiB less 1 KiB of the call that
+    allocates nothing; 1024 x 1024 fill it): packed, plain, without allocation, and as a transposed layer of one pixel; two-pass tables too."""
+    rng = np.random.default_rng(K)
+    for t in (table("beyond", 8, rng), rng.integers(-100000, 100000, size=(256, 256)).astype(np.int32)):
+        L = B.Lut(t, 8)
+        a, w = rng.integers(-128, 128, size=(M, K)).astype(np.int8), wl.random_i8(rng, (N, K), 8)
+        want = orc.approx_linear(t, 8, a, w, threads=4)
+        assert (host(B.adapt_approx_linear(L, dev(a), dev(w))) == want).all()
+        assert (host(B.adapt_approx_linear_packed(B.adapt_weights_pack_linear(L, dev(w)), dev(a))) == want).all()
+        out = torch.empty((M, N), dtype=torch.int32, device="cuda")
+        B.adapt_approx_linear_noalloc(L, dev(a), dev(w), out)
+        assert (host(out) == want).all()
+        if N % 4 == 0 and K < 100:
+            wt = wl.random_i8(rng, (K, N // 4, 2, 2), 8)
+            x = a.reshape(M, K, 1, 1)
+            pw = B.adapt_weights_pack_conv_transpose2d(L, dev(wt), 2)
+            assert (host(B.adapt_approx_conv_transpose2d_packed(pw, dev(x), 0)) == orc.approx_conv_transpose2d(t, 8, x, wt, 2, 0, threads=4)).all()
