@@ -24,7 +24,10 @@ void launch_r(const adapt::ByteParams &p, unsigned grid, int level, hipStream_t 
 }  // namespace
 
 hipError_t launch_byte(const adapt::ByteParams &p, unsigned grid, int R, int level, hipStream_t s) {
-    if (R == 8) launch_r<8>(p, grid, level, s);
+    const bool at_once = R == 2 && p.copy_lines <= 64 && p.m_tiles == 1;       // (see lut_byte_kernel)
+    if (at_once && level == 0) adapt::lut_byte_kernel<1, 2, 0, true><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
+    else if (at_once && level == 4) adapt::lut_byte_kernel<1, 2, 4, true><<<grid, adapt::BYTE_THREADS, 0, s>>>(p);
+    else if (R == 8) launch_r<8>(p, grid, level, s);
     else if (R == 4) launch_r<4>(p, grid, level, s);
     else launch_r<2>(p, grid, level, s);
     return hipGetLastError();

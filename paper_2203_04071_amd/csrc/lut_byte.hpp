@@ -395,7 +395,8 @@ __device__ __forceinline__ void byte_epilogue(const ByteParams &p, const bi32x4_
 
 // DOPS: table copy operations per wave and step = copied lines * 256 B / (16 waves * 1 KB): 4 / 2 / 1 for 256 / 128 / <= 64
 // lines (fewer: one operation with fewer lanes).  R: pixels per row slot.  LEVEL: see byte_epilogue.
-template <int DOPS, int R, int LEVEL>
+// AT_ONCE: a step's memory operations ahead of its reads (see below)
+template <int DOPS, int R, int LEVEL, bool AT_ONCE = false>
 __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams p) {
     static_assert(R == 8 || R == 4 || R == 2, "pixels per row slot");
     constexpr int V = R < 4 ? R : 4;        // pixels per run: one load
@@ -600,6 +601,11 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
     // All of it is spread over the step's reads: issued in one go ahead of them, it kept the last waves from their reads for
     // half of the step (32 KB tables, 8 pixels per row slot: 2200 of 4000 clocks).  The exact product of two steps goes between the
     // reads of the step behind them.
+    // AT_ONCE (two pixels per row slot, tables of 16 KB and less, one row tile, so that every table is read once): what is issued late in a step is waited
+    // for a step and a third later, and with steps this short a stream of tables from memory had too little in flight.  Issued ahead of
+    // the wait for the step's own words it has two steps.  Linear layers of 6 bits: 3000 x 3000, 128 and 256 rows 124 and 136 -> 110 and 118 us; 4096 x 4096,
+    // 256 rows 207 -> 200.  With several row tiles or tables of 32 KB enough is in flight, and spread is the faster one
+    // (128 images of 8 x 8, 64 -> 64 channels: 17.6 us, 18.4 at once).
     uint32_t gv = 0;                        // group offset of the next step
     uint32_t gaddr = (uint32_t)(uintptr_t)(lds_ptr_t)goff + (uint32_t)g * 4u + 32u;         // that of the step after it
     auto step = [&](auto kc, int s) {
@@ -607,10 +613,6 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
         constexpr int NW = k % 2 == 0 ? 1 : 0;              // loads of weights
         constexpr int EV = NL + NW + DOPS;                  // operations of a step,
         constexpr int FIRST_LOAD = DEEP ? 0 : DOPS;         // of which these come first: the loads, or the copies
-        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(DEEP ? DOPS : 0) : "memory");
-#pragma unroll
-        for (int i = 0; i < NRUN; ++i) asm volatile("" : "+v"(W[k][i]));
-        if constexpr (k % 2 == 0) asm volatile("" : "+v"(wa[k == 0 ? 1 : 0]));
         auto issue = [&](int j) {
             const int l = j - FIRST_LOAD;
             if (l >= 0 && l < NL) {
@@ -625,6 +627,14 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
                 dma(DEEP ? j - NL - NW : j, s + AHEAD, DEEP ? (k + AHEAD) & 3 : (k + 1) & 1, std::false_type{}, pf_sink);
             }
         };
+        if constexpr (AT_ONCE) {
+#pragma unroll
+            for (int j = 0; j < EV; ++j) issue(j);
+        }
+        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(DEEP ? DOPS + (AT_ONCE ? EV : 0) : 0) : "memory");
+#pragma unroll
+        for (int i = 0; i < NRUN; ++i) asm volatile("" : "+v"(W[k][i]));
+        if constexpr (k % 2 == 0) asm volatile("" : "+v"(wa[k == 0 ? 1 : 0]));
         asm volatile("s_setprio 3");
         run_step(std::integral_constant<int, DEEP ? k : (k & 1)>{}, W[k], [&](int m) {
             if (m == NPAIR / 4 - 1) asm volatile("s_setprio 2");
@@ -632,7 +642,7 @@ __global__ __launch_bounds__(BYTE_THREADS) void lut_byte_kernel(const ByteParams
             if (m == NPAIR * 3 / 4 - 1) asm volatile("s_setprio 0");
 #pragma unroll
             for (int j = 0; j < EV; ++j)
-                if (m == j * (DEEP ? NPAIR - 1 : NPAIR * 3 / 4) / EV) issue(j);
+                if (!AT_ONCE && m == j * (DEEP ? NPAIR - 1 : NPAIR * 3 / 4) / EV) issue(j);
             // (into accumulators that the pairs around do not use)
             if constexpr (k % 2 == 0) {
                 constexpr int from = k == 0 ? 2 : 0;

@@ -497,3 +497,20 @@ def test_row_offsets_a_multiple_of_two_kilobytes_apart(B, M, K, N):
             x = a.reshape(M, K, 1, 1)
             pw = B.adapt_weights_pack_conv_transpose2d(L, dev(wt), 2)
             assert (host(B.adapt_approx_conv_transpose2d_packed(pw, dev(x), 0)) == orc.approx_conv_transpose2d(t, 8, x, wt, 2, 0, threads=4)).all()
+
+
+@pytest.mark.parametrize("bits,kind", [(6, "product"), (6, "one_side"), (4, "product"), (8, "share2"), (2, "product")])
+def test_one_row_tile_on_small_tables(B, bits, kind):
+    """Up to 512 rows on tables of at most 16 KB: every remainder of a group of four steps, waves without rows, slices, and outputs that
+    are no whole tile; sums, and the fused layer."""
+    rng = np.random.default_rng(bits)
+    t = table(kind, bits, rng)
+    L = B.Lut(t, bits)
+    for hw, K, N in [(1, 16, 16)] + [(22, k, 17) for k in range(4, 150, 16)] + [(3, 300, 40), (16, 517, 33), (22, 1030, 250)]:
+        x, w = rng.standard_normal((1, K, hw, hw)).astype(np.float32), wl.random_i8(rng, (N, K, 1, 1), bits)
+        s_x, s_out = np.float32(0.02), np.float32(2e-4)
+        q, bias = orc.quantize(x, s_x, bits), rng.standard_normal(N).astype(np.float32)
+        acc = orc.approx_conv2d(t, bits, q, w, (1, 1), (0, 0), threads=4)
+        pw = B.adapt_weights_pack_conv2d(L, dev(w))
+        assert (host(B.adapt_approx_conv2d_packed(pw, dev(q))) == acc).all(), (hw, K, N)
+        assert bits_equal(host(B.adapt_conv2d_layer_f32(pw, dev(x), s_x, s_out, (1, 1), (0, 0), bias=dev(bias), act=1)), finish(acc, s_out, bias, None, 1))
