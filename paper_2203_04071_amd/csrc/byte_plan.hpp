@@ -124,7 +124,8 @@ inline RowsShape rows_shape(long long M, long long N, long long K, int groups, i
 
 // Estimated clocks of a linear layer on it (one MI355X, 2.2 GHz): 16 waves of ceil(K / slices) NT reads of LDS at 4.3 clocks each where
 // activations come as whole words, 8 where they come byte by byte (K no multiple of 4), behind the copy of the
-// table into LDS at 10 B per clock.  Measured 4096 x 4096 x 4000 rows: 8.5 ms (8.2 estimated), 777 x 999 x 1024: 193 us (196).
+// table into LDS at 10 B per clock.  Measured 777 x 999 x 1024 rows, 8 bits: 190 us (196 estimated); 4096 x 4096 x 4000 rows, 8, 7 and 6 bits: 11.3, 8.1 and
+// 5.3 ms (8.2: the clocks of a read are about 6, 4.5 and 3.2 where many rows share a table; see byte_beats_rows for what the choice loses).
 inline long long rows_clocks_in(const RowsShape &r, int bits, long long M, long long N, long long K, int cu) {
     const long long slices = 1024 / r.MT, kc = (K + slices - 1) / slices, wgs = (M + r.MT - 1) / r.MT * ((N + r.NT - 1) / r.NT);
     const long long table = ((1LL << bits) * ((1LL << bits) + 2)) * 2, red = slices > 1 ? 4096LL * r.NT : 0;
@@ -166,9 +167,12 @@ inline long long byte_call_clocks_floor(int steps, int copy_lines, size_t table_
 }
 
 // Where tables of the byte form exist (or are to be made), the byte kernel is taken if its estimate times 1.2 is below that of
-// the whole-table kernel.  Measured both ways for 16 to 4000 rows, six pairs of K and N from 64 x 10 to 4096 x 4096, 6 to 8 bits:
-// the rule loses at most 20 % or 3 us to the better one; e.g. 8 bits, K = 777, N = 999: 256 rows 66 / 53 us (whole table / byte
-// kernel), 1024 rows 194 / 72 us; K = N = 4096: 256 rows 628 / 891 us, 1024 rows 2243 / 1158 us.
+// the whole-table kernel.  Both estimates were fitted to earlier forms of the kernels, which have become faster by different factors since.
+// Measured both ways on the present ones (330 packed layers of 1 to 4095 rows, K from 16 and N from 8 to 4096, 6 to 8 bits): 2.7 % slower in the mean
+// than with the better kernel each time.  14 of them lose more than 20 % and 3 us, most on the whole-table kernel with slices that are no whole
+// words, whose loop takes up to twice the 8 clocks assumed; e.g. (whole table / byte kernel) 8 bits, 195 rows, K = 2529, N = 391: 147 / 53 us, taken: whole
+// table.  8 bits, K = 777, N = 999: 256 rows 58 / 39 us (whole table), 1024 rows 190 / 50 (byte); K = N = 4096: 256 rows 715 / 733 (whole table), 1024 rows
+// 2842 / 749 (byte).  Tables made for the call: 8 bits, K = N = 1024, 1024 rows 197 / 153 (whole table).
 inline bool byte_beats_rows(long long byte_clk, long long rows_clk) { return byte_clk + byte_clk / 5 < rows_clk; }
 
 }  // namespace adapt_api
